@@ -418,6 +418,40 @@ def test_speculation_misled_by_its_sample_falls_back_to_the_exact_select(dtype, 
         assert H.same_err(H.to_host(err)[0], re, ERR_RTOL)
 
 
+@pytest.mark.parametrize("n,k,scale", [(1_048_576, 10_486, 64.0), (1_048_576, 10_486, 1.0 / 64.0),
+                                       (8_400_005, 1_600_001, 64.0), (8_400_005, 1_600_001, 1.0 / 64.0)])
+def test_misled_samples_on_several_streams_at_once(n, k, scale):
+    # the exact passes wait for one another's workgroups inside one launch: calls on four streams compete for the
+    # compute units; one tile per chunk, and ragged chunks whose candidate lists are cut into parts
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    xs = []
+    for seed in range(4):
+        x = wl.small_case("normal", n, seed=400 + seed, dtype="f32")
+        if seed != 2:  # one of the four finds its window held
+            x[_sampled_elements(n, 4)] *= np.float32(scale)
+        xs.append(x)
+    ds = [H.to_device(x) for x in xs]
+    idx = [torch.full((k,), -7, dtype=torch.int32, device="cuda") for _ in xs]
+    val = [torch.zeros(k, device="cuda") for _ in xs]
+    err = [torch.full((1,), -1.0, device="cuda") for _ in xs]
+    ws = [B.new_workspace(n, 1, torch.float32) for _ in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for s, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                B.adatopk_compress(ds[s], k, idx[s], val[s], err[s], ws[s])
+    torch.cuda.synchronize()
+    for s, x in enumerate(xs):
+        ri, rv, re = orc.compress(x, k)
+        assert np.array_equal(H.to_host(idx[s]), ri) and np.array_equal(H.bits(H.to_host(val[s])), H.bits(rv)), s
+        assert H.same_err(H.to_host(err[s])[0], re, ERR_RTOL), s
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_midsize_tensors_value_structures_and_boundaries(dtype):
     # between the one-launch path for small tensors and the sizes at which a sample of the tensor is taken
