@@ -2653,59 +2653,74 @@ __device__ __forceinline__ void merge_span(const I *idx, const R *val, uint32_t 
     }
 }
 // The same for many entries per line (k / n of a few per cent and more), where k_merge's value
-// stores would rewrite most output lines a second time: same spans, same search, but the span is
-// built piece by piece in LDS (zeros, then the entries that fall into the piece) and every
-// piece is written out once with 16-byte stores, so no output line is written twice.  Entries are
-// ascending, so every thread walks its own (strided) subsequence of them forwards.  An entry
-// whose index lies outside the piece that the walk assigned it to (possible only when idx is not
+// stores would rewrite most output lines a second time: same spans, but the span is built piece by
+// piece in LDS (zeros, then the entries that fall into the piece) and every piece is written out once
+// with 16-byte stores, so no output line is written twice.  The wavefronts search the pieces' ends at
+// the same time, one each: with a piece's entries known beforehand, every thread asks for MERGE_AT_ONCE
+// of them at a time without conditions (an entry past the end is read as the last one and not
+// used).  Walking on from entry to entry until one lies past the piece was a memory round trip per index and
+// another per value: a batch of 24 x 33.5 MB of which 45 % are kept 386 -> 295 us (what a copy of as many bytes takes).  An entry
+// whose index lies outside the piece that the search assigned it to (possible only when idx is not
 // ascending) is skipped: every store stays inside the span.
-constexpr int MERGE_PIECE = 32768;  // bytes of LDS per piece
+constexpr int MERGE_PIECE = 32768;  // bytes of LDS per piece: four workgroups share a compute unit
+constexpr int MERGE_AT_ONCE = 8;
+constexpr int MERGE_PIECES = static_cast<int>((MERGE_MAX_SPAN + MERGE_PIECE - 1) / MERGE_PIECE);  // of a span, at most
+static_assert(MERGE_PIECES + 1 <= NW, "one wavefront per piece end");
 template <typename R, typename I>
 __device__ __forceinline__ void merge_span_lds(const I *idx, const R *val, uint32_t k, unsigned char *y, size_t total,
                                                size_t head, size_t span, uint32_t blk, uint32_t nblk, bool stream,
                                                unsigned char *piece, uint32_t *s_range) {
     const size_t byte_a = blk == 0 ? 0 : head + static_cast<size_t>(blk) * span;
     const size_t byte_b = blk + 1 == nblk ? total : head + static_cast<size_t>(blk + 1) * span;
+    // the few bytes before the first aligned address (workgroup 0 of the tensor) go straight to memory
+    const size_t va = blk == 0 ? (head < byte_b ? head : byte_b) : byte_a;  // 16-byte aligned start of the pieces
     const int w = threadIdx.x >> 6;
-    if (w < 2) {
-        const int64_t bound = static_cast<int64_t>((w == 0 ? byte_a : byte_b) / sizeof(R));
-        const uint32_t pos = wave_lower_bound(idx, k, bound);
+    if (w <= MERGE_PIECES) {  // s_range[p]: first entry of piece p; entries of the unaligned head count as piece 0's
+        const size_t at = va + static_cast<size_t>(w) * MERGE_PIECE;
+        const size_t bound = w == 0 ? byte_a : (at < byte_b ? at : byte_b);
+        const uint32_t pos = wave_lower_bound(idx, k, static_cast<int64_t>(bound / sizeof(R)));
         if ((threadIdx.x & 63) == 0) s_range[w] = pos;
     }
-    // unaligned head of the whole tensor (workgroup 0 only, < 16 bytes): entries there are written
-    // after the zeros by the same thread order below, so handle it as part of the first piece
-    const size_t va = blk == 0 ? (head < byte_b ? head : byte_b) : byte_a;  // 16-byte aligned start
+    uint4 *pz = reinterpret_cast<uint4 *>(piece);
+    for (int i = threadIdx.x; i < MERGE_PIECE / 16; i += BLOCK) pz[i] = make_uint4(0, 0, 0, 0);
+    for (size_t i = byte_a + threadIdx.x; i < va; i += BLOCK) y[i] = 0;
     __syncthreads();
-    uint32_t j = s_range[0] + threadIdx.x;  // this thread's next entry
-    const uint32_t jb = s_range[1];
-    R *out = reinterpret_cast<R *>(y);
-    if (va > byte_a) {  // workgroup 0: the few bytes before the first aligned address, straight to memory
-        for (size_t i = byte_a + threadIdx.x; i < va; i += BLOCK) y[i] = 0;
-        __syncthreads();
+    if (va > byte_a) {
+        R *out = reinterpret_cast<R *>(y);
         const int64_t e1 = static_cast<int64_t>(va / sizeof(R));
-        for (uint32_t jj = s_range[0] + threadIdx.x; jj < jb; jj += BLOCK) {
-            const int64_t i = idx[jj];
+        for (uint32_t j = s_range[0] + threadIdx.x; j < s_range[1]; j += BLOCK) {
+            const int64_t i = static_cast<int64_t>(idx[j]);
             if (i >= e1) break;
-            if (i >= 0) out[i] = val[jj];
+            if (i >= 0) out[i] = val[j];
         }
     }
-    for (size_t p0 = va; p0 < byte_b; p0 += MERGE_PIECE) {
+    R *pl = reinterpret_cast<R *>(piece);
+    int p = 0;
+    for (size_t p0 = va; p0 < byte_b; p0 += MERGE_PIECE, ++p) {
         const size_t p1 = (p0 + MERGE_PIECE < byte_b) ? p0 + MERGE_PIECE : byte_b;
         const int64_t e0 = static_cast<int64_t>(p0 / sizeof(R)), e1 = static_cast<int64_t>(p1 / sizeof(R));
-        uint4 *pz = reinterpret_cast<uint4 *>(piece);
-        for (int i = threadIdx.x; i < MERGE_PIECE / 16; i += BLOCK) pz[i] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        R *pl = reinterpret_cast<R *>(piece);
-        while (j < jb) {
-            const int64_t i = idx[j];
-            if (i >= e1) break;
-            if (i >= e0) pl[i - e0] = val[j];
-            j += BLOCK;
+        const uint32_t ja = s_range[p], jb = s_range[p + 1];
+        for (uint32_t j0 = ja + threadIdx.x; j0 < jb; j0 += MERGE_AT_ONCE * BLOCK) {
+            I i[MERGE_AT_ONCE];
+            R v[MERGE_AT_ONCE];
+#pragma unroll
+            for (int u = 0; u < MERGE_AT_ONCE; ++u) {
+                const uint32_t j = j0 + u * BLOCK;
+                const uint32_t jc = opaque(j < jb ? j : jb - 1);
+                i[u] = idx[jc];
+                v[u] = val[jc];
+            }
+#pragma unroll
+            for (int u = 0; u < MERGE_AT_ONCE; ++u)
+                if (j0 + u * BLOCK < jb && i[u] >= e0 && i[u] < e1) pl[i[u] - e0] = v[u];
         }
         __syncthreads();
         const size_t nvec = (p1 - p0) / 16;
         uint4 *dst = reinterpret_cast<uint4 *>(y + p0);
-        for (size_t i = threadIdx.x; i < nvec; i += BLOCK) store16(&dst[i], pz[i], stream);
+        for (size_t i = threadIdx.x; i < nvec; i += BLOCK) {
+            store16(&dst[i], pz[i], stream);
+            pz[i] = make_uint4(0, 0, 0, 0);  // for the next piece (a shorter piece is the last one)
+        }
         for (size_t i = p0 + nvec * 16 + threadIdx.x; i < p1; i += BLOCK) y[i] = piece[i - p0];  // ragged end of the tensor
         __syncthreads();
     }
@@ -2722,7 +2737,7 @@ template <typename R, typename I>
 __global__ __launch_bounds__(BLOCK) void k_merge_lds(const I *idx, const R *val, uint32_t k, unsigned char *y,
                                                      size_t total, size_t head, size_t span, uint32_t stream) {
     __shared__ __attribute__((aligned(16))) unsigned char piece[MERGE_PIECE];
-    __shared__ uint32_t s_range[2];
+    __shared__ uint32_t s_range[MERGE_PIECES + 1];
     merge_span_lds<R, I>(idx, val, k, y, total, head, span, blockIdx.x, gridDim.x, stream != 0, piece, s_range);
 }
 
@@ -2753,7 +2768,7 @@ static_assert(MERGE_MAXSEG <= 128, "two table entries per lane");
 
 template <typename R> __global__ __launch_bounds__(BLOCK) void k_merge_seg(const MergeLaunch a) {
     __shared__ __attribute__((aligned(16))) unsigned char piece[MERGE_PIECE];
-    __shared__ uint32_t s_range[2];
+    __shared__ uint32_t s_range[MERGE_PIECES + 1];
     // owner of this workgroup: the last tensor whose first workgroup is <= blockIdx.x (first workgroups
     // never decrease and the first is 0); lane l looks at table entries l and l + 64
     const int lane = threadIdx.x & 63;
