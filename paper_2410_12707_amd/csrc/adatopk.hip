@@ -115,7 +115,8 @@ constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
-constexpr int64_t MERGE_DENSE_RATIO = 32;  // k > n / 32 takes the LDS-built variant of the one-kernel decompress
+constexpr int64_t MERGE_DENSE_RATIO = 64;  // k > n / 64 takes the LDS-built variant of the one-kernel decompress, and so does any large output
+                                           // (merge_dense)
 constexpr size_t MERGE_MIN_SPAN = 16384;   // bytes; smaller outputs use fewer workgroups
 constexpr size_t MERGE_MAX_SPAN = 98304;   // bytes; larger outputs use more workgroups
 static_assert(LU * NW <= 64, "per-tile wave counts must fit one wavefront scan");
@@ -2751,7 +2752,7 @@ struct MergeSeg {   // 40 bytes
     int64_t n;             // elements
     uint32_t k;
     uint32_t first_block;  // its spans are workgroups [first_block, first_block of the next tensor)
-    uint32_t dense;        // k > n / MERGE_DENSE_RATIO: build the lines in LDS
+    uint32_t dense;        // build the lines in LDS (merge_dense)
     uint32_t pad;
 };
 struct MergeLaunch {
@@ -3228,6 +3229,13 @@ adatopk_status accumulate_impl(const void *idx, int ib, const void *val, int64_t
     return hipGetLastError() == hipSuccess ? ADATOPK_OK : ADATOPK_ERUNTIME;
 }
 
+// Which variant of the one-kernel decompress: values stored over zeros, or the lines built in LDS first.  Storing over
+// zeros writes a line with an entry twice.  While the output fits the last-level cache the second write stays there,
+// and the variant without the LDS stage is the faster one for few entries (26 M bf16 at 0.5 %: 10.4 against 12.0 us;
+// 25 M fp32 at 1 %: 22.2 against 22.5, at 2 %: 27.9 against 25.7).  Beyond it the line has left for memory and comes
+// back for its four bytes: 400 MB at 0.05 % 78.3 against 78.8 us, at 1 % 104.6 against 79.0, at 3 % 171 against 79.
+inline bool merge_dense(int64_t k, int64_t n, bool stream) { return stream || k > n / MERGE_DENSE_RATIO; }
+
 template <typename R, typename I>
 void launch_merge(bool dense, unsigned grid, hipStream_t st, const I *idx, const R *val, uint32_t k, unsigned char *y,
                   size_t total, size_t head, size_t span) {
@@ -3248,7 +3256,7 @@ adatopk_status decompress_sorted_impl(const void *idx, int ib, const void *val, 
     const size_t body = total - head;
     const size_t span = merge_span_bytes(body);
     const unsigned grid = static_cast<unsigned>(body / span + 1);  // the last workgroup takes the remainder
-    const bool dense = k > n / MERGE_DENSE_RATIO;  // more than one entry per few lines: build the lines in LDS
+    const bool dense = merge_dense(k, n, total > STREAM_STORE_BYTES);
     const uint32_t ku = static_cast<uint32_t>(k);
     unsigned char *yb = static_cast<unsigned char *>(dense_out);
     if (es == 4) {
@@ -3297,7 +3305,7 @@ adatopk_status decompress_segmented_impl(const int32_t *idx, const void *val, co
             g.n = n[s];
             g.k = static_cast<uint32_t>(k);
             g.first_block = static_cast<uint32_t>(blocks);
-            g.dense = k > n[s] / MERGE_DENSE_RATIO ? 1u : 0u;
+            g.dense = merge_dense(k, n[s], a.stream != 0) ? 1u : 0u;
             if (n[s] > 0) {  // same span count as the kernel derives: (bytes behind the unaligned head) / span + 1
                 const size_t total = static_cast<size_t>(n[s]) * es;
                 size_t head = (16 - reinterpret_cast<uintptr_t>(dense_out[s]) % 16) % 16;
