@@ -154,7 +154,8 @@ def _dtype_code(t: torch.dtype) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # (the handle alone: a Stream object around it costs a microsecond and a half per call)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor) -> int:
@@ -187,6 +188,39 @@ def _check_pairs(dtype: torch.dtype, k_total: int, idx: torch.Tensor, val: torch
         raise ValueError("idx must be int32 with at least %d entries" % k_total)
     if val.dtype != dtype or val.numel() < k_total:
         raise ValueError("val must have the dense tensor's dtype (%s) and at least %d entries" % (dtype, k_total))
+
+
+_marshal = None  # the extension that reads the arguments of the segmented calls
+
+
+def _load_marshal():
+    global _marshal
+    if _marshal is None:
+        try:
+            from . import _marshal as m
+        except ImportError as e:
+            raise ImportError("_marshal.so is not built: run `python -m paper_2410_12707_amd.build`") from e
+        _marshal = m
+    return _marshal
+
+
+def _segments(tensors: Sequence[torch.Tensor]):
+    """(addresses, lengths, dtype) of the tensors of a segmented call, or None if they want a closer look in Python."""
+    return _load_marshal().tensors(tensors)
+
+
+def _counts(values: Sequence[int], count: int):
+    """(int64 array, sum) of `count` numbers of a segmented call."""
+    packed = _load_marshal().int64s(values, count)
+    if packed is None:
+        ints = [int(v) for v in values]
+        packed = (ctypes.c_int64 * max(count, 1))(*ints), sum(ints)
+    return packed
+
+
+def _segment_arrays(tensors: Sequence[torch.Tensor]):
+    S = max(len(tensors), 1)
+    return (ctypes.c_void_p * S)(*[_dev(t) for t in tensors]), (ctypes.c_int64 * S)(*[t.numel() for t in tensors])
 
 
 def _one_dtype(tensors: Sequence[torch.Tensor]) -> None:
@@ -253,13 +287,15 @@ def adatopk_decompress_segmented(idx: torch.Tensor, val: torch.Tensor, out_offse
     """Decompress of S tensors from the concatenated, per-tensor ascending pairs in few launches."""
     lib = load_library()
     S = len(dense_out)
-    dt = _dtype_code(dense_out[0].dtype) if S else F32
+    segments = _segments(dense_out)
+    dtype = segments[2] if segments else dense_out[0].dtype if S else torch.float32
+    dt = _dtype_code(dtype)
     if S:
-        _one_dtype(dense_out)
-        _check_pairs(dense_out[0].dtype, int(out_offset[S]), idx, val)
-    ptrs = (ctypes.c_void_p * max(S, 1))(*[_dev(t) for t in dense_out])
-    ns = (ctypes.c_int64 * max(S, 1))(*[t.numel() for t in dense_out])
-    off = (ctypes.c_int64 * (S + 1))(*[int(v) for v in out_offset])
+        if not segments:
+            _one_dtype(dense_out)
+        _check_pairs(dtype, int(out_offset[S]), idx, val)
+    ptrs, ns = segments[:2] if segments else _segment_arrays(dense_out)
+    off, _ = _counts(out_offset, S + 1)
     _check(lib.adatopk_decompress_segmented(_dev(idx), _dev(val), off, S, dt, ptrs, ns, _stream()),
            "adatopk_decompress_segmented")
 
@@ -305,13 +341,13 @@ def adatopk_compress_wire_segmented(dense: Sequence[torch.Tensor], ks: Sequence[
     """One wire message per tensor, message s at byte wire_offset[s] of the uint8 tensor wire_out."""
     lib = load_library()
     S = len(dense)
-    dt = _dtype_code(dense[0].dtype) if S else F32
-    if S:
+    segments = _segments(dense)
+    dt = _dtype_code(segments[2] if segments else dense[0].dtype) if S else F32
+    if S and not segments:
         _one_dtype(dense)
-    ptrs = (ctypes.c_void_p * max(S, 1))(*[_dev(t) for t in dense])
-    ns = (ctypes.c_int64 * max(S, 1))(*[t.numel() for t in dense])
-    kk = (ctypes.c_int64 * max(S, 1))(*[int(v) for v in ks])
-    off = (ctypes.c_int64 * max(S, 1))(*[int(v) for v in wire_offset])
+    ptrs, ns = segments[:2] if segments else _segment_arrays(dense)
+    kk, _ = _counts(ks, S)
+    off, _ = _counts(wire_offset, S)
     rr = _dbl_array(ratios) if ratios is not None else None
     _check(lib.adatopk_compress_wire_segmented(ptrs, ns, kk, S, dt, int(index_bytes), rr, _dev_or_pinned(wire_out), off,
                                                wire_out.numel() * wire_out.element_size(), _dev(workspace),
@@ -331,14 +367,16 @@ def adatopk_compress_segmented(dense: Sequence[torch.Tensor], ks: Sequence[int],
                                err_norm_out: Optional[torch.Tensor], workspace: torch.Tensor) -> None:
     lib = load_library()
     S = len(dense)
-    dt = _dtype_code(dense[0].dtype) if S else F32
-    if S:
+    segments = _segments(dense)
+    dtype = segments[2] if segments else dense[0].dtype if S else torch.float32
+    dt = _dtype_code(dtype)
+    if S and not segments:
         _one_dtype(dense)
-        _check_outputs(dense[0].dtype, sum(int(v) for v in ks), idx_out, val_out, err_norm_out, S)
-    ptrs = (ctypes.c_void_p * max(S, 1))(*[_dev(t) for t in dense])
-    ns = (ctypes.c_int64 * max(S, 1))(*[t.numel() for t in dense])
-    kk = (ctypes.c_int64 * max(S, 1))(*[int(v) for v in ks])
-    off = (ctypes.c_int64 * (S + 1))(*[int(v) for v in out_offset])
+    kk, k_total = _counts(ks, S)
+    if S:
+        _check_outputs(dtype, k_total, idx_out, val_out, err_norm_out, S)
+    ptrs, ns = segments[:2] if segments else _segment_arrays(dense)
+    off, _ = _counts(out_offset, S + 1)
     err_ptr = _dev(err_norm_out) if err_norm_out is not None else None
     _check(lib.adatopk_compress_segmented(ptrs, ns, kk, S, dt, _dev(idx_out), _dev(val_out), off, err_ptr,
                                           _dev(workspace), workspace.numel(), _stream()),

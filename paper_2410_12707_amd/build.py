@@ -12,6 +12,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadatopk.so")
 MEASURE_LIB = os.path.join(HERE, "libadatopk_measure.so")
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = [os.path.join(CSRC, "adatopk.hip"), os.path.join(CSRC, "adatopk_host.cpp")]
 
 HIPCC_FLAGS = [
@@ -36,6 +38,24 @@ def build_measure_library(verbose: bool = False) -> str:
     return build_library(verbose, MEASURE_LIB, ("ADATOPK_MEASURE_BUILD",))
 
 
+def build_marshal(verbose: bool = False) -> str:
+    """The Python extension that reads the arguments of the segmented calls (host code only)."""
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-Wall", "-Wextra", "-o", MARSHAL_LIB, MARSHAL_SOURCE,
+           "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return MARSHAL_LIB
+
+
 def library_is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
@@ -48,3 +68,4 @@ def library_is_stale() -> bool:
 if __name__ == "__main__":
     print(build_library(verbose=True))
     print(build_measure_library(verbose=True))
+    print(build_marshal(verbose=True))

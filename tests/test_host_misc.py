@@ -56,3 +56,25 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
             "sys.exit(3)\n") % (ROOT, str(tmp_path / "missing.so"))
     r = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
     assert r.returncode == 0 and "RAISED" in r.stdout, (r.stdout, r.stderr)
+
+
+def test_marshalling_of_segmented_arguments():
+    # what the extension packs is what ctypes would have packed; anything but the plain case is left to Python
+    import ctypes
+
+    import torch
+
+    from paper_2410_12707_amd import binding as B
+
+    m = B._load_marshal()
+    for values in ([], [0], [1, 2, 3], [2**62, -5], list(range(129))):
+        for seq in (values, tuple(values)):
+            packed, total = m.int64s(seq, len(values))
+            assert packed == bytes((ctypes.c_int64 * len(values))(*values)) and total == sum(values)
+    for odd in ([1, 2.0], [True], ["1"], [2**63], [2**62, 2**62], range(2), "12", None):
+        assert m.int64s(odd, 2 if odd is None else len(odd)) is None
+    assert m.int64s([1, 2], 3) is None and m.int64s([1, 2], 1) is None
+    kk, total = B._counts([1, 2.9], 2)  # as int() takes them
+    assert list(kk) == [1, 2] and total == 3
+    for odd in ([], [torch.zeros(3)], [torch.zeros(3), 1], [torch.nn.Parameter(torch.zeros(2))], torch.zeros(2), None, (x for x in ())):
+        assert m.tensors(odd) is None  # host memory, nothing at all, not a tensor, not a list
