@@ -102,6 +102,7 @@ constexpr int MAXSUB = 8;             // parts that the list kernels cut a chunk
 constexpr int MAXSUB_ONE = 4;         // ... and for a single tensor, whose chunks are a quarter as long as a large batch's
 constexpr int SUB_ENTRIES = 8192;     // ... so that a part has about this many
 constexpr int MAXSEG = 64;            // segments per launch (the table travels as kernel arguments)
+constexpr int64_t SPLIT_MIN_N = 16 << 20;  // elements of either kind from which a batch's speculating and exact tensors are launched apart
 constexpr int CTARGET = 512;          // chunks of a launch of several tensors, at most (two workgroups per compute unit)
 // ... and of a single tensor: one workgroup per compute unit.  Half the rows for every prologue to
 // sum; a batch of tensors with unequal keep counts wants the finer split, whose workgroups even out.
@@ -148,6 +149,8 @@ __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
 
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
 constexpr uint32_t FLAG_SPEC = 2u;      // the speculative pass runs for this tensor
+constexpr uint32_t FLAG_NO_LIST = 4u;   // so much is kept that no chunk's list would hold its candidates: none is stored
+constexpr int FLAG_SLOT_SHIFT = 8;      // bits from here up: the tensor's entry of err_out
 struct SegDesc {
     const void *x;       // device pointer of the tensor
     int64_t out_off;     // first output slot of this segment; in wire mode the byte offset of its index section
@@ -1174,9 +1177,9 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
     const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
     const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
     uint32_t nxt[St::SLOTS], far[St::SLOTS], valid[St::SLOTS];  // far: DEPTH 3 only
-    uint32_t cap = a.cap;  // 0 once a dense tile has made the scan give the chunk's list up
-    int32_t *Li = a.L_idx + static_cast<size_t>(g) * cap;
-    R *Lv = static_cast<R *>(a.L_val) + static_cast<size_t>(g) * cap;
+    uint32_t cap = (sg.flags & FLAG_NO_LIST) ? 0u : a.cap;  // 0 also once a dense tile has made the scan give the chunk's list up
+    int32_t *Li = a.L_idx + static_cast<size_t>(g) * a.cap;
+    R *Lv = static_cast<R *>(a.L_val) + static_cast<size_t>(g) * a.cap;
 
     uint2 *stage = reinterpret_cast<uint2 *>(l.smem);
     uint32_t *hw = l.smem + 2 * STAGE_CAP;
@@ -1801,7 +1804,7 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
 // ones of a bin add count * value^2.  Fixed summation order.  count_t: the candidate count of chunk threadIdx.x.
 template <int VEC>
-__device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &sg, int s, const Threshold &t, uint32_t bin_key,
+__device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &sg, const Threshold &t, uint32_t bin_key,
                                                const uint32_t (&my_bins)[NB3 / BLOCK], uint32_t count_t, uint32_t sub, double *smd) {
     double sum = 0.0;
     static_assert(CTARGET <= BLOCK, "thread t has chunk t");
@@ -1824,7 +1827,7 @@ __device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &s
         }
     }
     const double tot = block_sum_f64(sum, smd);
-    if (threadIdx.x == 0) a.err_out[s] = static_cast<float>(sqrt(tot));
+    if (threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = static_cast<float>(sqrt(tot));
 }
 
 // 16-bit types: a window bin is one pattern (the window's shift is the 16 zero bits below the pattern), so
@@ -1846,7 +1849,7 @@ __device__ __forceinline__ Threshold threshold_16(const Launch &a, const ColumnP
 // the global suffix sums S[0 .. Bw + 1], which this one workgroup adds up from the chunks' rows: 64 columns
 // at a time, eight row groups side by side.  h: what column_pick has left; NBW + 1 words of LDS.
 template <int VEC>
-__device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg, int s, const Threshold &t, uint32_t lo, uint32_t shw,
+__device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg, const Threshold &t, uint32_t lo, uint32_t shw,
                                               double below_t, uint32_t *h, double *smd) {
     // nothing kept means k = 0, for which the window starts above every key: no candidates at all
     const uint32_t Bw = t.t_bin;
@@ -1892,7 +1895,7 @@ __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg
         }
     }
     const double tot = block_sum_f64(sum, smd);
-    if (threadIdx.x == 0) a.err_out[s] = static_cast<float>(sqrt(tot));
+    if (threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = static_cast<float>(sqrt(tot));
     __syncthreads();
 }
 
@@ -2074,13 +2077,13 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         first_tile();
         __builtin_amdgcn_sched_barrier(0);
         t = threshold_f32(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, h, l.sm, l.s_pick);
-        if (sums_error) error_norm_f32<VEC>(a, sg, s, t, lo + (stw.Bw << shw), my_bins, count_t, sub, l.smd);
+        if (sums_error) error_norm_f32<VEC>(a, sg, t, lo + (stw.Bw << shw), my_bins, count_t, sub, l.smd);
     } else {
         const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
                                                     a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks,
                                                     0, kout, h, first_tile);
         t = threshold_16(a, pw, kout, lo, shw);
-        if (sums_error) error_norm_16<VEC>(a, sg, s, t, lo, shw, below_t, h, l.smd);
+        if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
     emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, count_t, raw, id, l);
 }
@@ -2241,7 +2244,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
             if (src.len != 0) refine_part<VEC, WIDE>(a, 0, src, static_cast<size_t>(c) * sub + pp, pw.B, lo, shw, raw, h, sl.sm, sl.smd);
         } else {
             const Threshold t = threshold_16(a, pw, kout, lo, shw);
-            if (sums_error) error_norm_16<VEC>(a, sg, 0, t, lo, shw, below_t, h, el.smd);
+            if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, el.smd);
             emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, el);
         }
     };
@@ -2323,7 +2326,7 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
     const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, n, wide, a.wire != 0, sizeof(R));
     const R *x = static_cast<const R *>(sg.x);
     R *ov = static_cast<R *>(op.val);
-    if (c == 0 && threadIdx.x == 0 && a.err_out != nullptr) a.err_out[s] = 0.0f;
+    if (c == 0 && threadIdx.x == 0 && a.err_out != nullptr) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = 0.0f;
     if (wide) {
         for (uint32_t i = beg + threadIdx.x; i < end; i += BLOCK) op.i64[i] = static_cast<int64_t>(i);
     } else {
@@ -3036,20 +3039,21 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         return ADATOPK_OK;
     }
 
-    for (int32_t s0 = 0; s0 < S; s0 += MAXSEG) {
+    // Tensors kept whole (k = n) take no part in the selection: they go through it as empty tensors
+    // (one empty chunk each) and get their pairs from k_keep_all below.
+    auto kept_whole = [&](int32_t s) { return n[s] > 0 && k[s] == n[s]; };
+    auto n_select = [&](int32_t s) { return kept_whole(s) ? static_cast<int64_t>(0) : n[s]; };
+    // One launch of the kernels for the tensors `which[0 .. count)` of the call.
+    auto select_group = [&](const int32_t *which, int32_t count) -> adatopk_status {
         Launch a{};
-        a.S = (S - s0 < MAXSEG) ? S - s0 : MAXSEG;
+        a.S = count;
         // Chunk size of this launch: at most chunk_target() chunks in all, so that all workgroups are
         // resident at once (a few chunks beyond that would run as a second, nearly empty round).
-        // Tensors kept whole (k = n) take no part in the selection: they go through it as empty tensors
-        // (one empty chunk each) and get their pairs from k_keep_all below.
-        auto kept_whole = [&](int32_t s) { return n[s] > 0 && k[s] == n[s]; };
-        auto n_select = [&](int32_t s) { return kept_whole(s) ? static_cast<int64_t>(0) : n[s]; };
         int64_t n_batch = 0;
         int32_t whole = 0;
         for (int32_t i = 0; i < a.S; ++i) {
-            n_batch += n_select(s0 + i);
-            whole += kept_whole(s0 + i) ? 1 : 0;
+            n_batch += n_select(which[i]);
+            whole += kept_whole(which[i]) ? 1 : 0;
         }
         const int64_t target = chunk_target(a.S);
         const int64_t E_fits = chunk_elems(n_batch, a.S, target);  // fits whatever the tensors' lengths are
@@ -3057,7 +3061,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         E = E < TILE ? TILE : (E + TILE - 1) / TILE * TILE;
         auto chunks_at = [&](int64_t e) {
             int64_t count = 0;
-            for (int32_t i = 0; i < a.S; ++i) count += n_select(s0 + i) > 0 ? (n_select(s0 + i) + e - 1) / e : 1;
+            for (int32_t i = 0; i < a.S; ++i) count += n_select(which[i]) > 0 ? (n_select(which[i]) + e - 1) / e : 1;
             return count;
         };
         while (E < E_fits && chunks_at(E) > target) E += TILE;
@@ -3081,13 +3085,13 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.idx64 = idx_bytes == 8 ? 1u : 0u;
         a.wire = out.wire ? 1u : 0u;
         a.val_out = val_out;
-        a.err_out = err_out ? err_out + s0 : nullptr;
+        a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
         bool speculate = false;
         double densest = 0.0;  // largest keep fraction of the launch
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];
-            const int32_t s = s0 + i;
+            const int32_t s = which[i];
             d.x = dense[s];
             d.out_off = out_offset[s] + header;
             const int64_t ns = n_select(s), ks = kept_whole(s) ? 0 : k[s];
@@ -3096,7 +3100,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             d.chunk_begin = chunks;
             d.nchunks = ns > 0 ? static_cast<int32_t>((ns + E - 1) / E) : 1;  // an empty tensor keeps one (empty) chunk
             const bool aligned4 = reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
-            d.flags = aligned4 ? FLAG_ALIGNED4 : 0u;
+            d.flags = (aligned4 ? FLAG_ALIGNED4 : 0u) | (static_cast<uint32_t>(s - which[0]) << FLAG_SLOT_SHIFT);
+            if (ks > ns / LIST_DIV) d.flags |= FLAG_NO_LIST;
             const bool aligned16 = reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0;  // the sample is read with 16-byte loads
             if (speculation_ranks(ns, ks, dt, aligned16, &d.r_lo, &d.r_hi, &d.sample_batches)) {
                 d.flags |= FLAG_SPEC;
@@ -3127,7 +3132,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             int32_t tiles = 0;
             for (int32_t i = 0; i < a.S; ++i) {
                 SegDesc &d = w.seg[i];
-                const int32_t s = s0 + i;
+                const int32_t s = which[i];
                 d.n = kept_whole(s) ? static_cast<int32_t>(n[s]) : 0;
                 d.k = d.n;
                 d.chunk_begin = tiles;
@@ -3139,6 +3144,36 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             else launch(ST_ALL, k_keep_all<TAG_F16>, dim3(tiles), st, w);
             if (hipGetLastError() != hipSuccess) return ADATOPK_ERUNTIME;
         }
+        return ADATOPK_OK;
+    };
+    // MAXSEG tensors at a time; those that the speculative pass takes and those that need the exact passes apart if
+    // there is enough of both.  In one launch each kind's kernels find most workgroups' chunks not theirs: the
+    // exact passes over four of fifteen tensors of 33.5 MB ran on 137 of 512 workgroups (histogram 70 us,
+    // scan 209).  Apart, both kinds are cut into as many chunks as the chip takes; it costs five launches more, 20 us,
+    // which the exact passes of SPLIT_MIN_N elements are worth.
+    for (int32_t s0 = 0; s0 < S; s0 += MAXSEG) {
+        const int32_t count = (S - s0 < MAXSEG) ? S - s0 : MAXSEG;
+        int32_t order[MAXSEG], nspec = 0, nexact = 0;
+        int64_t n_spec = 0, n_exact = 0;
+        int32_t exact[MAXSEG];
+        for (int32_t i = 0; i < count; ++i) {
+            const int32_t s = s0 + i;
+            uint32_t lo, hi, batches;
+            const bool spec = speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, &lo, &hi, &batches);
+            if (spec) n_spec += n[s];
+            else n_exact += n_select(s);
+            if (spec || n_select(s) == 0) order[nspec++] = s;  // (what is not selected from goes with either)
+            else exact[nexact++] = s;
+        }
+        adatopk_status rc;
+        if (n_spec >= SPLIT_MIN_N && n_exact >= SPLIT_MIN_N) {
+            rc = select_group(order, nspec);
+            if (rc == ADATOPK_OK) rc = select_group(exact, nexact);
+        } else {
+            for (int32_t i = 0; i < count; ++i) order[i] = s0 + i;
+            rc = select_group(order, count);
+        }
+        if (rc != ADATOPK_OK) return rc;
     }
     return ADATOPK_OK;
 }

@@ -476,3 +476,22 @@ def test_midsize_tensors_in_one_segmented_call():
     for s in range(len(xs)):
         assert H.same_err(ge[s], re[s], ERR_RTOL), (s, ge[s], re[s])
     check_segmented_decompress(gi, gv, off, lens)
+
+
+@pytest.mark.parametrize("dtype,mix", [("f32", "many"), ("bf16", "many"), ("f32", "two"), ("f16", "two")])
+def test_batch_of_speculating_and_exact_tensors(dtype, mix):
+    # enough of both kinds that they are launched apart: every tensor's pairs and error norm are still its own,
+    # whatever its place in the call ("two": each launch holds a single tensor)
+    import gpu_harness as H
+
+    lens, shares = ([9_000_003, 70_000, 0, 17_000_001, 5_000, 8_000_005, 1_200_000], [0.30, 1.0, 0.0, 0.01, 0.1, 0.95, 0.05])
+    if mix == "two":
+        lens, shares = [16_900_000, 16_800_001], [0.4, 0.02]
+    xs = [wl.small_case("normal", n, seed=900 + i, dtype=dtype) for i, n in enumerate(lens)]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    gi, gv, off, ge = H.gpu_compress_segmented(xs, ks)
+    for s, (x, k) in enumerate(zip(xs, ks)):
+        ri, rv, re = orc.compress(x, k)
+        assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), s
+        assert H.same_err(ge[s], re, ERR_RTOL), (s, ge[s], re)
+    check_segmented_decompress(gi, gv, off, lens)
