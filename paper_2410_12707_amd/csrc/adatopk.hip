@@ -307,14 +307,33 @@ __device__ __forceinline__ uint32_t lanes_below_plus(uint64_t mask, uint32_t bas
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), base));
 }
 
+// Sums over a wavefront move inside the vector unit (DPP): four shifts within the rows of 16 lanes, then lane 15 and
+// lane 31 of what stands below to the rows above.  Through __shfl each of the six steps is a trip to the LDS
+// unit and back, a hundred cycles, and the short kernels are chains of such sums.
+// Every lane takes part (no divergent callers).
+constexpr int DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;
+// v moved by the control; `otherwise` where no lane is read
+template <int CTRL> __device__ __forceinline__ uint32_t dpp(uint32_t v, uint32_t otherwise) {
+    constexpr int ROWS = CTRL == DPP_BCAST15 ? 0xA : (CTRL == DPP_BCAST31 ? 0xC : 0xF);
+    return static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(static_cast<int>(otherwise), static_cast<int>(v), CTRL, ROWS, 0xF, false));
+}
+template <int CTRL> __device__ __forceinline__ double dpp(double v) {  // 0.0 where no lane is read
+    const uint64_t u = static_cast<uint64_t>(__double_as_longlong(v));
+    const uint64_t lo = dpp<CTRL>(static_cast<uint32_t>(u), 0u), hi = dpp<CTRL>(static_cast<uint32_t>(u >> 32), 0u);
+    return __longlong_as_double(static_cast<long long>(lo | (hi << 32)));
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(v, d);
-        if (lane >= d) v += t;
-    }
+    v += dpp<DPP_SHR1>(v, 0u);
+    v += dpp<DPP_SHR2>(v, 0u);
+    v += dpp<DPP_SHR4>(v, 0u);
+    v += dpp<DPP_SHR8>(v, 0u);
+    v += dpp<DPP_BCAST15>(v, 0u);
+    v += dpp<DPP_BCAST31>(v, 0u);
     return v;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {  // lane: the same in all lanes
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
 }
 
 // Counts that lane 0 of every wavefront has put into cnt[0 .. NW) before a barrier: the sum over the
@@ -359,10 +378,14 @@ __device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t *sm, ui
 // Block sum of doubles in a fixed order (same grouping every run).  sm holds NW doubles.
 __device__ __forceinline__ double block_sum_f64(double v, double *sm) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_down(v, d);
+    v += dpp<DPP_SHR1>(v);
+    v += dpp<DPP_SHR2>(v);
+    v += dpp<DPP_SHR4>(v);
+    v += dpp<DPP_SHR8>(v);
+    v += dpp<DPP_BCAST15>(v);
+    v += dpp<DPP_BCAST31>(v);
     __syncthreads();
-    if (lane == 0) sm[w] = v;
+    if (lane == 63) sm[w] = v;
     __syncthreads();
     double s = 0.0;
 #pragma unroll
@@ -625,13 +648,10 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
 // Sums of two counters over the workgroup.  sm holds 2 * NW words.
 __device__ __forceinline__ void block_sum2_u32(uint32_t &a, uint32_t &b, uint32_t *sm) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        a += __shfl_down(a, d);
-        b += __shfl_down(b, d);
-    }
+    a = wave_incl_scan(a);
+    b = wave_incl_scan(b);
     __syncthreads();
-    if (lane == 0) {
+    if (lane == 63) {
         sm[w] = a;
         sm[NW + w] = b;
     }
@@ -1075,11 +1095,14 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                 }
         }
     uint32_t floor_key = mine;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = __shfl_xor(floor_key, d);
-        floor_key = o < floor_key ? o : floor_key;
-    }
+    auto lower = [&](uint32_t o) { floor_key = o < floor_key ? o : floor_key; };
+    lower(dpp<DPP_SHR1>(floor_key, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR2>(floor_key, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR4>(floor_key, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR8>(floor_key, 0xFFFFFFFFu));
+    lower(dpp<DPP_BCAST15>(floor_key, 0xFFFFFFFFu));
+    lower(dpp<DPP_BCAST31>(floor_key, 0xFFFFFFFFu));
+    floor_key = lane_value(floor_key, 63);  // the wavefront's
     if (lane == 0) sm[w] = floor_key;
     __syncthreads();
 #pragma unroll
@@ -1846,8 +1869,8 @@ __device__ __forceinline__ Threshold threshold_16(const Launch &a, const ColumnP
 
 // Error norm of a 16-bit tensor: the squares below the window (below_t: chunk threadIdx.x's, from the scan) and, for
 // every window bin below Bw and for the dropped part of bin Bw, count * value^2.  The counts are differences of
-// the global suffix sums S[0 .. Bw + 1], which this one workgroup adds up from the chunks' rows: 64 columns
-// at a time, eight row groups side by side.  h: what column_pick has left; NBW + 1 words of LDS.
+// the global suffix sums S[0 .. Bw + 1], which this one workgroup adds up from the chunks' rows: 256 columns
+// at a time, four to a thread, eight row groups side by side.  h: what column_pick has left; NBW + 1 words of LDS.
 template <int VEC>
 __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg, const Threshold &t, uint32_t lo, uint32_t shw,
                                               double below_t, uint32_t *h, double *smd) {
@@ -1863,25 +1886,31 @@ __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg
         for (uint32_t b = threadIdx.x; b < NBW + 1; b += BLOCK) h[b] = 0;
         __syncthreads();
     }
-    const uint32_t col = threadIdx.x & 63, rg = threadIdx.x >> 6;
-    for (uint32_t c0 = 0; !have_sums && c0 < ncols && c0 < NBW; c0 += 64) {
-        const uint32_t b = c0 + col;
-        if (b < ncols && b < NBW) {
-            const uint32_t *p = a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW + b;
-            uint32_t sum = 0;
-            for (int r0 = rg; r0 < sg.nchunks; r0 += NW * 8) {
-                uint32_t v[8];
+    static_assert(NBW % 256 == 0, "whole groups of columns");
+    const uint32_t col = 4 * (threadIdx.x & 63), rg = threadIdx.x >> 6;
+    for (uint32_t c0 = 0; !have_sums && c0 < ncols && c0 < NBW; c0 += 256) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW + c0 + col);
+        uint4 sum = make_uint4(0, 0, 0, 0);
+        for (int r0 = rg; r0 < sg.nchunks; r0 += NW * 8) {
+            uint4 v[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {  // (loads without a condition, see ChunkSource)
-                    const int rr = r0 + u * NW;
-                    const uint32_t w = p[static_cast<size_t>(opaque(static_cast<uint32_t>(rr < sg.nchunks ? rr : sg.nchunks - 1))) * NBW];
-                    v[u] = w & keep_mask(rr < sg.nchunks);
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) sum += v[u];
+            for (int u = 0; u < 8; ++u) {  // (loads without a condition, see ChunkSource)
+                const int rr = r0 + u * NW;
+                v[u] = p[static_cast<size_t>(opaque(static_cast<uint32_t>(rr < sg.nchunks ? rr : sg.nchunks - 1))) * (NBW / 4)];
             }
-            atomicAdd(&h[b], sum);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t keep = keep_mask(r0 + u * NW < sg.nchunks);
+                sum.x += v[u].x & keep;
+                sum.y += v[u].y & keep;
+                sum.z += v[u].z & keep;
+                sum.w += v[u].w & keep;
+            }
         }
+        atomicAdd(&h[c0 + col], sum.x);
+        atomicAdd(&h[c0 + col + 1], sum.y);
+        atomicAdd(&h[c0 + col + 2], sum.z);
+        atomicAdd(&h[c0 + col + 3], sum.w);
     }
     __syncthreads();
     static_assert(CTARGET <= BLOCK, "thread t has chunk t");
@@ -1934,7 +1963,7 @@ template <int VEC, bool WIDE>
 __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, const ChunkSource<VEC> &src, int c, uint32_t part, uint32_t sub,
                                           const Threshold &t, uint32_t count_t, uint32_t (&raw)[LU], int32_t (&id)[LU], EmitLds &l) {
     using R = typename Raw<VEC>::type;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t T = t.T, q = t.q, kout = static_cast<uint32_t>(sg.k);
     // Output offsets of this part = sums over the earlier chunks, and over the earlier parts of this
     // chunk, of (#keys above T, #keys equal to T).  Thread t takes chunk t.
@@ -2015,11 +2044,11 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
         const uint32_t cg = (lane < LU * NW) ? l.wcnt[buf][0][lane] : 0u;
         const uint32_t ce = (lane < LU * NW) ? l.wcnt[buf][1][lane] : 0u;
         const uint32_t ig = wave_incl_scan(cg), ie = wave_incl_scan(ce);
-        const uint32_t tg = __shfl(ig, 63), te = __shfl(ie, 63);
+        const uint32_t tg = lane_value(ig, 63), te = lane_value(ie, 63);
 #pragma unroll
         for (int j = 0; j < LU; ++j) {
-            const uint32_t gt_before = run_gt + __shfl(ig - cg, j * NW + w) + pre_gt[j];
-            const uint32_t eq_before = run_eq + __shfl(ie - ce, j * NW + w) + pre_eq[j];
+            const uint32_t gt_before = run_gt + lane_value(ig - cg, j * NW + w) + pre_gt[j];
+            const uint32_t eq_before = run_eq + lane_value(ie - ce, j * NW + w) + pre_eq[j];
             if (cls[j] == 2u || (cls[j] == 1u && eq_before < q)) {
                 const uint32_t pos = gt_before + (eq_before < q ? eq_before : q);
                 if (pos < kout) {
@@ -2418,7 +2447,7 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
     const int n = sg.n;
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const R *x = static_cast<const R *>(sg.x);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     // the whole tensor in one round of loads without conditions (see ChunkSource): an element past the end
     // reads the last one and is masked out
@@ -2484,7 +2513,7 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
         if (e * BLOCK < n) {  // uniform
             const int i = e * BLOCK + static_cast<int>(threadIdx.x);
             const int entry = e * NW + w;
-            const uint32_t before = __shfl((entry & 1) ? ex1 : ex0, entry >> 1);  // one entry for the whole wave
+            const uint32_t before = lane_value((entry & 1) ? ex1 : ex0, entry >> 1);  // one entry for the whole wave
             const uint32_t key = key_of<VEC>(raw[e]);
             const bool valid = i < n;
             const uint32_t gt_before = (before & 0xFFFFu) + (rk[e] & 0xFFFFu);
