@@ -1,7 +1,8 @@
 """Builds libadatopk.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree, and next to it
 libadatopk_measure.so: the same sources compiled with ADATOPK_MEASURE_BUILD, which adds the
 benchmark-only hooks of include/adatopk_measure.h (per-kernel dispatch timing, plain streaming
-kernels).  The product library carries none of them."""
+kernels).  The product library carries none of them.  _marshal.so is the Python extension that reads
+the arguments of the segmented calls (marshal.cpp, host code only)."""
 from __future__ import annotations
 
 import os
