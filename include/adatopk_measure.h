@@ -37,6 +37,16 @@ const char *adatopk_measure_stage_name(int32_t stage);
  * the last read are reported as -1.  Returns ADATOPK_OK or ADATOPK_ERUNTIME. */
 adatopk_status adatopk_measure_read(float *ms_out);
 
+/* For tests of the compress of a single tensor whose sample misled it: from now on the kernel that then makes
+ * the exact passes is launched without its last `missing_workgroups` workgroups, as if they started too late;
+ * those that are there do their chunks for them.  Wrong results for a tensor whose sample did not mislead.
+ * 0: all workgroups. */
+void adatopk_measure_judge(int32_t missing_workgroups);
+
+/* Byte offset in the workspace of the record of who worked: per chunk (256 uint32) 1 + the number of the workgroup
+ * that took it, 0 if none had to. */
+size_t adatopk_measure_judge_claims_offset(int64_t n_total, int32_t num_segments, adatopk_dtype dtype);
+
 /* Plain streaming kernels on `hip_stream`; all pointers are device memory, 16-byte
  * aligned; bytes must be a multiple of 16.
  *   copy:      dst[i] = src[i]                        (reads bytes, writes bytes)

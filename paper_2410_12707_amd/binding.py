@@ -64,6 +64,10 @@ def load_measure_library() -> ctypes.CDLL:
     lib.adatopk_measure_stage_name.restype = ctypes.c_char_p
     lib.adatopk_measure_read.argtypes = [p]
     lib.adatopk_measure_read.restype = i32
+    lib.adatopk_measure_judge.argtypes = [i32]
+    lib.adatopk_measure_judge.restype = None
+    lib.adatopk_measure_judge_claims_offset.argtypes = [ctypes.c_int64, i32, i32]
+    lib.adatopk_measure_judge_claims_offset.restype = sz
     lib.adatopk_measure_copy.argtypes = [p, p, sz, p]
     lib.adatopk_measure_copy.restype = i32
     lib.adatopk_measure_read_only.argtypes = [p, sz, p, p]
@@ -439,6 +443,14 @@ def measure_read():
     buf = (ctypes.c_float * n)()
     _check(lib.adatopk_measure_read(buf), "adatopk_measure_read")
     return [buf[i] for i in range(n)]
+
+
+def measure_judge(missing_workgroups: int) -> None:
+    load_measure_library().adatopk_measure_judge(int(missing_workgroups))
+
+
+def measure_judge_claims_offset(n_total: int, num_segments: int, dtype: torch.dtype) -> int:
+    return int(load_measure_library().adatopk_measure_judge_claims_offset(int(n_total), int(num_segments), _dtype_code(dtype)))
 
 
 def measure_copy(dst: torch.Tensor, src: torch.Tensor) -> None:

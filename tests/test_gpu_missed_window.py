@@ -1,0 +1,84 @@
+"""A single tensor whose sample misled it: k_judge then makes the exact passes in the launch that judges the
+window, with waits between its workgroups instead of kernel boundaries.  The results, against the oracle, and who
+did the work."""
+import numpy as np
+import pytest
+
+from oracle import adatopk_oracle as orc
+from paper_2410_12707_amd import workloads as wl
+from test_gpu_parity import ERR_RTOL, _sampled_elements
+
+pytestmark = pytest.mark.gpu
+
+
+def misled(n, dtype, scale, seed=321):
+    """Normal values, those that a sample may look at `scale` times as large."""
+    x = wl.small_case("normal", n, seed=seed, dtype="f32")
+    x[_sampled_elements(n, 4 if dtype == "f32" else 2)] *= np.float32(scale)
+    if dtype == "bf16":
+        return wl.f32_to_bf16_bits(x)
+    return x.astype(np.float16) if dtype == "f16" else x
+
+
+class Call:
+    """Device buffers of one compress call."""
+
+    def __init__(self, x, k):
+        import torch
+
+        import gpu_harness as H
+        from paper_2410_12707_amd import binding as B
+
+        self.d, self.k = H.to_device(x), k
+        self.idx = torch.full((k,), -7, dtype=torch.int32, device="cuda")
+        self.val = torch.zeros(k, dtype=self.d.dtype, device="cuda")
+        self.err = torch.full((1,), -1.0, dtype=torch.float32, device="cuda")
+        self.ws = B.new_workspace(x.size, 1, self.d.dtype)
+
+    def run(self):
+        from paper_2410_12707_amd import binding as B
+
+        B.adatopk_compress(self.d, self.k, self.idx, self.val, self.err, self.ws)
+
+    def held(self):
+        """The verdict on the window: the seventh word of the state record that opens the workspace."""
+        import torch
+
+        torch.cuda.synchronize()
+        return int(self.ws[:64].view(torch.int32)[6].item())
+
+    def check(self, x, label=None):
+        import torch
+
+        import gpu_harness as H
+
+        torch.cuda.synchronize()
+        ri, rv, re = orc.compress(x, self.k)
+        assert np.array_equal(H.to_host(self.idx), ri), label
+        assert np.array_equal(H.bits(H.to_host(self.val)), H.bits(rv)), label
+        assert H.same_err(H.to_host(self.err)[0], re, ERR_RTOL), label
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
+    # 128 chunks, 16 workgroups: the rest of the chunks is taken by those that wait, one at a time, so that none of
+    # them ends up with most (8 each if all were equally fast; claimed in sweeps, one had 65 and another 49)
+    import torch
+
+    from paper_2410_12707_amd import binding as B
+
+    n, chunks, workgroups = 1_048_576, 128, 16
+    x = misled(n, dtype, 64.0)
+    c = Call(x, n // 100)
+    at = B.measure_judge_claims_offset(n, 1, c.d.dtype)
+    with B.measuring():
+        try:
+            B.measure_judge(chunks - workgroups)
+            c.run()
+            assert c.held() == 0
+        finally:
+            B.measure_judge(0)
+    c.check(x, dtype)
+    owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
+    assert owner.min() >= 1 and owner.max() <= workgroups
+    assert np.bincount(owner).max() <= 3 * chunks // workgroups, np.bincount(owner)
