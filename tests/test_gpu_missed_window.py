@@ -82,3 +82,23 @@ def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
     owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
     assert owner.min() >= 1 and owner.max() <= workgroups
     assert np.bincount(owner).max() <= 3 * chunks // workgroups, np.bincount(owner)
+
+
+@pytest.mark.parametrize("percent", [10, 20])
+def test_exact_passes_use_the_whole_chip_when_lists_are_cut_into_parts(percent):
+    # two or four workgroups to a chunk: the exact passes' owners must not all be on the XCDs of the chunks' first
+    # parts (workgroups are dealt out over the eight XCDs in turn)
+    import torch
+
+    from paper_2410_12707_amd import binding as B
+
+    n, chunks = 25_165_824, 256
+    x = misled(n, "f32", 64.0)
+    c = Call(x, n * percent // 100)
+    at = B.measure_judge_claims_offset(n, 1, c.d.dtype)
+    c.run()
+    assert c.held() == 0
+    c.check(x, percent)
+    owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
+    assert owner.min() >= 1
+    assert np.unique((owner - 1) % 8).size == 8 and np.unique(owner).size >= chunks * 3 // 4, np.unique(owner)
