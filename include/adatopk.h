@@ -67,7 +67,9 @@ size_t adatopk_workspace_bytes(int64_t n_total, int32_t num_segments, adatopk_dt
  *   k             0 <= k <= n; k == 0 or n == 0 keep nothing
  *   idx_out       device, k int32: kept indices, ascending
  *   val_out       device, k values of type dt: val_out[j] = bits of dense[idx_out[j]]
- *   err_norm_out  device, 1 float, or NULL to skip the store
+ *   err_norm_out  device, 1 float, or NULL to skip the store.  NaN if the input holds a NaN that is dropped, or
+ *                 if the call could not be finished because its workspace was overwritten meanwhile (two calls
+ *                 at once on one workspace): idx_out and val_out are then not to be used
  *   workspace     device, 256-byte aligned, at least adatopk_workspace_bytes(n, 1, dt)
  * EINVAL: n < 0, k < 0, k > n, n >= 2^31, unknown dt, NULL where a buffer is needed,
  * misaligned pointer.  EWORKSPACE: workspace too small. */

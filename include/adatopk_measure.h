@@ -40,8 +40,9 @@ adatopk_status adatopk_measure_read(float *ms_out);
 /* For tests of the compress of a single tensor whose sample misled it: from now on the kernel that then makes
  * the exact passes is launched without its last `missing_workgroups` workgroups, as if they started too late;
  * those that are there do their chunks for them.  Wrong results for a tensor whose sample did not mislead.
- * 0: all workgroups. */
-void adatopk_measure_judge(int32_t missing_workgroups);
+ * 0: all workgroups.  wait_rounds: how often a workgroup looks for the others before it gives up (the call then
+ * ends with a NaN error norm); negative: as in the product library. */
+void adatopk_measure_judge(int32_t missing_workgroups, int32_t wait_rounds);
 
 /* Byte offset in the workspace of the record of who worked: per chunk (256 uint32) 1 + the number of the workgroup
  * that took it, 0 if none had to. */

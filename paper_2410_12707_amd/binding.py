@@ -64,7 +64,7 @@ def load_measure_library() -> ctypes.CDLL:
     lib.adatopk_measure_stage_name.restype = ctypes.c_char_p
     lib.adatopk_measure_read.argtypes = [p]
     lib.adatopk_measure_read.restype = i32
-    lib.adatopk_measure_judge.argtypes = [i32]
+    lib.adatopk_measure_judge.argtypes = [i32, i32]
     lib.adatopk_measure_judge.restype = None
     lib.adatopk_measure_judge_claims_offset.argtypes = [ctypes.c_int64, i32, i32]
     lib.adatopk_measure_judge_claims_offset.restype = sz
@@ -445,8 +445,8 @@ def measure_read():
     return [buf[i] for i in range(n)]
 
 
-def measure_judge(missing_workgroups: int) -> None:
-    load_measure_library().adatopk_measure_judge(int(missing_workgroups))
+def measure_judge(missing_workgroups: int = 0, wait_rounds: int = -1) -> None:
+    load_measure_library().adatopk_measure_judge(int(missing_workgroups), int(wait_rounds))
 
 
 def measure_judge_claims_offset(n_total: int, num_segments: int, dtype: torch.dtype) -> int:

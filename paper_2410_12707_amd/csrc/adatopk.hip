@@ -133,18 +133,19 @@ struct SegState {  // one per segment; 64 bytes
     uint32_t loB, shwB;   // window of the exact pass (likewise)
     uint32_t Bw, c_gtw;   // window bin that holds the k-th key, #keys in the bins above it (written by k_refine)
     uint32_t spec_held;   // the speculative pass bracketed the k-th key (written by k_hist1 or k_judge, one of which always runs)
-    uint32_t pad[9];
+    uint32_t failed;      // the exact passes gave up (k_judge): the call's pairs are not to be used
+    uint32_t pad[8];
 };
 static_assert(sizeof(SegState) == 64, "state record size");
 
 // The first eight words of a state record in two 16-byte loads (one memory round trip; field by field, the
 // window's fields are asked for only after spec_held has arrived).
 struct SegStateWords {
-    uint32_t loA, shwA, loB, shwB, Bw, c_gtw, spec_held;
+    uint32_t loA, shwA, loB, shwB, Bw, c_gtw, spec_held, failed;
 };
 __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
     const uint4 a = reinterpret_cast<const uint4 *>(st)[0], b = reinterpret_cast<const uint4 *>(st)[1];
-    return SegStateWords{a.x, a.y, a.z, a.w, b.x, b.y, b.z};
+    return SegStateWords{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 }
 
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
@@ -168,6 +169,7 @@ struct Launch {
     uint32_t cap;   // list slots per chunk (E / LIST_DIV)
     uint32_t sub;   // workgroups per chunk in the list kernels (1 .. MAXSUB): long candidate lists are cut into parts
     uint32_t idx64;
+    uint32_t wait_rounds;  // k_judge: rounds of waiting for other workgroups before it gives up
     uint32_t wire;  // outputs are wire messages in one buffer (idx_out): values follow the padded index section
     SegState *state;
     uint32_t *G3;                 // [MAXSEG][NB3] global histogram of the last digit
@@ -808,7 +810,10 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
     const SegDesc &sg = a.seg[s];
     const int c = g - sg.chunk_begin;
     const bool held = spec_holds(a, sg, sm);
-    if (c == 0 && threadIdx.x == 0) a.state[s].spec_held = held ? 1u : 0u;
+    if (c == 0 && threadIdx.x == 0) {
+        a.state[s].spec_held = held ? 1u : 0u;
+        a.state[s].failed = 0u;
+    }
     if (held) return;  // the speculative pass bracketed the k-th key: no exact pass is needed
 
     hist1_chunk<VEC, false>(a, sg, g, h, sm);
@@ -1323,6 +1328,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
             if (threadIdx.x == 0) {
                 a.state[s].loA = lo;
                 a.state[s].shwA = shw;
+                a.state[s].failed = 0u;
             }
         }
     } else {
@@ -1789,6 +1795,8 @@ __device__ __attribute__((noinline)) uint2 emit_dense_tiles(const ChunkSource<VE
     return make_uint2(run_gt, run_eq);
 }
 
+constexpr uint32_t QUIET_NAN = 0x7FC00000u;
+
 // What a part's placing needs to know of the tensor: the threshold key T, the quota q of keys equal to T
 // (the first q of them are kept), and where the per-part counts of keys above and equal to T are found.
 struct Threshold {
@@ -1924,7 +1932,7 @@ __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg
         }
     }
     const double tot = block_sum_f64(sum, smd);
-    if (threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = static_cast<float>(sqrt(tot));
+    if (threadIdx.x == 0) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], static_cast<float>(sqrt(tot)));  // (see give_up)
     __syncthreads();
 }
 
@@ -2087,6 +2095,10 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, sub, lo);
     // the tensor's last chunk is the short one, and the last part of a chunk the shortest
     const bool sums_error = c == sg.nchunks - 1 && part == sub - 1 && a.err_out != nullptr;
+    if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
+        if (sums_error && threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = __uint_as_float(QUIET_NAN);
+        return;
+    }
     // 16-bit types: thread t of that workgroup asks for chunk t's sum of squares below the window now, so that it
     // arrives behind the prologue instead of costing the error sum a memory round trip of its own at the end
     double below_t = 0.0;
@@ -2139,9 +2151,11 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
 //     chunk still there, and what is left is shared by all that wait.  (Claimed in one sweep, everything that had
 //     not started within the first polls was one workgroup's to the end: 8.1 ms instead of 0.35 for 25 M
 //     fp32 values of which a fifth is kept, on a GPU that nothing else used.)  So whatever the counter is waited
-//     up to is in the hands of running workgroups, and they all arrive; the number of polls is bounded all the same.
+//     up to is in the hands of running workgroups, and they all arrive; the number of polls is bounded all the
+//     same, so that the launch ends even if the counters are overwritten from outside (a workspace that
+//     two calls use at once).  The error norm is then NaN (give_up).
 constexpr int POLLS_BEFORE_HELP = 32;      // tens of us: far beyond the spread of workgroups that run side by side
-constexpr int MAX_POLL_ROUNDS = 1 << 18;   // seconds: never reached unless the counters are overwritten from outside
+constexpr int MAX_POLL_ROUNDS = 1 << 18;   // seconds
 struct Owned {
     uint32_t count;              // chunks this workgroup has claimed ...
     uint32_t arrived;
@@ -2160,9 +2174,9 @@ __device__ __forceinline__ void claim_chunk(JudgeSync *sync, uint32_t chunk, Own
 // Works on this workgroup's chunks, reports them, and waits until all `nchunks` have been through the pass,
 // helping with unclaimed ones.  work(chunk) is called by the whole workgroup.  False: gave up.
 template <typename Work>
-__device__ __forceinline__ bool exact_pass(JudgeSync *sync, int pass, uint32_t nchunks, Owned &o, Work &&work) {
+__device__ __forceinline__ bool exact_pass(JudgeSync *sync, int pass, uint32_t nchunks, uint32_t rounds, Owned &o, Work &&work) {
     uint32_t from = 0;
-    for (int round = 0; round < MAX_POLL_ROUNDS; ++round) {
+    for (uint32_t round = 0; round < rounds; ++round) {
         const uint32_t to = o.count;  // uniform
         for (uint32_t i = from; i < to; ++i) work(static_cast<uint32_t>(o.chunk[i]));
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every thread's stores have arrived ...
@@ -2191,6 +2205,20 @@ __device__ __forceinline__ bool exact_pass(JudgeSync *sync, int pass, uint32_t n
         __syncthreads();
     }
     return false;
+}
+
+// What is left of a call whose waits did not end: its error norm is NaN, the pairs are not to be used.  fp32: k_emit
+// stores it.  16-bit types: nothing follows this launch, and another workgroup may be past the waits and add up the norm.
+// Both store to where everybody sees it, this one behind the mark; the other looks for the mark behind its
+// norm (norm_or_nan) and then stores NaN as well.  Called by one thread.
+template <int VEC> __device__ __forceinline__ void give_up(const Launch &a, const SegDesc &sg) {
+    store_agent(&a.state[0].failed, 1u);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (VEC != TAG_F32 && a.err_out != nullptr) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], __uint_as_float(QUIET_NAN));
+}
+__device__ __forceinline__ void norm_or_nan(const Launch &a, const SegDesc &sg) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (load_agent(&a.state[0].failed) != 0) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], __uint_as_float(QUIET_NAN));
 }
 
 // The exact passes over the candidates of one chunk alone, for a k-th key above the window's bins: the window then
@@ -2308,17 +2336,20 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     if (own.count == 0) return;
     const bool above = pw.B == NBW - 1;  // the k-th key lies above the window's bins: the candidates are enough
     const uint32_t lo_list = lo;         // where the lists start
-    if (!exact_pass(sync, 0, nchunks, own, [&](uint32_t c) {
+    auto gave_up = [&]() {
+        if (threadIdx.x == 0) give_up<VEC>(a, sg);
+    };
+    if (!exact_pass(sync, 0, nchunks, a.wait_rounds, own, [&](uint32_t c) {
             const int ci = static_cast<int>(c);
             if (above) hist1_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, a.cnt[ci], 0, 1, lo_list), ci, h, sl.sm);
             else hist1_chunk<VEC, true>(a, sg, ci, h, sl.sm);
             __syncthreads();
         }))
-        return;
+        return gave_up();
     const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1, a.coarse1, sg.nchunks, 0, kout, h);
     lo = p1.B << SH1;
     shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;
-    if (!exact_pass(sync, 1, nchunks, own, [&](uint32_t c) {
+    if (!exact_pass(sync, 1, nchunks, a.wait_rounds, own, [&](uint32_t c) {
             const int ci = static_cast<int>(c);
             if (above) {
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, a.cnt[ci], 0, 1, lo_list), ci, lo, shw, h, sl.sm, sl.smd);
@@ -2331,7 +2362,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
             }
             __syncthreads();
         }))
-        return;
+        return gave_up();
     pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h);
     count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;
     for (uint32_t i = 0; i < own.count; ++i) {
@@ -2346,6 +2377,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
             src = chunk_source<VEC>(a, sg, c, load_agent(&a.cnt[c]), pp, sub, lo);
             first_entries();
             next_step(c, pp, sums_error);
+            if (sums_error && threadIdx.x == 0) norm_or_nan(a, sg);
             __syncthreads();  // the scratch changes hands
         }
     }
@@ -2932,6 +2964,7 @@ bool g_events_made = false;
 hipEvent_t g_start[NSTAGE], g_stop[NSTAGE];
 bool g_ran[NSTAGE];  // launched, with events, since the last read
 int32_t g_judge_missing = 0;  // workgroups that k_judge is launched without
+int32_t g_judge_rounds = -1;  // its rounds of waiting, if not negative
 #endif
 
 template <typename K, typename... Args>
@@ -3131,6 +3164,10 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.L_val = ws + cv.L_val;
         a.idx_out = idx_out;
         a.idx64 = idx_bytes == 8 ? 1u : 0u;
+        a.wait_rounds = MAX_POLL_ROUNDS;
+#ifdef ADATOPK_MEASURE_BUILD
+        if (g_judge_rounds >= 0) a.wait_rounds = static_cast<uint32_t>(g_judge_rounds);
+#endif
         a.wire = out.wire ? 1u : 0u;
         a.val_out = val_out;
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
@@ -3641,7 +3678,10 @@ adatopk_status adatopk_measure_read(float *ms_out) {
     return ADATOPK_OK;
 }
 
-void adatopk_measure_judge(int32_t missing_workgroups) { g_judge_missing = missing_workgroups; }
+void adatopk_measure_judge(int32_t missing_workgroups, int32_t wait_rounds) {
+    g_judge_missing = missing_workgroups;
+    g_judge_rounds = wait_rounds;
+}
 
 size_t adatopk_measure_judge_claims_offset(int64_t n_total, int32_t num_segments, adatopk_dtype dtype) {
     int64_t max_chunks, list_slots;

@@ -77,7 +77,7 @@ def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
             c.run()
             assert c.held() == 0
         finally:
-            B.measure_judge(0)
+            B.measure_judge()
     c.check(x, dtype)
     owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
     assert owner.min() >= 1 and owner.max() <= workgroups
@@ -102,3 +102,32 @@ def test_exact_passes_use_the_whole_chip_when_lists_are_cut_into_parts(percent):
     owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
     assert owner.min() >= 1
     assert np.unique((owner - 1) % 8).size == 8 and np.unique(owner).size >= chunks * 3 // 4, np.unique(owner)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("missing,rounds", [(0, 0), (112, 1)])
+def test_giving_up_is_marked_by_the_error_norm(dtype, missing, rounds):
+    # a launch that stops waiting for its other workgroups (here because it is told not to wait at all, or not long
+    # enough to do the chunks of those that do not start) must not pass for a good one; the next call is
+    import torch
+
+    from paper_2410_12707_amd import binding as B
+
+    n = 1_048_576
+    x = misled(n, dtype, 64.0)
+    c = Call(x, n // 100)
+    code = ["f32", "bf16", "f16"].index(dtype)
+    wire = torch.zeros(B.adatopk_wire_bytes(c.k, code, 4), dtype=torch.uint8, device="cuda")
+    with B.measuring():
+        try:
+            B.measure_judge(missing, rounds)
+            c.run()
+            assert c.held() == 0 and np.isnan(c.err.cpu().numpy()[0])
+            B.adatopk_compress_wire(c.d, c.k, 4, 100.0, wire, c.ws)
+            message = wire.cpu().numpy().tobytes()
+            assert np.isnan(B.adatopk_wire_parse_header(message, len(message)).err_norm)
+        finally:
+            B.measure_judge()
+    c.run()
+    assert c.held() == 0
+    c.check(x, dtype)
