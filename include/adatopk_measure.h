@@ -44,9 +44,14 @@ adatopk_status adatopk_measure_read(float *ms_out);
  * ends with a NaN error norm); negative: as in the product library. */
 void adatopk_measure_judge(int32_t missing_workgroups, int32_t wait_rounds);
 
-/* Byte offset in the workspace of the record of who worked: per chunk (256 uint32) 1 + the number of the workgroup
- * that took it, 0 if none had to. */
-size_t adatopk_measure_judge_claims_offset(int64_t n_total, int32_t num_segments, adatopk_dtype dtype);
+/* Byte offset in the workspace of a call over `n_total` elements of
+ *   ADATOPK_MEASURE_CLAIMS        (a single tensor whose sample misled it) who worked: per chunk 1 + the number of the
+ *                                 workgroup that took it, 0 if none had to (uint32)
+ *   ADATOPK_MEASURE_CHUNK_COUNTS  per chunk its candidates, more than a quarter of the chunk's length: the chunk
+ *                                 has no list (uint32) */
+#define ADATOPK_MEASURE_CLAIMS 0
+#define ADATOPK_MEASURE_CHUNK_COUNTS 1
+size_t adatopk_measure_workspace_offset(int32_t what, int64_t n_total, int32_t num_segments, adatopk_dtype dtype);
 
 /* Plain streaming kernels on `hip_stream`; all pointers are device memory, 16-byte
  * aligned; bytes must be a multiple of 16.

@@ -66,8 +66,8 @@ def load_measure_library() -> ctypes.CDLL:
     lib.adatopk_measure_read.restype = i32
     lib.adatopk_measure_judge.argtypes = [i32, i32]
     lib.adatopk_measure_judge.restype = None
-    lib.adatopk_measure_judge_claims_offset.argtypes = [ctypes.c_int64, i32, i32]
-    lib.adatopk_measure_judge_claims_offset.restype = sz
+    lib.adatopk_measure_workspace_offset.argtypes = [i32, ctypes.c_int64, i32, i32]
+    lib.adatopk_measure_workspace_offset.restype = sz
     lib.adatopk_measure_copy.argtypes = [p, p, sz, p]
     lib.adatopk_measure_copy.restype = i32
     lib.adatopk_measure_read_only.argtypes = [p, sz, p, p]
@@ -449,8 +449,11 @@ def measure_judge(missing_workgroups: int = 0, wait_rounds: int = -1) -> None:
     load_measure_library().adatopk_measure_judge(int(missing_workgroups), int(wait_rounds))
 
 
-def measure_judge_claims_offset(n_total: int, num_segments: int, dtype: torch.dtype) -> int:
-    return int(load_measure_library().adatopk_measure_judge_claims_offset(int(n_total), int(num_segments), _dtype_code(dtype)))
+MEASURE_CLAIMS, MEASURE_CHUNK_COUNTS = 0, 1
+
+
+def measure_workspace_offset(what: int, n_total: int, num_segments: int, dtype: torch.dtype) -> int:
+    return int(load_measure_library().adatopk_measure_workspace_offset(int(what), int(n_total), int(num_segments), _dtype_code(dtype)))
 
 
 def measure_copy(dst: torch.Tensor, src: torch.Tensor) -> None:

@@ -2221,9 +2221,11 @@ __device__ __forceinline__ void norm_or_nan(const Launch &a, const SegDesc &sg) 
     if (load_agent(&a.state[0].failed) != 0) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], __uint_as_float(QUIET_NAN));
 }
 
-// The exact passes over the candidates of one chunk alone, for a k-th key above the window's bins: the window then
-// started below it, so the lists (or, for a chunk without one, the input from `src.lo` up) hold all that counts.
-// f(raw, candidate) for every entry; the whole workgroup takes part.
+// The exact passes over the list of one chunk alone, for a k-th key above the window's bins: the window then
+// started below it, so the lists hold all that counts.  (A chunk without a list is streamed from the input as for
+// any other missed window, which also gives it a list if its candidates fit one now.  Read entry by entry like a
+// list, the input came in at a quarter of the rate, here and in k_emit: 25 M fp32 values of which nearly all were
+// candidates, 140 + 43 instead of 68 + 6 us.)  f(raw, candidate) for every entry; the whole workgroup takes part.
 template <int VEC, typename F> __device__ __forceinline__ void each_candidate(const ChunkSource<VEC> &src, F &&f) {
     for (uint32_t i0 = 0; i0 < src.len; i0 += LU * BLOCK) {
         uint32_t r[LU];
@@ -2341,7 +2343,8 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     };
     if (!exact_pass(sync, 0, nchunks, a.wait_rounds, own, [&](uint32_t c) {
             const int ci = static_cast<int>(c);
-            if (above) hist1_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, a.cnt[ci], 0, 1, lo_list), ci, h, sl.sm);
+            const uint32_t listed = a.cnt[ci];
+            if (above && listed <= a.cap) hist1_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, listed, 0, 1, lo_list), ci, h, sl.sm);
             else hist1_chunk<VEC, true>(a, sg, ci, h, sl.sm);
             __syncthreads();
         }))
@@ -2351,8 +2354,9 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;
     if (!exact_pass(sync, 1, nchunks, a.wait_rounds, own, [&](uint32_t c) {
             const int ci = static_cast<int>(c);
-            if (above) {
-                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, a.cnt[ci], 0, 1, lo_list), ci, lo, shw, h, sl.sm, sl.smd);
+            const uint32_t listed = a.cnt[ci];
+            if (above && listed <= a.cap) {
+                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, listed, 0, 1, lo_list), ci, lo, shw, h, sl.sm, sl.smd);
             } else {
                 uint32_t cur[St::SLOTS];
                 const int64_t beg = static_cast<int64_t>(c) * a.E;
@@ -3683,10 +3687,11 @@ void adatopk_measure_judge(int32_t missing_workgroups, int32_t wait_rounds) {
     g_judge_rounds = wait_rounds;
 }
 
-size_t adatopk_measure_judge_claims_offset(int64_t n_total, int32_t num_segments, adatopk_dtype dtype) {
+size_t adatopk_measure_workspace_offset(int32_t what, int64_t n_total, int32_t num_segments, adatopk_dtype dtype) {
     int64_t max_chunks, list_slots;
     bounds_for(n_total, num_segments, &max_chunks, &list_slots);
-    return carve(max_chunks, list_slots, num_segments, dtype).G3 + sizeof(uint32_t) * NB3 + offsetof(JudgeSync, claim);
+    const Carve c = carve(max_chunks, list_slots, num_segments, dtype);
+    return what == ADATOPK_MEASURE_CLAIMS ? c.G3 + sizeof(uint32_t) * NB3 + offsetof(JudgeSync, claim) : c.cnt;
 }
 
 adatopk_status adatopk_measure_copy(void *dst, const void *src, size_t bytes, void *hip_stream) {

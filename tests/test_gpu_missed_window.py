@@ -47,6 +47,15 @@ class Call:
         torch.cuda.synchronize()
         return int(self.ws[:64].view(torch.int32)[6].item())
 
+    def words(self, what, count):
+        """`count` words of the workspace (see adatopk_measure_workspace_offset)."""
+        import torch
+
+        from paper_2410_12707_amd import binding as B
+
+        at = B.measure_workspace_offset(what, self.d.numel(), 1, self.d.dtype)
+        return self.ws[at:at + 4 * count].view(torch.int32).cpu().numpy()
+
     def check(self, x, label=None):
         import torch
 
@@ -63,14 +72,11 @@ class Call:
 def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
     # 128 chunks, 16 workgroups: the rest of the chunks is taken by those that wait, one at a time, so that none of
     # them ends up with most (8 each if all were equally fast; claimed in sweeps, one had 65 and another 49)
-    import torch
-
     from paper_2410_12707_amd import binding as B
 
     n, chunks, workgroups = 1_048_576, 128, 16
     x = misled(n, dtype, 64.0)
     c = Call(x, n // 100)
-    at = B.measure_judge_claims_offset(n, 1, c.d.dtype)
     with B.measuring():
         try:
             B.measure_judge(chunks - workgroups)
@@ -79,7 +85,7 @@ def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
         finally:
             B.measure_judge()
     c.check(x, dtype)
-    owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
+    owner = c.words(B.MEASURE_CLAIMS, chunks)
     assert owner.min() >= 1 and owner.max() <= workgroups
     assert np.bincount(owner).max() <= 3 * chunks // workgroups, np.bincount(owner)
 
@@ -88,18 +94,15 @@ def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
 def test_exact_passes_use_the_whole_chip_when_lists_are_cut_into_parts(percent):
     # two or four workgroups to a chunk: the exact passes' owners must not all be on the XCDs of the chunks' first
     # parts (workgroups are dealt out over the eight XCDs in turn)
-    import torch
-
     from paper_2410_12707_amd import binding as B
 
     n, chunks = 25_165_824, 256
     x = misled(n, "f32", 64.0)
     c = Call(x, n * percent // 100)
-    at = B.measure_judge_claims_offset(n, 1, c.d.dtype)
     c.run()
     assert c.held() == 0
     c.check(x, percent)
-    owner = c.ws[at:at + 4 * chunks].view(torch.int32).cpu().numpy()
+    owner = c.words(B.MEASURE_CLAIMS, chunks)
     assert owner.min() >= 1
     assert np.unique((owner - 1) % 8).size == 8 and np.unique(owner).size >= chunks * 3 // 4, np.unique(owner)
 
@@ -131,3 +134,46 @@ def test_giving_up_is_marked_by_the_error_norm(dtype, missing, rounds):
     c.run()
     assert c.held() == 0
     c.check(x, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_chunks_that_were_all_candidates_get_lists_of_the_second_window(dtype):
+    # the sample put the window far too low: nearly every element was a candidate, no chunk has a list.  The exact
+    # passes read the input and leave lists of the few that are candidates now; the steps that follow read those
+    from paper_2410_12707_amd import binding as B
+
+    n, chunk = 4_200_003, 24576
+    x = misled(n, dtype, 1.0 / 64.0)
+    c = Call(x, n // 100)
+    c.run()
+    assert c.held() == 0
+    c.check(x, dtype)
+    assert c.words(B.MEASURE_CHUNK_COUNTS, -(-n // chunk)).max() <= chunk // 4
+
+
+@pytest.mark.parametrize("dtype,power,scale", [("f32", 1.0, 1e-3), ("f16", 4.0, 1e-9)])
+@pytest.mark.parametrize("n", [1_048_576, 4_200_003])
+def test_kth_key_above_the_window_is_found_among_the_candidates(dtype, power, scale, n):
+    # tails so heavy that the k-th key lies beyond the window's bins although the sample is as good as any: the
+    # chunks' lists hold all that counts, and the exact passes go over them alone
+    import torch
+
+    from paper_2410_12707_amd import binding as B
+
+    rng = np.random.default_rng(77)
+    k = n // 1000
+    u = rng.random(n, dtype=np.float32)
+    x = (np.float32(scale) * np.power(u + np.float32(1e-7), np.float32(-power)) * rng.choice(np.float32([-1, 1]), n)).astype(np.float32)
+    if dtype == "f16":
+        x = np.clip(x, -6e4, 6e4).astype(np.float16)
+    c = Call(x, k)
+    c.run()
+    assert c.held() == 0
+    c.check(x, dtype)
+    lo, shift = (int(v) for v in c.ws[:8].view(torch.int32).cpu().numpy())
+    kept = np.abs(c.val.cpu().numpy())
+    kth = int(kept.min().view(np.uint32 if dtype == "f32" else np.uint16)) << (0 if dtype == "f32" else 16)
+    assert kth >= lo + (2047 << shift)  # beyond the window's bins
+    chunk = -(-(-(-n // 256)) // 8192) * 8192
+    counts = c.words(B.MEASURE_CHUNK_COUNTS, -(-n // chunk))
+    assert counts.max() <= chunk // 4 and counts.sum() >= k  # every chunk has its list
