@@ -1168,8 +1168,8 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
 // What the workgroups of k_judge (further down) share, cleared by the scan in front of it: in the last-digit
 // histograms of tensors 1 and up, which a launch of one tensor does not use.
 struct JudgeSync {
-    uint32_t done[2][64];         // chunks that have been through an exact pass; each counter on cache lines of its own
-    uint32_t claim[CTARGET_ONE];  // 1 + the workgroup that has taken the chunk, 0: nobody has
+    uint32_t done[2][CTARGET_ONE];  // per exact pass and chunk: nonzero once the chunk has been through it
+    uint32_t claim[CTARGET_ONE];    // 1 + the workgroup that has taken the chunk, 0: nobody has
 };
 static_assert(sizeof(JudgeSync) <= sizeof(uint32_t) * NB3 * (MAXSEG - 1), "fits behind tensor 0's histogram");
 __device__ __forceinline__ JudgeSync *judge_sync(const Launch &a) { return reinterpret_cast<JudgeSync *>(a.G3 + NB3); }
@@ -2135,25 +2135,33 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
 // ahead at once: refine_part (fp32; k_emit follows), or emit_part (16-bit types, whose rows alone give the
 // threshold and the offsets; nothing follows).  Otherwise the two exact passes run first, in this same launch:
 // over the candidates alone if the k-th key lies above the window's bins (heavy tails and small samples: the bins
-// span a quarter of a binade at most), over the input if fewer than k keys reached the window.
+// span a quarter of an fp32 binade at most, 2047 patterns of a 16-bit type), over the input if fewer than k keys reached
+// the window.
 // As launches of their own (k_hist1 and k_scan, which a batch of tensors still has) they returned at once in
-// nearly every call and cost 2.4 us each: a bf16 tensor of 26 M elements 46.5 -> 42.1 us without them.
-// (Taking k_emit in as well, behind a third wait, costs an fp32 tensor 3 us more than its launch does.)
+// nearly every call of independent values and cost 2.4 us each: a bf16 tensor of 26 M elements 46.5 -> 42.1 us
+// without them.  A window that misses pays for it: a wait is 3.3 us from the last store to the last workgroup's
+// notice, more than a launch.  The whole compress of fp32 values, 1 % kept, as launches / as waits: 25 M held 46 / 39 us,
+// missed 81 / 87; 4.9 M held 33 / 25, missed 42 / 48; 25 M at 10 % (lists in two parts, one workgroup of the two
+// makes the exact passes) held 65 / 59, missed 103 / 121.  Values with a scale per run of 1600, standard deviation
+// 0.5 of its logarithm, miss in three calls of eight and come out at 62 / 52 us on average; with 1.0 they miss in seven,
+// 91 / 88.  (Taking k_emit in as well, behind a third wait, costs an fp32 tensor 3 us more than its launch does.)
 //
 // The exact passes are separated by waits for the other workgroups' stores instead of kernel boundaries:
 //   - what one workgroup hands to another goes through store_agent / atomics; a workgroup lets its stores
-//     drain (s_waitcnt) before it adds to the pass's counter.  No cache is written back for it: an
-//     agent-scope release fence would write back the XCD's L2, 1.5 us per workgroup, serialised;
+//     drain (s_waitcnt) before it marks its chunks.  No cache is written back for it: an
+//     agent-scope release fence would write back the XCD's L2, 1.5 us per workgroup, serialised.  A mark per
+//     chunk, all of them looked at by one wavefront: one counter that every workgroup added to and polled made a
+//     wait 6 to 9 us (bytes or longer pauses between the looks change nothing, or make it longer);
 //   - nobody depends on a workgroup that has not started.  Every chunk is claimed by an atomic before it is
 //     worked on; its claimer then works through the pass without waiting.  A workgroup that waits long
 //     claims a chunk that is left (its home workgroup is not running: another stream has the compute
 //     units), works on it and looks again, one chunk at a time: a home workgroup that starts meanwhile finds its
 //     chunk still there, and what is left is shared by all that wait.  (Claimed in one sweep, everything that had
 //     not started within the first polls was one workgroup's to the end: 8.1 ms instead of 0.35 for 25 M
-//     fp32 values of which a fifth is kept, on a GPU that nothing else used.)  So whatever the counter is waited
-//     up to is in the hands of running workgroups, and they all arrive; the number of polls is bounded all the
-//     same, so that the launch ends even if the counters are overwritten from outside (a workspace that
-//     two calls use at once).  The error norm is then NaN (give_up).
+//     fp32 values of which a fifth is kept, on a GPU that nothing else used.)  So whatever is waited for is in
+//     the hands of running workgroups, and they all arrive; the number of polls is bounded all the same, so that
+//     the launch ends even if the marks are overwritten from outside (a workspace that two calls use at
+//     once).  The error norm is then NaN (give_up).
 constexpr int POLLS_BEFORE_HELP = 32;      // tens of us: far beyond the spread of workgroups that run side by side
 constexpr int MAX_POLL_ROUNDS = 1 << 18;   // seconds
 struct Owned {
@@ -2171,29 +2179,52 @@ __device__ __forceinline__ void claim_chunk(JudgeSync *sync, uint32_t chunk, Own
         o.chunk[o.count++] = static_cast<uint16_t>(chunk);
 }
 
+// The launch's arguments once more, as if from another address: what is read through the result is read again where it
+// is used instead of being kept, in a scalar register or in a lane of a vector register, from one phase of a long kernel
+// to the next.  (The vector registers that this takes up push a tile's values to scratch memory, and a reload from
+// there waits for the tiles ahead: exact passes at a fifth kept 115 -> 93 us.  A function that is not inlined
+// keeps its registers apart but saves half of its caller's, 37 MB of scratch stores over the grid, 20 us.)
+template <typename T> using ArgsPtr = const T __attribute__((address_space(4))) *;
+__device__ __forceinline__ const Launch &args_again() {
+    ArgsPtr<Launch> p = (ArgsPtr<Launch>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Launch *)p;
+}
+
 // Works on this workgroup's chunks, reports them, and waits until all `nchunks` have been through the pass,
 // helping with unclaimed ones.  work(chunk) is called by the whole workgroup.  False: gave up.
 template <typename Work>
-__device__ __forceinline__ bool exact_pass(JudgeSync *sync, int pass, uint32_t nchunks, uint32_t rounds, Owned &o, Work &&work) {
+__device__ __forceinline__ bool exact_pass(int pass, uint32_t nchunks, Owned &o, Work &&work) {
     uint32_t from = 0;
-    for (uint32_t round = 0; round < rounds; ++round) {
+    for (uint32_t round = 0; round < args_again().wait_rounds; ++round) {
         const uint32_t to = o.count;  // uniform
         for (uint32_t i = from; i < to; ++i) work(static_cast<uint32_t>(o.chunk[i]));
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every thread's stores have arrived ...
         __syncthreads();
-        if (threadIdx.x == 0) {                           // ... before the chunks are reported
-            if (to != from) __hip_atomic_fetch_add(&sync->done[pass][0], to - from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            uint32_t seen = load_agent(&sync->done[pass][0]);
+        JudgeSync *sync = judge_sync(args_again());
+        if (threadIdx.x < 64) {                           // ... before the chunks are marked, by one wavefront
+            const uint32_t lane = threadIdx.x;
+            for (uint32_t i = from + lane; i < to; i += 64) store_agent(&sync->done[pass][o.chunk[i]], 1u);
             // (one that has just helped looks for the next chunk at once)
-            for (int p = 0; p < (to != from && round != 0 ? 1 : POLLS_BEFORE_HELP) && seen < nchunks; ++p) {
+            const int polls = to != from && round != 0 ? 1 : POLLS_BEFORE_HELP;
+            bool all;
+            for (int p = 0;; ++p) {
+                uint32_t missing = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < CTARGET_ONE; i += 64)  // (the marks behind the last chunk's are there, and zero)
+                    missing |= load_agent(&sync->done[pass][i + lane]) == 0 && i + lane < nchunks ? 1u : 0u;
+                all = __ballot(missing != 0) == 0;
+                if (all || p >= polls) break;
                 __builtin_amdgcn_s_sleep(1);
-                seen = load_agent(&sync->done[pass][0]);
             }
-            o.arrived = seen >= nchunks ? 1u : 0u;
-            o.help = nchunks;
-            // Rows of an earlier pass or call may be in this XCD's L2 and this compute unit's L1.  One wavefront drops
-            // them for all: every wavefront doing it kept the caches busy for 8 to 13 us (now 2).
-            if (o.arrived) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            // The first window's rows, which this launch has read, may be in this XCD's L2 and this compute unit's L1.
+            // One wavefront drops them for all: every wavefront doing it kept the caches busy for 8 to 13 us (now 2).
+            // (Nobody has read what the first pass stores, since the caches were emptied for this launch.)
+            if (all && pass != 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (lane == 0) {
+                o.arrived = all ? 1u : 0u;
+                o.help = nchunks;
+            }
         }
         from = to;
         __syncthreads();
@@ -2261,27 +2292,129 @@ __device__ __forceinline__ void rewindow_candidates(const Launch &a, const Chunk
     store_rows<NBW, NCW, true>(hw, a.rowsW, a.coarseW, g, sm);
 }
 
-template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) void k_judge(Launch a) {
+// LDS of k_judge.
+struct JudgeLds {
+    ScanLds sl;
+    EmitLds el;
+    Owned own;
+};
+
+// k_judge for a sample that misled: the two exact passes, then the next step on the chunks this workgroup owns.
+// `above`: the k-th key lies above the window's bins.
+template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(JudgeLds &l, bool above) {
+    const Launch &a0 = args_again();
     using St = Stream<VEC>;
     constexpr int DEPTH = WIDE ? 3 : 2;  // see scan_chunk
-    __shared__ ScanLds sl;
-    __shared__ EmitLds el;
-    __shared__ Owned own;
-    uint32_t *h = sl.smem;
+    uint32_t *h = l.sl.smem;
+    const uint32_t nchunks = static_cast<uint32_t>(a0.seg[0].nchunks);
+    const uint32_t lo_list = a0.state[0].loA;  // where the lists start
+
+    // The first workgroups of the grid take a chunk each, whatever the number of parts: the grid is dealt out over the
+    // XCDs in turn, and the workgroups of the chunks' first parts, every second or fourth, all lie on half or a
+    // quarter of them (25 M fp32 values, a tenth kept: 132 us in this kernel, from all XCDs 98; a fifth kept: 348, 115).
+    if (threadIdx.x == 0) {
+        l.own.count = 0;
+        if (blockIdx.x < nchunks) claim_chunk(judge_sync(a0), blockIdx.x, l.own);
+    }
+    __syncthreads();
+    if (l.own.count == 0) return;
+    auto gave_up = [&]() {
+        const Launch &a = args_again();
+        if (threadIdx.x == 0) give_up<VEC>(a, a.seg[0]);
+    };
+    if (!exact_pass(0, nchunks, l.own, [&](uint32_t c) {
+            const Launch &a = args_again();
+            const int ci = static_cast<int>(c);
+            const uint32_t listed = a.cnt[ci];
+            if (above && listed <= a.cap) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, h, l.sl.sm);
+            else hist1_chunk<VEC, true>(a, a.seg[0], ci, h, l.sl.sm);
+            __syncthreads();
+        }))
+        return gave_up();
+    // (the first tile of the first chunk does not depend on the bucket search: see k_scan)
+    uint32_t cur[St::SLOTS];
+    auto first_tile = [&](uint32_t c) {
+        const Launch &a = args_again();
+        const SegDesc &sg = a.seg[0];
+        const int64_t beg = static_cast<int64_t>(c) * a.E;
+        if ((sg.flags & FLAG_ALIGNED4) && (beg + a.E < sg.n ? a.E : sg.n - beg) >= TILE) St::load_fast(sg.x, beg, cur);
+    };
+    const uint32_t first_chunk = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[0])));
+    const Launch &a1 = args_again();
+    const ColumnPick p1 = column_pick<NB1, NC1, 16>(a1.rows1, a1.coarse1, a1.seg[0].nchunks, 0, static_cast<uint32_t>(a1.seg[0].k), h, [&]() { first_tile(first_chunk); });
+    const uint32_t lo = p1.B << SH1;
+    const uint32_t shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;
+    if (!exact_pass(1, nchunks, l.own, [&](uint32_t c) {
+            const Launch &a = args_again();
+            const int ci = static_cast<int>(c);
+            const uint32_t listed = a.cnt[ci];
+            if (above && listed <= a.cap) {
+                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
+            } else {
+                if (c != first_chunk) first_tile(c);
+                scan_chunk<VEC, false, DEPTH, true>(a, a.seg[0], ci, lo, shw, cur, l.sl);
+            }
+            __syncthreads();
+        }))
+        return gave_up();
+    const Launch &a = args_again();
+    const SegDesc &sg = a.seg[0];
+    const uint32_t kout = static_cast<uint32_t>(sg.k);
+    const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;
+    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h);
+    const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;
+    for (uint32_t i = 0; i < l.own.count; ++i) {
+        const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[i]));
+        const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(load_agent(&a.cnt[c]))));
+        uint32_t raw[LU];
+        if constexpr (VEC == TAG_F32) {
+            if (c == 0 && threadIdx.x == 0) {
+                a.state[0].loB = lo;
+                a.state[0].shwB = shw;
+                a.state[0].Bw = pw.B;
+                a.state[0].c_gtw = pw.above;
+            }
+            for (uint32_t pp = 0; pp < sub; ++pp) {
+                const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, pp, sub, lo);
+                if (src.len == 0) continue;
+#pragma unroll
+                for (int j = 0; j < LU; ++j) raw[j] = src.raw(j * BLOCK + threadIdx.x);
+                refine_part<VEC, WIDE>(a, 0, src, static_cast<size_t>(c) * sub + pp, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
+                __syncthreads();  // the scratch changes hands
+            }
+        } else {
+            const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, 0, 1, lo);
+            int32_t id[LU];
+            load_entries<VEC>(src, 0, raw, id);
+            const Threshold t = threshold_16(a, pw, kout, lo, shw);
+            if (c == sg.nchunks - 1 && a.err_out != nullptr) {
+                const double below_t = threadIdx.x < nchunks ? a.chunk_err[threadIdx.x] : 0.0;
+                error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
+                if (threadIdx.x == 0) norm_or_nan(a, sg);
+            }
+            emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
+            __syncthreads();  // the scratch changes hands
+        }
+    }
+}
+
+template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) void k_judge(Launch a) {
+    __shared__ JudgeLds l;
+    uint32_t *h = l.sl.smem;
     static_assert(NBW + 1 <= SCAN_SMEM_WORDS && NCW + 2 * (NBW / NCW) <= SCAN_SMEM_WORDS, "shared scratch fits");
 
     const SegDesc &sg = a.seg[0];
     const uint32_t nchunks = static_cast<uint32_t>(sg.nchunks), kout = static_cast<uint32_t>(sg.k);
     const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;  // 16-bit types: one part per chunk (their counts are per chunk)
-    const int home = static_cast<int>(blockIdx.x / sub);
+    const int c = static_cast<int>(blockIdx.x / sub);
     const uint32_t part = blockIdx.x % sub;
     const SegStateWords stw = read_state(&a.state[0]);
-    uint32_t lo = stw.loA, shw = stw.shwA;
-    uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;  // candidates of chunk threadIdx.x
-    ChunkSource<VEC> src = chunk_source<VEC>(a, sg, home, a.cnt[home], part, sub, lo);
+    const uint32_t lo = stw.loA, shw = stw.shwA;
+    const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;  // candidates of chunk threadIdx.x
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, a.cnt[c], part, sub, lo);
     double below_t = 0.0;  // 16-bit types, the workgroup that adds up the error norm: see k_emit
-    const bool last_home = VEC != TAG_F32 && home == sg.nchunks - 1 && a.err_out != nullptr;
-    if (last_home && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
+    const bool sums_error = VEC != TAG_F32 && c == sg.nchunks - 1 && a.err_out != nullptr;
+    if (sums_error && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
 
     uint32_t raw[LU];
     int32_t id[LU];
@@ -2294,96 +2427,30 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
         }
     };
     // The exact passes overwrite the rows, and they do not wait for a workgroup that starts late: it could judge by
-    // rows of the second window.  That pass begins when all chunks have been through the first, so a count of those
-    // taken after the rows were read tells; after the coarse rows is enough, unless the pick is in their last interval.
+    // rows of the second window.  That pass begins when all chunks have been through the first, so a chunk's mark
+    // looked at after the rows were read tells; after the coarse rows is enough, unless the pick is in their last interval.
     JudgeSync *sync = judge_sync(a);
     uint32_t exact_seen = 0;
-    ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h, first_entries,
-                                          [&]() { exact_seen = load_agent(&sync->done[0][0]); });
+    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h, first_entries,
+                                                [&]() { exact_seen = load_agent(&sync->done[0][0]); });
     if (pw.B < NBW - 1 && pw.B >= NBW - NBW / NCW) exact_seen = load_agent(&sync->done[0][0]);  // uniform
     // held: at least k keys reached the window, fewer than k its open-ended last bin
     const bool held = pw.B < NBW - 1 && __ballot(exact_seen != 0) == 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.state[0].spec_held = held ? 1u : 0u;
-
-    // Straight-line code for the window that held; the same step once more for the other case, in a loop over
-    // the chunks (one loop for both kept the registers of either alive in it: 37 instead of 30 us for an fp16
-    // tensor of 6.5 M elements).
-    auto next_step = [&](int c, uint32_t pp, bool sums_error) {
-        if constexpr (VEC == TAG_F32) {
-            if (c == 0 && pp == 0 && threadIdx.x == 0) {
-                a.state[0].Bw = pw.B;
-                a.state[0].c_gtw = pw.above;
-            }
-            if (src.len != 0) refine_part<VEC, WIDE>(a, 0, src, static_cast<size_t>(c) * sub + pp, pw.B, lo, shw, raw, h, sl.sm, sl.smd);
-        } else {
-            const Threshold t = threshold_16(a, pw, kout, lo, shw);
-            if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, el.smd);
-            emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, el);
-        }
-    };
-    if (__builtin_expect(held, 1)) {
-        next_step(home, part, last_home);
+    if (__builtin_expect(!held, 0)) {
+        judge_missed<VEC, WIDE>(l, pw.B == NBW - 1);
         return;
     }
-
-    // The sample misled: the two exact passes, then the same step on the chunks owned from here on.  The first
-    // workgroups of the grid take a chunk each, whatever the number of parts: the grid is dealt out over the XCDs
-    // in turn, and the workgroups of the chunks' first parts, every second or fourth, all lie on half or a quarter
-    // of them (25 M fp32 values, a tenth kept: 132 us in this kernel, from all XCDs 98; a fifth kept: 348, 115).
-    if (threadIdx.x == 0) {
-        own.count = 0;
-        if (blockIdx.x < nchunks) claim_chunk(sync, blockIdx.x, own);
-    }
-    __syncthreads();
-    if (own.count == 0) return;
-    const bool above = pw.B == NBW - 1;  // the k-th key lies above the window's bins: the candidates are enough
-    const uint32_t lo_list = lo;         // where the lists start
-    auto gave_up = [&]() {
-        if (threadIdx.x == 0) give_up<VEC>(a, sg);
-    };
-    if (!exact_pass(sync, 0, nchunks, a.wait_rounds, own, [&](uint32_t c) {
-            const int ci = static_cast<int>(c);
-            const uint32_t listed = a.cnt[ci];
-            if (above && listed <= a.cap) hist1_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, listed, 0, 1, lo_list), ci, h, sl.sm);
-            else hist1_chunk<VEC, true>(a, sg, ci, h, sl.sm);
-            __syncthreads();
-        }))
-        return gave_up();
-    const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1, a.coarse1, sg.nchunks, 0, kout, h);
-    lo = p1.B << SH1;
-    shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;
-    if (!exact_pass(sync, 1, nchunks, a.wait_rounds, own, [&](uint32_t c) {
-            const int ci = static_cast<int>(c);
-            const uint32_t listed = a.cnt[ci];
-            if (above && listed <= a.cap) {
-                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, sg, ci, listed, 0, 1, lo_list), ci, lo, shw, h, sl.sm, sl.smd);
-            } else {
-                uint32_t cur[St::SLOTS];
-                const int64_t beg = static_cast<int64_t>(c) * a.E;
-                const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
-                if ((sg.flags & FLAG_ALIGNED4) && end - beg >= TILE) St::load_fast(sg.x, beg, cur);
-                scan_chunk<VEC, false, DEPTH, true>(a, sg, ci, lo, shw, cur, sl);
-            }
-            __syncthreads();
-        }))
-        return gave_up();
-    pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h);
-    count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;
-    for (uint32_t i = 0; i < own.count; ++i) {
-        const int c = own.chunk[i];
-        const bool sums_error = VEC != TAG_F32 && c == sg.nchunks - 1 && a.err_out != nullptr;
-        if (sums_error) below_t = threadIdx.x < nchunks ? a.chunk_err[threadIdx.x] : 0.0;
-        if (VEC == TAG_F32 && c == 0 && threadIdx.x == 0) {
-            a.state[0].loB = lo;
-            a.state[0].shwB = shw;
+    if constexpr (VEC == TAG_F32) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            a.state[0].Bw = pw.B;
+            a.state[0].c_gtw = pw.above;
         }
-        for (uint32_t pp = 0; pp < sub; ++pp) {
-            src = chunk_source<VEC>(a, sg, c, load_agent(&a.cnt[c]), pp, sub, lo);
-            first_entries();
-            next_step(c, pp, sums_error);
-            if (sums_error && threadIdx.x == 0) norm_or_nan(a, sg);
-            __syncthreads();  // the scratch changes hands
-        }
+        if (src.len != 0) refine_part<VEC, WIDE>(a, 0, src, blockIdx.x, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
+    } else {
+        const Threshold t = threshold_16(a, pw, kout, lo, shw);
+        if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
+        emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
     }
 }
 

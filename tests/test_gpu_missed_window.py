@@ -78,6 +78,8 @@ def test_chunks_of_workgroups_that_do_not_start_are_shared_out(dtype):
     x = misled(n, dtype, 64.0)
     c = Call(x, n // 100)
     with B.measuring():
+        for _ in range(3):  # (the code itself comes from memory in the first call, on some XCDs a long time after others)
+            c.run()
         try:
             B.measure_judge(chunks - workgroups)
             c.run()
@@ -99,7 +101,8 @@ def test_exact_passes_use_the_whole_chip_when_lists_are_cut_into_parts(percent):
     n, chunks = 25_165_824, 256
     x = misled(n, "f32", 64.0)
     c = Call(x, n * percent // 100)
-    c.run()
+    for _ in range(3):  # (see above)
+        c.run()
     assert c.held() == 0
     c.check(x, percent)
     owner = c.words(B.MEASURE_CLAIMS, chunks)
@@ -177,3 +180,42 @@ def test_kth_key_above_the_window_is_found_among_the_candidates(dtype, power, sc
     chunk = -(-(-(-n // 256)) // 8192) * 8192
     counts = c.words(B.MEASURE_CHUNK_COUNTS, -(-n // chunk))
     assert counts.max() <= chunk // 4 and counts.sum() >= k  # every chunk has its list
+
+
+@pytest.mark.parametrize("percent", [1, 10, 20])
+def test_a_missed_window_costs_little_more_than_the_exact_passes_as_launches(percent):
+    # a tensor whose base is not 16-byte aligned is never sampled: the same passes, as launches of their own
+    import statistics
+
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    n = 25_165_824
+    x = misled(n, "f32", 64.0)
+    c, plain = Call(x, n * percent // 100), Call(x, n * percent // 100)
+    plain.d = H.to_device(x, offset_elems=1)
+
+    def microseconds(call):
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                call.run()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 100.0)
+        return statistics.median(times[2:])
+
+    missed, exact = microseconds(c), microseconds(plain)
+    assert c.held() == 0 and plain.held() == 0
+    with B.measuring():
+        for _ in range(5):
+            c.run()
+            torch.cuda.synchronize()
+            sampled_scan = B.measure_read()[B.measure_stage_names().index("k_scan_spec")] * 1e3
+    # (1.08 to 1.2 times; 1.2, 1.6 and 42 times with chunks taken over in one sweep, by half or a quarter of the
+    # chip's workgroups, and one counter for all)
+    assert missed <= 1.4 * (exact + sampled_scan), (missed, exact, sampled_scan)
