@@ -150,7 +150,6 @@ __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
 
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
 constexpr uint32_t FLAG_SPEC = 2u;      // the speculative pass runs for this tensor
-constexpr uint32_t FLAG_NO_LIST = 4u;   // so much is kept that no chunk's list would hold its candidates: none is stored
 constexpr int FLAG_SLOT_SHIFT = 8;      // bits from here up: the tensor's entry of err_out
 struct SegDesc {
     const void *x;       // device pointer of the tensor
@@ -1194,9 +1193,10 @@ struct ScanLds {
 // kernel to stay within 128 vector registers: one tile ahead.
 //
 // One chunk with the window (lo, shw); `cur` holds the chunk's first tile if it has a full one.  PAIR: leave
-// the two counts by which k_hist1 judges a speculative window.
+// the two counts by which k_hist1 judges a speculative window.  `cap`: a.cap, or 0 for no list, if the chunk's candidates
+// are known (listed_room) not to fit one.
 template <int VEC, bool PAIR, int DEPTH, bool SHARED>
-__device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t lo, uint32_t shw,
+__device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t lo, uint32_t shw, uint32_t cap,
                                            uint32_t (&cur)[Stream<VEC>::SLOTS], ScanLds &l) {
     static_assert(DEPTH == 2 || DEPTH == 3, "one or two tiles ahead");
     using R = typename Raw<VEC>::type;
@@ -1205,7 +1205,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
     const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
     const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
     uint32_t nxt[St::SLOTS], far[St::SLOTS], valid[St::SLOTS];  // far: DEPTH 3 only
-    uint32_t cap = (sg.flags & FLAG_NO_LIST) ? 0u : a.cap;  // 0 also once a dense tile has made the scan give the chunk's list up
+    // (cap becomes 0 also when a dense tile makes the scan give the chunk's list up)
     int32_t *Li = a.L_idx + static_cast<size_t>(g) * a.cap;
     R *Lv = static_cast<R *>(a.L_val) + static_cast<size_t>(g) * a.cap;
 
@@ -1292,6 +1292,19 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
     store_rows<NBW, NCW, SHARED>(hw, a.rowsW, a.coarseW, g, l.sm);
 }
 
+// The exact scan knows a chunk's candidates beforehand: the keys of the bucket B of the k-th key and of those above, which
+// the chunk's row of the first pass has counted.  Too many for a list: none is stored, and the chunk is read from the input
+// again.  (A tensor that keeps more than a quarter has such chunks; storing lists until they were full took the
+// exact scan of 4 x 8.4 M fp32 values of 15 tensors' 209 us to 39, together with launches of their own.  Giving up the
+// lists of all its chunks instead cost tensors whose kept values lie together, sorted or behind zeros, the empty and
+// short lists that spare the next kernel the input: 6 x 8.4 M at 30 %, sorted 263 us, behind zeros 227; chunk by
+// chunk 223 and 187, spread evenly 254 either way.)
+template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Launch &a, int g, uint32_t B) {
+    const uint32_t *at = a.rows1 + static_cast<size_t>(g) * NB1 + (B < NB1 ? B : NB1 - 1);
+    const uint32_t candidates = SHARED ? load_agent(at) : *at;
+    return B < NB1 && candidates > a.cap ? 0u : a.cap;  // (B = NB1: nothing is kept, nothing reaches the window)
+}
+
 template <int VEC, bool SPEC, int DEPTH>
 __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
     using St = Stream<VEC>;
@@ -1318,7 +1331,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
         if (ntiles > 0) St::load_fast(sg.x, beg, cur);
     };
 
-    uint32_t lo, shw;
+    uint32_t lo, shw, cap = a.cap;
     if (SPEC) {
         sample_window<VEC>(sg, l.smem, l.sm, l.s_pick, first_tile, lo, shw);
         if (c == 0) {  // the accumulators of the kernels that follow
@@ -1337,6 +1350,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
         const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1 + static_cast<size_t>(sg.chunk_begin) * NB1,
                                                         a.coarse1 + static_cast<size_t>(sg.chunk_begin) * NC1, sg.nchunks,
                                                         0, static_cast<uint32_t>(sg.k), l.smem, first_tile);
+        cap = listed_room<false>(a, g, p1.B);
         lo = p1.B << SH1;  // 2^31 when nothing is kept (k = 0): no key reaches it
         shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;  // fp32: the bucket's 2^20 keys in 1024 bins; 16-bit: its 16 patterns in 16
         if (c == 0 && threadIdx.x == 0) {
@@ -1344,7 +1358,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, DEPTH, false>(a, sg, g, lo, shw, cur, l);
+    scan_chunk<VEC, SPEC, DEPTH, false>(a, sg, g, lo, shw, cap, cur, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -2352,7 +2366,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
-                scan_chunk<VEC, false, DEPTH, true>(a, a.seg[0], ci, lo, shw, cur, l.sl);
+                scan_chunk<VEC, false, DEPTH, true>(a, a.seg[0], ci, lo, shw, listed_room<true>(a, ci, p1.B), cur, l.sl);
             }
             __syncthreads();
         }))
@@ -3257,7 +3271,6 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             d.nchunks = ns > 0 ? static_cast<int32_t>((ns + E - 1) / E) : 1;  // an empty tensor keeps one (empty) chunk
             const bool aligned4 = reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
             d.flags = (aligned4 ? FLAG_ALIGNED4 : 0u) | (static_cast<uint32_t>(s - which[0]) << FLAG_SLOT_SHIFT);
-            if (ks > ns / LIST_DIV) d.flags |= FLAG_NO_LIST;
             const bool aligned16 = reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0;  // the sample is read with 16-byte loads
             if (speculation_ranks(ns, ks, dt, aligned16, &d.r_lo, &d.r_hi, &d.sample_batches)) {
                 d.flags |= FLAG_SPEC;

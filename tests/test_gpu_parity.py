@@ -495,3 +495,39 @@ def test_batch_of_speculating_and_exact_tensors(dtype, mix):
         assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), s
         assert H.same_err(ge[s], re, ERR_RTOL), (s, ge[s], re)
     check_segmented_decompress(gi, gv, off, lens)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["sorted", "zeros first"])
+@pytest.mark.parametrize("tensors", [1, 2])
+def test_kept_values_that_lie_together_leave_the_other_chunks_lists(dtype, kind, tensors):
+    # more than a quarter is kept, all of it in some of the chunks: those are read from the input again by the later
+    # kernels, but not the chunks without a candidate
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    n, chunk = (4_915_200, 24_576) if tensors == 1 else (2_457_600, 16_384)
+    xs = []
+    for s in range(tensors):
+        x = wl.small_case("normal", n, seed=70 + s, dtype="f32")
+        x = np.sort(np.abs(x)) if kind == "sorted" else np.where(np.arange(n) < n * 6 // 10, np.float32(0), x)
+        xs.append(wl.f32_to_bf16_bits(x) if dtype == "bf16" else x)
+    k = n * 3 // 10
+    ds = [H.to_device(x) for x in xs]
+    off = [k * s for s in range(tensors + 1)]
+    idx = torch.full((off[-1],), -7, dtype=torch.int32, device="cuda")
+    val = torch.zeros(off[-1], dtype=ds[0].dtype, device="cuda")
+    err = torch.full((tensors,), -1.0, device="cuda")
+    ws = B.new_workspace(n * tensors, tensors, ds[0].dtype)
+    B.adatopk_compress_segmented(ds, [k] * tensors, idx, val, off, err, ws)
+    torch.cuda.synchronize()
+    for s, x in enumerate(xs):
+        ri, rv, re = orc.compress(x, k)
+        assert np.array_equal(H.to_host(idx)[off[s]:off[s + 1]], ri)
+        assert np.array_equal(H.bits(H.to_host(val)[off[s]:off[s + 1]]), H.bits(rv))
+        assert H.same_err(H.to_host(err)[s], re, ERR_RTOL)
+    at = B.measure_workspace_offset(B.MEASURE_CHUNK_COUNTS, n * tensors, tensors, ds[0].dtype)
+    counts = ws[at:at + 4 * tensors * (n // chunk)].view(torch.int32).cpu().numpy()
+    assert np.count_nonzero(counts == 0) >= counts.size // 2 and counts.max() > chunk // 4
