@@ -116,8 +116,9 @@ constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
-constexpr int64_t MERGE_DENSE_RATIO = 64;  // k > n / 64 takes the LDS-built variant of the one-kernel decompress, and so does any large output
-                                           // (merge_dense)
+constexpr int64_t MERGE_DENSE_RATIO = 64;        // k > n / 64 takes the LDS-built variant of the one-kernel decompress ...
+constexpr int64_t MERGE_DENSE_RATIO_SMALL = 32;  // ... for outputs up to MERGE_SMALL_BYTES n / 32, and any large output takes it (merge_dense)
+constexpr size_t MERGE_SMALL_BYTES = static_cast<size_t>(32) << 20;
 constexpr size_t MERGE_MIN_SPAN = 16384;   // bytes; smaller outputs use fewer workgroups
 constexpr size_t MERGE_MAX_SPAN = 98304;   // bytes; larger outputs use more workgroups
 static_assert(LU * NW <= 64, "per-tile wave counts must fit one wavefront scan");
@@ -3434,11 +3435,22 @@ adatopk_status accumulate_impl(const void *idx, int ib, const void *val, int64_t
 }
 
 // Which variant of the one-kernel decompress: values stored over zeros, or the lines built in LDS first.  Storing over
-// zeros writes a line with an entry twice.  While the output fits the last-level cache the second write stays there,
-// and the variant without the LDS stage is the faster one for few entries (26 M bf16 at 0.5 %: 10.4 against 12.0 us;
-// 25 M fp32 at 1 %: 22.2 against 22.5, at 2 %: 27.9 against 25.7).  Beyond it the line has left for memory and comes
-// back for its four bytes: 400 MB at 0.05 % 78.3 against 78.8 us, at 1 % 104.6 against 79.0, at 3 % 171 against 79.
-inline bool merge_dense(int64_t k, int64_t n, bool stream) { return stream || k > n / MERGE_DENSE_RATIO; }
+// zeros writes a line with an entry twice.  The second write is cheap where the line is still in a cache: then the
+// variant without the LDS stage is the faster one for few entries; once it has left for memory it comes back for its
+// few bytes.  Values over zeros / lines built in LDS, us, the same output buffer again and (a new one each time):
+//                  1.6 % kept                 3 % kept
+//   8 MB fp32      5.0 / 5.5  (5.1 / 6.0)     4.9 / 5.4  (5.1 / 6.2)
+//   13 MB bf16     5.2 / 6.1  (6.4 / 7.5)     5.3 / 6.2  (7.2 / 7.8)
+//   26 MB fp32     6.7 / 8.0 (11.9 / 10.7)    7.0 / 8.2 (13.3 / 11.0)
+//   52 MB fp32    10.9 / 11.9 (21.5 / 16.8)  11.6 / 12.5 (23.1 / 17.9)
+//   52 MB bf16    11.6 / 12.5 (23.1 / 17.5)  13.3 / 12.8 (25.0 / 18.1)
+//   105 MB fp32   18.8 / 18.9 (37.0 / 25.9)  21.7 / 19.6 (39.5 / 27.9)
+//   130 MB bf16   26.1 / 22.9 (47.5 / 36.3)  31.6 / 24.5 (57.9 / 40.4)
+// Beyond the last-level cache: 400 MB at 0.05 % 78.3 / 78.8, at 1 % 104.6 / 79.0, at 3 % 171 / 79.  `bytes`: of the
+// call's whole output.
+inline bool merge_dense(int64_t k, int64_t n, size_t bytes) {
+    return bytes > STREAM_STORE_BYTES || k > n / (bytes > MERGE_SMALL_BYTES ? MERGE_DENSE_RATIO : MERGE_DENSE_RATIO_SMALL);
+}
 
 template <typename R, typename I>
 void launch_merge(bool dense, unsigned grid, hipStream_t st, const I *idx, const R *val, uint32_t k, unsigned char *y,
@@ -3460,7 +3472,7 @@ adatopk_status decompress_sorted_impl(const void *idx, int ib, const void *val, 
     const size_t body = total - head;
     const size_t span = merge_span_bytes(body);
     const unsigned grid = static_cast<unsigned>(body / span + 1);  // the last workgroup takes the remainder
-    const bool dense = merge_dense(k, n, total > STREAM_STORE_BYTES);
+    const bool dense = merge_dense(k, n, total);
     const uint32_t ku = static_cast<uint32_t>(k);
     unsigned char *yb = static_cast<unsigned char *>(dense_out);
     if (es == 4) {
@@ -3509,7 +3521,7 @@ adatopk_status decompress_segmented_impl(const int32_t *idx, const void *val, co
             g.n = n[s];
             g.k = static_cast<uint32_t>(k);
             g.first_block = static_cast<uint32_t>(blocks);
-            g.dense = merge_dense(k, n[s], a.stream != 0) ? 1u : 0u;
+            g.dense = merge_dense(k, n[s], bytes_all) ? 1u : 0u;
             if (n[s] > 0) {  // same span count as the kernel derives: (bytes behind the unaligned head) / span + 1
                 const size_t total = static_cast<size_t>(n[s]) * es;
                 size_t head = (16 - reinterpret_cast<uintptr_t>(dense_out[s]) % 16) % 16;

@@ -531,3 +531,20 @@ def test_kept_values_that_lie_together_leave_the_other_chunks_lists(dtype, kind,
     at = B.measure_workspace_offset(B.MEASURE_CHUNK_COUNTS, n * tensors, tensors, ds[0].dtype)
     counts = ws[at:at + 4 * tensors * (n // chunk)].view(torch.int32).cpu().numpy()
     assert np.count_nonzero(counts == 0) >= counts.size // 2 and counts.max() > chunk // 4
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_decompress_on_either_side_of_its_variants_lines(dtype):
+    # values stored over zeros or lines built in LDS: outputs of up to and above 32 MB, keep shares around 1/32 and 1/64
+    import gpu_harness as H
+
+    limit = (32 << 20) // (4 if dtype == "f32" else 2)
+    for n, k in [(n, k) for n in (50_001, limit, limit + 1) for k in (n // 32, n // 32 + 1, n // 64, n // 64 + 1)]:
+        x = wl.small_case("normal", n, seed=k % 97, dtype=dtype)
+        idx = np.arange(k, dtype=np.int32) * (n // k) + (np.arange(k, dtype=np.int32) % 7)
+        val = x[idx]
+        want = np.zeros_like(x)
+        want[idx] = val
+        assert np.array_equal(H.bits(H.gpu_decompress(idx, val, n, sorted_call=True)), H.bits(want)), (n, k)
+        (got,) = H.gpu_decompress_segmented(idx, val, [0, k], [n])
+        assert np.array_equal(H.bits(got), H.bits(want)), (n, k)
