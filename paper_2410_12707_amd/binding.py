@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import torch
@@ -157,9 +158,14 @@ def _dtype_code(t: torch.dtype) -> int:
     raise TypeError("adatopk supports float32, bfloat16 and float16 tensors, got %s" % t)
 
 
+# The handle alone: a Stream object around it costs a microsecond and a half per call.  (Not a public name of torch.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # (the handle alone: a Stream object around it costs a microsecond and a half per call)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor) -> int:
@@ -194,28 +200,34 @@ def _check_pairs(dtype: torch.dtype, k_total: int, idx: torch.Tensor, val: torch
         raise ValueError("val must have the dense tensor's dtype (%s) and at least %d entries" % (dtype, k_total))
 
 
-_marshal = None  # the extension that reads the arguments of the segmented calls
+_marshal = None  # the extension that reads the arguments of the segmented calls; False: there is none
 
 
 def _load_marshal():
+    """The extension, or None where it is not built (for this Python): Python then reads the arguments itself, with the
+    same result, half a microsecond per tensor and call slower."""
     global _marshal
     if _marshal is None:
         try:
             from . import _marshal as m
         except ImportError as e:
-            raise ImportError("_marshal.so is not built: run `python -m paper_2410_12707_amd.build`") from e
+            warnings.warn("segmented calls go without the _marshal extension (%s): run `python -m paper_2410_12707_amd.build`" % e,
+                          RuntimeWarning, stacklevel=3)
+            m = False
         _marshal = m
-    return _marshal
+    return _marshal or None
 
 
 def _segments(tensors: Sequence[torch.Tensor]):
     """(addresses, lengths, dtype) of the tensors of a segmented call, or None if they want a closer look in Python."""
-    return _load_marshal().tensors(tensors)
+    m = _load_marshal()
+    return m.tensors(tensors) if m else None
 
 
 def _counts(values: Sequence[int], count: int):
     """(int64 array, sum) of `count` numbers of a segmented call."""
-    packed = _load_marshal().int64s(values, count)
+    m = _load_marshal()
+    packed = m.int64s(values, count) if m else None
     if packed is None:
         ints = [int(v) for v in values]
         packed = (ctypes.c_int64 * max(count, 1))(*ints), sum(ints)

@@ -1,19 +1,21 @@
 """Builds libadatopk.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree, and next to it
 libadatopk_measure.so: the same sources compiled with ADATOPK_MEASURE_BUILD, which adds the
 benchmark-only hooks of include/adatopk_measure.h (per-kernel dispatch timing, plain streaming
-kernels).  The product library carries none of them.  _marshal.so is the Python extension that reads
-the arguments of the segmented calls (marshal.cpp, host code only)."""
+kernels).  The product library carries none of them.  _marshal is the Python extension that reads
+the arguments of the segmented calls (marshal.cpp, host code only); the package works without it."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadatopk.so")
 MEASURE_LIB = os.path.join(HERE, "libadatopk_measure.so")
-MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
+# (the suffix names the Python it is built for: another one does not load it)
+MARSHAL_LIB = os.path.join(HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = [os.path.join(CSRC, "adatopk.hip"), os.path.join(CSRC, "adatopk_host.cpp")]
 
@@ -41,8 +43,6 @@ def build_measure_library(verbose: bool = False) -> str:
 
 def build_marshal(verbose: bool = False) -> str:
     """The Python extension that reads the arguments of the segmented calls (host code only)."""
-    import sysconfig
-
     import torch
 
     base = os.path.dirname(torch.__file__)
@@ -64,6 +64,10 @@ def library_is_stale() -> bool:
     deps = SOURCES + [os.path.join(ROOT, "include", "adatopk.h"), os.path.join(ROOT, "include", "adatopk_measure.h"),
                       os.path.join(CSRC, "wire_layout.h")]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def marshal_is_stale() -> bool:
+    return not os.path.exists(MARSHAL_LIB) or os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL_LIB)
 
 
 if __name__ == "__main__":

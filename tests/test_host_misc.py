@@ -78,3 +78,38 @@ def test_marshalling_of_segmented_arguments():
     assert list(kk) == [1, 2] and total == 3
     for odd in ([], [torch.zeros(3)], [torch.zeros(3), 1], [torch.nn.Parameter(torch.zeros(2))], torch.zeros(2), None, (x for x in ())):
         assert m.tensors(odd) is None  # host memory, nothing at all, not a tensor, not a list
+
+
+def test_segmented_arguments_without_the_extension():
+    # a package of which only the library was built, or one built for another Python: the same arrays, read in Python
+    code = ("import sys, warnings; sys.path.insert(0, %r); sys.modules['paper_2410_12707_amd._marshal'] = None\n"
+            "import ctypes, torch\n"
+            "from paper_2410_12707_amd import binding as B\n"
+            "with warnings.catch_warnings(record=True) as seen:\n"
+            "    warnings.simplefilter('always')\n"
+            "    assert B._segments([torch.zeros(3)]) is None and B._segments([]) is None\n"
+            "    kk, total = B._counts([1, 2, 3], 3)\n"
+            "assert bytes(kk) == bytes((ctypes.c_int64 * 3)(1, 2, 3)) and total == 6\n"
+            "assert len(seen) == 1 and issubclass(seen[0].category, RuntimeWarning)\n"
+            "try:\n    B.adatopk_compress_segmented([torch.zeros(3)], [1], torch.zeros(1, dtype=torch.int32), torch.zeros(1), [0, 1], None, torch.zeros(1))\n"
+            "except ValueError as e:\n    assert 'device' in str(e); print('REFUSED')\n") % ROOT
+    r = subprocess.run([sys.executable, "-c", code], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    assert r.returncode == 0 and "REFUSED" in r.stdout, (r.stdout, r.stderr)
+
+
+def test_extension_is_built_for_this_python_and_rebuilt_after_a_change(tmp_path, monkeypatch):
+    import sysconfig
+
+    from paper_2410_12707_amd import build as b
+
+    assert b.MARSHAL_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    source, lib = tmp_path / "marshal.cpp", tmp_path / "_marshal.so"
+    source.write_text("")
+    monkeypatch.setattr(b, "MARSHAL_SOURCE", str(source))
+    monkeypatch.setattr(b, "MARSHAL_LIB", str(lib))
+    assert b.marshal_is_stale()
+    lib.write_text("")
+    os.utime(source, (1, 1))
+    assert not b.marshal_is_stale()
+    os.utime(lib, (0, 0))
+    assert b.marshal_is_stale()
