@@ -99,6 +99,23 @@ def median(v):
     return s[len(s) // 2]
 
 
+def judge_reads(state_words, kth_key: int) -> int:
+    """Full reads of the input that the judging kernel of a single tensor made, from the tensor's state record (first
+    eight words of the workspace) and the key of the k-th kept value: two exact passes if fewer than k keys
+    reached the window (which starts at word 0).  None if the window held (word 6); none counted if the k-th key
+    lies above the window, when the passes go over the candidates alone."""
+    return 2 if not state_words[6] and kth_key < state_words[0] else 0
+
+
+def input_passes(stage_us, input_bytes: int, judged: int) -> int:
+    """Full reads of the input in a step: the passes that ran, and what the judging kernel read.  A pass over the input
+    that finishes faster than the peak allows did not read it (the exact passes return at once when the
+    speculative pass held, and the other way round)."""
+    ran = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small")
+              if nm in stage_us and input_bytes / stage_us[nm] / 1e3 <= HBM_PEAK_GBS)
+    return ran + (judged if "k_judge" in stage_us else 0)
+
+
 def load_workload(wl, name):
     return {"1": wl.config1, "2a": lambda: wl.config2((1, 1000)), "2": lambda: wl.config2((1, 100)),
             "2c": lambda: wl.config2((1, 10)), "3": wl.config3, "4": wl.config4, "4r": wl.config4_links, "5": wl.config5,
@@ -215,10 +232,22 @@ class Bench:
         return {nm: {"median_us": round(median(v), 2), "min_us": round(min(v), 2), "max_us": round(max(v), 2),
                      "launches": len(v)} for nm, v in zip(names, seen) if v}
 
+    def judged(self) -> int:
+        """judge_reads of the last call (0 where several tensors are compressed: their exact passes are kernels apart)."""
+        if self.S != 1 or self.k == 0:
+            return 0
+        torch = self.torch
+        torch.cuda.synchronize()
+        words = self.ws[:32].view(torch.int32).cpu().numpy().view(self.np.uint32)
+        least = self.val.abs().min().cpu().view(torch.int16 if self.esize == 2 else torch.int32)
+        return judge_reads([int(v) for v in words], int(least) << (16 if self.esize == 2 else 0))
+
     def algorithmic_bytes(self):
         """What each full-size kernel must move per launch (b bytes per value, n elements, k kept)."""
         b, n, k = self.esize, self.n, self.k
+        judged = self.judged()
         return {
+            **({"k_judge": judged * b * n} if judged else {}),  # (its other work is on the chunks' lists)
             "k_scan_spec": b * n + (4 + b) * k,  # one read of the input + the candidate pairs written (at least the k kept ones)
             "k_hist1": b * n,                    # exact passes (when they do not return at once): one read of the input ...
             "k_scan": b * n + (4 + b) * k,       # ... and another, with the candidate pairs written
@@ -399,8 +428,7 @@ def other_config_line(B, torch, np, wl, orc, name):
     med = median(us)
     dense = bench.n * bench.esize
     stage_us = {nm: v["median_us"] for nm, v in bench.stage_medians(20).items()}
-    reads = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small")
-                if nm in stage_us and bench.esize * bench.n / stage_us[nm] / 1e3 <= HBM_PEAK_GBS)
+    reads = input_passes(stage_us, bench.esize * bench.n, bench.judged())
     line = {"config": name, "workload": w.name, "dtype": w.dtype, "tensors": bench.S, "n": bench.n, "k": bench.k,
             "step_us_median": round(med, 2), "step_us_min_max": [round(min(us), 2), round(max(us), 2)],
             "dense_input_GBs": round(dense / med / 1e3, 1), "stage_us": stage_us, "input_reads_per_step": reads,
@@ -565,7 +593,7 @@ def main() -> int:
     # return at once when the speculative pass held (and the other way round), so they are left out.
     algo = {nm: v for nm, v in bench.algorithmic_bytes().items()
             if nm in stage_us and v / stage_us[nm] / 1e3 <= HBM_PEAK_GBS}
-    input_reads = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small") if nm in algo)
+    input_reads = input_passes(stage_us, bench.esize * n, bench.judged())
     traffic = measured_traffic() if args.config == "2" else None
 
     def roof(nm):

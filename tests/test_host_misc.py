@@ -113,3 +113,17 @@ def test_extension_is_built_for_this_python_and_rebuilt_after_a_change(tmp_path,
     assert not b.marshal_is_stale()
     os.utime(lib, (0, 0))
     assert b.marshal_is_stale()
+
+
+def test_bench_counts_the_judging_kernels_reads_of_the_input():
+    import bench
+
+    lo = 0x3F800000
+    assert bench.judge_reads([lo, 3, 0, 0, 0, 0, 1, 0], lo - 1) == 0   # the window held
+    assert bench.judge_reads([lo, 3, 0, 0, 0, 0, 0, 0], lo - 1) == 2   # the k-th key below it: two passes over the input
+    assert bench.judge_reads([lo, 3, 0, 0, 0, 0, 0, 0], lo + (2048 << 3)) == 0  # above it: passes over the candidates
+    hit = {"k_scan_spec": 24.0, "k_judge": 6.2, "k_emit": 5.7, "k_merge": 18.0}
+    assert bench.input_passes(hit, 100_663_296, 0) == 1
+    assert bench.input_passes(dict(hit, k_judge=57.0), 100_663_296, 2) == 3
+    assert bench.input_passes({"k_hist1": 17.0, "k_scan": 24.0, "k_refine": 6.0}, 100_663_296, 0) == 2
+    assert bench.input_passes({"k_scan_spec": 24.0, "k_hist1": 3.9, "k_scan": 4.0}, 100_663_296, 0) == 1  # returned at once
