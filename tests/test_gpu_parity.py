@@ -418,9 +418,10 @@ def test_speculation_misled_by_its_sample_falls_back_to_the_exact_select(dtype, 
         assert H.same_err(H.to_host(err)[0], re, ERR_RTOL)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("n,k,scale", [(1_048_576, 10_486, 64.0), (1_048_576, 10_486, 1.0 / 64.0),
                                        (8_400_005, 1_600_001, 64.0), (8_400_005, 1_600_001, 1.0 / 64.0)])
-def test_misled_samples_on_several_streams_at_once(n, k, scale):
+def test_misled_samples_on_several_streams_at_once(n, k, scale, dtype):
     # the exact passes wait for one another's workgroups inside one launch: calls on four streams compete for the
     # compute units; one tile per chunk, and ragged chunks whose candidate lists are cut into parts
     import torch
@@ -432,13 +433,13 @@ def test_misled_samples_on_several_streams_at_once(n, k, scale):
     for seed in range(4):
         x = wl.small_case("normal", n, seed=400 + seed, dtype="f32")
         if seed != 2:  # one of the four finds its window held
-            x[_sampled_elements(n, 4)] *= np.float32(scale)
-        xs.append(x)
+            x[_sampled_elements(n, 4 if dtype == "f32" else 2)] *= np.float32(scale)
+        xs.append(wl.f32_to_bf16_bits(x) if dtype == "bf16" else x.astype(np.float16) if dtype == "f16" else x)
     ds = [H.to_device(x) for x in xs]
     idx = [torch.full((k,), -7, dtype=torch.int32, device="cuda") for _ in xs]
-    val = [torch.zeros(k, device="cuda") for _ in xs]
+    val = [torch.zeros(k, dtype=ds[0].dtype, device="cuda") for _ in xs]
     err = [torch.full((1,), -1.0, device="cuda") for _ in xs]
-    ws = [B.new_workspace(n, 1, torch.float32) for _ in xs]
+    ws = [B.new_workspace(n, 1, ds[0].dtype) for _ in xs]
     streams = [torch.cuda.Stream() for _ in xs]
     torch.cuda.synchronize()
     for _ in range(5):
@@ -447,6 +448,9 @@ def test_misled_samples_on_several_streams_at_once(n, k, scale):
                 B.adatopk_compress(ds[s], k, idx[s], val[s], err[s], ws[s])
     torch.cuda.synchronize()
     for s, x in enumerate(xs):
+        held = int(ws[s][:64].view(torch.int32)[6].item())
+        # (a bf16 window spans 16 binades: a bracket that is far too low holds all the same)
+        assert held == (1 if s == 2 or (dtype == "bf16" and scale < 1.0) else 0), (s, held)
         ri, rv, re = orc.compress(x, k)
         assert np.array_equal(H.to_host(idx[s]), ri) and np.array_equal(H.bits(H.to_host(val[s])), H.bits(rv)), s
         assert H.same_err(H.to_host(err[s])[0], re, ERR_RTOL), s

@@ -175,3 +175,33 @@ def test_message_written_straight_into_pinned_host_memory():
         assert got[len(ref):] == b"\xAB" * GUARD
         assert got[:12] == ref[:12] and got[16:len(ref)] == ref[16:]
         assert H.same_err(struct.unpack("<f", got[12:16])[0], re, ERR_RTOL)
+
+
+@pytest.mark.parametrize("dtype,ib", [("f32", 8), ("bf16", 4), ("f16", 8)])
+def test_messages_of_speculating_and_exact_tensors(dtype, ib):
+    # enough of both kinds that they are launched apart: each message with its own error norm in its header
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    lens, shares = [9_000_003, 70_000, 0, 17_000_001, 5_000, 8_000_005, 1_200_000], [0.30, 1.0, 0.0, 0.01, 0.1, 0.95, 0.05]
+    xs = [wl.small_case("normal", n, seed=950 + i, dtype=dtype) for i, n in enumerate(lens)]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    offs, pos = [], 0
+    for x, k in zip(xs, ks):
+        offs.append(pos)
+        pos += (wf.message_bytes(k, x.dtype, ib) + 15) // 16 * 16
+    buf = torch.full((pos + GUARD,), 0xAB, dtype=torch.uint8, device="cuda")
+    ds = [H.to_device(x) for x in xs]
+    ws = B.new_workspace(sum(lens), len(lens), ds[0].dtype)
+    B.adatopk_compress_wire_segmented(ds, ks, ib, [2.0] * len(lens), buf[:pos], offs, ws)
+    torch.cuda.synchronize()
+    raw = buf.cpu().numpy().tobytes()
+    assert raw[pos:] == b"\xAB" * GUARD
+    for i, (x, k) in enumerate(zip(xs, ks)):
+        ri, rv, re = orc.compress(x, k)
+        ref = wf.pack(ri, rv, lens[i], float(re), 2.0, ib)
+        got = raw[offs[i]:offs[i] + len(ref)]
+        assert got[:12] == ref[:12] and got[16:] == ref[16:], i
+        assert H.same_err(struct.unpack("<f", got[12:16])[0], re, ERR_RTOL), i
