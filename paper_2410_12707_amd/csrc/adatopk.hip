@@ -132,7 +132,7 @@ static_assert(TILE % (LIST_DIV * BLOCK * LU) == 0, "a chunk's list capacity is w
 struct SegState {  // one per segment; 64 bytes
     uint32_t loA, shwA;   // window of the speculative pass (written by its first chunk's workgroup)
     uint32_t loB, shwB;   // window of the exact pass (likewise)
-    uint32_t Bw, c_gtw;   // window bin that holds the k-th key, #keys in the bins above it (written by k_refine)
+    uint32_t Bw, c_gtw;   // window bin that holds the k-th key, #keys in the bins above it (written by k_refine or k_judge)
     uint32_t spec_held;   // the speculative pass bracketed the k-th key (written by k_hist1 or k_judge, one of which always runs)
     uint32_t failed;      // the exact passes gave up (k_judge): the call's pairs are not to be used
     uint32_t pad[8];
@@ -175,7 +175,7 @@ struct Launch {
     uint32_t *G3;                 // [MAXSEG][NB3] global histogram of the last digit
     uint32_t *rows1, *coarse1;    // [chunks][NB1], [chunks][NC1]: suffix sums of the chunks' top-digit histograms (k_hist1)
     uint32_t *rowsW, *coarseW;    // [chunks][NBW], [chunks][NCW]: the same for the window bins of the candidates (k_scan)
-    uint2 *cpairA;                // [chunks] speculative pass only: #candidates, #candidates in the open-ended last bin
+    uint2 *cpairA;                // [chunks] speculative pass of several tensors only: #candidates, #candidates in the open-ended last bin
     uint32_t *cnt;                // [chunks] #candidates of the chunk; more than cap: the list is incomplete
     double *chunk_err;            // [chunks] sum of squares of the chunk's elements below the window
     uint32_t *rows3;              // [chunks * sub][NB3] suffix sums of the last digit inside the k-th key's window bin
@@ -342,7 +342,7 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {  // lane:
 // wavefronts before this one and the sum over all.  Lanes 0 .. NW-1 load the counts in wavefront order
 // and scan them with row shifts inside the vector unit (NW <= 16, one row); the two results are read out
 // of the scanned lanes into scalar registers.  A dozen instructions, where selecting every count by
-// "is that wavefront before mine" took about fifty in the streaming loop of k_gather.
+// "is that wavefront before mine" took about fifty, in every tile of the scan.
 template <int DPP_CTRL> __device__ __forceinline__ uint32_t row_shr_add(uint32_t v) {
     return v + static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), DPP_CTRL, 0xF, 0xF, true));
 }
@@ -537,14 +537,12 @@ template <bool SHARED, typename T> __device__ __forceinline__ void store_count(T
 // its keys whose digit is >= d at entry d; coarse[r][NC] repeats every (NB / NC)-th entry
 // contiguously.  The column sums over the nrows rows are the global suffix sums S[d], non-increasing
 // in d, and the bucket is B = max d with S[d] >= krem.  Step A sums the NC coarse columns and finds
-// the coarse interval, step B sums its NB / NC fine columns (and, aside, the part of those sums that
-// belongs to rows < below_rows).  16-byte loads, 8 in flight per thread.  Every thread of the
-// workgroup calls it and gets the same result; red is LDS scratch of NC + 2 * (NB / NC) words.
+// the coarse interval, step B sums its NB / NC fine columns.  16-byte loads, 8 in flight per thread.
+// Every thread of the workgroup calls it and gets the same result; red is LDS scratch of NC + NB / NC words, in which
+// the coarse sums and the fine sums of that interval are left.
 struct ColumnPick {
     uint32_t B;      // NB when krem == 0 (nothing to select)
     uint32_t above;  // S[B + 1]
-    uint32_t total;  // S[B]
-    uint32_t below;  // the part of S[B] that comes from rows < below_rows
 };
 // `after_first_loads` is called once, right after the first batch of step-A loads has been issued and
 // before anything waits for it: loads that the caller issues there (a first input tile) are behind
@@ -555,17 +553,16 @@ struct NoPrefetch {
 };
 // `after_step_a` is called when every thread has its step-A loads and before step B issues any.
 template <int NB, int NC, int UA = 8, typename Prefetch = NoPrefetch, typename Between = NoPrefetch>
-__device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const uint32_t *coarse, int nrows,
-                                                  int below_rows, uint32_t krem, uint32_t *red,
+__device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const uint32_t *coarse, int nrows, uint32_t krem, uint32_t *red,
                                                   Prefetch after_first_loads = Prefetch(), Between after_step_a = Between()) {
     constexpr int FINE = NB / NC;
     static_assert(NC <= 64 && FINE <= 64 && NC % 4 == 0 && FINE % 4 == 0 && BLOCK % (NC / 4) == 0 &&
-                      BLOCK % (FINE / 4) == 0 && NC + 2 * FINE <= BLOCK,
+                      BLOCK % (FINE / 4) == 0 && NC + FINE <= BLOCK,
                   "column_pick geometry");
-    uint32_t *redA = red, *redB = red + NC, *redBelow = red + NC + FINE;
-    ColumnPick r{static_cast<uint32_t>(NB), 0u, 0u, 0u};
+    uint32_t *redA = red, *redB = red + NC;
+    ColumnPick r{static_cast<uint32_t>(NB), 0u};
     __syncthreads();
-    if (threadIdx.x < NC + 2 * FINE) red[threadIdx.x] = 0;
+    if (threadIdx.x < NC + FINE) red[threadIdx.x] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
     {
@@ -607,7 +604,7 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
             constexpr int Q = FINE / 4, G = BLOCK / Q;
             const int q = threadIdx.x % Q;
             const uint4 *col = reinterpret_cast<const uint4 *>(rows + J * FINE) + q;
-            uint4 all = make_uint4(0, 0, 0, 0), below = make_uint4(0, 0, 0, 0);
+            uint4 all = make_uint4(0, 0, 0, 0);
             for (int r0 = threadIdx.x / Q; r0 < nrows; r0 += G * 8) {
                 uint4 v[8];
 #pragma unroll
@@ -618,29 +615,18 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     all.x += v[u].x; all.y += v[u].y; all.z += v[u].z; all.w += v[u].w;
-                    if (r0 + u * G < below_rows) {
-                        below.x += v[u].x; below.y += v[u].y; below.z += v[u].z; below.w += v[u].w;
-                    }
                 }
             }
             atomicAdd(&redB[4 * q + 0], all.x);
             atomicAdd(&redB[4 * q + 1], all.y);
             atomicAdd(&redB[4 * q + 2], all.z);
             atomicAdd(&redB[4 * q + 3], all.w);
-            if (below_rows > 0) {
-                atomicAdd(&redBelow[4 * q + 0], below.x);
-                atomicAdd(&redBelow[4 * q + 1], below.y);
-                atomicAdd(&redBelow[4 * q + 2], below.z);
-                atomicAdd(&redBelow[4 * q + 3], below.w);
-            }
         }
         __syncthreads();
         const uint64_t okB = __ballot(lane < FINE && redB[lane % FINE] >= krem);
         const int I = 63 - __builtin_clzll(okB | 1ull);  // bit 0 is set anyway: S[J * FINE] >= krem
         r.B = J * FINE + I;
         r.above = (I + 1 < FINE) ? redB[I + 1] : ((J + 1 < NC) ? redA[J + 1] : 0u);
-        r.total = redB[I];
-        r.below = redBelow[I];
     }
     __syncthreads();
     return r;
@@ -1288,7 +1274,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
         store_count<SHARED>(&a.cnt[g], (cap == 0 && running <= a.cap) ? a.cap + 1 : running);
     }
     __syncthreads();
-    if (PAIR && threadIdx.x == 0) a.cpairA[g] = make_uint2(running, hw[NBW - 1]);
+    if (PAIR && a.S != 1 && threadIdx.x == 0) a.cpairA[g] = make_uint2(running, hw[NBW - 1]);  // (k_judge reads the rows)
     // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
     store_rows<NBW, NCW, SHARED>(hw, a.rowsW, a.coarseW, g, l.sm);
 }
@@ -1310,7 +1296,7 @@ template <int VEC, bool SPEC, int DEPTH>
 __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
     using St = Stream<VEC>;
     __shared__ ScanLds l;
-    static_assert(NSB_PADDED <= SCAN_SMEM_WORDS && NC1 + 2 * FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
+    static_assert(NSB_PADDED <= SCAN_SMEM_WORDS && NC1 + FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
 
     const int g = blockIdx.x;
     const int s = find_segment(a, g);
@@ -1350,7 +1336,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
         // is the window, its 2^20 keys in the first 1024 bins.
         const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1 + static_cast<size_t>(sg.chunk_begin) * NB1,
                                                         a.coarse1 + static_cast<size_t>(sg.chunk_begin) * NC1, sg.nchunks,
-                                                        0, static_cast<uint32_t>(sg.k), l.smem, first_tile);
+                                                        static_cast<uint32_t>(sg.k), l.smem, first_tile);
         cap = listed_room<false>(a, g, p1.B);
         lo = p1.B << SH1;  // 2^31 when nothing is kept (k = 0): no key reaches it
         shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;  // fp32: the bucket's 2^20 keys in 1024 bins; 16-bit: its 16 patterns in 16
@@ -1689,7 +1675,7 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
 // k_refine.  Prologue (every workgroup of the tensor, redundantly): the column sums of the chunks'
 // window rows give the window bin Bw that holds the k-th key.  Then refine_part on the workgroup's part.
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(Launch a) {
-    __shared__ uint32_t h[NB3 > NCW + 2 * (NBW / NCW) ? NB3 : NCW + 2 * (NBW / NCW)];
+    __shared__ uint32_t h[NB3 > NCW + NBW / NCW ? NB3 : NCW + NBW / NCW];
     __shared__ uint32_t sm[2 * NW];
     __shared__ double smd[NW];
 
@@ -1713,7 +1699,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(
         for (int j = 0; j < LU; ++j) first[j] = src.raw(j * BLOCK + threadIdx.x);
     };
     const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
-                                                a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks, 0,
+                                                a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks,
                                                 static_cast<uint32_t>(sg.k), h, first_entries);
     if (c == 0 && part == 0 && threadIdx.x == 0) {
         a.state[s].Bw = pw.B;  // NBW when nothing is kept
@@ -2137,7 +2123,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     } else {
         const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
                                                     a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks,
-                                                    0, kout, h, first_tile);
+                                                    kout, h, first_tile);
         t = threshold_16(a, pw, kout, lo, shw);
         if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
@@ -2356,7 +2342,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     };
     const uint32_t first_chunk = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[0])));
     const Launch &a1 = args_again();
-    const ColumnPick p1 = column_pick<NB1, NC1, 16>(a1.rows1, a1.coarse1, a1.seg[0].nchunks, 0, static_cast<uint32_t>(a1.seg[0].k), h, [&]() { first_tile(first_chunk); });
+    const ColumnPick p1 = column_pick<NB1, NC1, 16>(a1.rows1, a1.coarse1, a1.seg[0].nchunks, static_cast<uint32_t>(a1.seg[0].k), h, [&]() { first_tile(first_chunk); });
     const uint32_t lo = p1.B << SH1;
     const uint32_t shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;
     if (!exact_pass(1, nchunks, l.own, [&](uint32_t c) {
@@ -2376,7 +2362,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     const SegDesc &sg = a.seg[0];
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;
-    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h);
+    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, kout, h);
     const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;
     for (uint32_t i = 0; i < l.own.count; ++i) {
         const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[i]));
@@ -2416,7 +2402,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) void k_judge(Launch a) {
     __shared__ JudgeLds l;
     uint32_t *h = l.sl.smem;
-    static_assert(NBW + 1 <= SCAN_SMEM_WORDS && NCW + 2 * (NBW / NCW) <= SCAN_SMEM_WORDS, "shared scratch fits");
+    static_assert(NBW + 1 <= SCAN_SMEM_WORDS && NCW + NBW / NCW <= SCAN_SMEM_WORDS, "shared scratch fits");
 
     const SegDesc &sg = a.seg[0];
     const uint32_t nchunks = static_cast<uint32_t>(sg.nchunks), kout = static_cast<uint32_t>(sg.k);
@@ -2446,7 +2432,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     // looked at after the rows were read tells; after the coarse rows is enough, unless the pick is in their last interval.
     JudgeSync *sync = judge_sync(a);
     uint32_t exact_seen = 0;
-    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, 0, kout, h, first_entries,
+    const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, kout, h, first_entries,
                                                 [&]() { exact_seen = load_agent(&sync->done[0][0]); });
     if (pw.B < NBW - 1 && pw.B >= NBW - NBW / NCW) exact_seen = load_agent(&sync->done[0][0]);  // uniform
     // held: at least k keys reached the window, fewer than k its open-ended last bin
@@ -3319,8 +3305,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     // MAXSEG tensors at a time; those that the speculative pass takes and those that need the exact passes apart if
     // there is enough of both.  In one launch each kind's kernels find most workgroups' chunks not theirs: the
     // exact passes over four of fifteen tensors of 33.5 MB ran on 137 of 512 workgroups (histogram 70 us,
-    // scan 209).  Apart, both kinds are cut into as many chunks as the chip takes; it costs five launches more, 20 us,
-    // which the exact passes of SPLIT_MIN_N elements are worth.
+    // scan 209).  Apart, both kinds are cut into as many chunks as the chip takes; it costs four launches more (16-bit types:
+    // three), 10 to 15 us, which the exact passes of SPLIT_MIN_N elements are worth.
     for (int32_t s0 = 0; s0 < S; s0 += MAXSEG) {
         const int32_t count = (S - s0 < MAXSEG) ? S - s0 : MAXSEG;
         int32_t order[MAXSEG], nspec = 0, nexact = 0;
