@@ -825,7 +825,8 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
 // end of sorted data) does not go through the stage; in the scan of a single tensor it gives the
 // chunk's list up at once, so that nothing more is stored for a chunk that will be read again
 // (storing such tiles until the list was full cost a constant tensor 50 MB of writes that nobody
-// read); in the scan of a batch it stores directly while the list has room.
+// read); in the speculative scan of a batch it stores directly while the list has room.  (The exact scan knows
+// beforehand which chunks get a list: listed_room.)
 constexpr int STAGE_CAP = 2048;
 
 // Writes list slots [from, to) of the chunk from the stage to memory and counts their window bins.
@@ -2163,7 +2164,8 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
 //     the hands of running workgroups, and they all arrive; the number of polls is bounded all the same, so that
 //     the launch ends even if the marks are overwritten from outside (a workspace that two calls use at
 //     once).  The error norm is then NaN (give_up).
-constexpr int POLLS_BEFORE_HELP = 32;      // tens of us: far beyond the spread of workgroups that run side by side
+constexpr int POLLS_BEFORE_HELP = 32;      // tens of us: far beyond the spread of workgroups that run side by side (but not in a
+                                           // process's first call, when some XCDs have the code much later than others)
 constexpr int MAX_POLL_ROUNDS = 1 << 18;   // seconds
 struct Owned {
     uint32_t count;              // chunks this workgroup has claimed ...
@@ -3306,7 +3308,10 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     // there is enough of both.  In one launch each kind's kernels find most workgroups' chunks not theirs: the
     // exact passes over four of fifteen tensors of 33.5 MB ran on 137 of 512 workgroups (histogram 70 us,
     // scan 209).  Apart, both kinds are cut into as many chunks as the chip takes; it costs four launches more (16-bit types:
-    // three), 10 to 15 us, which the exact passes of SPLIT_MIN_N elements are worth.
+    // three), 10 to 15 us, which the exact passes of SPLIT_MIN_N elements are worth.  Together / apart, us, so many elements of either
+    // kind (1 and 30 % kept) in 4 + 4 tensors: fp32 4 Mi 70 / 73, 8 Mi 103 / 101, 16 Mi 155 / 132, 32 Mi 259 / 214;
+    // bf16 52 / 52, 92 / 73, 161 / 113, 303 / 186.  In 1 + 1: fp32 8 Mi 92 / 107, 16 Mi 138 / 147 (10 and 90 %: 197 / 187),
+    // 32 Mi 237 / 260 (365 / 344); bf16 8 Mi 81 / 75, 16 Mi 140 / 111.
     for (int32_t s0 = 0; s0 < S; s0 += MAXSEG) {
         const int32_t count = (S - s0 < MAXSEG) ? S - s0 : MAXSEG;
         int32_t order[MAXSEG], nspec = 0, nexact = 0;
