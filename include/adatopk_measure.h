@@ -1,5 +1,5 @@
 /*
- * adatopk_measure.h -- measurement hooks of libadatopk (benchmark and profiling only).
+ * adatopk_measure.h -- measurement hooks of libadatopk (benchmarks, profiling and tests only).
  *
  * Not part of the compressor's contract: these calls exist so that a benchmark can
  * time the individual kernels of a compress / decompress call with HIP events on the
