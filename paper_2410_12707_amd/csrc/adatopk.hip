@@ -1181,10 +1181,10 @@ struct ScanLds {
 // kernel to stay within 128 vector registers: one tile ahead.
 //
 // One chunk with the window (lo, shw); `cur` holds the chunk's first tile if it has a full one.  PAIR: leave
-// the two counts by which k_hist1 judges a speculative window.  `cap`: a.cap, or 0 for no list, if the chunk's candidates
-// are known (listed_room) not to fit one.
+// the two counts by which k_hist1 judges a speculative window.  `room`: a.cap, or 0 for no list, if the chunk's candidates
+// are known (listed_room) not to fit one; a speculative scan knows nothing yet.
 template <int VEC, bool PAIR, int DEPTH, bool SHARED>
-__device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t lo, uint32_t shw, uint32_t cap,
+__device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t lo, uint32_t shw, uint32_t room,
                                            uint32_t (&cur)[Stream<VEC>::SLOTS], ScanLds &l) {
     static_assert(DEPTH == 2 || DEPTH == 3, "one or two tiles ahead");
     using R = typename Raw<VEC>::type;
@@ -1193,7 +1193,10 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
     const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
     const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
     uint32_t nxt[St::SLOTS], far[St::SLOTS], valid[St::SLOTS];  // far: DEPTH 3 only
-    // (cap becomes 0 also when a dense tile makes the scan give the chunk's list up)
+    // Becomes 0 also when a dense tile makes the scan give the chunk's list up.  (Every speculating tensor has a sample: the
+    // condition only keeps this count apart from a.cap.  Left equal to it at the start, the compiler spills a dozen
+    // scalar registers more in the tile loop of the 16-bit scan: 26 M bf16 41.5 -> 42.3 us per compress and decompress.)
+    uint32_t cap = PAIR ? (sg.sample_batches != 0 ? a.cap : 0u) : room;
     int32_t *Li = a.L_idx + static_cast<size_t>(g) * a.cap;
     R *Lv = static_cast<R *>(a.L_val) + static_cast<size_t>(g) * a.cap;
 
@@ -1319,7 +1322,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
         if (ntiles > 0) St::load_fast(sg.x, beg, cur);
     };
 
-    uint32_t lo, shw, cap = a.cap;
+    uint32_t lo, shw, room = 0;
     if (SPEC) {
         sample_window<VEC>(sg, l.smem, l.sm, l.s_pick, first_tile, lo, shw);
         if (c == 0) {  // the accumulators of the kernels that follow
@@ -1338,7 +1341,8 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
         const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1 + static_cast<size_t>(sg.chunk_begin) * NB1,
                                                         a.coarse1 + static_cast<size_t>(sg.chunk_begin) * NC1, sg.nchunks,
                                                         static_cast<uint32_t>(sg.k), l.smem, first_tile);
-        cap = listed_room<false>(a, g, p1.B);
+        // (asked only where many chunks can be in question: the answer costs a short tensor a memory round trip)
+        room = sg.k > sg.n / LIST_DIV ? listed_room<false>(a, g, p1.B) : a.cap;
         lo = p1.B << SH1;  // 2^31 when nothing is kept (k = 0): no key reaches it
         shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;  // fp32: the bucket's 2^20 keys in 1024 bins; 16-bit: its 16 patterns in 16
         if (c == 0 && threadIdx.x == 0) {
@@ -1346,7 +1350,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, DEPTH, false>(a, sg, g, lo, shw, cap, cur, l);
+    scan_chunk<VEC, SPEC, DEPTH, false>(a, sg, g, lo, shw, room, cur, l);
 }
 
 // ------------------------------------------------------------------ list kernels
