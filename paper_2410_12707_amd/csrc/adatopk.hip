@@ -116,8 +116,8 @@ constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
-constexpr int64_t MERGE_DENSE_RATIO = 64;        // k > n / 64 takes the LDS-built variant of the one-kernel decompress ...
-constexpr int64_t MERGE_DENSE_RATIO_SMALL = 32;  // ... for outputs up to MERGE_SMALL_BYTES n / 32, and any large output takes it (merge_dense)
+constexpr uint32_t MERGE_DENSE_SHIFT = 6;        // k > n / 64 takes the LDS-built variant of the one-kernel decompress ...
+constexpr uint32_t MERGE_DENSE_SHIFT_SMALL = 5;  // ... for outputs up to MERGE_SMALL_BYTES n / 32, and any large output takes it (merge_dense)
 constexpr size_t MERGE_SMALL_BYTES = static_cast<size_t>(32) << 20;
 constexpr size_t MERGE_MIN_SPAN = 16384;   // bytes; smaller outputs use fewer workgroups
 constexpr size_t MERGE_MAX_SPAN = 98304;   // bytes; larger outputs use more workgroups
@@ -2901,24 +2901,26 @@ __global__ __launch_bounds__(BLOCK) void k_merge_lds(const I *idx, const R *val,
 // Decompress of several tensors in one launch: the spans of all tensors form one grid, a table in
 // the kernel arguments says which workgroups belong to which tensor, and every workgroup runs the
 // one-tensor code above on its span (the sparse or the LDS-built variant, per tensor).
-constexpr int MERGE_MAXSEG = 96;
-struct MergeSeg {   // 40 bytes
+// 28 bytes per tensor, so that the 128 messages of one compress launch of small tensors are one launch here, too (with
+// the number of the first workgroup and a flag inside records of 40 bytes 96 fitted: 128 messages of 1 to 8 K values took a
+// second launch, 22.0 us per compress and decompress instead of 17.6).
+constexpr int MERGE_MAXSEG = 128;
+struct MergeSeg {
     unsigned char *y;
     int64_t pair_off;      // first pair of this tensor in idx / val
-    int64_t n;             // elements
+    int32_t n;             // elements
     uint32_t k;
-    uint32_t first_block;  // its spans are workgroups [first_block, first_block of the next tensor)
-    uint32_t dense;        // build the lines in LDS (merge_dense)
-    uint32_t pad;
 };
 struct MergeLaunch {
     MergeSeg seg[MERGE_MAXSEG];
+    uint32_t first_block[MERGE_MAXSEG];  // tensor s's spans are workgroups [first_block[s], first_block[s + 1])
     const int32_t *idx;
     const void *val;
     size_t span;           // bytes of output per workgroup, the same for every tensor of the call
     uint32_t blocks;       // workgroups of the launch
     int32_t S;
     uint32_t stream;       // the call's output is larger than the last-level cache: nontemporal stores
+    uint32_t dense_shift;  // k > n >> dense_shift: the lines are built in LDS (merge_dense)
 };
 static_assert(sizeof(MergeLaunch) <= 4096, "kernel arguments stay within 4 KB");
 static_assert(MERGE_MAXSEG <= 128, "two table entries per lane");
@@ -2930,20 +2932,22 @@ template <typename R> __global__ __launch_bounds__(BLOCK) void k_merge_seg(const
     // never decrease and the first is 0); lane l looks at table entries l and l + 64
     const int lane = threadIdx.x & 63;
     uint32_t first_lo = 0xFFFFFFFFu, first_hi = 0xFFFFFFFFu;
-    if (lane < a.S) first_lo = a.seg[lane].first_block;
-    if (lane + 64 < a.S) first_hi = a.seg[lane + 64].first_block;
+    if (lane < a.S) first_lo = a.first_block[lane];
+    if (lane + 64 < a.S) first_hi = a.first_block[lane + 64];
     const uint64_t lo = __ballot(blockIdx.x >= first_lo), hi = __ballot(blockIdx.x >= first_hi);
     const int s = hi ? 127 - __builtin_clzll(hi) : 63 - __builtin_clzll(lo | 1ull);
     const MergeSeg &sg = a.seg[s];
-    const uint32_t next_first = (s + 1 < a.S) ? a.seg[s + 1].first_block : a.blocks;
-    const uint32_t blk = blockIdx.x - sg.first_block, nblk = next_first - sg.first_block;
+    const uint32_t first = a.first_block[s];
+    const uint32_t next_first = (s + 1 < a.S) ? a.first_block[s + 1] : a.blocks;
+    const uint32_t blk = blockIdx.x - first, nblk = next_first - first;
     const size_t total = static_cast<size_t>(sg.n) * sizeof(R);
     size_t head = (16 - reinterpret_cast<uintptr_t>(sg.y) % 16) % 16;
     if (head > total) head = total;
     const int32_t *idx = a.idx + sg.pair_off;
     const R *val = static_cast<const R *>(a.val) + sg.pair_off;
     const bool stream = a.stream != 0;
-    if (sg.dense) merge_span_lds<R, int32_t>(idx, val, sg.k, sg.y, total, head, a.span, blk, nblk, stream, piece, s_range);
+    const bool dense = sg.k > static_cast<uint32_t>(sg.n) >> a.dense_shift;
+    if (dense) merge_span_lds<R, int32_t>(idx, val, sg.k, sg.y, total, head, a.span, blk, nblk, stream, piece, s_range);
     else merge_span<R, int32_t>(idx, val, sg.k, sg.y, total, head, a.span, blk, nblk, stream, s_range);
 }
 
@@ -3443,9 +3447,10 @@ adatopk_status accumulate_impl(const void *idx, int ib, const void *val, int64_t
 //   130 MB bf16   26.1 / 22.9 (47.5 / 36.3)  31.6 / 24.5 (57.9 / 40.4)
 // Beyond the last-level cache: 400 MB at 0.05 % 78.3 / 78.8, at 1 % 104.6 / 79.0, at 3 % 171 / 79.  `bytes`: of the
 // call's whole output.
-inline bool merge_dense(int64_t k, int64_t n, size_t bytes) {
-    return bytes > STREAM_STORE_BYTES || k > n / (bytes > MERGE_SMALL_BYTES ? MERGE_DENSE_RATIO : MERGE_DENSE_RATIO_SMALL);
+inline uint32_t merge_dense_shift(size_t bytes) {  // lines are built in LDS for k > n >> shift (31: for any k)
+    return bytes > STREAM_STORE_BYTES ? 31u : (bytes > MERGE_SMALL_BYTES ? MERGE_DENSE_SHIFT : MERGE_DENSE_SHIFT_SMALL);
 }
+inline bool merge_dense(int64_t k, int64_t n, size_t bytes) { return k > n >> merge_dense_shift(bytes); }
 
 template <typename R, typename I>
 void launch_merge(bool dense, unsigned grid, hipStream_t st, const I *idx, const R *val, uint32_t k, unsigned char *y,
@@ -3506,17 +3511,16 @@ adatopk_status decompress_segmented_impl(const int32_t *idx, const void *val, co
         a.val = val;
         a.span = span;
         a.stream = bytes_all > STREAM_STORE_BYTES ? 1u : 0u;
+        a.dense_shift = merge_dense_shift(bytes_all);
         uint64_t blocks = 0;
         for (int32_t i = 0; i < a.S; ++i) {
             const int32_t s = s0 + i;
             MergeSeg &g = a.seg[i];
-            const int64_t k = out_offset[s + 1] - out_offset[s];
             g.y = static_cast<unsigned char *>(dense_out[s]);
             g.pair_off = out_offset[s];
-            g.n = n[s];
-            g.k = static_cast<uint32_t>(k);
-            g.first_block = static_cast<uint32_t>(blocks);
-            g.dense = merge_dense(k, n[s], bytes_all) ? 1u : 0u;
+            g.n = static_cast<int32_t>(n[s]);
+            g.k = static_cast<uint32_t>(out_offset[s + 1] - out_offset[s]);
+            a.first_block[i] = static_cast<uint32_t>(blocks);
             if (n[s] > 0) {  // same span count as the kernel derives: (bytes behind the unaligned head) / span + 1
                 const size_t total = static_cast<size_t>(n[s]) * es;
                 size_t head = (16 - reinterpret_cast<uintptr_t>(dense_out[s]) % 16) % 16;

@@ -552,3 +552,19 @@ def test_decompress_on_either_side_of_its_variants_lines(dtype):
         assert np.array_equal(H.bits(H.gpu_decompress(idx, val, n, sorted_call=True)), H.bits(want)), (n, k)
         (got,) = H.gpu_decompress_segmented(idx, val, [0, k], [n])
         assert np.array_equal(H.bits(got), H.bits(want)), (n, k)
+
+
+@pytest.mark.parametrize("tensors", [64, 65, 128, 129])
+def test_decompress_of_as_many_tensors_as_a_launch_holds_and_one_more(tensors):
+    # the table is searched 64 entries at a time and holds 128; empty tensors and empty keep sets among them
+    import gpu_harness as H
+
+    rng = np.random.Generator(np.random.PCG64(tensors))
+    ns = [int(v) for v in rng.integers(0, 9000, size=tensors)]
+    ns[0], ns[63], ns[-1] = 0, 0, 4097
+    idx = [np.sort(rng.permutation(n)[:n // (3 + i % 90)]).astype(np.int32) for i, n in enumerate(ns)]
+    val = [wl.small_case("normal", max(i.size, 1), seed=j)[:i.size] for j, i in enumerate(idx)]
+    off = np.concatenate([[0], np.cumsum([i.size for i in idx])])
+    got = H.gpu_decompress_segmented(np.concatenate(idx), np.concatenate(val), off, ns)
+    for n, i, v, y in zip(ns, idx, val, got):
+        assert np.array_equal(H.bits(y), H.bits(orc.decompress(i, v, n))), (n, i.size)
