@@ -160,6 +160,7 @@ struct SegDesc {
     uint32_t flags;
     uint32_t r_lo, r_hi; // speculative pass: ranks in the sample (counted from the largest key) that bracket the k-th key
     uint32_t sample_batches;  // ... and the sample's size in batches of SAMPLE_BATCH dword loads per thread
+    double ratio;        // wire mode: goes into the message's header
 };
 
 struct Launch {
@@ -214,6 +215,15 @@ __device__ __forceinline__ OutPtrs out_ptrs(void *idx_out, void *val_out, int64_
     return o;
 }
 
+// Where a tensor's error norm goes: its entry of err_out, or the header in front of its message's index section
+// (nullptr: nowhere).
+__device__ __forceinline__ float *err_ptr(const Launch &a, const SegDesc &sg) {
+    if (a.wire)
+        return reinterpret_cast<float *>(static_cast<char *>(a.idx_out) + sg.out_off - sizeof(adatopk_wire_header) +
+                                         offsetof(adatopk_wire_header, err_norm));
+    return a.err_out != nullptr ? a.err_out + (sg.flags >> FLAG_SLOT_SHIFT) : nullptr;
+}
+
 // ------------------------------------------------------------------ element access
 // VEC tags the dtype: 4 = fp32 (one element per dword), 8 = bf16 and 9 = fp16 (two per dword, low
 // half first).  VEC / 4 is the number of elements in a dword; the two 16-bit types differ only in
@@ -237,6 +247,35 @@ template <int VEC> __device__ __forceinline__ uint32_t elem_of(uint32_t dword, i
 }
 
 typedef uint32_t dword4 __attribute__((ext_vector_type(4)));
+
+// A message's header, the error norm aside (whoever adds it up stores it in place), and the zeros between its index
+// and its value section.  Called by one workgroup of the kernel that places the tensor's pairs, behind its own part of them: as a
+// launch of its own behind that kernel it cost every message 2 to 4 us.
+template <int VEC>
+__device__ __forceinline__ void write_header(void *messages, int64_t idx_at, int64_t n, int64_t k, bool idx64, double ratio) {
+    constexpr uint32_t WORDS = sizeof(adatopk_wire_header) / 4, ERR_WORD = offsetof(adatopk_wire_header, err_norm) / 4;
+    const int64_t idx_bytes = k * (idx64 ? 8 : 4), padded_bytes = (idx_bytes + 15) / 16 * 16;
+    adatopk_wire_header h = {};
+    h.magic = ADATOPK_WIRE_MAGIC;
+    h.version = ADATOPK_WIRE_VERSION;
+    h.algorithm = ADATOPK_WIRE_TOPK;
+    h.dtype = VEC == TAG_F32 ? ADATOPK_F32 : (VEC == TAG_BF16 ? ADATOPK_BF16 : ADATOPK_F16);
+    h.index_bytes = idx64 ? 8 : 4;
+    h.n = n;
+    h.k = k;
+    h.ratio = ratio;
+    h.idx_offset = sizeof(adatopk_wire_header);
+    h.val_offset = static_cast<int64_t>(sizeof(adatopk_wire_header)) + padded_bytes;
+    uint32_t words[WORDS];
+    __builtin_memcpy(words, &h, sizeof h);
+    const uint32_t t = threadIdx.x;
+    uint32_t mine = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < WORDS; ++i) mine = t == i ? words[i] : mine;
+    char *indices = static_cast<char *>(messages) + idx_at;
+    if (t < WORDS && t != ERR_WORD) reinterpret_cast<uint32_t *>(indices - sizeof h)[t] = mine;
+    if (idx_bytes + t < padded_bytes) indices[idx_bytes + t] = 0;  // at most 15 bytes
+}
 
 // Streaming layout of the two full-input kernels.  A tile is TILE consecutive elements; wave w
 // of the workgroup owns the w-th contiguous 1/NW of it and reads it as SLOTS dword loads of
@@ -1864,7 +1903,7 @@ __device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &s
         }
     }
     const double tot = block_sum_f64(sum, smd);
-    if (threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = static_cast<float>(sqrt(tot));
+    if (threadIdx.x == 0) *err_ptr(a, sg) = static_cast<float>(sqrt(tot));
 }
 
 // 16-bit types: a window bin is one pattern (the window's shift is the 16 zero bits below the pattern), so
@@ -1938,7 +1977,7 @@ __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg
         }
     }
     const double tot = block_sum_f64(sum, smd);
-    if (threadIdx.x == 0) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], static_cast<float>(sqrt(tot)));  // (see give_up)
+    if (threadIdx.x == 0) store_agent(err_ptr(a, sg), static_cast<float>(sqrt(tot)));  // (see give_up)
     __syncthreads();
 }
 
@@ -2100,9 +2139,11 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, sub, lo);
     // the tensor's last chunk is the short one, and the last part of a chunk the shortest
-    const bool sums_error = c == sg.nchunks - 1 && part == sub - 1 && a.err_out != nullptr;
+    const bool sums_error = c == sg.nchunks - 1 && part == sub - 1 && err_ptr(a, sg) != nullptr;
+    const bool writes_header = a.wire != 0 && c == 0 && part == 0;
     if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
-        if (sums_error && threadIdx.x == 0) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = __uint_as_float(QUIET_NAN);
+        if (sums_error && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
+        if (writes_header) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
         return;
     }
     // 16-bit types: thread t of that workgroup asks for chunk t's sum of squares below the window now, so that it
@@ -2133,6 +2174,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
     emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, count_t, raw, id, l);
+    if (writes_header) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
 }
 
 // ------------------------------------------------------------------ k_judge
@@ -2252,11 +2294,11 @@ __device__ __forceinline__ bool exact_pass(int pass, uint32_t nchunks, Owned &o,
 template <int VEC> __device__ __forceinline__ void give_up(const Launch &a, const SegDesc &sg) {
     store_agent(&a.state[0].failed, 1u);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (VEC != TAG_F32 && a.err_out != nullptr) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], __uint_as_float(QUIET_NAN));
+    if (VEC != TAG_F32 && err_ptr(a, sg) != nullptr) store_agent(err_ptr(a, sg), __uint_as_float(QUIET_NAN));
 }
 __device__ __forceinline__ void norm_or_nan(const Launch &a, const SegDesc &sg) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (load_agent(&a.state[0].failed) != 0) store_agent(&a.err_out[sg.flags >> FLAG_SLOT_SHIFT], __uint_as_float(QUIET_NAN));
+    if (load_agent(&a.state[0].failed) != 0) store_agent(err_ptr(a, sg), __uint_as_float(QUIET_NAN));
 }
 
 // The exact passes over the list of one chunk alone, for a k-th key above the window's bins: the window then
@@ -2394,7 +2436,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             int32_t id[LU];
             load_entries<VEC>(src, 0, raw, id);
             const Threshold t = threshold_16(a, pw, kout, lo, shw);
-            if (c == sg.nchunks - 1 && a.err_out != nullptr) {
+            if (c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr) {
                 const double below_t = threadIdx.x < nchunks ? a.chunk_err[threadIdx.x] : 0.0;
                 error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
                 if (threadIdx.x == 0) norm_or_nan(a, sg);
@@ -2420,7 +2462,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;  // candidates of chunk threadIdx.x
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, a.cnt[c], part, sub, lo);
     double below_t = 0.0;  // 16-bit types, the workgroup that adds up the error norm: see k_emit
-    const bool sums_error = VEC != TAG_F32 && c == sg.nchunks - 1 && a.err_out != nullptr;
+    const bool sums_error = VEC != TAG_F32 && c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr;
     if (sums_error && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
 
     uint32_t raw[LU];
@@ -2444,6 +2486,9 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     // held: at least k keys reached the window, fewer than k its open-ended last bin
     const bool held = pw.B < NBW - 1 && __ballot(exact_seen != 0) == 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) a.state[0].spec_held = held ? 1u : 0u;
+    if constexpr (VEC != TAG_F32) {  // (no k_emit follows; here and not at the end, where it cost every fp16 tensor 0.6 us)
+        if (blockIdx.x == 0 && a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
+    }
     if (__builtin_expect(!held, 0)) {
         judge_missed<VEC, WIDE>(l, pw.B == NBW - 1);
         return;
@@ -2479,7 +2524,11 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
     const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, n, wide, a.wire != 0, sizeof(R));
     const R *x = static_cast<const R *>(sg.x);
     R *ov = static_cast<R *>(op.val);
-    if (c == 0 && threadIdx.x == 0 && a.err_out != nullptr) a.err_out[sg.flags >> FLAG_SLOT_SHIFT] = 0.0f;
+    if (c == 0) {
+        float *err = err_ptr(a, sg);
+        if (threadIdx.x == 0 && err != nullptr) *err = 0.0f;
+        if (a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, n, n, wide, sg.ratio);
+    }
     if (wide) {
         for (uint32_t i = beg + threadIdx.x; i < end; i += BLOCK) op.i64[i] = static_cast<int64_t>(i);
     } else {
@@ -2503,17 +2552,18 @@ constexpr int SMALL_MAXSEG = 128;              // tensors per launch (the table 
 struct SmallDesc {
     const void *x;
     int64_t out_off;
-    int32_t n, k;
 };
 struct SmallLaunch {
     SmallDesc seg[SMALL_MAXSEG];
+    double ratio[SMALL_MAXSEG];                    // wire mode: goes into the message's header
+    uint16_t n[SMALL_MAXSEG], k[SMALL_MAXSEG];
     void *idx_out;
     void *val_out;
     float *err_out;
     uint32_t idx64;
     uint32_t wire;
 };
-static_assert(sizeof(SmallLaunch) <= 3584, "kernel arguments stay below 4 KB");
+static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments stay within 4 KB");
 static_assert(SMALL_EPT * NW <= 128, "the (slot, wave) counts are scanned two per lane");
 static_assert(SMALL_N < 65536, "two 16-bit counts travel in one word");
 
@@ -2568,8 +2618,8 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
     __shared__ uint32_t wcnt[SMALL_EPT * NW];  // (#above T) | (#equal to T) << 16 of every (slot, wave)
 
     const SmallDesc &sg = a.seg[blockIdx.x];
-    const int n = sg.n;
-    const uint32_t kout = static_cast<uint32_t>(sg.k);
+    const int n = a.n[blockIdx.x];
+    const uint32_t kout = a.k[blockIdx.x];
     const R *x = static_cast<const R *>(sg.x);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -2655,9 +2705,15 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
             acc = fma(v, v, acc);
         }
     }
-    if (a.err_out != nullptr) {
+    float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
+    if (a.wire != 0) {
+        write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, a.ratio[blockIdx.x]);
+        err = reinterpret_cast<float *>(static_cast<char *>(a.idx_out) + sg.out_off - sizeof(adatopk_wire_header) +
+                                        offsetof(adatopk_wire_header, err_norm));
+    }
+    if (err != nullptr) {
         const double tot = block_sum_f64(acc, smd);
-        if (threadIdx.x == 0) a.err_out[blockIdx.x] = static_cast<float>(sqrt(tot));
+        if (threadIdx.x == 0) *err = static_cast<float>(sqrt(tot));
     }
 }
 
@@ -2988,8 +3044,7 @@ int64_t chunk_elems(int64_t n_batch, int32_t S_batch, int64_t target) {
 inline int64_t chunk_target(int32_t S_batch) { return S_batch == 1 ? CTARGET_ONE : CTARGET; }
 
 struct Carve {
-    size_t state, G3, rows1, coarse1, rowsW, coarseW, cpairA, cnt, chunk_err, rows3, ldef, lerr, wire_err, L_idx, L_val,
-        total;
+    size_t state, G3, rows1, coarse1, rowsW, coarseW, cpairA, cnt, chunk_err, rows3, ldef, lerr, L_idx, L_val, total;
 };
 
 // Workspace layout for up to max_chunks chunks and list_slots candidate-list slots.
@@ -3014,7 +3069,6 @@ Carve carve(int64_t max_chunks, int64_t list_slots, int32_t S, adatopk_dtype dt)
     c.rows3 = take(sizeof(uint32_t) * NB3 * max_parts);
     c.ldef = take(sizeof(uint32_t) * max_parts);
     c.lerr = take(sizeof(double) * max_parts);
-    c.wire_err = take(sizeof(float) * static_cast<size_t>(S < 1 ? 1 : S));  // error norms on their way into message headers
     c.L_idx = take(sizeof(int32_t) * static_cast<size_t>(list_slots));
     c.L_val = take(static_cast<size_t>(elem_size(dt)) * static_cast<size_t>(list_slots));
     c.total = p;
@@ -3036,11 +3090,11 @@ void bounds_for(int64_t n_total, int32_t S, int64_t *max_chunks, int64_t *list_s
 // library), which gives every launch start / stop events carrying the timestamps of the dispatch
 // itself, as a profiler sees it; the product build launches plainly and keeps no state.
 enum Stage {
-    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_HEADER, ST_SMALL, ST_ALL, NSTAGE
+    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_SMALL, ST_ALL, NSTAGE
 };
 #ifdef ADATOPK_MEASURE_BUILD
 const char *const kStageNames[NSTAGE] = {"k_scan_spec", "k_judge", "k_hist1", "k_scan", "k_refine", "k_emit",
-                                         "k_fill", "k_scatter", "k_merge", "k_wire_header", "k_small", "k_keep_all"};
+                                         "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all"};
 bool g_measure = false;
 bool g_events_made = false;
 hipEvent_t g_start[NSTAGE], g_stop[NSTAGE];
@@ -3100,14 +3154,15 @@ template <int VEC> adatopk_status launch_batch(const Launch &a, int total_chunks
 // Where a compress call writes.  Plain: idx_out / val_out arrays, tensor s at element offset[s]
 // (offset = exclusive scan of k, S + 1 entries).  Wire: one message buffer (idx_out), tensor s's
 // message at byte offset[s] (S entries): its index section behind the header, its values behind the
-// padded indices, and the error norms in the workspace (err_out is ignored) for the header kernel
-// to pick up.
+// padded indices, the error norm in the header (err_out is not used); ratio: what the headers name, or
+// nullptr for n / k.
 struct OutSpec {
     void *idx_out;
     int idx_bytes;
     void *val_out;
     const int64_t *offset;
     bool wire;
+    const double *ratio;
 };
 
 // Size of the sample and the ranks in it that bracket the k-th key of a tensor of n elements, or
@@ -3173,9 +3228,11 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     bounds_for(n_total, S, &max_chunks, &list_slots);
     const Carve cv = carve(max_chunks, list_slots, S, dt);
     char *ws = static_cast<char *>(workspace);
-    if (out.wire) err_out = reinterpret_cast<float *>(ws + cv.wire_err);
     const int64_t header = out.wire ? static_cast<int64_t>(sizeof(adatopk_wire_header)) : 0;
 
+    auto ratio_of = [&](int32_t s) {  // as a message's header names it
+        return out.ratio ? out.ratio[s] : (k[s] > 0 ? static_cast<double>(n[s]) / static_cast<double>(k[s]) : 0.0);
+    };
     // Only small tensors: one launch, one workgroup per tensor, no workspace traffic.
     bool all_small = true;
     for (int32_t s = 0; s < S; ++s) all_small = all_small && n[s] <= SMALL_N;
@@ -3186,8 +3243,9 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             for (int32_t i = 0; i < cnt; ++i) {
                 sl.seg[i].x = dense[s0 + i];
                 sl.seg[i].out_off = out_offset[s0 + i] + header;
-                sl.seg[i].n = static_cast<int32_t>(n[s0 + i]);
-                sl.seg[i].k = static_cast<int32_t>(k[s0 + i]);
+                sl.n[i] = static_cast<uint16_t>(n[s0 + i]);
+                sl.k[i] = static_cast<uint16_t>(k[s0 + i]);
+                if (out.wire) sl.ratio[i] = ratio_of(s0 + i);
             }
             sl.idx_out = idx_out;
             sl.idx64 = idx_bytes == 8 ? 1u : 0u;
@@ -3261,6 +3319,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             const int32_t s = which[i];
             d.x = dense[s];
             d.out_off = out_offset[s] + header;
+            if (out.wire) d.ratio = ratio_of(s);
             const int64_t ns = n_select(s), ks = kept_whole(s) ? 0 : k[s];
             d.n = static_cast<int32_t>(ns);
             d.k = static_cast<int32_t>(ks);
@@ -3540,37 +3599,6 @@ adatopk_status decompress_segmented_impl(const int32_t *idx, const void *val, co
 }
 
 // ---- wire message: header | indices, padded to 16 bytes | values
-struct WireWords {
-    uint32_t w[sizeof(adatopk_wire_header) / 4];
-};
-// Headers of up to HDR_MAXSEG messages in one launch, after the compress kernels: workgroup s stores
-// the header words of message s (built on the host; the error norm comes from err[s], which the
-// compress kernels left in the workspace) and zeroes the padding between its index and value sections.
-constexpr int HDR_MAXSEG = 48;
-struct HeaderLaunch {
-    WireWords hdr[HDR_MAXSEG];
-    int64_t msg_off[HDR_MAXSEG];  // byte offset of the message in the buffer
-    unsigned char *base;
-    const float *err;
-};
-static_assert(sizeof(HeaderLaunch) <= 4096, "kernel arguments stay within 4 KB");
-__global__ __launch_bounds__(BLOCK) void k_wire_header(const HeaderLaunch a) {
-    const int s = blockIdx.x;
-    const uint32_t t = threadIdx.x;
-    unsigned char *msg = a.base + a.msg_off[s];
-    constexpr uint32_t ERR_WORD = offsetof(adatopk_wire_header, err_norm) / 4;
-    if (t < sizeof(adatopk_wire_header) / 4)
-        reinterpret_cast<uint32_t *>(msg)[t] = (t == ERR_WORD) ? __float_as_uint(a.err[s]) : a.hdr[s].w[t];
-    const WireWords &h = a.hdr[s];
-    const uint64_t k = h.w[offsetof(adatopk_wire_header, k) / 4] |
-                       (static_cast<uint64_t>(h.w[offsetof(adatopk_wire_header, k) / 4 + 1]) << 32);
-    const uint64_t voff = h.w[offsetof(adatopk_wire_header, val_offset) / 4] |
-                          (static_cast<uint64_t>(h.w[offsetof(adatopk_wire_header, val_offset) / 4 + 1]) << 32);
-    const uint32_t ib = h.w[offsetof(adatopk_wire_header, index_bytes) / 4] & 0xFFu;
-    const uint64_t pad_a = sizeof(adatopk_wire_header) + k * ib;
-    if (pad_a + t < voff) msg[pad_a + t] = 0;  // at most 15 bytes
-}
-
 // Compress of S tensors into S wire messages in one buffer (message s at byte msg_off[s]).
 adatopk_status compress_wire_impl(const void *const *dense, const int64_t *n, const int64_t *k, int32_t S,
                                   adatopk_dtype dt, int32_t index_bytes, const double *ratio, void *wire_out,
@@ -3589,42 +3617,8 @@ adatopk_status compress_wire_impl(const void *const *dense, const int64_t *n, co
         end_prev = msg_off[s] + static_cast<int64_t>(bytes);
     }
     if (static_cast<uint64_t>(end_prev) > wire_capacity) return ADATOPK_EINVAL;
-    const OutSpec out{wire_out, index_bytes, nullptr, msg_off, true};
-    const adatopk_status rc = compress_impl(dense, n, k, S, dt, out, nullptr, workspace, workspace_bytes, st);
-    if (rc != ADATOPK_OK) return rc;
-    // the error norms are in the workspace now (stream order): write the headers around them
-    int64_t n_total = 0;
-    for (int32_t s = 0; s < S; ++s) n_total += n[s];
-    int64_t max_chunks, list_slots;
-    bounds_for(n_total, S, &max_chunks, &list_slots);
-    const float *err = reinterpret_cast<const float *>(static_cast<char *>(workspace) +
-                                                       carve(max_chunks, list_slots, S, dt).wire_err);
-    for (int32_t s0 = 0; s0 < S; s0 += HDR_MAXSEG) {
-        HeaderLaunch a{};
-        const int32_t cnt = (S - s0 < HDR_MAXSEG) ? S - s0 : HDR_MAXSEG;
-        for (int32_t i = 0; i < cnt; ++i) {
-            const int32_t s = s0 + i;
-            adatopk_wire_header h;
-            memset(&h, 0, sizeof h);
-            h.magic = ADATOPK_WIRE_MAGIC;
-            h.version = ADATOPK_WIRE_VERSION;
-            h.algorithm = ADATOPK_WIRE_TOPK;
-            h.dtype = static_cast<uint8_t>(dt);
-            h.index_bytes = static_cast<uint8_t>(index_bytes);
-            h.n = n[s];
-            h.k = k[s];
-            h.ratio = ratio ? ratio[s] : (k[s] > 0 ? static_cast<double>(n[s]) / static_cast<double>(k[s]) : 0.0);
-            h.idx_offset = sizeof(adatopk_wire_header);
-            h.val_offset = static_cast<int64_t>(wire_val_offset(k[s], index_bytes));
-            memcpy(&a.hdr[i], &h, sizeof h);
-            a.msg_off[i] = msg_off[s];
-        }
-        a.base = static_cast<unsigned char *>(wire_out);
-        a.err = err + s0;
-        launch(ST_HEADER, k_wire_header, dim3(cnt), st, a);
-        if (hipGetLastError() != hipSuccess) return ADATOPK_ERUNTIME;
-    }
-    return ADATOPK_OK;
+    const OutSpec out{wire_out, index_bytes, nullptr, msg_off, true, ratio};
+    return compress_impl(dense, n, k, S, dt, out, nullptr, workspace, workspace_bytes, st);
 }
 
 // Device address of `scratch` on the current device: every GPU holds its own copy of the array at
@@ -3660,7 +3654,7 @@ adatopk_status adatopk_compress(const void *dense, int64_t n, adatopk_dtype dt, 
                                 void *hip_stream) {
     const void *ptrs[1] = {dense};
     const int64_t off[2] = {0, k};
-    const OutSpec out{idx_out, 4, val_out, off, false};
+    const OutSpec out{idx_out, 4, val_out, off, false, nullptr};
     return compress_impl(ptrs, &n, &k, 1, dt, out, err_norm_out, workspace, workspace_bytes,
                          static_cast<hipStream_t>(hip_stream));
 }
@@ -3676,7 +3670,7 @@ adatopk_status adatopk_compress_noalloc(const void *dense, int64_t n, adatopk_dt
     // call left in the array does not matter.
     const void *ptrs[1] = {dense};
     const int64_t off[2] = {0, k};
-    const OutSpec out{idx_out, 4, val_out, off, false};
+    const OutSpec out{idx_out, 4, val_out, off, false, nullptr};
     return compress_impl(ptrs, &n, &k, 1, dt, out, err_norm_out, ptr, ADATOPK_NOALLOC_SCRATCH_BYTES,
                          static_cast<hipStream_t>(hip_stream));
 }
@@ -3685,7 +3679,7 @@ adatopk_status adatopk_compress_segmented(const void *const *dense, const int64_
                                           adatopk_dtype dt, int32_t *idx_out, void *val_out,
                                           const int64_t *out_offset, float *err_norm_out, void *workspace,
                                           size_t workspace_bytes, void *hip_stream) {
-    const OutSpec out{idx_out, 4, val_out, out_offset, false};
+    const OutSpec out{idx_out, 4, val_out, out_offset, false, nullptr};
     return compress_impl(dense, n, k, S, dt, out, err_norm_out, workspace, workspace_bytes,
                          static_cast<hipStream_t>(hip_stream));
 }
