@@ -151,6 +151,7 @@ __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
 
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
 constexpr uint32_t FLAG_SPEC = 2u;      // the speculative pass runs for this tensor
+constexpr int FLAG_SAMPLE_SHIFT = 4;    // four bits from here up: the sample's size in batches of SAMPLE_BATCH dword loads per thread
 constexpr int FLAG_SLOT_SHIFT = 8;      // bits from here up: the tensor's entry of err_out
 struct SegDesc {
     const void *x;       // device pointer of the tensor
@@ -158,16 +159,16 @@ struct SegDesc {
     int32_t n, k;
     int32_t chunk_begin, nchunks;  // its chunks are workgroups [chunk_begin, chunk_begin + nchunks) of every compress kernel
     uint32_t flags;
-    uint32_t r_lo, r_hi; // speculative pass: ranks in the sample (counted from the largest key) that bracket the k-th key
-    uint32_t sample_batches;  // ... and the sample's size in batches of SAMPLE_BATCH dword loads per thread
+    uint32_t ranks;      // speculative pass: ranks in the sample (counted from the largest key) that bracket the k-th key, the lower
+                         // key's in the low half
+    int32_t E;           // elements per chunk (multiple of the tile)
+    uint32_t list_tiles; // tiles of the chunks of the tensors before this one: where its candidate lists begin
     double ratio;        // wire mode: goes into the message's header
 };
 
 struct Launch {
     SegDesc seg[MAXSEG];
     int32_t S;
-    int32_t E;      // elements per chunk (multiple of the tile)
-    uint32_t cap;   // list slots per chunk (E / LIST_DIV)
     uint32_t sub;   // workgroups per chunk in the list kernels (1 .. MAXSUB): long candidate lists are cut into parts
     uint32_t idx64;
     uint32_t wait_rounds;  // k_judge: rounds of waiting for other workgroups before it gives up
@@ -189,6 +190,12 @@ struct Launch {
     float *err_out;
 };
 static_assert(sizeof(Launch) <= 4096, "kernel arguments stay within 4 KB");
+
+// List slots of a chunk of the tensor, and the first one of its chunk c.
+__device__ __forceinline__ uint32_t list_cap(const SegDesc &sg) { return static_cast<uint32_t>(sg.E) / LIST_DIV; }
+__device__ __forceinline__ size_t list_at(const SegDesc &sg, int c) {
+    return (static_cast<size_t>(sg.list_tiles) + static_cast<size_t>(c) * (static_cast<uint32_t>(sg.E) / TILE)) * (TILE / LIST_DIV);
+}
 
 // Where a segment's k pairs go.  Plain mode: element out_off of the idx / val arrays.  Wire mode:
 // byte out_off of the message buffer holds the indices, the values start at the next multiple of
@@ -804,8 +811,8 @@ __device__ __forceinline__ void store_rows(uint32_t *h, uint32_t *rows, uint32_t
 template <int VEC, bool SHARED>
 __device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t *h, uint32_t *sm) {
     using St = Stream<VEC>;
-    const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * a.E;
-    const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
+    const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
+    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     for (int b = threadIdx.x; b < NB1; b += BLOCK) h[b] = 0;
     __syncthreads();
 
@@ -1075,7 +1082,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     static_assert(MAXB == 4 || MAXB == 2, "sample batches");
     const int lane = threadIdx.x & 63;
     const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));  // in a scalar register
-    const int nbatch = static_cast<int>(sg.sample_batches);           // uniform; 1 .. MAXB
+    const int nbatch = static_cast<int>((sg.flags >> FLAG_SAMPLE_SHIFT) & 15u);  // uniform; 1 .. MAXB
     // 16-byte loads: a run is 64 lanes x 16 bytes = 1 KB; nbatch * (SAMPLE_BATCH / 4) * NW runs, a power of two
     constexpr int QUADS = SAMPLE_BATCH / 4;
     const int run_shift = __builtin_ctz(QUADS * NW) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
@@ -1138,7 +1145,8 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NW; ++i) floor_key = sm[i] < floor_key ? sm[i] : floor_key;
-    if (sg.r_lo > BLOCK) floor_key = 0;
+    const uint32_t r_lo = sg.ranks & 0xFFFFu, r_hi = sg.ranks >> 16;
+    if (r_lo > BLOCK) floor_key = 0;
     uint32_t floor_bin = floor_key >> SAMPLE_SH;
     floor_bin = floor_bin < 1 ? 1 : floor_bin;
     // A thread whose sampled keys all lie in one bin (a constant tensor) adds them with one add:
@@ -1171,7 +1179,6 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     uint32_t total;
     const uint32_t inc = block_incl_scan(own, sm, &total);
     uint32_t above = total - inc;  // sampled (and counted) keys in the bins of the threads after this one
-    const uint32_t r_lo = sg.r_lo, r_hi = sg.r_hi;
 #pragma unroll
     for (int j = PER - 1; j >= 0; --j) {
         const uint32_t with = above + cnt[j];  // suffix sum at this bin
@@ -1211,6 +1218,18 @@ struct ScanLds {
     uint32_t s_pick[4];
 };
 
+// The launch's arguments once more, as if from another address: what is read through the result is read again where it
+// is used instead of being kept, in a scalar register or in a lane of a vector register, from one phase of a long kernel
+// to the next.  (The vector registers that this takes up push a tile's values to scratch memory, and a reload from
+// there waits for the tiles ahead: exact passes at a fifth kept 115 -> 93 us.  A function that is not inlined
+// keeps its registers apart but saves half of its caller's, 37 MB of scratch stores over the grid, 20 us.)
+template <typename T> using ArgsPtr = const T __attribute__((address_space(4))) *;
+__device__ __forceinline__ const Launch &args_again() {
+    ArgsPtr<Launch> p = (ArgsPtr<Launch>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Launch *)p;
+}
+
 // DEPTH = register buffers of one tile each that the streaming loop rotates through, i.e. DEPTH - 1
 // tiles of loads in flight while one is processed.  The loop waits for memory, not for instructions
 // (one workgroup per compute unit with one tile ahead keeps 32 KB per compute unit in flight, which at
@@ -1220,24 +1239,25 @@ struct ScanLds {
 // kernel to stay within 128 vector registers: one tile ahead.
 //
 // One chunk with the window (lo, shw); `cur` holds the chunk's first tile if it has a full one.  PAIR: leave
-// the two counts by which k_hist1 judges a speculative window.  `room`: a.cap, or 0 for no list, if the chunk's candidates
+// the two counts by which k_hist1 judges a speculative window.  `room`: the list's capacity, or 0 for no list, if the chunk's candidates
 // are known (listed_room) not to fit one; a speculative scan knows nothing yet.
 template <int VEC, bool PAIR, int DEPTH, bool SHARED>
-__device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t lo, uint32_t shw, uint32_t room,
+__device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32_t lo, uint32_t shw, uint32_t room,
                                            uint32_t (&cur)[Stream<VEC>::SLOTS], ScanLds &l) {
     static_assert(DEPTH == 2 || DEPTH == 3, "one or two tiles ahead");
+    const SegDesc &sg = a.seg[s];
     using R = typename Raw<VEC>::type;
     using St = Stream<VEC>;
-    const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * a.E;
-    const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
+    const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
+    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
     uint32_t nxt[St::SLOTS], far[St::SLOTS], valid[St::SLOTS];  // far: DEPTH 3 only
     // Becomes 0 also when a dense tile makes the scan give the chunk's list up.  (Every speculating tensor has a sample: the
-    // condition only keeps this count apart from a.cap.  Left equal to it at the start, the compiler spills a dozen
+    // condition only keeps this count apart from the capacity.  Left equal to it at the start, the compiler spills a dozen
     // scalar registers more in the tile loop of the 16-bit scan: 26 M bf16 41.5 -> 42.3 us per compress and decompress.)
-    uint32_t cap = PAIR ? (sg.sample_batches != 0 ? a.cap : 0u) : room;
-    int32_t *Li = a.L_idx + static_cast<size_t>(g) * a.cap;
-    R *Lv = static_cast<R *>(a.L_val) + static_cast<size_t>(g) * a.cap;
+    uint32_t cap = PAIR ? (sg.ranks != 0 ? list_cap(sg) : 0u) : room;
+    int32_t *Li = a.L_idx + list_at(sg, g - sg.chunk_begin);
+    R *Lv = static_cast<R *>(a.L_val) + list_at(sg, g - sg.chunk_begin);
 
     uint2 *stage = reinterpret_cast<uint2 *>(l.smem);
     uint32_t *hw = l.smem + 2 * STAGE_CAP;
@@ -1311,15 +1331,17 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
     flush_stage<VEC>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
 
     const double bsum = block_sum_f64(acc, l.smd);
+    const Launch &again = args_again();  // (what the end of the chunk needs of them does not take up registers in the tile loop)
+    const uint32_t capacity = list_cap(again.seg[s]);
     if (threadIdx.x == 0) {
-        store_count<SHARED>(&a.chunk_err[g], bsum);
+        store_count<SHARED>(&again.chunk_err[g], bsum);
         // more than the list holds = "read this chunk from the input", also for a list that was given up
-        store_count<SHARED>(&a.cnt[g], (cap == 0 && running <= a.cap) ? a.cap + 1 : running);
+        store_count<SHARED>(&again.cnt[g], (cap == 0 && running <= capacity) ? capacity + 1 : running);
     }
     __syncthreads();
-    if (PAIR && a.S != 1 && threadIdx.x == 0) a.cpairA[g] = make_uint2(running, hw[NBW - 1]);  // (k_judge reads the rows)
+    if (PAIR && again.S != 1 && threadIdx.x == 0) again.cpairA[g] = make_uint2(running, hw[NBW - 1]);  // (k_judge reads the rows)
     // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
-    store_rows<NBW, NCW, SHARED>(hw, a.rowsW, a.coarseW, g, l.sm);
+    store_rows<NBW, NCW, SHARED>(hw, again.rowsW, again.coarseW, g, l.sm);
 }
 
 // The exact scan knows a chunk's candidates beforehand: the keys of the bucket B of the k-th key and of those above, which
@@ -1329,10 +1351,10 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, const SegDesc &sg, i
 // lists of all its chunks instead cost tensors whose kept values lie together, sorted or behind zeros, the empty and
 // short lists that spare the next kernel the input: 6 x 8.4 M at 30 %, sorted 263 us, behind zeros 227; chunk by
 // chunk 223 and 187, spread evenly 254 either way.)
-template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Launch &a, int g, uint32_t B) {
+template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Launch &a, const SegDesc &sg, int g, uint32_t B) {
     const uint32_t *at = a.rows1 + static_cast<size_t>(g) * NB1 + (B < NB1 ? B : NB1 - 1);
     const uint32_t candidates = SHARED ? load_agent(at) : *at;
-    return B < NB1 && candidates > a.cap ? 0u : a.cap;  // (B = NB1: nothing is kept, nothing reaches the window)
+    return B < NB1 && candidates > list_cap(sg) ? 0u : list_cap(sg);  // (B = NB1: nothing is kept, nothing reaches the window)
 }
 
 template <int VEC, bool SPEC, int DEPTH>
@@ -1345,8 +1367,8 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
     const int s = find_segment(a, g);
     const SegDesc &sg = a.seg[s];
     const int c = g - sg.chunk_begin;
-    const int64_t beg = static_cast<int64_t>(c) * a.E;
-    const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
+    const int64_t beg = static_cast<int64_t>(c) * sg.E;
+    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     if (SPEC) {
         if (!(sg.flags & FLAG_SPEC)) return;  // this tensor goes straight to the exact passes
     } else {
@@ -1381,7 +1403,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
                                                         a.coarse1 + static_cast<size_t>(sg.chunk_begin) * NC1, sg.nchunks,
                                                         static_cast<uint32_t>(sg.k), l.smem, first_tile);
         // (asked only where many chunks can be in question: the answer costs a short tensor a memory round trip)
-        room = sg.k > sg.n / LIST_DIV ? listed_room<false>(a, g, p1.B) : a.cap;
+        room = sg.k > sg.n / LIST_DIV ? listed_room<false>(a, sg, g, p1.B) : list_cap(sg);
         lo = p1.B << SH1;  // 2^31 when nothing is kept (k = 0): no key reaches it
         shw = VEC == TAG_F32 ? SH1 - BITS3 : 16;  // fp32: the bucket's 2^20 keys in 1024 bins; 16-bit: its 16 patterns in 16
         if (c == 0 && threadIdx.x == 0) {
@@ -1389,7 +1411,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, DEPTH, false>(a, sg, g, lo, shw, room, cur, l);
+    scan_chunk<VEC, SPEC, DEPTH, false>(a, s, g, lo, shw, room, cur, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -1428,13 +1450,13 @@ template <int VEC> struct ChunkSource {
 // Entries of part `part` of `sub` of chunk g's candidates (list entries, or the chunk's elements when
 // its list overflowed): the same cut as chunk_source below.  A short list leaves its later parts empty;
 // the list kernels return at once for those and skip what they would have stored.
-__device__ __forceinline__ uint32_t part_entries(const Launch &a, const SegDesc &sg, int g, uint32_t count, uint32_t part,
+__device__ __forceinline__ uint32_t part_entries(const SegDesc &sg, int g, uint32_t count, uint32_t part,
                                                  uint32_t sub) {  // count = a.cnt[g], loaded by the caller
     constexpr uint32_t LT = BLOCK * LU;
     const int c = g - sg.chunk_begin;
-    const int64_t beg = static_cast<int64_t>(c) * a.E;
-    const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
-    const uint32_t entries = count > a.cap ? static_cast<uint32_t>(end - beg) : count;
+    const int64_t beg = static_cast<int64_t>(c) * sg.E;
+    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
+    const uint32_t entries = count > list_cap(sg) ? static_cast<uint32_t>(end - beg) : count;
     if (sub == 1) return entries;
     uint32_t per = (entries + sub - 1) / sub;
     per = (per + LT - 1) / LT * LT;
@@ -1452,9 +1474,9 @@ __device__ __forceinline__ ChunkSource<VEC> chunk_source(const Launch &a, const 
     constexpr uint32_t LT = BLOCK * LU;
     ChunkSource<VEC> src;
     const int c = g - sg.chunk_begin;
-    const int64_t beg = static_cast<int64_t>(c) * a.E;
-    const int64_t end = (beg + a.E < sg.n) ? beg + a.E : sg.n;
-    src.from_input = count > a.cap;
+    const int64_t beg = static_cast<int64_t>(c) * sg.E;
+    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
+    src.from_input = count > list_cap(sg);
     const uint32_t entries = src.from_input ? static_cast<uint32_t>(end - beg) : count;
     uint32_t per = (entries + sub - 1) / sub;
     per = (per + LT - 1) / LT * LT;
@@ -1464,8 +1486,8 @@ __device__ __forceinline__ ChunkSource<VEC> chunk_source(const Launch &a, const 
     // (an empty part, or one that is read from the input, points at the start of the chunk's list: the loads
     // that ChunkSource issues without a condition then stay inside the chunk's own region)
     const uint32_t list_off = (src.from_input || src.len == 0) ? 0u : off;
-    src.Li = a.L_idx + static_cast<size_t>(g) * a.cap + list_off;
-    src.Lv = static_cast<const R *>(a.L_val) + static_cast<size_t>(g) * a.cap + list_off;
+    src.Li = a.L_idx + list_at(sg, c) + list_off;
+    src.Lv = static_cast<const R *>(a.L_val) + list_at(sg, c) + list_off;
     src.x = static_cast<const R *>(sg.x) + beg + off;
     src.base = static_cast<uint32_t>(beg) + off;
     src.lo = lo;
@@ -1888,7 +1910,7 @@ __device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &s
         const int cc = threadIdx.x;
         sum += a.chunk_err[sg.chunk_begin + cc];
         for (uint32_t pp = 0; pp < sub; ++pp)
-            if (part_entries(a, sg, sg.chunk_begin + cc, count_t, pp, sub) != 0)  // an empty part stored nothing
+            if (part_entries(sg, sg.chunk_begin + cc, count_t, pp, sub) != 0)  // an empty part stored nothing
                 sum += a.lerr[static_cast<size_t>(sg.chunk_begin + cc) * sub + pp];
     }
 #pragma unroll
@@ -2025,7 +2047,7 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
         uint32_t gt_own = 0, eq_own = 0;                    // what part `part` itself holds
         if (static_cast<int>(threadIdx.x) < sg.nchunks && t.any_kept) {
             for (uint32_t pp = 0; pp < sub; ++pp) {
-                if (part_entries(a, sg, sg.chunk_begin + threadIdx.x, count_t, pp, sub) == 0) continue;  // nothing stored for it, nothing in it
+                if (part_entries(sg, sg.chunk_begin + threadIdx.x, count_t, pp, sub) == 0) continue;  // nothing stored for it, nothing in it
                 const size_t e = static_cast<size_t>(sg.chunk_begin + threadIdx.x) * sub + pp;
                 const uint32_t *r = t.rows + e * t.row_len;
                 const uint32_t above = (t.t_bin + 1 < t.row_len) ? r[t.t_bin + 1] : 0u;
@@ -2228,18 +2250,6 @@ __device__ __forceinline__ void claim_chunk(JudgeSync *sync, uint32_t chunk, Own
         o.chunk[o.count++] = static_cast<uint16_t>(chunk);
 }
 
-// The launch's arguments once more, as if from another address: what is read through the result is read again where it
-// is used instead of being kept, in a scalar register or in a lane of a vector register, from one phase of a long kernel
-// to the next.  (The vector registers that this takes up push a tile's values to scratch memory, and a reload from
-// there waits for the tiles ahead: exact passes at a fifth kept 115 -> 93 us.  A function that is not inlined
-// keeps its registers apart but saves half of its caller's, 37 MB of scratch stores over the grid, 20 us.)
-template <typename T> using ArgsPtr = const T __attribute__((address_space(4))) *;
-__device__ __forceinline__ const Launch &args_again() {
-    ArgsPtr<Launch> p = (ArgsPtr<Launch>)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(p));
-    return *(const Launch *)p;
-}
-
 // Works on this workgroup's chunks, reports them, and waits until all `nchunks` have been through the pass,
 // helping with unclaimed ones.  work(chunk) is called by the whole workgroup.  False: gave up.
 template <typename Work>
@@ -2375,7 +2385,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             const Launch &a = args_again();
             const int ci = static_cast<int>(c);
             const uint32_t listed = a.cnt[ci];
-            if (above && listed <= a.cap) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, h, l.sl.sm);
+            if (above && listed <= list_cap(a.seg[0])) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, h, l.sl.sm);
             else hist1_chunk<VEC, true>(a, a.seg[0], ci, h, l.sl.sm);
             __syncthreads();
         }))
@@ -2385,8 +2395,8 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     auto first_tile = [&](uint32_t c) {
         const Launch &a = args_again();
         const SegDesc &sg = a.seg[0];
-        const int64_t beg = static_cast<int64_t>(c) * a.E;
-        if ((sg.flags & FLAG_ALIGNED4) && (beg + a.E < sg.n ? a.E : sg.n - beg) >= TILE) St::load_fast(sg.x, beg, cur);
+        const int64_t beg = static_cast<int64_t>(c) * sg.E;
+        if ((sg.flags & FLAG_ALIGNED4) && (beg + sg.E < sg.n ? sg.E : sg.n - beg) >= TILE) St::load_fast(sg.x, beg, cur);
     };
     const uint32_t first_chunk = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[0])));
     const Launch &a1 = args_again();
@@ -2397,11 +2407,11 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             const Launch &a = args_again();
             const int ci = static_cast<int>(c);
             const uint32_t listed = a.cnt[ci];
-            if (above && listed <= a.cap) {
+            if (above && listed <= list_cap(a.seg[0])) {
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
-                scan_chunk<VEC, false, DEPTH, true>(a, a.seg[0], ci, lo, shw, listed_room<true>(a, ci, p1.B), cur, l.sl);
+                scan_chunk<VEC, false, DEPTH, true>(a, 0, ci, lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), cur, l.sl);
             }
             __syncthreads();
         }))
@@ -3043,6 +3053,48 @@ int64_t chunk_elems(int64_t n_batch, int32_t S_batch, int64_t target) {
 }
 inline int64_t chunk_target(int32_t S_batch) { return S_batch == 1 ? CTARGET_ONE : CTARGET; }
 
+// Elements per chunk, E[i], for each of S tensors of one launch: at most `target` chunks and `list_slots` list slots in all
+// (an empty tensor still gets one chunk).  n(i), k(i): elements and kept elements.
+// All workgroups of a scan run at once, so it takes as long as the chunk with the most work: an element that is kept costs
+// SCAN_KEPT_COST times what reading one does (single fp32 tensors of 25 M: 20 us of streaming at 1 % kept, 28 at 10 %), and the tensors
+// of a batch keep anything from 0.1 to 20 %.  Tensors that need the exact passes beside ones that speculate have
+// the chip to themselves in those two passes, so their chunks are cut finer: with m chunks for n elements of
+// either kind, n / m + 2 n' / m' is least at m' / m = sqrt(2 n' / n).
+constexpr double SCAN_KEPT_COST = 4.5;
+template <typename N, typename K>
+void plan_chunks(int32_t S, int64_t target, int64_t list_slots, N &&n, K &&k, const bool *spec, int64_t n_batch, int64_t *E) {
+    const int64_t tile = TILE;
+    double weight[MAXSEG], cost_spec = 0.0, cost_exact = 0.0;
+    for (int32_t i = 0; i < S; ++i) {
+        const double kept = n(i) > 0 ? static_cast<double>(k(i)) / static_cast<double>(n(i)) : 0.0;
+        weight[i] = 1.0 + SCAN_KEPT_COST * (kept < 1.0 / LIST_DIV ? kept : 1.0 / LIST_DIV);  // (beyond that nothing is listed)
+        (spec[i] ? cost_spec : cost_exact) += weight[i] * static_cast<double>(n(i));
+    }
+    const double finer = cost_spec > 0.0 && cost_exact > 0.0 ? sqrt(2.0 * cost_spec / cost_exact) : 1.0;
+    for (int32_t i = 0; i < S; ++i)
+        if (!spec[i]) weight[i] *= finer;
+    double budget = (cost_spec + cost_exact * finer) / static_cast<double>(S == 1 ? target : target - S / 2);  // of a chunk
+    auto tiles_of = [&](int32_t i) {
+        const int64_t t = static_cast<int64_t>(budget / (weight[i] * TILE) + (S == 1 ? 0.999999 : 0.5));
+        return t < 1 ? static_cast<int64_t>(1) : t;
+    };
+    int64_t tiles = 0;
+    for (;; budget *= 1.05) {
+        int64_t chunks = 0;
+        tiles = 0;
+        for (int32_t i = 0; i < S; ++i) {
+            E[i] = tiles_of(i) * tile;
+            const int64_t c = n(i) > 0 ? (n(i) + E[i] - 1) / E[i] : 1;
+            chunks += c;
+            tiles += c * (E[i] / tile);
+        }
+        if (chunks <= target) break;
+    }
+    if (tiles * (tile / LIST_DIV) <= list_slots) return;
+    const int64_t fits = chunk_elems(n_batch, S, target);  // whatever the tensors' lengths are
+    for (int32_t i = 0; i < S; ++i) E[i] = fits;
+}
+
 struct Carve {
     size_t state, G3, rows1, coarse1, rowsW, coarseW, cpairA, cnt, chunk_err, rows3, ldef, lerr, L_idx, L_val, total;
 };
@@ -3175,8 +3227,7 @@ struct OutSpec {
 // key down to the lower end is a candidate in every call: 3.5 instead of 5 takes 3 us off a tensor
 // of 25 M elements at k = 10 %).  The sample is the smallest of a quarter, half or all of
 // SAMPLE_ELEMS that expects SPEC_GOOD_EXPECTED kept elements, and the largest otherwise.
-bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *r_lo, uint32_t *r_hi,
-                       uint32_t *batches) {
+bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
     if (!aligned16 || n < SPEC_MIN_N || k <= 0 || k > n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
     const int epd = 4 / elem_size(dt);
     const int max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;
@@ -3190,8 +3241,8 @@ bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, u
     if (mu < SPEC_MIN_EXPECTED) return false;
     const double margin = SPEC_SIGMAS * sqrt(mu) + 2.0;
     const double lo = ceil(mu + SPEC_SIGMAS_LOW * sqrt(mu) + 2.0), hi = floor(mu - margin);
-    *r_lo = lo > 4.0e9 ? 0xFFFFFFFFu : static_cast<uint32_t>(lo);
-    *r_hi = hi < 1.0 ? 0u : static_cast<uint32_t>(hi);
+    static_assert(SAMPLE_ELEMS < 65536, "a rank fits 16 bits");
+    *ranks = static_cast<uint32_t>(lo) | (hi < 1.0 ? 0u : static_cast<uint32_t>(hi) << 16);  // (lo: well below the sample's size, k being at most 21 %)
     *batches = static_cast<uint32_t>(nb);
     return true;
 }
@@ -3264,30 +3315,30 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     // (one empty chunk each) and get their pairs from k_keep_all below.
     auto kept_whole = [&](int32_t s) { return n[s] > 0 && k[s] == n[s]; };
     auto n_select = [&](int32_t s) { return kept_whole(s) ? static_cast<int64_t>(0) : n[s]; };
+    auto speculates = [&](int32_t s, uint32_t *ranks, uint32_t *batches) {
+        return speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, ranks, batches);
+    };
     // One launch of the kernels for the tensors `which[0 .. count)` of the call.
     auto select_group = [&](const int32_t *which, int32_t count) -> adatopk_status {
         Launch a{};
         a.S = count;
-        // Chunk size of this launch: at most chunk_target() chunks in all, so that all workgroups are
+        // Chunk sizes of this launch: at most chunk_target() chunks in all, so that all workgroups are
         // resident at once (a few chunks beyond that would run as a second, nearly empty round).
         int64_t n_batch = 0;
-        int32_t whole = 0;
+        int32_t whole = 0, nspec = 0;
+        uint32_t ranks[MAXSEG], batches[MAXSEG];
+        bool spec[MAXSEG];
         for (int32_t i = 0; i < a.S; ++i) {
-            n_batch += n_select(which[i]);
-            whole += kept_whole(which[i]) ? 1 : 0;
+            const int32_t s = which[i];
+            n_batch += n_select(s);
+            whole += kept_whole(s) ? 1 : 0;
+            spec[i] = speculates(s, &ranks[i], &batches[i]);
+            nspec += spec[i] ? 1 : 0;
         }
         const int64_t target = chunk_target(a.S);
-        const int64_t E_fits = chunk_elems(n_batch, a.S, target);  // fits whatever the tensors' lengths are
-        int64_t E = (n_batch + target - 1) / target;
-        E = E < TILE ? TILE : (E + TILE - 1) / TILE * TILE;
-        auto chunks_at = [&](int64_t e) {
-            int64_t count = 0;
-            for (int32_t i = 0; i < a.S; ++i) count += n_select(which[i]) > 0 ? (n_select(which[i]) + e - 1) / e : 1;
-            return count;
-        };
-        while (E < E_fits && chunks_at(E) > target) E += TILE;
-        a.E = static_cast<int32_t>(E);
-        a.cap = static_cast<uint32_t>(E / LIST_DIV);
+        int64_t E[MAXSEG];
+        plan_chunks(a.S, target, list_slots, [&](int32_t i) { return n_select(which[i]); },
+                    [&](int32_t i) { return kept_whole(which[i]) ? 0 : k[which[i]]; }, spec, n_batch, E);
         a.state = reinterpret_cast<SegState *>(ws + cv.state);
         a.G3 = reinterpret_cast<uint32_t *>(ws + cv.G3);
         a.rows1 = reinterpret_cast<uint32_t *>(ws + cv.rows1);
@@ -3312,8 +3363,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.val_out = val_out;
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
-        bool speculate = false;
-        double densest = 0.0;  // largest keep fraction of the launch
+        int64_t list_tiles = 0;
+        double longest = 0.0;  // the most kept elements that a chunk of the launch has on average
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];
             const int32_t s = which[i];
@@ -3324,31 +3375,34 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             d.n = static_cast<int32_t>(ns);
             d.k = static_cast<int32_t>(ks);
             d.chunk_begin = chunks;
-            d.nchunks = ns > 0 ? static_cast<int32_t>((ns + E - 1) / E) : 1;  // an empty tensor keeps one (empty) chunk
+            d.E = static_cast<int32_t>(E[i]);
+            d.list_tiles = static_cast<uint32_t>(list_tiles);
+            d.nchunks = ns > 0 ? static_cast<int32_t>((ns + E[i] - 1) / E[i]) : 1;  // an empty tensor keeps one (empty) chunk
             const bool aligned4 = reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
             d.flags = (aligned4 ? FLAG_ALIGNED4 : 0u) | (static_cast<uint32_t>(s - which[0]) << FLAG_SLOT_SHIFT);
-            const bool aligned16 = reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0;  // the sample is read with 16-byte loads
-            if (speculation_ranks(ns, ks, dt, aligned16, &d.r_lo, &d.r_hi, &d.sample_batches)) {
-                d.flags |= FLAG_SPEC;
-                speculate = true;
+            if (spec[i]) {
+                d.flags |= FLAG_SPEC | (batches[i] << FLAG_SAMPLE_SHIFT);
+                d.ranks = ranks[i];
             }
             chunks += d.nchunks;
-            if (ns > 0 && static_cast<double>(ks) / static_cast<double>(ns) > densest)
-                densest = static_cast<double>(ks) / static_cast<double>(ns);
+            list_tiles += d.nchunks * (E[i] / TILE);
+            if (ns > 0) {
+                const double kept = static_cast<double>(ks) / static_cast<double>(ns) * static_cast<double>(E[i]);
+                longest = kept > longest ? kept : longest;
+            }
         }
         // parts per chunk for the list kernels: a chunk's candidates are about a third more than its kept
         // elements; a part gets about SUB_ENTRIES of them
         {
-            const double per_chunk = 1.35 * densest * static_cast<double>(E);
-            int sub = static_cast<int>(per_chunk / SUB_ENTRIES) + 1;
+            int sub = static_cast<int>(1.35 * longest / SUB_ENTRIES) + 1;
             const int most = S == 1 ? MAXSUB_ONE : MAXSUB;  // what the workspace of this call was laid out for
             a.sub = static_cast<uint32_t>(sub > most ? most : sub);
         }
-        if (chunks > max_chunks || static_cast<int64_t>(chunks) * a.cap > list_slots) return ADATOPK_ERUNTIME;  // planner invariant
+        if (chunks > max_chunks || list_tiles * (TILE / LIST_DIV) > list_slots) return ADATOPK_ERUNTIME;  // planner invariant
         if (whole < a.S) {  // something to select
-            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, speculate, st)
-                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, speculate, st)
-                                                             : launch_batch<TAG_F16>(a, chunks, speculate, st);
+            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, st)
+                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, nspec > 0, st)
+                                                             : launch_batch<TAG_F16>(a, chunks, nspec > 0, st);
             if (rc != ADATOPK_OK) return rc;
         }
         if (whole > 0) {
@@ -3386,8 +3440,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         int32_t exact[MAXSEG];
         for (int32_t i = 0; i < count; ++i) {
             const int32_t s = s0 + i;
-            uint32_t lo, hi, batches;
-            const bool spec = speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, &lo, &hi, &batches);
+            uint32_t ranks, batches;
+            const bool spec = speculates(s, &ranks, &batches);
             if (spec) n_spec += n[s];
             else n_exact += n_select(s);
             if (spec || n_select(s) == 0) order[nspec++] = s;  // (what is not selected from goes with either)

@@ -568,3 +568,23 @@ def test_decompress_of_as_many_tensors_as_a_launch_holds_and_one_more(tensors):
     got = H.gpu_decompress_segmented(np.concatenate(idx), np.concatenate(val), off, ns)
     for n, i, v, y in zip(ns, idx, val, got):
         assert np.array_equal(H.bits(y), H.bits(orc.decompress(i, v, n))), (n, i.size)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("scale", [1, 2])
+def test_tensors_of_one_launch_have_chunks_of_their_own_length(dtype, scale):
+    # unequal keep shares and lengths: chunks of dense tensors and of those that need the exact passes are shorter; with
+    # scale 1 none speculates (less than 8 Mi elements could), with 2 four of the seven do
+    import gpu_harness as H
+
+    lens = [n * scale for n in (1_000_003, 35_000, 2_600_000, 0, 1_700_001, 4_500, 750_000)]
+    shares = [0.2, 0.01, 0.001, 0.0, 0.05, 0.9, 0.3]
+    kinds = ["normal", "normal", "normal", "normal", "sparse", "few_levels", "normal"]
+    xs = [wl.small_case(kd, n, seed=40 + i, dtype=dtype) for i, (kd, n) in enumerate(zip(kinds, lens))]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    gi, gv, off, ge = H.gpu_compress_segmented(xs, ks)
+    for s, (x, k) in enumerate(zip(xs, ks)):
+        ri, rv, re = orc.compress(x, k)
+        assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), s
+        assert H.same_err(ge[s], re, ERR_RTOL), (s, ge[s], re)
+    check_segmented_decompress(gi, gv, off, lens)
