@@ -172,6 +172,8 @@ struct Launch {
     uint32_t sub;   // workgroups per chunk in the list kernels (1 .. MAXSUB): long candidate lists are cut into parts
     uint32_t idx64;
     uint32_t wait_rounds;  // k_judge: rounds of waiting for other workgroups before it gives up
+    uint32_t norms; // k_emit, and k_judge for 16-bit types: workgroups in front of those of the parts that add up the tensors' error norms;
+                    // 0: the workgroup of a tensor's last part does it (where every compute unit has a part already)
     uint32_t wire;  // outputs are wire messages in one buffer (idx_out): values follow the padded index section
     SegState *state;
     uint32_t *G3;                 // [MAXSEG][NB3] global histogram of the last digit
@@ -1900,10 +1902,9 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 
 // Error norm of the tensor, by one workgroup.  Everything it needs was stored by earlier kernels: per-chunk sums of squares below the window (the scan), per-part sums of squares of
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
-// ones of a bin add count * value^2.  Fixed summation order.  count_t: the candidate count of chunk threadIdx.x.
-template <int VEC>
-__device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &sg, const Threshold &t, uint32_t bin_key,
-                                               const uint32_t (&my_bins)[NB3 / BLOCK], uint32_t count_t, uint32_t sub, double *smd) {
+// ones of a bin add count * value^2.  Fixed summation order.
+// dropped_below: the first two for chunk threadIdx.x, whose candidate count is count_t.
+__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t count_t, uint32_t sub) {
     double sum = 0.0;
     static_assert(CTARGET <= BLOCK, "thread t has chunk t");
     if (static_cast<int>(threadIdx.x) < sg.nchunks) {
@@ -1913,6 +1914,11 @@ __device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &s
             if (part_entries(sg, sg.chunk_begin + cc, count_t, pp, sub) != 0)  // an empty part stored nothing
                 sum += a.lerr[static_cast<size_t>(sg.chunk_begin + cc) * sub + pp];
     }
+    return sum;
+}
+template <int VEC>
+__device__ __forceinline__ void error_norm_f32(const Launch &a, const SegDesc &sg, const Threshold &t, uint32_t bin_key,
+                                               const uint32_t (&my_bins)[NB3 / BLOCK], double sum, double *smd) {
 #pragma unroll
     for (int j = 0; j < NB3 / BLOCK; ++j) {
         const uint32_t b = threadIdx.x * (NB3 / BLOCK) + j;
@@ -2138,19 +2144,24 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
     }
 }
 
-// k_emit.  Prologue -> threshold key T, tie quota q (threshold_f32 / threshold_16); the tensor's last chunk also
-// adds up the error norm; then emit_part on the workgroup's part.
+// k_emit.  Prologue -> threshold key T, tie quota q (threshold_f32 / threshold_16), then emit_part on the workgroup's
+// part.  Where there is room, one more workgroup for each tensor adds up its error norm (and writes its message's header): done by the
+// last part's workgroup as well, in front of its placing, the sum is what the launch ends with (6.5 M fp16 values 30.2 -> 28.6 us per
+// compress and decompress).
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(Launch a) {
     // fp32: the last digit's histogram; 16-bit types: the global suffix sums of the window bins up to Bw
     __shared__ uint32_t h[VEC == TAG_F32 ? NB3 : NBW + 1];
     __shared__ EmitLds l;
 
     const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;  // 16-bit types: one workgroup per chunk (their counts are per chunk)
-    const int g = blockIdx.x / sub;  // chunk
-    const uint32_t part = blockIdx.x % sub;
-    const int s = find_segment(a, g);
+    const bool norm_only = blockIdx.x < a.norms;       // uniform
+    const uint32_t slot = blockIdx.x - a.norms;
+    const int s = norm_only ? static_cast<int>(blockIdx.x) : find_segment(a, static_cast<int>(slot / sub));
     const SegDesc &sg = a.seg[s];
+    const int g = norm_only ? sg.chunk_begin : static_cast<int>(slot / sub);  // chunk
+    const uint32_t part = norm_only ? 0u : slot % sub;
     const int c = g - sg.chunk_begin;
+    const bool norm = norm_only || (a.norms == 0 && c == sg.nchunks - 1 && part == sub - 1 && err_ptr(a, sg) != nullptr);
     const SegStateWords stw = read_state(&a.state[s]);
     // thread t: the candidate count of the tensor's chunk t, for the offsets and the error sum further down
     // (asked for here, with the state record: one memory round trip less in front of the rows' loads)
@@ -2159,19 +2170,18 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
     const uint32_t kout = static_cast<uint32_t>(sg.k);
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, sub, lo);
-    // the tensor's last chunk is the short one, and the last part of a chunk the shortest
-    const bool sums_error = c == sg.nchunks - 1 && part == sub - 1 && err_ptr(a, sg) != nullptr;
-    const bool writes_header = a.wire != 0 && c == 0 && part == 0;
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, norm_only ? 0u : a.cnt[g], part, sub, lo);
+    if (norm && a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
     if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
-        if (sums_error && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
-        if (writes_header) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
+        if (norm && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
         return;
     }
-    // 16-bit types: thread t of that workgroup asks for chunk t's sum of squares below the window now, so that it
-    // arrives behind the prologue instead of costing the error sum a memory round trip of its own at the end
+    // what the error norm's workgroup needs of the chunks arrives behind the prologue
     double below_t = 0.0;
-    if (VEC != TAG_F32 && sums_error && static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
+    if (norm) {
+        if (VEC == TAG_F32) below_t = dropped_below(a, sg, count_t, sub);
+        else if (static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
+    }
 
     // The part's first tile is loaded behind the prologue's first loads (the wavefront's load counter is in order).
     uint32_t raw[LU];
@@ -2187,16 +2197,16 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         first_tile();
         __builtin_amdgcn_sched_barrier(0);
         t = threshold_f32(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, h, l.sm, l.s_pick);
-        if (sums_error) error_norm_f32<VEC>(a, sg, t, lo + (stw.Bw << shw), my_bins, count_t, sub, l.smd);
+        if (norm) error_norm_f32<VEC>(a, sg, t, lo + (stw.Bw << shw), my_bins, below_t, l.smd);
     } else {
         const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
                                                     a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks,
                                                     kout, h, first_tile);
         t = threshold_16(a, pw, kout, lo, shw);
-        if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
+        if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
+    if (norm_only) return;
     emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, count_t, raw, id, l);
-    if (writes_header) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
 }
 
 // ------------------------------------------------------------------ k_judge
@@ -2236,7 +2246,8 @@ constexpr int POLLS_BEFORE_HELP = 32;      // tens of us: far beyond the spread 
                                            // process's first call, when some XCDs have the code much later than others)
 constexpr int MAX_POLL_ROUNDS = 1 << 18;   // seconds
 struct Owned {
-    uint32_t count;              // chunks this workgroup has claimed ...
+    uint32_t me;                 // this workgroup's number among those of the chunks
+    uint32_t count;              // chunks it has claimed ...
     uint32_t arrived;
     uint32_t help;               // how far from this workgroup's own number the nearest unclaimed chunk is
     uint16_t chunk[CTARGET_ONE]; // ... and which
@@ -2245,7 +2256,7 @@ static_assert(CTARGET_ONE <= BLOCK, "one thread per claim word");
 // The whole chunk for this workgroup, if nobody else has it.  Called by one thread.
 __device__ __forceinline__ void claim_chunk(JudgeSync *sync, uint32_t chunk, Owned &o) {
     uint32_t nobody = 0;
-    if (__hip_atomic_compare_exchange_strong(&sync->claim[chunk], &nobody, blockIdx.x + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+    if (__hip_atomic_compare_exchange_strong(&sync->claim[chunk], &nobody, o.me + 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT))
         o.chunk[o.count++] = static_cast<uint16_t>(chunk);
 }
@@ -2289,9 +2300,9 @@ __device__ __forceinline__ bool exact_pass(int pass, uint32_t nchunks, Owned &o,
         __syncthreads();
         if (o.arrived) return true;
         // help: the first chunk from here on that nobody has claimed
-        if (threadIdx.x < nchunks && load_agent(&sync->claim[(blockIdx.x + threadIdx.x) % nchunks]) == 0) atomicMin(&o.help, threadIdx.x);
+        if (threadIdx.x < nchunks && load_agent(&sync->claim[(o.me + threadIdx.x) % nchunks]) == 0) atomicMin(&o.help, threadIdx.x);
         __syncthreads();
-        if (threadIdx.x == 0 && o.help < nchunks) claim_chunk(sync, (blockIdx.x + o.help) % nchunks, o);
+        if (threadIdx.x == 0 && o.help < nchunks) claim_chunk(sync, (o.me + o.help) % nchunks, o);
         __syncthreads();
     }
     return false;
@@ -2373,7 +2384,8 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     // quarter of them (25 M fp32 values, a tenth kept: 132 us in this kernel, from all XCDs 98; a fifth kept: 348, 115).
     if (threadIdx.x == 0) {
         l.own.count = 0;
-        if (blockIdx.x < nchunks) claim_chunk(judge_sync(a0), blockIdx.x, l.own);
+        l.own.me = blockIdx.x - (VEC == TAG_F32 ? 0u : a0.norms);  // (the norm's own workgroup: none of them)
+        if (l.own.me < nchunks) claim_chunk(judge_sync(a0), l.own.me, l.own);
     }
     __syncthreads();
     if (l.own.count == 0) return;
@@ -2465,15 +2477,18 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     const SegDesc &sg = a.seg[0];
     const uint32_t nchunks = static_cast<uint32_t>(sg.nchunks), kout = static_cast<uint32_t>(sg.k);
     const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;  // 16-bit types: one part per chunk (their counts are per chunk)
-    const int c = static_cast<int>(blockIdx.x / sub);
-    const uint32_t part = blockIdx.x % sub;
+    const uint32_t norms = VEC == TAG_F32 ? 0u : a.norms;   // (fp32: k_emit adds up the error norm)
+    const bool norm_only = blockIdx.x < norms;              // uniform
+    const uint32_t slot = norm_only ? 0u : blockIdx.x - norms;
+    const int c = static_cast<int>(slot / sub);
+    const uint32_t part = slot % sub;
+    const bool norm = VEC != TAG_F32 && (norm_only || (norms == 0 && c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr));
     const SegStateWords stw = read_state(&a.state[0]);
     const uint32_t lo = stw.loA, shw = stw.shwA;
     const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;  // candidates of chunk threadIdx.x
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, a.cnt[c], part, sub, lo);
-    double below_t = 0.0;  // 16-bit types, the workgroup that adds up the error norm: see k_emit
-    const bool sums_error = VEC != TAG_F32 && c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr;
-    if (sums_error && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, norm_only ? 0u : a.cnt[c], part, sub, lo);
+    double below_t = 0.0;
+    if (norm && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
 
     uint32_t raw[LU];
     int32_t id[LU];
@@ -2508,11 +2523,11 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
             a.state[0].Bw = pw.B;
             a.state[0].c_gtw = pw.above;
         }
-        if (src.len != 0) refine_part<VEC, WIDE>(a, 0, src, blockIdx.x, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
+        if (src.len != 0) refine_part<VEC, WIDE>(a, 0, src, slot, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
     } else {
         const Threshold t = threshold_16(a, pw, kout, lo, shw);
-        if (sums_error) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
-        emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
+        if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
+        if (!norm_only) emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
     }
 }
 
@@ -3171,7 +3186,7 @@ inline void launch(int stage, K kernel, dim3 grid, hipStream_t st, Args... args)
 // The kernels of one launch.  With `speculate` the first full read of the input is the speculative
 // scan; the two exact passes behind it return at once for every tensor whose speculation held and
 // do the work for the others, so what reaches k_refine is complete either way.
-template <int VEC> adatopk_status launch_batch(const Launch &a, int total_chunks, bool speculate, hipStream_t st) {
+template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, hipStream_t st) {
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
     if (speculate) {
@@ -3180,8 +3195,12 @@ template <int VEC> adatopk_status launch_batch(const Launch &a, int total_chunks
     }
     const dim3 parts(total_chunks * (VEC == TAG_F32 ? a.sub : 1u));
     const bool wide = one_per_cu && parts.x == grid.x;  // one workgroup per chunk, at most one per compute unit: see Wide
+    // (a wide kernel has a compute unit's registers to itself: one workgroup too many waits for another one to end, 2 us)
+    const uint32_t S = static_cast<uint32_t>(a.S);
+    a.norms = (a.err_out != nullptr || a.wire) && (!wide || parts.x + S <= CTARGET_ONE) ? S : 0u;
+    const dim3 parts_and_norms(parts.x + a.norms);
     if (speculate && a.S == 1) {
-        dim3 judges = parts;
+        dim3 judges = VEC == TAG_F32 ? parts : parts_and_norms;
 #ifdef ADATOPK_MEASURE_BUILD
         if (g_judge_missing > 0 && static_cast<uint32_t>(g_judge_missing) < parts.x) judges.x -= static_cast<uint32_t>(g_judge_missing);
 #endif
@@ -3197,8 +3216,8 @@ template <int VEC> adatopk_status launch_batch(const Launch &a, int total_chunks
         }
     }
     if (VEC == TAG_F32 || !(speculate && a.S == 1)) {
-        if (wide) launch(ST_EMIT, k_emit<VEC, true>, parts, st, a);
-        else launch(ST_EMIT, k_emit<VEC, false>, parts, st, a);
+        if (wide) launch(ST_EMIT, k_emit<VEC, true>, parts_and_norms, st, a);
+        else launch(ST_EMIT, k_emit<VEC, false>, parts_and_norms, st, a);
     }
     return hipGetLastError() == hipSuccess ? ADATOPK_OK : ADATOPK_ERUNTIME;
 }
