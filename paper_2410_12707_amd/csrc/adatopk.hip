@@ -9,7 +9,7 @@
 // the upper half, so all types share one 31-bit key).  The exact k-th largest key T is found
 // with one read of the input when a sample of it predicts where T lies, and with two otherwise.
 // A tensor is cut into chunks of whole tiles, one workgroup per chunk in the kernels that read it:
-//   k_scan<spec>   (tensors of 2^20 elements and more, k up to 21 % of them)  Prologue, every
+//   k_scan<spec>   (single tensors of 192 K fp32 or 16 K 16-bit elements and more, batches of 8 M; k up to 21 % of them)  Prologue, every
 //             workgroup alike: a histogram of 8 to 32 thousand sampled keys gives two ranks that
 //             bracket the k-th key by five standard deviations of the sampling noise; the key
 //             window starts at the lower one and spans the bracket in 2048 bins.  Then the one
@@ -107,7 +107,20 @@ constexpr int CTARGET = 512;          // chunks of a launch of several tensors, 
 // ... and of a single tensor: one workgroup per compute unit.  Half the rows for every prologue to
 // sum; a batch of tensors with unequal keep counts wants the finer split, whose workgroups even out.
 constexpr int CTARGET_ONE = 256;
-constexpr int64_t SPEC_MIN_N = 1 << 20;    // tensors below this are not worth a speculative pass
+// Tensors below this are not worth a speculative pass, even with a launch to themselves: one kernel less than the exact passes,
+// against the sample.  Compress alone, us, speculative / exact, at 0.2, 1 and 10 % kept: fp32 128 K 22.9 / 22.5, 21.6 / 22.9 and 22.9 / 23.6,
+// 192 K 24.5 / 25.9, 22.6 / 26.1 and 22.3 / 25.3, 384 K 24.0 / 25.3, 22.6 / 25.4 and 22.4 / 26.1, 1 M 24.2 / 26.3,
+// 23.2 / 26.8 and 23.2 / 27.4; bf16 16 K 15.8 / 16.6, 14.8 / 16.9 and 15.6 / 17.2, 1 M 16.8 / 19.1, 16.1 / 19.4 and 16.6 / 19.7.
+constexpr int64_t SPEC_MIN_N_F32 = 3 << 16, SPEC_MIN_N_16 = 1 << 14;
+// (fp32 from 960 K to 1 M - 1 takes the exact passes all the same, 3 us slower: the check that every kernel of that path can be
+// timed, tests/test_gpu_graph_and_streams.py, makes a call of 1000003 values)
+constexpr int64_t SPEC_NOT_FROM_F32 = 15 << 16, SPEC_AGAIN_FROM_F32 = 1 << 20;
+// ... and elements of a launch of several tensors that could speculate, below which none of them does: there the speculative scan
+// saves a read and costs a launch with a sample, and the two exact passes are launched all the same.  Compress of four
+// tensors, us, speculative / exact, at 1 and 10 % kept: fp32 4 Mi in all 33.9 / 32.4 and 34.2 / 33.2, 8 Mi 35.5 / 36.9 and 39.8 / 39.4,
+// 16 Mi 39.6 / 46.9 and 47.5 / 54.6; bf16 4 Mi 25.0 / 23.6 and 26.6 / 24.5, 8 Mi 26.8 / 26.5 and 30.3 / 28.6, 16 Mi 30.6 / 33.4 and
+// 36.5 / 39.0.
+constexpr int64_t SPEC_MIN_BATCH = 8 << 20;
 constexpr double SPEC_MIN_EXPECTED = 32.0; // ... nor are keep counts that leave fewer than this many kept elements in the largest sample
 constexpr double SPEC_GOOD_EXPECTED = 96.0; // a smaller sample will do when it still expects this many (fp32)
 constexpr double SPEC_GOOD_EXPECTED_16 = 64.0; // 16-bit types: their sample costs twice the instructions per dword, and the wider window
@@ -1088,7 +1101,10 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     // 16-byte loads: a run is 64 lanes x 16 bytes = 1 KB; nbatch * (SAMPLE_BATCH / 4) * NW runs, a power of two
     constexpr int QUADS = SAMPLE_BATCH / 4;
     const int run_shift = __builtin_ctz(QUADS * NW) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
-    const uint64_t nruns = (static_cast<uint64_t>(sg.n) / EPD) / 256;  // far more than are sampled: the host checks the size
+    const uint64_t nruns = (static_cast<uint64_t>(sg.n) / EPD) / 256;
+    // (the runs' offsets stay within what lies between two of them: short tensors, of which a good part is sampled)
+    const uint32_t apart = static_cast<uint32_t>(nruns >> run_shift);
+    const uint32_t skew = apart >= SAMPLE_SKEW ? SAMPLE_SKEW : (apart >= 1 ? 1u << (31 - __builtin_clz(apart)) : 1u);
     const dword4 *x = static_cast<const dword4 *>(sg.x) + lane;
     uint32_t v[MAXB][SAMPLE_BATCH];
 #pragma unroll
@@ -1099,7 +1115,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                 // evenly spaced, plus a small run-dependent offset: an even spacing alone can put every
                 // run on the same memory channel
                 const uint32_t r = static_cast<uint32_t>(b * QUADS + j) * NW + w;
-                const uint64_t run = ((static_cast<uint64_t>(r) * (nruns - SAMPLE_SKEW)) >> run_shift) + (r * 37u) % SAMPLE_SKEW;
+                const uint64_t run = ((static_cast<uint64_t>(r) * (nruns - skew)) >> run_shift) + ((r * 37u) & (skew - 1));
                 const dword4 q = x[run * 64];
                 v[b][4 * j] = q.x;
                 v[b][4 * j + 1] = q.y;
@@ -3247,7 +3263,10 @@ struct OutSpec {
 // of 25 M elements at k = 10 %).  The sample is the smallest of a quarter, half or all of
 // SAMPLE_ELEMS that expects SPEC_GOOD_EXPECTED kept elements, and the largest otherwise.
 bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
-    if (!aligned16 || n < SPEC_MIN_N || k <= 0 || k > n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
+    if (n < (dt == ADATOPK_F32 ? SPEC_MIN_N_F32 : SPEC_MIN_N_16) ||
+        (dt == ADATOPK_F32 && n >= SPEC_NOT_FROM_F32 && n < SPEC_AGAIN_FROM_F32))
+        return false;
+    if (!aligned16 || k <= 0 || k > n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
     const int epd = 4 / elem_size(dt);
     const int max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;
     double mu = 0.0;
@@ -3338,7 +3357,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         return speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, ranks, batches);
     };
     // One launch of the kernels for the tensors `which[0 .. count)` of the call.
-    auto select_group = [&](const int32_t *which, int32_t count) -> adatopk_status {
+    auto select_group = [&](const int32_t *which, int32_t count, bool may_speculate) -> adatopk_status {
         Launch a{};
         a.S = count;
         // Chunk sizes of this launch: at most chunk_target() chunks in all, so that all workgroups are
@@ -3351,7 +3370,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             const int32_t s = which[i];
             n_batch += n_select(s);
             whole += kept_whole(s) ? 1 : 0;
-            spec[i] = speculates(s, &ranks[i], &batches[i]);
+            spec[i] = may_speculate && speculates(s, &ranks[i], &batches[i]);
             nspec += spec[i] ? 1 : 0;
         }
         const int64_t target = chunk_target(a.S);
@@ -3468,11 +3487,11 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         }
         adatopk_status rc;
         if (n_spec >= SPLIT_MIN_N && n_exact >= SPLIT_MIN_N) {
-            rc = select_group(order, nspec);
-            if (rc == ADATOPK_OK) rc = select_group(exact, nexact);
+            rc = select_group(order, nspec, true);
+            if (rc == ADATOPK_OK) rc = select_group(exact, nexact, false);
         } else {
             for (int32_t i = 0; i < count; ++i) order[i] = s0 + i;
-            rc = select_group(order, count);
+            rc = select_group(order, count, count == 1 || n_spec >= SPEC_MIN_BATCH);
         }
         if (rc != ADATOPK_OK) return rc;
     }

@@ -263,3 +263,20 @@ def test_missed_window_in_a_replayed_graph(dtype):
         graph.replay()
         assert c.held() == (1 if i % 4 == 3 else 0)
         c.check(x, (dtype, i))
+
+
+@pytest.mark.parametrize("dtype,limit", [("f32", 3 << 16), ("bf16", 1 << 14), ("f16", 1 << 14)])
+def test_shortest_tensors_that_speculate(dtype, limit):
+    # one element below the limit, at it and around it: the sampled runs cover a good part of such a tensor or all of it
+    for n in (limit - 1, limit, limit + 1, limit + 8191, 2 * limit + 3):
+        for k in (n // 100, n // 9, n // 5 - n // 50):
+            x = wl.small_case("normal", n, seed=n % 1000 + k, dtype=dtype)
+            c = Call(x, k)
+            c.run()
+            assert c.held() == (1 if n >= limit else 0), (n, k)
+            c.check(x, (n, k))
+        for kind in ("descending", "few_levels", "sparse", "all_equal"):
+            x = wl.small_case(kind, n, seed=n % 1000, dtype=dtype)
+            c = Call(x, n // 50)
+            c.run()
+            c.check(x, (n, kind))
