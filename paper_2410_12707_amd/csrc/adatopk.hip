@@ -1919,16 +1919,16 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 // Error norm of the tensor, by one workgroup.  Everything it needs was stored by earlier kernels: per-chunk sums of squares below the window (the scan), per-part sums of squares of
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
 // ones of a bin add count * value^2.  Fixed summation order.
-// dropped_below: the first two for chunk threadIdx.x, whose candidate count is count_t.
-__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t count_t, uint32_t sub) {
+// dropped_below: this thread's share of the first two.
+__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t sub) {
     double sum = 0.0;
-    static_assert(CTARGET <= BLOCK, "thread t has chunk t");
-    if (static_cast<int>(threadIdx.x) < sg.nchunks) {
-        const int cc = threadIdx.x;
-        sum += a.chunk_err[sg.chunk_begin + cc];
-        for (uint32_t pp = 0; pp < sub; ++pp)
-            if (part_entries(sg, sg.chunk_begin + cc, count_t, pp, sub) != 0)  // an empty part stored nothing
-                sum += a.lerr[static_cast<size_t>(sg.chunk_begin + cc) * sub + pp];
+    const uint32_t nparts = static_cast<uint32_t>(sg.nchunks) * sub;
+    for (uint32_t e = threadIdx.x; e < nparts; e += BLOCK) {
+        const uint32_t cc = e / sub, pp = e - cc * sub;
+        const uint32_t count = a.cnt[sg.chunk_begin + cc];
+        const double below_bin = a.lerr[static_cast<size_t>(sg.chunk_begin) * sub + e], below_window = a.chunk_err[sg.chunk_begin + cc];
+        if (pp == 0) sum += below_window;
+        if (part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sub) != 0) sum += below_bin;  // (an empty part stored nothing)
     }
     return sum;
 }
@@ -2055,46 +2055,43 @@ __device__ __forceinline__ void load_entries(const ChunkSource<VEC> &src, uint32
 }
 
 // Stable compaction of one part into idx_out / val_out (key > T, plus the first q keys equal to T).  raw / id
-// hold the part's first entries; count_t is the candidate count of the tensor's chunk threadIdx.x.
+// hold the part's first entries.
 template <int VEC, bool WIDE>
 __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, const ChunkSource<VEC> &src, int c, uint32_t part, uint32_t sub,
-                                          const Threshold &t, uint32_t count_t, uint32_t (&raw)[LU], int32_t (&id)[LU], EmitLds &l) {
+                                          const Threshold &t, uint32_t (&raw)[LU], int32_t (&id)[LU], EmitLds &l) {
     using R = typename Raw<VEC>::type;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t T = t.T, q = t.q, kout = static_cast<uint32_t>(sg.k);
-    // Output offsets of this part = sums over the earlier chunks, and over the earlier parts of this
-    // chunk, of (#keys above T, #keys equal to T).  Thread t takes chunk t.
+    // Output offsets of this part = sums over the tensor's earlier parts of (#keys above T, #keys equal to T).  A thread
+    // takes every BLOCK-th part, all its loads in flight together.  (A thread per chunk that went through the chunk's parts was a memory
+    // round trip per part: a batch of 24 x 33.5 MB with up to eight parts to a chunk spent them in each of its workgroups.)
     {
-        uint32_t gt = 0, eq = 0, gt_mine = 0, eq_mine = 0;  // totals of chunk t; what its parts before `part` hold
-        uint32_t gt_own = 0, eq_own = 0;                    // what part `part` itself holds
-        if (static_cast<int>(threadIdx.x) < sg.nchunks && t.any_kept) {
-            for (uint32_t pp = 0; pp < sub; ++pp) {
-                if (part_entries(sg, sg.chunk_begin + threadIdx.x, count_t, pp, sub) == 0) continue;  // nothing stored for it, nothing in it
-                const size_t e = static_cast<size_t>(sg.chunk_begin + threadIdx.x) * sub + pp;
-                const uint32_t *r = t.rows + e * t.row_len;
-                const uint32_t above = (t.t_bin + 1 < t.row_len) ? r[t.t_bin + 1] : 0u;
-                const uint32_t g1 = (t.extra_gt != nullptr ? t.extra_gt[e] : 0u) + above;
-                const uint32_t e1 = r[t.t_bin] - above;
-                if (pp < part) {
-                    gt_mine += g1;
-                    eq_mine += e1;
-                }
-                if (pp == part) {
-                    gt_own = g1;
-                    eq_own = e1;
-                }
+        const uint32_t me = static_cast<uint32_t>(c) * sub + part;
+        uint32_t gt = 0, eq = 0;
+        for (uint32_t e0 = 0; t.any_kept && e0 <= me; e0 += BLOCK) {  // uniform
+            const uint32_t e = e0 + threadIdx.x, at = opaque(e < me ? e : me);
+            const uint32_t cc = at / sub, pp = at - cc * sub;
+            const size_t stored = static_cast<size_t>(sg.chunk_begin) * sub + at;
+            const uint32_t *r = t.rows + stored * t.row_len;
+            const uint32_t count = a.cnt[sg.chunk_begin + cc];
+            const uint32_t here = r[t.t_bin], next = r[t.t_bin + 1 < t.row_len ? t.t_bin + 1 : t.t_bin];
+            const uint32_t extra = t.extra_gt != nullptr ? t.extra_gt[stored] : 0u;
+            const bool any = part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sub) != 0;  // else nothing is stored for it
+            const uint32_t above = t.t_bin + 1 < t.row_len ? next : 0u;
+            const uint32_t g1 = any ? extra + above : 0u, e1 = any ? here - above : 0u;
+            if (e < me) {
                 gt += g1;
                 eq += e1;
+            } else if (e == me) {
+                l.s_off[2] = g1;
+                l.s_off[3] = e1;
             }
         }
-        uint32_t tot;
-        const uint32_t inc_gt = block_incl_scan(gt, l.sm, &tot);
-        const uint32_t inc_eq = block_incl_scan(eq, l.sm, &tot);
-        if (static_cast<int>(threadIdx.x) == c) {
-            l.s_off[0] = inc_gt - gt + gt_mine;
-            l.s_off[1] = inc_eq - eq + eq_mine;
-            l.s_off[2] = gt_own;
-            l.s_off[3] = eq_own;
+        if (!t.any_kept && threadIdx.x == 0) l.s_off[2] = l.s_off[3] = 0;
+        block_sum2_u32(gt, eq, l.sm);
+        if (threadIdx.x == 0) {
+            l.s_off[0] = gt;
+            l.s_off[1] = eq;
         }
         __syncthreads();
     }
@@ -2179,9 +2176,6 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const int c = g - sg.chunk_begin;
     const bool norm = norm_only || (a.norms == 0 && c == sg.nchunks - 1 && part == sub - 1 && err_ptr(a, sg) != nullptr);
     const SegStateWords stw = read_state(&a.state[s]);
-    // thread t: the candidate count of the tensor's chunk t, for the offsets and the error sum further down
-    // (asked for here, with the state record: one memory round trip less in front of the rows' loads)
-    const uint32_t count_t = static_cast<int>(threadIdx.x) < sg.nchunks ? a.cnt[sg.chunk_begin + threadIdx.x] : 0u;
     const bool spec = stw.spec_held != 0;
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
@@ -2195,7 +2189,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     // what the error norm's workgroup needs of the chunks arrives behind the prologue
     double below_t = 0.0;
     if (norm) {
-        if (VEC == TAG_F32) below_t = dropped_below(a, sg, count_t, sub);
+        if (VEC == TAG_F32) below_t = dropped_below(a, sg, sub);
         else if (static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
     }
 
@@ -2222,7 +2216,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
     if (norm_only) return;
-    emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, count_t, raw, id, l);
+    emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, raw, id, l);
 }
 
 // ------------------------------------------------------------------ k_judge
@@ -2449,7 +2443,6 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;
     const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, kout, h);
-    const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;
     for (uint32_t i = 0; i < l.own.count; ++i) {
         const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[i]));
         const uint32_t count = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(load_agent(&a.cnt[c]))));
@@ -2479,7 +2472,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
                 if (threadIdx.x == 0) norm_or_nan(a, sg);
             }
-            emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
+            emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, raw, id, l.el);
             __syncthreads();  // the scratch changes hands
         }
     }
@@ -2501,7 +2494,6 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     const bool norm = VEC != TAG_F32 && (norm_only || (norms == 0 && c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr));
     const SegStateWords stw = read_state(&a.state[0]);
     const uint32_t lo = stw.loA, shw = stw.shwA;
-    const uint32_t count_t = threadIdx.x < nchunks ? a.cnt[threadIdx.x] : 0u;  // candidates of chunk threadIdx.x
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, norm_only ? 0u : a.cnt[c], part, sub, lo);
     double below_t = 0.0;
     if (norm && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
@@ -2543,7 +2535,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     } else {
         const Threshold t = threshold_16(a, pw, kout, lo, shw);
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
-        if (!norm_only) emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, count_t, raw, id, l.el);
+        if (!norm_only) emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, raw, id, l.el);
     }
 }
 
