@@ -165,7 +165,8 @@ __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
 constexpr uint32_t FLAG_SPEC = 2u;      // the speculative pass runs for this tensor
 constexpr int FLAG_SAMPLE_SHIFT = 4;    // four bits from here up: the sample's size in batches of SAMPLE_BATCH dword loads per thread
-constexpr int FLAG_SLOT_SHIFT = 8;      // bits from here up: the tensor's entry of err_out
+constexpr int FLAG_SUB_SHIFT = 8;       // four bits: workgroups per chunk in the list kernels, the logarithm
+constexpr int FLAG_SLOT_SHIFT = 12;     // bits from here up: the tensor's entry of err_out
 struct SegDesc {
     const void *x;       // device pointer of the tensor
     int64_t out_off;     // first output slot of this segment; in wire mode the byte offset of its index section
@@ -181,8 +182,9 @@ struct SegDesc {
 
 struct Launch {
     SegDesc seg[MAXSEG];
+    uint16_t part_begin[MAXSEG];  // first part of a tensor: the list kernels cut the candidates of a chunk into parts (list_parts)
     int32_t S;
-    uint32_t sub;   // workgroups per chunk in the list kernels (1 .. MAXSUB): long candidate lists are cut into parts
+    uint32_t parts; // parts of all tensors
     uint32_t idx64;
     uint32_t wait_rounds;  // k_judge: rounds of waiting for other workgroups before it gives up
     uint32_t norms; // k_emit, and k_judge for 16-bit types: workgroups in front of those of the parts that add up the tensors' error norms;
@@ -195,9 +197,9 @@ struct Launch {
     uint2 *cpairA;                // [chunks] speculative pass of several tensors only: #candidates, #candidates in the open-ended last bin
     uint32_t *cnt;                // [chunks] #candidates of the chunk; more than cap: the list is incomplete
     double *chunk_err;            // [chunks] sum of squares of the chunk's elements below the window
-    uint32_t *rows3;              // [chunks * sub][NB3] suffix sums of the last digit inside the k-th key's window bin
-    uint32_t *ldef;               // [chunks * sub] #candidates in the window bins above that bin
-    double *lerr;                 // [chunks * sub] squares of the candidates in the window bins below it
+    uint32_t *rows3;              // [parts][NB3] suffix sums of the last digit inside the k-th key's window bin
+    uint32_t *ldef;               // [parts] #candidates in the window bins above that bin
+    double *lerr;                 // [parts] squares of the candidates in the window bins below it
     int32_t *L_idx;               // [chunks][cap] candidate lists, one region per chunk
     void *L_val;
     void *idx_out;     // int32 entries, or int64 when idx64 is set (the paper's index width, Sec. 5.2)
@@ -206,6 +208,9 @@ struct Launch {
 };
 static_assert(sizeof(Launch) <= 4096, "kernel arguments stay within 4 KB");
 
+// Workgroups per chunk of the tensor in the list kernels: its logarithm (1 .. MAXSUB workgroups; 16-bit types: 1, their counts
+// are per chunk).
+__device__ __forceinline__ uint32_t sub_log(const SegDesc &sg) { return (sg.flags >> FLAG_SUB_SHIFT) & 15u; }
 // List slots of a chunk of the tensor, and the first one of its chunk c.
 __device__ __forceinline__ uint32_t list_cap(const SegDesc &sg) { return static_cast<uint32_t>(sg.E) / LIST_DIV; }
 __device__ __forceinline__ size_t list_at(const SegDesc &sg, int c) {
@@ -565,6 +570,15 @@ __device__ __forceinline__ int find_segment(const Launch &a, int g) {
     if (lane < a.S) begin = a.seg[lane].chunk_begin;
     const uint64_t owner_or_before = __ballot(g >= begin);  // begins never decrease and the first is 0
     return 63 - __builtin_clzll(owner_or_before | 1ull);
+}
+
+// The same for a workgroup of the list kernels.
+__device__ __forceinline__ int find_segment_of_part(const Launch &a, uint32_t slot) {
+    if (a.S == 1) return 0;
+    const int lane = threadIdx.x & 63;
+    uint32_t begin = 0xFFFFFFFFu;
+    if (lane < a.S) begin = a.part_begin[lane];
+    return 63 - __builtin_clzll(__ballot(slot >= begin) | 1ull);
 }
 
 // An index the compiler knows nothing about.  For loads that are to be issued whatever a condition says
@@ -1465,29 +1479,29 @@ template <int VEC> struct ChunkSource {
         return static_cast<int32_t>((v & keep_mask(!from_input && i < len)) | ((base + i) & keep_mask(from_input)));
     }
 };
-// Entries of part `part` of `sub` of chunk g's candidates (list entries, or the chunk's elements when
+// Entries of part `part` of 1 << sl of chunk g's candidates (list entries, or the chunk's elements when
 // its list overflowed): the same cut as chunk_source below.  A short list leaves its later parts empty;
 // the list kernels return at once for those and skip what they would have stored.
 __device__ __forceinline__ uint32_t part_entries(const SegDesc &sg, int g, uint32_t count, uint32_t part,
-                                                 uint32_t sub) {  // count = a.cnt[g], loaded by the caller
+                                                 uint32_t sl) {  // count = a.cnt[g], loaded by the caller
     constexpr uint32_t LT = BLOCK * LU;
     const int c = g - sg.chunk_begin;
     const int64_t beg = static_cast<int64_t>(c) * sg.E;
     const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     const uint32_t entries = count > list_cap(sg) ? static_cast<uint32_t>(end - beg) : count;
-    if (sub == 1) return entries;
-    uint32_t per = (entries + sub - 1) / sub;
+    if (sl == 0) return entries;
+    uint32_t per = (entries + (1u << sl) - 1) >> sl;
     per = (per + LT - 1) / LT * LT;
     const uint64_t first = static_cast<uint64_t>(per) * part;
     if (first >= entries) return 0u;
     return (first + per < entries) ? per : entries - static_cast<uint32_t>(first);
 }
 
-// Part `part` of `sub` of chunk g's candidates: the entries are cut into `sub` runs of whole list
+// Part `part` of 1 << sl of chunk g's candidates: the entries are cut into that many runs of whole list
 // tiles; the later parts of a short list are empty.
 template <int VEC>
 __device__ __forceinline__ ChunkSource<VEC> chunk_source(const Launch &a, const SegDesc &sg, int g, uint32_t count, uint32_t part,
-                                                         uint32_t sub, uint32_t lo) {  // count = a.cnt[g], loaded by the caller
+                                                         uint32_t sl, uint32_t lo) {  // count = a.cnt[g], loaded by the caller
     using R = typename Raw<VEC>::type;
     constexpr uint32_t LT = BLOCK * LU;
     ChunkSource<VEC> src;
@@ -1496,7 +1510,7 @@ __device__ __forceinline__ ChunkSource<VEC> chunk_source(const Launch &a, const 
     const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     src.from_input = count > list_cap(sg);
     const uint32_t entries = src.from_input ? static_cast<uint32_t>(end - beg) : count;
-    uint32_t per = (entries + sub - 1) / sub;
+    uint32_t per = (entries + (1u << sl) - 1) >> sl;
     per = (per + LT - 1) / LT * LT;
     const uint64_t first = static_cast<uint64_t>(per) * part;
     const uint32_t off = first < entries ? static_cast<uint32_t>(first) : entries;
@@ -1763,16 +1777,15 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(
     __shared__ uint32_t sm[2 * NW];
     __shared__ double smd[NW];
 
-    const int g = blockIdx.x / a.sub;  // chunk
-    const uint32_t part = blockIdx.x % a.sub;
-    const int s = find_segment(a, g);
+    const int s = find_segment_of_part(a, blockIdx.x);
     const SegDesc &sg = a.seg[s];
-    const int c = g - sg.chunk_begin;
+    const uint32_t sl = sub_log(sg), at = blockIdx.x - a.part_begin[s], part = at & ((1u << sl) - 1);
+    const int c = static_cast<int>(at >> sl), g = sg.chunk_begin + c;  // chunk
     const SegStateWords stw = read_state(&a.state[s]);
     const bool spec = stw.spec_held != 0;
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, a.sub, lo);
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, sl, lo);
     if (src.len == 0 && !(c == 0 && part == 0)) return;  // an empty part (the tensor's first part still reports Bw)
 
     // The first LU entries of every thread do not depend on the prologue: their loads are in flight
@@ -1920,15 +1933,16 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
 // ones of a bin add count * value^2.  Fixed summation order.
 // dropped_below: this thread's share of the first two.
-__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t sub) {
+__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t first_part) {
     double sum = 0.0;
-    const uint32_t nparts = static_cast<uint32_t>(sg.nchunks) * sub;
+    const uint32_t sl = sub_log(sg);
+    const uint32_t nparts = static_cast<uint32_t>(sg.nchunks) << sl;
     for (uint32_t e = threadIdx.x; e < nparts; e += BLOCK) {
-        const uint32_t cc = e / sub, pp = e - cc * sub;
+        const uint32_t cc = e >> sl, pp = e & ((1u << sl) - 1);
         const uint32_t count = a.cnt[sg.chunk_begin + cc];
-        const double below_bin = a.lerr[static_cast<size_t>(sg.chunk_begin) * sub + e], below_window = a.chunk_err[sg.chunk_begin + cc];
+        const double below_bin = a.lerr[first_part + e], below_window = a.chunk_err[sg.chunk_begin + cc];
         if (pp == 0) sum += below_window;
-        if (part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sub) != 0) sum += below_bin;  // (an empty part stored nothing)
+        if (part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl) != 0) sum += below_bin;  // (an empty part stored nothing)
     }
     return sum;
 }
@@ -2057,7 +2071,7 @@ __device__ __forceinline__ void load_entries(const ChunkSource<VEC> &src, uint32
 // Stable compaction of one part into idx_out / val_out (key > T, plus the first q keys equal to T).  raw / id
 // hold the part's first entries.
 template <int VEC, bool WIDE>
-__device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, const ChunkSource<VEC> &src, int c, uint32_t part, uint32_t sub,
+__device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, const ChunkSource<VEC> &src, uint32_t first_part, int c, uint32_t part,
                                           const Threshold &t, uint32_t (&raw)[LU], int32_t (&id)[LU], EmitLds &l) {
     using R = typename Raw<VEC>::type;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2066,17 +2080,17 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
     // takes every BLOCK-th part, all its loads in flight together.  (A thread per chunk that went through the chunk's parts was a memory
     // round trip per part: a batch of 24 x 33.5 MB with up to eight parts to a chunk spent them in each of its workgroups.)
     {
-        const uint32_t me = static_cast<uint32_t>(c) * sub + part;
+        const uint32_t sl = sub_log(sg), me = (static_cast<uint32_t>(c) << sl) + part;
         uint32_t gt = 0, eq = 0;
         for (uint32_t e0 = 0; t.any_kept && e0 <= me; e0 += BLOCK) {  // uniform
             const uint32_t e = e0 + threadIdx.x, at = opaque(e < me ? e : me);
-            const uint32_t cc = at / sub, pp = at - cc * sub;
-            const size_t stored = static_cast<size_t>(sg.chunk_begin) * sub + at;
+            const uint32_t cc = at >> sl, pp = at & ((1u << sl) - 1);
+            const size_t stored = first_part + at;
             const uint32_t *r = t.rows + stored * t.row_len;
             const uint32_t count = a.cnt[sg.chunk_begin + cc];
             const uint32_t here = r[t.t_bin], next = r[t.t_bin + 1 < t.row_len ? t.t_bin + 1 : t.t_bin];
             const uint32_t extra = t.extra_gt != nullptr ? t.extra_gt[stored] : 0u;
-            const bool any = part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sub) != 0;  // else nothing is stored for it
+            const bool any = part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl) != 0;  // else nothing is stored for it
             const uint32_t above = t.t_bin + 1 < t.row_len ? next : 0u;
             const uint32_t g1 = any ? extra + above : 0u, e1 = any ? here - above : 0u;
             if (e < me) {
@@ -2166,21 +2180,19 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     __shared__ uint32_t h[VEC == TAG_F32 ? NB3 : NBW + 1];
     __shared__ EmitLds l;
 
-    const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;  // 16-bit types: one workgroup per chunk (their counts are per chunk)
     const bool norm_only = blockIdx.x < a.norms;       // uniform
     const uint32_t slot = blockIdx.x - a.norms;
-    const int s = norm_only ? static_cast<int>(blockIdx.x) : find_segment(a, static_cast<int>(slot / sub));
+    const int s = norm_only ? static_cast<int>(blockIdx.x) : find_segment_of_part(a, slot);
     const SegDesc &sg = a.seg[s];
-    const int g = norm_only ? sg.chunk_begin : static_cast<int>(slot / sub);  // chunk
-    const uint32_t part = norm_only ? 0u : slot % sub;
-    const int c = g - sg.chunk_begin;
-    const bool norm = norm_only || (a.norms == 0 && c == sg.nchunks - 1 && part == sub - 1 && err_ptr(a, sg) != nullptr);
+    const uint32_t first_part = a.part_begin[s], sl = sub_log(sg), at = norm_only ? 0u : slot - first_part, part = at & ((1u << sl) - 1);
+    const int c = static_cast<int>(at >> sl), g = sg.chunk_begin + c;  // chunk
+    const bool norm = norm_only || (a.norms == 0 && c == sg.nchunks - 1 && part + 1 == 1u << sl && err_ptr(a, sg) != nullptr);
     const SegStateWords stw = read_state(&a.state[s]);
     const bool spec = stw.spec_held != 0;
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
     const uint32_t kout = static_cast<uint32_t>(sg.k);
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, norm_only ? 0u : a.cnt[g], part, sub, lo);
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, norm_only ? 0u : a.cnt[g], part, sl, lo);
     if (norm && a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
     if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
         if (norm && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
@@ -2189,7 +2201,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     // what the error norm's workgroup needs of the chunks arrives behind the prologue
     double below_t = 0.0;
     if (norm) {
-        if (VEC == TAG_F32) below_t = dropped_below(a, sg, sub);
+        if (VEC == TAG_F32) below_t = dropped_below(a, sg, first_part);
         else if (static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
     }
 
@@ -2216,7 +2228,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
     if (norm_only) return;
-    emit_part<VEC, WIDE>(a, sg, src, c, part, sub, t, raw, id, l);
+    emit_part<VEC, WIDE>(a, sg, src, first_part, c, part, t, raw, id, l);
 }
 
 // ------------------------------------------------------------------ k_judge
@@ -2407,7 +2419,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             const Launch &a = args_again();
             const int ci = static_cast<int>(c);
             const uint32_t listed = a.cnt[ci];
-            if (above && listed <= list_cap(a.seg[0])) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, h, l.sl.sm);
+            if (above && listed <= list_cap(a.seg[0])) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, h, l.sl.sm);
             else hist1_chunk<VEC, true>(a, a.seg[0], ci, h, l.sl.sm);
             __syncthreads();
         }))
@@ -2430,7 +2442,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             const int ci = static_cast<int>(c);
             const uint32_t listed = a.cnt[ci];
             if (above && listed <= list_cap(a.seg[0])) {
-                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 1, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
+                rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
                 scan_chunk<VEC, false, DEPTH, true>(a, 0, ci, lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), cur, l.sl);
@@ -2441,7 +2453,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
     const Launch &a = args_again();
     const SegDesc &sg = a.seg[0];
     const uint32_t kout = static_cast<uint32_t>(sg.k);
-    const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;
+    const uint32_t sl = sub_log(sg);
     const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW, a.coarseW, sg.nchunks, kout, h);
     for (uint32_t i = 0; i < l.own.count; ++i) {
         const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[i]));
@@ -2454,16 +2466,16 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 a.state[0].Bw = pw.B;
                 a.state[0].c_gtw = pw.above;
             }
-            for (uint32_t pp = 0; pp < sub; ++pp) {
-                const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, pp, sub, lo);
+            for (uint32_t pp = 0; pp < 1u << sl; ++pp) {
+                const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, pp, sl, lo);
                 if (src.len == 0) continue;
 #pragma unroll
                 for (int j = 0; j < LU; ++j) raw[j] = src.raw(j * BLOCK + threadIdx.x);
-                refine_part<VEC, WIDE>(a, 0, src, static_cast<size_t>(c) * sub + pp, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
+                refine_part<VEC, WIDE>(a, 0, src, (static_cast<size_t>(c) << sl) + pp, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
                 __syncthreads();  // the scratch changes hands
             }
         } else {
-            const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, 0, 1, lo);
+            const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, 0, 0, lo);
             int32_t id[LU];
             load_entries<VEC>(src, 0, raw, id);
             const Threshold t = threshold_16(a, pw, kout, lo, shw);
@@ -2472,7 +2484,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
                 if (threadIdx.x == 0) norm_or_nan(a, sg);
             }
-            emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, raw, id, l.el);
+            emit_part<VEC, WIDE>(a, sg, src, 0, c, 0, t, raw, id, l.el);
             __syncthreads();  // the scratch changes hands
         }
     }
@@ -2485,16 +2497,16 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
 
     const SegDesc &sg = a.seg[0];
     const uint32_t nchunks = static_cast<uint32_t>(sg.nchunks), kout = static_cast<uint32_t>(sg.k);
-    const uint32_t sub = VEC == TAG_F32 ? a.sub : 1u;  // 16-bit types: one part per chunk (their counts are per chunk)
+    const uint32_t sl = sub_log(sg);
     const uint32_t norms = VEC == TAG_F32 ? 0u : a.norms;   // (fp32: k_emit adds up the error norm)
     const bool norm_only = blockIdx.x < norms;              // uniform
     const uint32_t slot = norm_only ? 0u : blockIdx.x - norms;
-    const int c = static_cast<int>(slot / sub);
-    const uint32_t part = slot % sub;
+    const int c = static_cast<int>(slot >> sl);
+    const uint32_t part = slot & ((1u << sl) - 1);
     const bool norm = VEC != TAG_F32 && (norm_only || (norms == 0 && c == sg.nchunks - 1 && err_ptr(a, sg) != nullptr));
     const SegStateWords stw = read_state(&a.state[0]);
     const uint32_t lo = stw.loA, shw = stw.shwA;
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, norm_only ? 0u : a.cnt[c], part, sub, lo);
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, norm_only ? 0u : a.cnt[c], part, sl, lo);
     double below_t = 0.0;
     if (norm && threadIdx.x < nchunks) below_t = a.chunk_err[threadIdx.x];
 
@@ -2535,7 +2547,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     } else {
         const Threshold t = threshold_16(a, pw, kout, lo, shw);
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.el.smd);
-        if (!norm_only) emit_part<VEC, WIDE>(a, sg, src, c, 0, 1, t, raw, id, l.el);
+        if (!norm_only) emit_part<VEC, WIDE>(a, sg, src, 0, c, 0, t, raw, id, l.el);
     }
 }
 
@@ -3201,7 +3213,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         if (one_per_cu) launch(ST_SPEC, k_scan<VEC, true, 3>, grid, st, a);
         else launch(ST_SPEC, k_scan<VEC, true, 2>, grid, st, a);
     }
-    const dim3 parts(total_chunks * (VEC == TAG_F32 ? a.sub : 1u));
+    const dim3 parts(a.parts);
     const bool wide = one_per_cu && parts.x == grid.x;  // one workgroup per chunk, at most one per compute unit: see Wide
     // (a wide kernel has a compute unit's registers to itself: one workgroup too many waits for another one to end, 2 us)
     const uint32_t S = static_cast<uint32_t>(a.S);
@@ -3394,7 +3406,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
         int64_t list_tiles = 0;
-        double longest = 0.0;  // the most kept elements that a chunk of the launch has on average
+        uint32_t parts = 0;
+        static_assert(CTARGET * MAXSUB < 65536 && MAXSUB < 16, "16-bit part numbers");
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];
             const int32_t s = which[i];
@@ -3416,18 +3429,20 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             }
             chunks += d.nchunks;
             list_tiles += d.nchunks * (E[i] / TILE);
-            if (ns > 0) {
-                const double kept = static_cast<double>(ks) / static_cast<double>(ns) * static_cast<double>(E[i]);
-                longest = kept > longest ? kept : longest;
+            // parts per chunk for the list kernels: a chunk's candidates are about a third more than its kept elements; a part gets
+            // about SUB_ENTRIES of them.  (Tensor by tensor: 24 tensors of which 0.1 to 20 % is kept, all cut as the densest one needs it,
+            // were 4096 workgroups, most of them empty.)
+            uint32_t sl = 0;
+            if (dt == ADATOPK_F32 && ns > 0) {
+                const double kept = static_cast<double>(ks) / static_cast<double>(ns) * static_cast<double>(E[i] < ns ? E[i] : ns);
+                const uint32_t most = S == 1 ? MAXSUB_ONE : MAXSUB;  // what the workspace of this call was laid out for
+                while ((1u << sl) < most && 1.35 * kept >= static_cast<double>(SUB_ENTRIES << sl)) ++sl;
             }
+            d.flags |= sl << FLAG_SUB_SHIFT;
+            a.part_begin[i] = static_cast<uint16_t>(parts);
+            parts += static_cast<uint32_t>(d.nchunks) << sl;
         }
-        // parts per chunk for the list kernels: a chunk's candidates are about a third more than its kept
-        // elements; a part gets about SUB_ENTRIES of them
-        {
-            int sub = static_cast<int>(1.35 * longest / SUB_ENTRIES) + 1;
-            const int most = S == 1 ? MAXSUB_ONE : MAXSUB;  // what the workspace of this call was laid out for
-            a.sub = static_cast<uint32_t>(sub > most ? most : sub);
-        }
+        a.parts = parts;
         if (chunks > max_chunks || list_tiles * (TILE / LIST_DIV) > list_slots) return ADATOPK_ERUNTIME;  // planner invariant
         if (whole < a.S) {  // something to select
             const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, st)
