@@ -443,15 +443,20 @@ __device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t *sm, ui
     return inc + pre;
 }
 
-// Block sum of doubles in a fixed order (same grouping every run).  sm holds NW doubles.
-__device__ __forceinline__ double block_sum_f64(double v, double *sm) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// Sum of doubles over the wavefront, in lane 63.
+__device__ __forceinline__ double wave_sum_f64(double v) {
     v += dpp<DPP_SHR1>(v);
     v += dpp<DPP_SHR2>(v);
     v += dpp<DPP_SHR4>(v);
     v += dpp<DPP_SHR8>(v);
     v += dpp<DPP_BCAST15>(v);
     v += dpp<DPP_BCAST31>(v);
+    return v;
+}
+// Block sum of doubles in a fixed order (same grouping every run).  sm holds NW doubles.
+__device__ __forceinline__ double block_sum_f64(double v, double *sm) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    v = wave_sum_f64(v);
     __syncthreads();
     if (lane == 63) sm[w] = v;
     __syncthreads();
@@ -459,6 +464,31 @@ __device__ __forceinline__ double block_sum_f64(double v, double *sm) {
 #pragma unroll
     for (int i = 0; i < NW; ++i) s += sm[i];
     return s;
+}
+
+// Both at once: the prefix sum of v and, in acc, the block sum of it.
+__device__ __forceinline__ uint32_t block_incl_scan_and_sum(uint32_t v, uint32_t *sm, uint32_t *total, double &acc, double *smd) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t inc = wave_incl_scan(v);
+    const double a = wave_sum_f64(acc);
+    __syncthreads();
+    if (lane == 63) {
+        sm[w] = inc;
+        smd[w] = a;
+    }
+    __syncthreads();
+    uint32_t pre = 0, tot = 0;
+    double sum = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const uint32_t t = sm[i];
+        pre += (i < w) ? t : 0u;
+        tot += t;
+        sum += smd[i];
+    }
+    *total = tot;
+    acc = sum;
+    return inc + pre;
 }
 
 // h[NB] raw counts -> inclusive suffix sums in place (h[b] = sum of counts of bins >= b).
@@ -828,17 +858,40 @@ __device__ __forceinline__ void hist1_full_tiles(const void *x, int64_t &t0, int
 
 // A chunk's counts h[NB] in LDS as its row of suffix sums in memory, and every (NB / NC)-th entry of it once
 // more, contiguously: whoever comes next finds the bucket of the k-th key from the column sums of the rows.
+// acc becomes the workgroup's sum of it (in a fixed order); the two reductions share their barriers.  sm: 2 * NW words,
+// smd: NW doubles.  The counts are complete (the caller has synchronised); h is not written.
 template <int NB, int NC, bool SHARED>
-__device__ __forceinline__ void store_rows(uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm) {
-    block_suffix_inplace<NB>(h, sm);
-    uint32_t *row = rows + static_cast<size_t>(g) * NB;
-    for (int b = threadIdx.x; b < NB; b += BLOCK) store_count<SHARED>(&row[b], h[b]);
-    if (threadIdx.x < NC) store_count<SHARED>(&coarse[static_cast<size_t>(g) * NC + threadIdx.x], h[threadIdx.x * (NB / NC)]);
+__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double &acc, double *smd) {
+    static_assert(NB == 4 * BLOCK && (NB / NC) % 4 == 0, "four counts per thread");
+    const uint4 c = reinterpret_cast<const uint4 *>(h)[threadIdx.x];
+    uint32_t total;
+    const uint32_t inc = block_incl_scan_and_sum(c.x + c.y + c.z + c.w, sm, &total, acc, smd);
+    uint4 suffix;
+    suffix.w = total - inc + c.w;
+    suffix.z = suffix.w + c.z;
+    suffix.y = suffix.z + c.y;
+    suffix.x = suffix.y + c.x;
+    uint32_t *row = rows + static_cast<size_t>(g) * NB + 4 * threadIdx.x;
+    if (SHARED) {
+        store_agent(&row[0], suffix.x);
+        store_agent(&row[1], suffix.y);
+        store_agent(&row[2], suffix.z);
+        store_agent(&row[3], suffix.w);
+    } else {
+        *reinterpret_cast<uint4 *>(row) = suffix;
+    }
+    constexpr uint32_t PER_COARSE = NB / NC / 4;  // threads
+    if (threadIdx.x % PER_COARSE == 0) store_count<SHARED>(&coarse[static_cast<size_t>(g) * NC + threadIdx.x / PER_COARSE], suffix.x);
+}
+template <int NB, int NC, bool SHARED>
+__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double *smd) {
+    double none = 0.0;
+    store_rows<NB, NC, SHARED>(h, rows, coarse, g, sm, none, smd);
 }
 
 // The histogram of one chunk.
 template <int VEC, bool SHARED>
-__device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t *h, uint32_t *sm) {
+__device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, int g, uint32_t *h, uint32_t *sm, double *smd) {
     using St = Stream<VEC>;
     const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
     const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
@@ -859,12 +912,13 @@ __device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, 
     }
     __syncthreads();
 
-    store_rows<NB1, NC1, SHARED>(h, a.rows1, a.coarse1, g, sm);
+    store_rows<NB1, NC1, SHARED>(h, a.rows1, a.coarse1, g, sm, smd);
 }
 
 template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
-    __shared__ uint32_t h[NB1];
+    __shared__ __attribute__((aligned(16))) uint32_t h[NB1];
     __shared__ uint32_t sm[2 * NW];
+    __shared__ double smd[NW];
 
     const int g = blockIdx.x;
     const int s = find_segment(a, g);
@@ -877,7 +931,7 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
     }
     if (held) return;  // the speculative pass bracketed the k-th key: no exact pass is needed
 
-    hist1_chunk<VEC, false>(a, sg, g, h, sm);
+    hist1_chunk<VEC, false>(a, sg, g, h, sm, smd);
     if (c == 0)  // first chunk of the tensor: clear what k_refine accumulates into
         for (int b = threadIdx.x; b < NB3; b += BLOCK) a.G3[s * NB3 + b] = 0;
 }
@@ -1092,16 +1146,21 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
 // beyond the sample's size puts the lower end at key 0; rank 0 leaves the upper end open.  All
 // integer work on the same data: every workgroup gets the same window.
 //
-// The histogram lives in LDS with one unused word after every 32 (a thread then walks its NSB / BLOCK
-// consecutive bins without the 16-fold bank conflict of an unpadded stride).  The whole prologue is
+// The histogram lives in LDS; a thread reads its eight consecutive bins with two 16-byte loads.  The whole prologue is
 // bound by instruction issue (two wavefronts per SIMD), so the work per sampled element is kept to a
-// handful of instructions: one compare against a floor below which nothing needs counting, one add.
+// handful of instructions: two for its bin's byte offset (the sign falls out of the shift), half of one each for the largest and
+// the smallest, one compare against a floor below which nothing needs counting, one add.  (With keys, a shift per use and
+// padded bins: 3.0 us from the sample's arrival to the window at 16 K fp32 values, now 2.1.)
 // The bins holding the two ranks are found while the suffix sums are formed in registers.
-constexpr int NSB_PADDED = NSB + NSB / 32;
 constexpr int SCAN_SMEM_WORDS = 2 * STAGE_CAP + NBW;  // k_scan's stage and window histogram; its prologue's scratch fits inside
 constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by up to this many run lengths
 constexpr int SAMPLE_BATCH = 16;  // dword loads per thread and batch; the host picks 1, 2 or 4 batches (fp32: 8192 elements each)
-__device__ __forceinline__ uint32_t padded(uint32_t bin) { return bin + (bin >> 5); }
+// Byte offset of the sample bin (4 * (key >> SAMPLE_SH)) of element hh of a dword.
+template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword, int hh) {
+    static_assert(SAMPLE_SH == 19, "the shifts below");
+    constexpr uint32_t MASK = (NSB - 1) * 4;
+    return (VEC == TAG_F32 || hh == 1 ? dword >> 17 : dword >> 1) & MASK;
+}
 template <int VEC, typename Prefetch>
 __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, uint32_t *s_pick,
                                               Prefetch after_loads, uint32_t &lo, uint32_t &shw) {
@@ -1140,18 +1199,21 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     __builtin_amdgcn_sched_barrier(0);
     after_loads();
     __builtin_amdgcn_sched_barrier(0);
-    for (int b = threadIdx.x; b < NSB_PADDED; b += BLOCK) hs[b] = 0;
+    static_assert(NSB == 2 * 4 * BLOCK && PER == 8, "two 16-byte accesses per thread");
+    uint4 *hs4 = reinterpret_cast<uint4 *>(hs);
+    hs4[threadIdx.x] = make_uint4(0, 0, 0, 0);
+    hs4[BLOCK + threadIdx.x] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) {
         s_pick[0] = NSB;  // what stays when no bin holds the rank
         s_pick[1] = NSB;
     }
-    // Only the largest few per cent of the sample decide the two ranks.  Every thread's largest key
-    // is at least `floor` = the smallest of the threads' largest keys, so at least BLOCK sampled keys
-    // are >= floor: when the lower rank is within BLOCK, keys below floor need not be counted at all.
+    // Only the largest few per cent of the sample decide the two ranks.  Every thread's largest bin
+    // is at least `floor` = the smallest of the threads' largest bins, so at least BLOCK sampled keys
+    // are in it or above: when the lower rank is within BLOCK, bins below it need not be counted at all.
     // Bin 0 (zeros and the smallest denormals) is never counted: a rank that falls into it is not
     // found, which puts the window's lower end at key 0 just the same, and a tensor that is mostly
     // zeros does not pile its lanes onto one word.
-    uint32_t mine = 0, least = 0xFFFFFFFFu;
+    uint32_t most = 0, least = 0xFFFFFFFFu;
 #pragma unroll
     for (int b = 0; b < MAXB; ++b)
         if (b < nbatch) {
@@ -1159,34 +1221,33 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
             for (int j = 0; j < SAMPLE_BATCH; ++j)
 #pragma unroll
                 for (int hh = 0; hh < EPD; ++hh) {
-                    const uint32_t key = key_of<VEC>(elem_of<VEC>(v[b][j], hh));
-                    mine = key > mine ? key : mine;
-                    least = key < least ? key : least;
+                    const uint32_t bin = sample_bin<VEC>(v[b][j], hh);
+                    most = bin > most ? bin : most;
+                    least = bin < least ? bin : least;
+                    if (VEC == TAG_F32) v[b][j] = bin;  // (16-bit types: two to a dword, formed again below)
                 }
         }
-    uint32_t floor_key = mine;
-    auto lower = [&](uint32_t o) { floor_key = o < floor_key ? o : floor_key; };
-    lower(dpp<DPP_SHR1>(floor_key, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR2>(floor_key, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR4>(floor_key, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR8>(floor_key, 0xFFFFFFFFu));
-    lower(dpp<DPP_BCAST15>(floor_key, 0xFFFFFFFFu));
-    lower(dpp<DPP_BCAST31>(floor_key, 0xFFFFFFFFu));
-    floor_key = lane_value(floor_key, 63);  // the wavefront's
-    if (lane == 0) sm[w] = floor_key;
+    uint32_t floor_bin = most;
+    auto lower = [&](uint32_t o) { floor_bin = o < floor_bin ? o : floor_bin; };
+    lower(dpp<DPP_SHR1>(floor_bin, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR2>(floor_bin, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR4>(floor_bin, 0xFFFFFFFFu));
+    lower(dpp<DPP_SHR8>(floor_bin, 0xFFFFFFFFu));
+    lower(dpp<DPP_BCAST15>(floor_bin, 0xFFFFFFFFu));
+    lower(dpp<DPP_BCAST31>(floor_bin, 0xFFFFFFFFu));
+    floor_bin = lane_value(floor_bin, 63);  // the wavefront's
+    if (lane == 0) sm[w] = floor_bin;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NW; ++i) floor_key = sm[i] < floor_key ? sm[i] : floor_key;
+    for (int i = 0; i < NW; ++i) floor_bin = sm[i] < floor_bin ? sm[i] : floor_bin;
     const uint32_t r_lo = sg.ranks & 0xFFFFu, r_hi = sg.ranks >> 16;
-    if (r_lo > BLOCK) floor_key = 0;
-    uint32_t floor_bin = floor_key >> SAMPLE_SH;
-    floor_bin = floor_bin < 1 ? 1 : floor_bin;
+    if (r_lo > BLOCK) floor_bin = 0;
+    floor_bin = floor_bin < 4 ? 4 : floor_bin;
+    auto count = [&](uint32_t bin, uint32_t c) { atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hs) + bin), c); };
     // A thread whose sampled keys all lie in one bin (a constant tensor) adds them with one add:
     // element by element the whole sample would go to one LDS word, one key after the other.
-    const uint32_t top_bin = mine >> SAMPLE_SH;
-    const bool one_bin = (least >> SAMPLE_SH) == top_bin;
-    if (one_bin) {
-        if (top_bin >= floor_bin) atomicAdd(&hs[padded(top_bin)], static_cast<uint32_t>(nbatch * SAMPLE_BATCH * EPD));
+    if (least == most) {
+        if (most >= floor_bin) count(most, static_cast<uint32_t>(nbatch * SAMPLE_BATCH * EPD));
     } else {
 #pragma unroll
         for (int b = 0; b < MAXB; ++b)
@@ -1195,39 +1256,41 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                 for (int j = 0; j < SAMPLE_BATCH; ++j)
 #pragma unroll
                     for (int hh = 0; hh < EPD; ++hh) {
-                        const uint32_t bin = key_of<VEC>(elem_of<VEC>(v[b][j], hh)) >> SAMPLE_SH;
-                        if (bin >= floor_bin) atomicAdd(&hs[padded(bin)], 1u);
+                        const uint32_t bin = VEC == TAG_F32 ? v[b][j] : sample_bin<VEC>(v[b][j], hh);
+                        if (bin >= floor_bin) count(bin, 1u);
                     }
             }
     }
     __syncthreads();
     // thread t owns bins [t * PER, (t + 1) * PER); higher bins hold larger keys
-    uint32_t cnt[PER], own = 0;
+    const uint4 c_lo = hs4[2 * threadIdx.x], c_hi = hs4[2 * threadIdx.x + 1];
+    const uint32_t cnt[PER] = {c_lo.x, c_lo.y, c_lo.z, c_lo.w, c_hi.x, c_hi.y, c_hi.z, c_hi.w};
+    uint32_t own = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        cnt[j] = hs[padded(threadIdx.x * PER + j)];
-        own += cnt[j];
-    }
+    for (int j = 0; j < PER; ++j) own += cnt[j];
     uint32_t total;
     const uint32_t inc = block_incl_scan(own, sm, &total);
     uint32_t above = total - inc;  // sampled (and counted) keys in the bins of the threads after this one
+    // (r_hi = 0: no bin holds it)
+    if ((above < r_lo && above + own >= r_lo) || (above < r_hi && above + own >= r_hi)) {  // two threads of the workgroup
 #pragma unroll
-    for (int j = PER - 1; j >= 0; --j) {
-        const uint32_t with = above + cnt[j];  // suffix sum at this bin
-        if (above < r_lo && with >= r_lo) s_pick[0] = threadIdx.x * PER + j;
-        if (r_hi != 0 && above < r_hi && with >= r_hi) s_pick[1] = threadIdx.x * PER + j;
-        above = with;
+        for (int j = PER - 1; j >= 0; --j) {
+            const uint32_t with = above + cnt[j];  // suffix sum at this bin
+            if (above < r_lo && with >= r_lo) s_pick[0] = threadIdx.x * PER + j;
+            if (above < r_hi && with >= r_hi) s_pick[1] = threadIdx.x * PER + j;
+            above = with;
+        }
     }
     __syncthreads();
-    const uint32_t b_lo = s_pick[0], b_hi = s_pick[1];
-    __syncthreads();
+    const uint32_t b_lo = __builtin_amdgcn_readfirstlane(s_pick[0]), b_hi = __builtin_amdgcn_readfirstlane(s_pick[1]);
     lo = b_lo < NSB ? b_lo << SAMPLE_SH : 0u;
     const uint32_t hi = b_hi < NSB ? (b_hi + 1u) << SAMPLE_SH : 0x80000000u;  // first key above the bracket
-    // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow.  16-bit types: a bin is one
-    // pattern (their keys have 16 zero bits below it), 2047 patterns upwards of lo, no last digit.
-    const uint64_t width = hi > lo ? hi - lo : 1u;
-    shw = VEC == TAG_F32 ? 0u : 16u;
-    while (VEC == TAG_F32 && shw < static_cast<uint32_t>(BITS3) && (static_cast<uint64_t>(NBW - 1) << shw) < width) ++shw;
+    // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow, the least shift that makes NBW - 1 bins
+    // span it.  16-bit types: a bin is one pattern (their keys have 16 zero bits below it), 2047 patterns upwards of lo, no last digit.
+    const uint32_t width = hi > lo ? hi - lo : 1u;
+    const uint32_t keys_per_bin = (width - 1) / (NBW - 1) + 1;
+    const uint32_t shift = keys_per_bin > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(keys_per_bin - 1)) : 0u;
+    shw = VEC != TAG_F32 ? 16u : (shift < static_cast<uint32_t>(BITS3) ? shift : static_cast<uint32_t>(BITS3));
 }
 
 // What the workgroups of k_judge (further down) share, cleared by the scan in front of it: in the last-digit
@@ -1362,18 +1425,17 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32
     __syncthreads();
     flush_stage<VEC>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
 
-    const double bsum = block_sum_f64(acc, l.smd);
     const Launch &again = args_again();  // (what the end of the chunk needs of them does not take up registers in the tile loop)
     const uint32_t capacity = list_cap(again.seg[s]);
+    __syncthreads();
+    // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
+    store_rows<NBW, NCW, SHARED>(hw, again.rowsW, again.coarseW, g, l.sm, acc, l.smd);
     if (threadIdx.x == 0) {
-        store_count<SHARED>(&again.chunk_err[g], bsum);
+        store_count<SHARED>(&again.chunk_err[g], acc);
         // more than the list holds = "read this chunk from the input", also for a list that was given up
         store_count<SHARED>(&again.cnt[g], (cap == 0 && running <= capacity) ? capacity + 1 : running);
     }
-    __syncthreads();
     if (PAIR && again.S != 1 && threadIdx.x == 0) again.cpairA[g] = make_uint2(running, hw[NBW - 1]);  // (k_judge reads the rows)
-    // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
-    store_rows<NBW, NCW, SHARED>(hw, again.rowsW, again.coarseW, g, l.sm);
 }
 
 // The exact scan knows a chunk's candidates beforehand: the keys of the bucket B of the k-th key and of those above, which
@@ -1393,7 +1455,7 @@ template <int VEC, bool SPEC, int DEPTH>
 __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
     using St = Stream<VEC>;
     __shared__ ScanLds l;
-    static_assert(NSB_PADDED <= SCAN_SMEM_WORDS && NC1 + FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
+    static_assert(NSB <= SCAN_SMEM_WORDS && NC1 + FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
 
     const int g = blockIdx.x;
     const int s = find_segment(a, g);
@@ -2358,12 +2420,12 @@ template <int VEC, typename F> __device__ __forceinline__ void each_candidate(co
         for (int j = 0; j < LU; ++j) f(r[j], src.is_candidate(i0 + j * BLOCK + threadIdx.x, r[j]));
     }
 }
-template <int VEC> __device__ __forceinline__ void hist1_candidates(const Launch &a, const ChunkSource<VEC> &src, int g, uint32_t *h, uint32_t *sm) {
+template <int VEC> __device__ __forceinline__ void hist1_candidates(const Launch &a, const ChunkSource<VEC> &src, int g, uint32_t *h, uint32_t *sm, double *smd) {
     for (int b = threadIdx.x; b < NB1; b += BLOCK) h[b] = 0;
     __syncthreads();
     each_candidate<VEC>(src, [&](uint32_t raw, bool cand) { hist_add(h, key_of<VEC>(raw) >> SH1, cand); });
     __syncthreads();
-    store_rows<NB1, NC1, true>(h, a.rows1, a.coarse1, g, sm);
+    store_rows<NB1, NC1, true>(h, a.rows1, a.coarse1, g, sm, smd);
 }
 // ... the window bins of a window that starts higher, at lo; what lies below it now joins the chunk's sum of squares.
 template <int VEC>
@@ -2378,10 +2440,9 @@ __device__ __forceinline__ void rewindow_candidates(const Launch &a, const Chunk
         const double xd = cand && key < lo ? static_cast<double>(value_of<VEC>(raw)) : 0.0;
         acc = fma(xd, xd, acc);
     });
-    const double below = block_sum_f64(acc, smd);
-    if (threadIdx.x == 0) store_agent(&a.chunk_err[g], load_agent(&a.chunk_err[g]) + below);
     __syncthreads();
-    store_rows<NBW, NCW, true>(hw, a.rowsW, a.coarseW, g, sm);
+    store_rows<NBW, NCW, true>(hw, a.rowsW, a.coarseW, g, sm, acc, smd);
+    if (threadIdx.x == 0) store_agent(&a.chunk_err[g], load_agent(&a.chunk_err[g]) + acc);
 }
 
 // LDS of k_judge.
@@ -2419,8 +2480,8 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             const Launch &a = args_again();
             const int ci = static_cast<int>(c);
             const uint32_t listed = a.cnt[ci];
-            if (above && listed <= list_cap(a.seg[0])) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, h, l.sl.sm);
-            else hist1_chunk<VEC, true>(a, a.seg[0], ci, h, l.sl.sm);
+            if (above && listed <= list_cap(a.seg[0])) hist1_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, h, l.sl.sm, l.sl.smd);
+            else hist1_chunk<VEC, true>(a, a.seg[0], ci, h, l.sl.sm, l.sl.smd);
             __syncthreads();
         }))
         return gave_up();
