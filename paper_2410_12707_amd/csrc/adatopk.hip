@@ -583,13 +583,6 @@ struct BinRun {
     }
 };
 
-// Adds the non-zero bins of an LDS histogram into a global one.
-template <int NB> __device__ __forceinline__ void flush_bins(const uint32_t *h, uint32_t *G) {
-    for (int b = threadIdx.x; b < NB; b += BLOCK) {
-        const uint32_t c = h[b];
-        if (c) __hip_atomic_fetch_add(&G[b], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
 // Segment that owns workgroup g: the last one whose first chunk is <= g.  One lane per table entry
 // and one ballot instead of a loop of dependent scalar loads, which costs about 0.1 us per segment.
 static_assert(MAXSEG <= 64, "one lane per segment");
@@ -1782,7 +1775,7 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
     const uint32_t shl = VEC == TAG_F32 ? 0u : 16u;
     uint32_t *h3 = h;
     for (int b = threadIdx.x; b < NB3; b += BLOCK) h3[b] = 0;
-    __syncthreads();
+    __syncthreads();  // (and whoever used sm and smd before is done with them)
     const uint32_t in_bin = (1u << shw) - 1u;
     uint32_t def = 0;  // candidates above bin Bw
     double acc = 0.0;  // squares of the candidates below bin Bw
@@ -1819,23 +1812,44 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
 #pragma unroll
         for (int j = 0; j < LU; ++j) count_entry(i0 + j * BLOCK + threadIdx.x, more[j]);
     }
-    const double bsum = block_sum_f64(acc, smd);
-    if (threadIdx.x == 0) a.lerr[slot] = bsum;
+    // The counts to G3, the row of suffix sums from registers, the counts above bin Bw and the squares: one pair of barriers
+    // for the three sums.
     __syncthreads();
-    flush_bins<NB3>(h3, a.G3 + s * NB3);
+    static_assert(NB3 == 2 * BLOCK, "two counts per thread");
+    const uint2 mine = reinterpret_cast<const uint2 *>(h3)[threadIdx.x];
+    uint32_t *G = a.G3 + s * NB3 + 2 * threadIdx.x;
+    if (mine.x) __hip_atomic_fetch_add(&G[0], mine.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (mine.y) __hip_atomic_fetch_add(&G[1], mine.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t inc = wave_incl_scan(mine.x + mine.y), wave_def = wave_incl_scan(def);
+    const double wave_acc = wave_sum_f64(acc);
+    if (lane == 63) {
+        sm[w] = inc;
+        sm[NW + w] = wave_def;
+        smd[w] = wave_acc;
+    }
     __syncthreads();
-    block_suffix_inplace<NB3>(h3, sm);
-    uint32_t *row = a.rows3 + slot * NB3;
-    for (int b = threadIdx.x; b < NB3; b += BLOCK) row[b] = h3[b];
-    uint32_t deftot;
-    block_incl_scan(def, sm, &deftot);
-    if (threadIdx.x == 0) a.ldef[slot] = deftot;
+    uint32_t up_to = inc, total = 0, deftot = 0;
+    double below = 0.0;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        up_to += i < w ? sm[i] : 0u;
+        total += sm[i];
+        deftot += sm[NW + i];
+        below += smd[i];
+    }
+    const uint32_t above = total - up_to;  // counts of the threads after this one
+    reinterpret_cast<uint2 *>(a.rows3 + slot * NB3)[threadIdx.x] = make_uint2(above + mine.y + mine.x, above + mine.y);
+    if (threadIdx.x == 0) {
+        a.ldef[slot] = deftot;
+        a.lerr[slot] = below;
+    }
 }
 
 // k_refine.  Prologue (every workgroup of the tensor, redundantly): the column sums of the chunks'
 // window rows give the window bin Bw that holds the k-th key.  Then refine_part on the workgroup's part.
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(Launch a) {
-    __shared__ uint32_t h[NB3 > NCW + NBW / NCW ? NB3 : NCW + NBW / NCW];
+    __shared__ __attribute__((aligned(16))) uint32_t h[NB3 > NCW + NBW / NCW ? NB3 : NCW + NBW / NCW];
     __shared__ uint32_t sm[2 * NW];
     __shared__ double smd[NW];
 
@@ -1968,18 +1982,32 @@ struct Threshold {
 };
 
 // fp32: the last digit B3 of the k-th key from its histogram (my_bins: the bins [threadIdx.x * NB3 / BLOCK, ...)
-// of G3), hence T and q.  All candidates of one last-digit bin share one key.  h: NB3 words of LDS.
+// of G3), hence T and q.  All candidates of one last-digit bin share one key.
 __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32_t (&my_bins)[NB3 / BLOCK], uint32_t kout,
-                                                   uint32_t Bw, uint32_t c_gtw, uint32_t lo, uint32_t shw, uint32_t *h, uint32_t *sm,
+                                                   uint32_t Bw, uint32_t c_gtw, uint32_t lo, uint32_t shw, uint32_t *sm,
                                                    uint32_t *s_pick) {
+    constexpr int PER = NB3 / BLOCK;
+    const uint32_t krem = kout - c_gtw;
+    if (threadIdx.x == 0) {  // what stays when no bin holds the rank: nothing to keep
+        s_pick[0] = NB3;
+        s_pick[1] = 0;
+    }
+    uint32_t own = 0;
 #pragma unroll
-    for (int j = 0; j < NB3 / BLOCK; ++j) h[threadIdx.x * (NB3 / BLOCK) + j] = my_bins[j];
-    __syncthreads();
-    block_suffix_inplace<NB3>(h, sm);
-    block_pick_bucket<NB3>(h, kout - c_gtw, s_pick);
+    for (int j = 0; j < PER; ++j) own += my_bins[j];
+    uint32_t total;
+    const uint32_t inc = block_incl_scan(own, sm, &total);  // (synchronises)
+    uint32_t higher = total - inc;                          // counts of the threads after this one
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
+        if (higher < krem && higher + my_bins[j] >= krem) {
+            s_pick[0] = threadIdx.x * PER + j;
+            s_pick[1] = higher;
+        }
+        higher += my_bins[j];
+    }
     __syncthreads();
     const uint32_t B3 = s_pick[0], above3 = s_pick[1];
-    __syncthreads();
     Threshold t;
     t.any_kept = Bw < NBW && B3 < NB3;
     t.T = t.any_kept ? lo + (Bw << shw) + B3 : 0xFFFFFFFFu;
@@ -2238,8 +2266,7 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
 // last part's workgroup as well, in front of its placing, the sum is what the launch ends with (6.5 M fp16 values 30.2 -> 28.6 us per
 // compress and decompress).
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(Launch a) {
-    // fp32: the last digit's histogram; 16-bit types: the global suffix sums of the window bins up to Bw
-    __shared__ uint32_t h[VEC == TAG_F32 ? NB3 : NBW + 1];
+    __shared__ uint32_t h[VEC == TAG_F32 ? 1 : NBW + 1];  // 16-bit types: the global suffix sums of the window bins up to Bw
     __shared__ EmitLds l;
 
     const bool norm_only = blockIdx.x < a.norms;       // uniform
@@ -2280,7 +2307,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         __builtin_amdgcn_sched_barrier(0);
         first_tile();
         __builtin_amdgcn_sched_barrier(0);
-        t = threshold_f32(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, h, l.sm, l.s_pick);
+        t = threshold_f32(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, l.sm, l.s_pick);
         if (norm) error_norm_f32<VEC>(a, sg, t, lo + (stw.Bw << shw), my_bins, below_t, l.smd);
     } else {
         const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
