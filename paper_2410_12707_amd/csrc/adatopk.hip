@@ -491,46 +491,6 @@ __device__ __forceinline__ uint32_t block_incl_scan_and_sum(uint32_t v, uint32_t
     return inc + pre;
 }
 
-// h[NB] raw counts -> inclusive suffix sums in place (h[b] = sum of counts of bins >= b).
-template <int NB> __device__ __forceinline__ void block_suffix_inplace(uint32_t *h, uint32_t *sm) {
-    constexpr int PER = NB / BLOCK;
-    const int b0 = threadIdx.x * PER;
-    uint32_t s = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) s += h[b0 + j];
-    uint32_t total;
-    const uint32_t inc = block_incl_scan(s, sm, &total);
-    uint32_t run = total - inc;  // counts owned by higher threads
-#pragma unroll
-    for (int j = PER - 1; j >= 0; --j) {
-        run += h[b0 + j];
-        h[b0 + j] = run;
-    }
-    __syncthreads();
-}
-
-// On suffix sums suf[NB]: the bucket B with suf[B] >= krem > suf[B+1]; out[0] = B, out[1] = suf[B+1].
-// krem == 0 selects nothing: B = NB.  out[] is in LDS; every thread calls; the caller syncs before reading it.
-template <int NB> __device__ __forceinline__ void block_pick_bucket(const uint32_t *suf, uint32_t krem, uint32_t *out) {
-    constexpr int PER = NB / BLOCK;
-    if (threadIdx.x == 0) {  // also what stays when no bin qualifies (counts that do not add up)
-        out[0] = NB;
-        out[1] = 0;
-    }
-    __syncthreads();
-    if (krem != 0) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int b = threadIdx.x * PER + j;
-            const uint32_t above = (b + 1 < NB) ? suf[b + 1] : 0u;
-            if (suf[b] >= krem && above < krem) {
-                out[0] = b;
-                out[1] = above;
-            }
-        }
-    }
-}
-
 // One count per active lane into h[bin].  Lanes of a wavefront that hit the same LDS word are
 // served one after the other; with most of the 64 lanes on one word (a constant or mostly-zero
 // tensor, sorted data) a histogram pass gets several times slower.  So when at least half of the
@@ -2673,12 +2633,15 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
 // ------------------------------------------------------------------ small tensors: one launch
 // Many small messages (a few thousand elements each) are bound by launch latency in the
 // four-kernel path: about 5 us per kernel whatever the size.  Here one workgroup does the whole
-// selection of one tensor that fits its registers: one read, three histogram rounds (the same
-// 11/10/10-bit digits, LDS histograms, the same bucket search) that fix the threshold key T and
-// the tie quota q, then one ordered round that writes the kept pairs in ascending index order and
-// sums the squares of the dropped ones.  Same results as the big path.  One compute unit works
-// through about 3 elements per ns in the ordered round, so tensors beyond one register tile stay
-// with the four-kernel path, which spreads them over many compute units.
+// selection of one tensor that fits its registers, with one read.  Such a workgroup has its compute unit to itself,
+// two wavefronts per SIMD, and its time is the number of its instructions; so only two passes look at all elements: a
+// histogram of the top digit (LDS), and one that sets the candidates apart, the elements in the bucket of the k-th key or
+// above it, and sums the squares of the others.  What follows (two more digits, which fix the threshold key T and the tie
+// quota q, and the placing) works on the candidates, a few hundred of 8192 elements at 1 %.
+// Every wavefront owns a contiguous eighth of the tensor and a segment of the candidate list, so the candidates are
+// in index order without an exchange between the wavefronts; only their totals are added up before the placing.  (All
+// three digits and the placing over all elements: 12.1 us for 128 tensors of 1 to 8 K fp32 values.)
+// Tensors beyond one register tile stay with the four-kernel path, which spreads them over many compute units.
 constexpr int SMALL_EPT = 128 / NW;            // elements per thread (16 with 512 threads)
 constexpr int SMALL_N = BLOCK * SMALL_EPT;     // largest tensor this path takes
 constexpr int SMALL_MAXSEG = 128;              // tensors per launch (the table travels as kernel arguments)
@@ -2689,7 +2652,7 @@ struct SmallDesc {
 struct SmallLaunch {
     SmallDesc seg[SMALL_MAXSEG];
     double ratio[SMALL_MAXSEG];                    // wire mode: goes into the message's header
-    uint16_t n[SMALL_MAXSEG], k[SMALL_MAXSEG];
+    uint32_t nk[SMALL_MAXSEG];                     // elements, and kept elements in the upper half
     void *idx_out;
     void *val_out;
     float *err_out;
@@ -2697,147 +2660,184 @@ struct SmallLaunch {
     uint32_t wire;
 };
 static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments stay within 4 KB");
-static_assert(SMALL_EPT * NW <= 128, "the (slot, wave) counts are scanned two per lane");
 static_assert(SMALL_N < 65536, "two 16-bit counts travel in one word");
 
-// One histogram round over the tensor in registers: counts digit (key >> shift) & (NB - 1) of the
-// keys whose bits above the digit equal `prefix` (every key when use_prefix is false), then picks
-// the bucket holding the krem-th largest.  Returns the bucket (NB when krem == 0) and the count
-// above it.  Slot e of thread t is element e * BLOCK + t; slots past the end are skipped by a
-// uniform branch.
-template <int VEC, int NB>
-__device__ __forceinline__ void small_round(const uint32_t (&raw)[SMALL_EPT], int n, int shift, int prefix_shift,
-                                            uint32_t prefix, bool use_prefix, uint32_t krem, uint32_t *h, uint32_t *sm,
-                                            uint32_t *s_pick, uint32_t &B, uint32_t &above) {
-    for (int b = threadIdx.x; b < NB; b += BLOCK) h[b] = 0;
+// The bucket of the krem-th largest (krem >= 1) of the counts h[NB] in LDS and the number of counts above it, found while
+// the suffix sums are formed in registers.  pick: two words of LDS.  Synchronises before it reads h and before it returns.
+template <int NB> __device__ __forceinline__ void small_pick(const uint32_t *h, uint32_t krem, uint32_t *sm, uint32_t *pick, uint32_t &B, uint32_t &above) {
+    constexpr int PER = NB / BLOCK;
+    if (threadIdx.x == 0) pick[0] = pick[1] = 0;  // (counts that do not add up)
     __syncthreads();
-    // probe on the first slot: do half of the wavefront's lanes count, and into one bin?  Then the
-    // round adds through hist_add (equal keys would serialise on one LDS word), else every lane for itself
-    bool skewed;
-    {
-        const uint32_t key = key_of<VEC>(raw[0]);
-        const bool in = static_cast<int>(threadIdx.x) < n && (!use_prefix || (key >> prefix_shift) == prefix);
-        const uint32_t bin = (key >> shift) & (NB - 1);
-        const uint64_t act = __ballot(in);
-        const uint32_t lbin = __builtin_amdgcn_readlane(bin, act ? __ffsll(static_cast<unsigned long long>(act)) - 1 : 0);
-        skewed = __popcll(__ballot(in && bin == lbin)) >= 32;  // wave-uniform
-    }
+    uint32_t cnt[PER], own = 0;
 #pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e) {
-        if (e * BLOCK < n) {  // uniform
-            const int i = e * BLOCK + static_cast<int>(threadIdx.x);
-            const uint32_t key = key_of<VEC>(raw[e]);
-            const bool in = i < n && (!use_prefix || (key >> prefix_shift) == prefix);
-            const uint32_t bin = (key >> shift) & (NB - 1);
-            if (skewed) hist_add(h, bin, in);
-            else if (in) atomicAdd(&h[bin], 1u);
+    for (int j = 0; j < PER; ++j) {
+        cnt[j] = h[threadIdx.x * PER + j];
+        own += cnt[j];
+    }
+    uint32_t total;
+    const uint32_t inc = block_incl_scan(own, sm, &total);
+    uint32_t higher = total - inc;  // counts of the threads after this one
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
+        if (higher < krem && higher + cnt[j] >= krem) {
+            pick[0] = threadIdx.x * PER + j;
+            pick[1] = higher;
         }
+        higher += cnt[j];
     }
     __syncthreads();
-    block_suffix_inplace<NB>(h, sm);
-    block_pick_bucket<NB>(h, krem, s_pick);
-    __syncthreads();
-    B = s_pick[0];
-    above = s_pick[1];
-    __syncthreads();
+    B = pick[0];
+    above = pick[1];
 }
 
 template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallLaunch a) {
     using R = typename Raw<VEC>::type;
-    __shared__ uint32_t h[NB1];
+    __shared__ __attribute__((aligned(16))) uint32_t h[NB1];
     __shared__ uint32_t sm[NW];
     __shared__ double smd[NW];
     __shared__ uint32_t s_pick[2];
-    __shared__ uint32_t wcnt[SMALL_EPT * NW];  // (#above T) | (#equal to T) << 16 of every (slot, wave)
+    __shared__ uint2 candidates[SMALL_N];  // (index, raw pattern); the wavefronts' segments are SMALL_EPT * 64 long
 
     const SmallDesc &sg = a.seg[blockIdx.x];
-    const int n = a.n[blockIdx.x];
-    const uint32_t kout = a.k[blockIdx.x];
+    const int n = static_cast<int>(a.nk[blockIdx.x] & 0xFFFFu);
+    const uint32_t kout = a.nk[blockIdx.x] >> 16;
     const R *x = static_cast<const R *>(sg.x);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slots = (n + BLOCK - 1) / BLOCK;      // element (slot e, lane) of wavefront w is i0 + 64 * e
+    const int i0 = w * slots * 64 + lane;
+    uint2 *mine = candidates + w * (SMALL_EPT * 64);
 
-    // the whole tensor in one round of loads without conditions (see ChunkSource): an element past the end
-    // reads the last one and is masked out
+    // The whole tensor in one round of loads.  (The wavefront with the tensor's end without conditions, too, see ChunkSource:
+    // an element past the end reads the last one and is masked out.)
     uint32_t raw[SMALL_EPT];
 #pragma unroll
     for (int e = 0; e < SMALL_EPT; ++e) raw[e] = 0;
-    if (n > 0) {  // uniform
+    if ((w + 1) * slots * 64 <= n) {  // wave-uniform
+        const R *own = x + i0;
 #pragma unroll
-        for (int e = 0; e < SMALL_EPT; ++e) {
-            const int i = e * BLOCK + static_cast<int>(threadIdx.x);
-            raw[e] = static_cast<uint32_t>(x[opaque(static_cast<uint32_t>(i < n ? i : n - 1))]) & keep_mask(i < n);
-        }
+        for (int e = 0; e < SMALL_EPT; ++e)
+            if (e < slots) raw[e] = static_cast<uint32_t>(own[64 * e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < SMALL_EPT; ++e)
+            if (e < slots) {  // uniform
+                const int i = i0 + 64 * e;
+                raw[e] = static_cast<uint32_t>(x[opaque(static_cast<uint32_t>(i < n ? i : n - 1))]) & keep_mask(i < n);
+            }
     }
 
-    // threshold key T, number of keys above it, tie quota q
+    // the bucket of the k-th key on the top digit: keys from lo up are candidates
+    uint32_t lo = 0x80000000u, B1 = 0, above1 = 0;  // (k = 0: none)
+    if (kout != 0) {  // uniform
+        static_assert(NB1 == 4 * BLOCK, "four words per thread");
+        reinterpret_cast<uint4 *>(h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        // Equal keys would serialise on one LDS word: a wavefront half of whose first slot falls into one bucket adds
+        // through hist_add, any other every lane for itself.
+        const uint32_t first = key_of<VEC>(raw[0]) >> SH1;
+        const bool skewed = __popcll(__ballot(i0 < n && first == static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(first))))) >= 32;
+#pragma unroll
+        for (int e = 0; e < SMALL_EPT; ++e)
+            if (e < slots) {
+                const bool in = i0 + 64 * e < n;
+                const uint32_t bin = key_of<VEC>(raw[e]) >> SH1;
+                if (skewed) hist_add(h, bin, in);
+                else if (in) atomicAdd(&h[bin], 1u);
+            }
+        small_pick<NB1>(h, kout, sm, s_pick, B1, above1);
+        lo = B1 << SH1;
+    }
+
+    // the candidates, in index order, and the squares of all other elements
+    uint32_t count = 0;  // of this wavefront
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < SMALL_EPT; ++e)
+        if (e < slots) {
+            const bool keep = i0 + 64 * e < n && key_of<VEC>(raw[e]) >= lo;
+            const uint64_t m = __ballot(keep);
+            if (keep) mine[lanes_below_plus(m, count)] = make_uint2(static_cast<uint32_t>(i0 + 64 * e), raw[e]);
+            count += static_cast<uint32_t>(__popcll(m));
+            float xs = keep ? 0.0f : value_of<VEC>(raw[e]);  // (past the end: 0)
+            asm("" : "+v"(xs));                              // (see scan_tile)
+            const double xd = static_cast<double>(xs);
+            acc = fma(xd, xd, acc);
+        }
+
+    // f(candidate, whether there is one) for this wavefront's candidates, 64 at a time
+    auto each = [&](auto &&f) {
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < count; j0 += 64) {
+            const uint32_t j = j0 + lane;
+            f(mine[j < count ? j : 0], j < count);
+        }
+    };
+    // T and the number of keys above it, from the digits below the first
     uint32_t T = 0xFFFFFFFFu, c_gt = 0;
     if (kout != 0) {
-        uint32_t B1, a1, B2, a2, B3, a3;
-        small_round<VEC, NB1>(raw, n, SH1, 0, 0u, false, kout, h, sm, s_pick, B1, a1);
-        small_round<VEC, NB2>(raw, n, SH2, SH1, B1, true, kout - a1, h, sm, s_pick, B2, a2);
+        uint32_t B2, above2;
+        static_assert(NB2 == 2 * BLOCK && NB3 == 2 * BLOCK, "two words per thread");
+        // (every thread has read what it needs of h: small_pick synchronises behind that)
+        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);
+        __syncthreads();
+        each([&](uint2 c, bool in) {
+            const uint32_t key = key_of<VEC>(c.y);
+            hist_add(h, (key >> SH2) & (NB2 - 1), in && key >> SH1 == B1);
+        });
+        small_pick<NB2>(h, kout - above1, sm, s_pick, B2, above2);
+        c_gt = above1 + above2;
         const uint32_t P = (B1 << BITS2) | B2;
-        small_round<VEC, NB3>(raw, n, 0, SH2, P, true, kout - a1 - a2, h, sm, s_pick, B3, a3);
+        uint32_t B3 = 0, above3 = 0;
+        if (VEC == TAG_F32) {  // (a 16-bit pattern ends within the second digit)
+            reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);
+            __syncthreads();
+            each([&](uint2 c, bool in) {
+                const uint32_t key = key_of<VEC>(c.y);
+                hist_add(h, key & (NB3 - 1), in && key >> SH2 == P);
+            });
+            small_pick<NB3>(h, kout - c_gt, sm, s_pick, B3, above3);
+        }
+        c_gt += above3;
         T = (P << BITS3) | B3;
-        c_gt = a1 + a2 + a3;
     }
     const uint32_t q = kout - c_gt;
 
-    // Ordered round.  Index order is (slot, wave, lane): per slot the rank of every lane among the
-    // wave's keys above / equal to T (two 16-bit fields of one register; the lane masks themselves
-    // are not kept), the counts to LDS (lane e writes slot e's), one barrier, then every wavefront
-    // scans the SMALL_EPT * NW counts in index order, two entries per lane.
-    uint32_t rk[SMALL_EPT];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e) {
-        rk[e] = 0;
-        uint32_t c = 0;
-        if (e * BLOCK < n) {  // uniform
-            const int i = e * BLOCK + static_cast<int>(threadIdx.x);
-            const uint32_t key = key_of<VEC>(raw[e]);
-            const uint64_t bg = __ballot(i < n && key > T);
-            const uint64_t be = __ballot(i < n && key == T);
-            rk[e] = lanes_below(bg) | (lanes_below(be) << 16);
-            c = static_cast<uint32_t>(__popcll(bg)) | (static_cast<uint32_t>(__popcll(be)) << 16);
-        }
-        mine = (lane == e) ? c : mine;
-    }
-    if (lane < SMALL_EPT) wcnt[lane * NW + w] = mine;
+    // The placing: the wavefronts' counts above and equal to T (two 16-bit counts in a word), then the candidates once more.
+    uint32_t total = 0;
+    each([&](uint2 c, bool in) {
+        const uint32_t key = key_of<VEC>(c.y);
+        total += static_cast<uint32_t>(__popcll(__ballot(in && key > T))) + (static_cast<uint32_t>(__popcll(__ballot(in && key == T))) << 16);
+    });
+    __syncthreads();  // (the sums in sm have been read)
+    if (lane == 0) sm[w] = total;
     __syncthreads();
-    const uint32_t c0 = (2 * lane < SMALL_EPT * NW) ? wcnt[2 * lane] : 0u;
-    const uint32_t c1 = (2 * lane + 1 < SMALL_EPT * NW) ? wcnt[2 * lane + 1] : 0u;
-    const uint32_t inc = wave_incl_scan(c0 + c1);
-    const uint32_t ex0 = inc - c0 - c1, ex1 = inc - c1;  // counts before entry 2 * lane and before 2 * lane + 1
+    uint32_t before, all;
+    wave_counts(sm, before, all);
+    uint32_t run_gt = before & 0xFFFFu, run_eq = before >> 16;
 
     const bool wide = a.idx64 != 0;
     const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, kout, wide, a.wire != 0, sizeof(R));
     int32_t *oi = op.i32;
     int64_t *oi64 = op.i64;
     R *ov = static_cast<R *>(op.val);
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e) {
-        if (e * BLOCK < n) {  // uniform
-            const int i = e * BLOCK + static_cast<int>(threadIdx.x);
-            const int entry = e * NW + w;
-            const uint32_t before = lane_value((entry & 1) ? ex1 : ex0, entry >> 1);  // one entry for the whole wave
-            const uint32_t key = key_of<VEC>(raw[e]);
-            const bool valid = i < n;
-            const uint32_t gt_before = (before & 0xFFFFu) + (rk[e] & 0xFFFFu);
-            const uint32_t eq_before = (before >> 16) + (rk[e] >> 16);
-            const bool keep = valid && (key > T || (key == T && eq_before < q));
-            if (keep) {
-                const uint32_t pos = gt_before + (eq_before < q ? eq_before : q);
-                if (pos < kout) {
-                    if (wide) oi64[pos] = i;
-                    else oi[pos] = i;
-                    ov[pos] = static_cast<R>(raw[e]);
-                }
+    each([&](uint2 c, bool in) {
+        const uint32_t key = key_of<VEC>(c.y);
+        const uint64_t bg = __ballot(in && key > T), be = __ballot(in && key == T);
+        const uint32_t gt_before = lanes_below_plus(bg, run_gt), eq_before = lanes_below_plus(be, run_eq);
+        run_gt += static_cast<uint32_t>(__popcll(bg));
+        run_eq += static_cast<uint32_t>(__popcll(be));
+        const bool keep = in && (key > T || (key == T && eq_before < q));
+        if (keep) {
+            const uint32_t pos = gt_before + (eq_before < q ? eq_before : q);
+            if (pos < kout) {
+                if (wide) oi64[pos] = static_cast<int64_t>(c.x);
+                else oi[pos] = static_cast<int32_t>(c.x);
+                ov[pos] = static_cast<R>(c.y);
             }
-            const double v = static_cast<double>((valid && !keep) ? value_of<VEC>(raw[e]) : 0.0f);
-            acc = fma(v, v, acc);
         }
-    }
+        const double v = static_cast<double>((in && !keep) ? value_of<VEC>(c.y) : 0.0f);
+        acc = fma(v, v, acc);
+    });
     float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
     if (a.wire != 0) {
         write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, a.ratio[blockIdx.x]);
@@ -3424,8 +3424,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             for (int32_t i = 0; i < cnt; ++i) {
                 sl.seg[i].x = dense[s0 + i];
                 sl.seg[i].out_off = out_offset[s0 + i] + header;
-                sl.n[i] = static_cast<uint16_t>(n[s0 + i]);
-                sl.k[i] = static_cast<uint16_t>(k[s0 + i]);
+                sl.nk[i] = static_cast<uint32_t>(n[s0 + i]) | static_cast<uint32_t>(k[s0 + i]) << 16;
                 if (out.wire) sl.ratio[i] = ratio_of(s0 + i);
             }
             sl.idx_out = idx_out;
