@@ -3294,7 +3294,8 @@ inline void launch(int stage, K kernel, dim3 grid, hipStream_t st, Args... args)
 // The kernels of one launch.  With `speculate` the first full read of the input is the speculative
 // scan; the two exact passes behind it return at once for every tensor whose speculation held and
 // do the work for the others, so what reaches k_refine is complete either way.
-template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, hipStream_t st) {
+// `no_lists`: most elements belong to tensors without lists.
+template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, bool no_lists, hipStream_t st) {
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
     if (speculate) {
@@ -3302,7 +3303,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         else launch(ST_SPEC, k_scan<VEC, true, 2>, grid, st, a);
     }
     const dim3 parts(a.parts);
-    const bool wide = one_per_cu && parts.x == grid.x;  // one workgroup per chunk, at most one per compute unit: see Wide
+    const bool wide = (one_per_cu && parts.x == grid.x) || (no_lists && !speculate);  // one workgroup per chunk, at most one per compute unit: see Wide
     // (a wide kernel has a compute unit's registers to itself: one workgroup too many waits for another one to end, 2 us)
     const uint32_t S = static_cast<uint32_t>(a.S);
     a.norms = (a.err_out != nullptr || a.wire) && (!wide || parts.x + S <= CTARGET_ONE) ? S : 0u;
@@ -3447,6 +3448,11 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     auto speculates = [&](int32_t s, uint32_t *ranks, uint32_t *batches) {
         return speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, ranks, batches);
     };
+    // Tensors whose chunks have no lists, mostly, and are placed from the input: a launch in which they hold the majority of the elements takes
+    // the list kernels' wide form, one workgroup per chunk.  With parts of 8 K entries and the plain form, us: four tensors of
+    // 8.4 M at 26, 50 and 90 % kept: bf16 149 / 161 / 173 -> 121 / 126 / 131, fp32 167 / 196 / 230 -> 180 / 189 / 199; 25 M fp32
+    // 140 / 151 / 178 -> 145 / 147 / 150.
+    auto listless = [&](int32_t s) { return !kept_whole(s) && k[s] > n[s] / (dt == ADATOPK_F32 ? 2 : LIST_DIV); };
     // One launch of the kernels for the tensors `which[0 .. count)` of the call.
     auto select_group = [&](const int32_t *which, int32_t count, bool may_speculate) -> adatopk_status {
         Launch a{};
@@ -3454,12 +3460,14 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         // Chunk sizes of this launch: at most chunk_target() chunks in all, so that all workgroups are
         // resident at once (a few chunks beyond that would run as a second, nearly empty round).
         int64_t n_batch = 0;
+        int64_t n_dense = 0;  // elements of the tensors that keep so much that their chunks have no lists, mostly
         int32_t whole = 0, nspec = 0;
         uint32_t ranks[MAXSEG], batches[MAXSEG];
         bool spec[MAXSEG];
         for (int32_t i = 0; i < a.S; ++i) {
             const int32_t s = which[i];
             n_batch += n_select(s);
+            if (listless(s)) n_dense += n[s];
             whole += kept_whole(s) ? 1 : 0;
             spec[i] = may_speculate && speculates(s, &ranks[i], &batches[i]);
             nspec += spec[i] ? 1 : 0;
@@ -3493,6 +3501,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
         int64_t list_tiles = 0;
+        const bool no_lists = 2 * n_dense > n_batch;
         uint32_t parts = 0;
         static_assert(CTARGET * MAXSUB < 65536 && MAXSUB < 16, "16-bit part numbers");
         for (int32_t i = 0; i < a.S; ++i) {
@@ -3520,7 +3529,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             // about SUB_ENTRIES of them.  (Tensor by tensor: 24 tensors of which 0.1 to 20 % is kept, all cut as the densest one needs it,
             // were 4096 workgroups, most of them empty.)
             uint32_t sl = 0;
-            if (dt == ADATOPK_F32 && ns > 0) {
+            if (dt == ADATOPK_F32 && ns > 0 && !(no_lists && listless(s))) {
                 const double kept = static_cast<double>(ks) / static_cast<double>(ns) * static_cast<double>(E[i] < ns ? E[i] : ns);
                 const uint32_t most = S == 1 ? MAXSUB_ONE : MAXSUB;  // what the workspace of this call was laid out for
                 while ((1u << sl) < most && 1.35 * kept >= static_cast<double>(SUB_ENTRIES << sl)) ++sl;
@@ -3532,9 +3541,9 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.parts = parts;
         if (chunks > max_chunks || list_tiles * (TILE / LIST_DIV) > list_slots) return ADATOPK_ERUNTIME;  // planner invariant
         if (whole < a.S) {  // something to select
-            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, st)
-                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, nspec > 0, st)
-                                                             : launch_batch<TAG_F16>(a, chunks, nspec > 0, st);
+            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, no_lists, st)
+                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, nspec > 0, no_lists, st)
+                                                             : launch_batch<TAG_F16>(a, chunks, nspec > 0, no_lists, st);
             if (rc != ADATOPK_OK) return rc;
         }
         if (whole > 0) {

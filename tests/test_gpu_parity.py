@@ -588,3 +588,20 @@ def test_tensors_of_one_launch_have_chunks_of_their_own_length(dtype, scale):
         assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), s
         assert H.same_err(ge[s], re, ERR_RTOL), (s, ge[s], re)
     check_segmented_decompress(gi, gv, off, lens)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("kind", ["normal", "few_levels", "descending"])
+def test_batch_of_tensors_without_lists(dtype, kind):
+    # most elements belong to tensors that keep more than half: placed from the input, one workgroup per chunk, while the
+    # others of the launch have lists
+    import gpu_harness as H
+
+    lens, shares = [300_001, 8_193, 200_000, 70_003, 16_384], [0.6, 0.02, 0.97, 0.01, 0.51]
+    xs = [wl.small_case(kind, n, seed=70 + i, dtype=dtype) for i, n in enumerate(lens)]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    gi, gv, off, ge = H.gpu_compress_segmented(xs, ks)
+    ri, rv, roff, re = orc.compress_segmented(xs, ks)
+    assert np.array_equal(off, roff) and np.array_equal(gi, ri) and np.array_equal(H.bits(gv), H.bits(rv))
+    assert all(H.same_err(ge[s], re[s], ERR_RTOL) for s in range(len(xs)))
+    check_segmented_decompress(gi, gv, off, lens)
