@@ -134,7 +134,6 @@ constexpr uint32_t MERGE_DENSE_SHIFT_SMALL = 5;  // ... for outputs up to MERGE_
 constexpr size_t MERGE_SMALL_BYTES = static_cast<size_t>(32) << 20;
 constexpr size_t MERGE_MIN_SPAN = 16384;   // bytes; smaller outputs use fewer workgroups
 constexpr size_t MERGE_MAX_SPAN = 98304;   // bytes; larger outputs use more workgroups
-static_assert(LU * NW <= 64, "per-tile wave counts must fit one wavefront scan");
 static_assert(NB1 % BLOCK == 0 && NBW % BLOCK == 0 && NB3 % BLOCK == 0 && NSB % BLOCK == 0, "bins split evenly over threads");
 static_assert(CTARGET <= BLOCK, "k_emit scans the chunks of a segment with one thread each");
 static_assert(BLOCK % 64 == 0, "whole wavefronts");
@@ -182,7 +181,7 @@ struct SegDesc {
 
 struct Launch {
     SegDesc seg[MAXSEG];
-    uint16_t part_begin[MAXSEG];  // first part of a tensor: the list kernels cut the candidates of a chunk into parts (list_parts)
+    uint32_t part_begin[MAXSEG];  // first part of a tensor: the list kernels cut the candidates of a chunk into parts (sub_log)
     int32_t S;
     uint32_t parts; // parts of all tensors
     uint32_t idx64;
@@ -1541,6 +1540,27 @@ __device__ __forceinline__ ChunkSource<VEC> chunk_source(const Launch &a, const 
     return src;
 }
 
+// A list tile is BLOCK * LU entries; a wavefront takes LU * 64 consecutive ones, entry (slot j, lane) of the tile at t0 being
+// list_entry(t0) + 64 * j.  So every wavefront but the one with the list's end loads without conditions, and index order
+// is (wavefront, slot, lane): the wavefronts exchange one count each.
+__device__ __forceinline__ uint32_t list_entry(uint32_t t0) {
+    return t0 + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6))) * (LU * 64) + (threadIdx.x & 63);
+}
+template <int VEC> __device__ __forceinline__ bool whole_wave(const ChunkSource<VEC> &src, uint32_t t0) {  // wave-uniform
+    return t0 + static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)) + 1) * (LU * 64) <= src.len;
+}
+// The raw patterns of this thread's entries of a tile.
+template <int VEC> __device__ __forceinline__ void load_raw(const ChunkSource<VEC> &src, uint32_t t0, uint32_t (&raw)[LU]) {
+    const uint32_t i = list_entry(t0);
+    if (whole_wave<VEC>(src, t0)) {
+#pragma unroll
+        for (int j = 0; j < LU; ++j) raw[j] = src.raw_inside(i + 64 * j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < LU; ++j) raw[j] = src.raw(i + 64 * j);
+    }
+}
+
 // A part that is read from the input is long (a quarter of the chunk's elements were candidates, or
 // more), and a loop that loads LU entries per thread and then works on them moves 8 KB per
 // workgroup and memory round trip: 1.8 TB/s over the whole chip when every chunk is dense (a
@@ -1744,7 +1764,7 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
         const uint32_t key = key_of<VEC>(raw);
         const uint32_t bin = window_bin(key, lo, shw);
         def += (cand && bin > Bw) ? 1u : 0u;
-        hist_add(h3, ((key - lo) & in_bin) >> shl, cand && bin == Bw);
+        if (__ballot(cand && bin == Bw) != 0) hist_add(h3, ((key - lo) & in_bin) >> shl, cand && bin == Bw);  // (a few of a list's entries)
         const double xd = (cand && bin < Bw) ? static_cast<double>(value_of<VEC>(raw)) : 0.0;
         acc = fma(xd, xd, acc);
     };
@@ -1757,20 +1777,14 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
         i_next = wide_tiles * Wide<VEC>::ELEMS;
     } else {
 #pragma unroll
-        for (int j = 0; j < LU; ++j) count_entry(j * BLOCK + threadIdx.x, first[j]);
+        for (int j = 0; j < LU; ++j) count_entry(list_entry(0) + 64 * j, first[j]);
     }
     // longer parts (large k, many ties), the end of a part read from the input: LU entries per thread at a time
     for (uint32_t i0 = i_next; i0 < src.len; i0 += LU * BLOCK) {
         uint32_t more[LU];
-        if (i0 + LU * BLOCK <= src.len) {  // uniform: a whole tile
+        load_raw<VEC>(src, i0, more);
 #pragma unroll
-            for (int j = 0; j < LU; ++j) more[j] = src.raw_inside(i0 + j * BLOCK + threadIdx.x);
-        } else {
-#pragma unroll
-            for (int j = 0; j < LU; ++j) more[j] = src.raw(i0 + j * BLOCK + threadIdx.x);
-        }
-#pragma unroll
-        for (int j = 0; j < LU; ++j) count_entry(i0 + j * BLOCK + threadIdx.x, more[j]);
+        for (int j = 0; j < LU; ++j) count_entry(list_entry(i0) + 64 * j, more[j]);
     }
     // The counts to G3, the row of suffix sums from registers, the counts above bin Bw and the squares: one pair of barriers
     // for the three sums.
@@ -1827,10 +1841,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(
     // The first LU entries of every thread do not depend on the prologue: their loads are in flight
     // while it runs (a typical chunk has no more than these), issued behind its first loads.
     uint32_t first[LU];
-    auto first_entries = [&]() {
-#pragma unroll
-        for (int j = 0; j < LU; ++j) first[j] = src.raw(j * BLOCK + threadIdx.x);
-    };
+    auto first_entries = [&]() { load_raw<VEC>(src, 0, first); };
     const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
                                                 a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks,
                                                 static_cast<uint32_t>(sg.k), h, first_entries);
@@ -2091,7 +2102,7 @@ __device__ __forceinline__ void error_norm_16(const Launch &a, const SegDesc &sg
 
 // LDS of the placing.
 struct EmitLds {
-    uint32_t wcnt[2][2][LU * NW];
+    uint32_t wcnt[2][NW];
     uint32_t sm[2 * NW];
     double smd[NW];
     uint32_t s_pick[2];
@@ -2101,19 +2112,18 @@ struct EmitLds {
 // One tile of list entries in registers: raw pattern and index.
 template <int VEC>
 __device__ __forceinline__ void load_entries(const ChunkSource<VEC> &src, uint32_t t0, uint32_t (&raw)[LU], int32_t (&id)[LU]) {
-    if (t0 + LU * BLOCK <= src.len) {  // uniform: a whole tile
+    const uint32_t i = list_entry(t0);
+    if (whole_wave<VEC>(src, t0)) {
 #pragma unroll
         for (int j = 0; j < LU; ++j) {
-            const uint32_t i = t0 + j * BLOCK + threadIdx.x;
-            raw[j] = src.raw_inside(i);
-            id[j] = src.index_inside(i);
+            raw[j] = src.raw_inside(i + 64 * j);
+            id[j] = src.index_inside(i + 64 * j);
         }
     } else {
 #pragma unroll
         for (int j = 0; j < LU; ++j) {
-            const uint32_t i = t0 + j * BLOCK + threadIdx.x;
-            raw[j] = src.raw(i);
-            id[j] = src.index(i);
+            raw[j] = src.raw(i + 64 * j);
+            id[j] = src.index(i + 64 * j);
         }
     }
 }
@@ -2175,39 +2185,36 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
     const uint32_t dense_tiles = (WIDE && src.from_input) ? src.len / DENSE_ELEMS : 0u;  // uniform over the workgroup
     if (WIDE && __builtin_expect(dense_tiles != 0, 0)) {
         const uint2 run = emit_dense_tiles<VEC>(src, dense_tiles, T, q, kout, run_gt, run_eq, l.s_off[2] == 0, oi, oi64, ov, wide,
-                                                &l.wcnt[0][0][0]);
+                                                &l.wcnt[0][0]);
         run_gt = run.x;
         run_eq = run.y;
         __syncthreads();  // the count array changes hands
     }
     for (uint32_t t0 = dense_tiles * DENSE_ELEMS; t0 < src.len; t0 += BLOCK * LU, buf ^= 1) {
         if (t0 != 0) load_entries<VEC>(src, t0, raw, id);
-        uint32_t pre_gt[LU], pre_eq[LU], cls[LU];  // cls: 0 not kept for sure, 1 equal to T, 2 above T
+        uint64_t bg[LU], be[LU];
+        bool gt[LU], eq[LU];  // live as the lane masks
+        uint32_t mine = 0;  // of this wavefront: (above T) | (equal to T) << 16
 #pragma unroll
         for (int j = 0; j < LU; ++j) {
-            const uint32_t i = t0 + j * BLOCK + threadIdx.x;
-            const bool valid = i < src.len;
+            const bool valid = list_entry(t0) + 64 * j < src.len;
             const uint32_t key = key_of<VEC>(raw[j]);
-            const bool gt = valid && key > T, eq = valid && key == T;
-            cls[j] = gt ? 2u : (eq ? 1u : 0u);
-            const uint64_t bg = __ballot(gt), be = __ballot(eq);
-            pre_gt[j] = lanes_below(bg);
-            pre_eq[j] = lanes_below(be);
-            if (lane == 0) {
-                l.wcnt[buf][0][j * NW + w] = __popcll(bg);
-                l.wcnt[buf][1][j * NW + w] = __popcll(be);
-            }
+            gt[j] = valid && key > T;
+            eq[j] = valid && key == T;
+            bg[j] = __ballot(gt[j]);
+            be[j] = __ballot(eq[j]);
+            mine += static_cast<uint32_t>(__popcll(bg[j])) + (static_cast<uint32_t>(__popcll(be[j])) << 16);
         }
+        static_assert(BLOCK * LU < 65536, "two 16-bit counts travel in one word");
+        if (lane == 0) l.wcnt[buf][w] = mine;
         __syncthreads();
-        const uint32_t cg = (lane < LU * NW) ? l.wcnt[buf][0][lane] : 0u;
-        const uint32_t ce = (lane < LU * NW) ? l.wcnt[buf][1][lane] : 0u;
-        const uint32_t ig = wave_incl_scan(cg), ie = wave_incl_scan(ce);
-        const uint32_t tg = lane_value(ig, 63), te = lane_value(ie, 63);
+        uint32_t before, total;
+        wave_counts(l.wcnt[buf], before, total);
+        uint32_t gt_wave = run_gt + (before & 0xFFFFu), eq_wave = run_eq + (before >> 16);
 #pragma unroll
         for (int j = 0; j < LU; ++j) {
-            const uint32_t gt_before = run_gt + lane_value(ig - cg, j * NW + w) + pre_gt[j];
-            const uint32_t eq_before = run_eq + lane_value(ie - ce, j * NW + w) + pre_eq[j];
-            if (cls[j] == 2u || (cls[j] == 1u && eq_before < q)) {
+            const uint32_t gt_before = lanes_below_plus(bg[j], gt_wave), eq_before = lanes_below_plus(be[j], eq_wave);
+            if (gt[j] || (eq[j] && eq_before < q)) {
                 const uint32_t pos = gt_before + (eq_before < q ? eq_before : q);
                 if (pos < kout) {
                     if (wide) oi64[pos] = id[j];
@@ -2215,7 +2222,10 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
                     ov[pos] = static_cast<R>(raw[j]);
                 }
             }
+            gt_wave += static_cast<uint32_t>(__popcll(bg[j]));
+            eq_wave += static_cast<uint32_t>(__popcll(be[j]));
         }
+        const uint32_t tg = total & 0xFFFFu, te = total >> 16;
         run_gt += tg;
         run_eq += te;
     }
@@ -2517,8 +2527,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
             for (uint32_t pp = 0; pp < 1u << sl; ++pp) {
                 const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, c, count, pp, sl, lo);
                 if (src.len == 0) continue;
-#pragma unroll
-                for (int j = 0; j < LU; ++j) raw[j] = src.raw(j * BLOCK + threadIdx.x);
+                load_raw<VEC>(src, 0, raw);
                 refine_part<VEC, WIDE>(a, 0, src, (static_cast<size_t>(c) << sl) + pp, pw.B, lo, shw, raw, h, l.sl.sm, l.sl.smd);
                 __syncthreads();  // the scratch changes hands
             }
@@ -2562,8 +2571,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) 
     int32_t id[LU];
     auto first_entries = [&]() {  // behind the bucket search's first loads
         if (VEC == TAG_F32) {
-#pragma unroll
-            for (int j = 0; j < LU; ++j) raw[j] = src.raw(j * BLOCK + threadIdx.x);
+            load_raw<VEC>(src, 0, raw);
         } else {
             load_entries<VEC>(src, 0, raw, id);
         }
@@ -3503,7 +3511,6 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         int64_t list_tiles = 0;
         const bool no_lists = 2 * n_dense > n_batch;
         uint32_t parts = 0;
-        static_assert(CTARGET * MAXSUB < 65536 && MAXSUB < 16, "16-bit part numbers");
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];
             const int32_t s = which[i];
@@ -3535,7 +3542,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
                 while ((1u << sl) < most && 1.35 * kept >= static_cast<double>(SUB_ENTRIES << sl)) ++sl;
             }
             d.flags |= sl << FLAG_SUB_SHIFT;
-            a.part_begin[i] = static_cast<uint16_t>(parts);
+            a.part_begin[i] = parts;
             parts += static_cast<uint32_t>(d.nchunks) << sl;
         }
         a.parts = parts;
