@@ -737,17 +737,22 @@ __device__ __forceinline__ uint32_t window_bin(uint32_t key, uint32_t lo, uint32
 }
 
 // ------------------------------------------------------------------ k_hist1
-// LDS histogram of the top digit of one tile.
+// LDS histogram of the top digit of one tile: two copies side by side, for even and odd lanes, because lanes on
+// one word are served one after the other (normal values: up to ten of a wavefront on one).  Digit 0, the zeros, is not counted: its
+// entry of the row is the chunk's length (half of the lanes of a wavefront on one word, values behind a ReLU,
+// made the kernel twice as long unless lane 0 happened to hold a zero).
+constexpr int HIST1_COPIES = 2;
 template <int VEC, bool FAST>
 __device__ __forceinline__ void hist1_tile(const uint32_t (&dw)[Stream<VEC>::SLOTS],
                                            const uint32_t (&valid)[Stream<VEC>::SLOTS], uint32_t *h) {
     constexpr int EPD = Stream<VEC>::EPD;
+    uint32_t *mine = h + (threadIdx.x & (HIST1_COPIES - 1));
     // Probe: does half of the wavefront share the top digit of lane 0's first element?  Then the tile
     // is counted with that digit's lanes taken together, slot by slot (one add per slot for them);
     // otherwise every lane adds for itself, which is the faster way when digits are spread.
     const uint32_t d0 = key_of<VEC>(elem_of<VEC>(dw[0], 0)) >> SH1;
     const uint32_t hot = __builtin_amdgcn_readfirstlane(d0);
-    const bool skewed = FAST && __popcll(__ballot(d0 == hot)) >= 32;  // wave-uniform
+    const bool skewed = FAST && hot != 0 && __popcll(__ballot(d0 == hot)) >= 32;  // wave-uniform
     if (skewed) {
         uint32_t hot_count = 0;
 #pragma unroll
@@ -756,17 +761,18 @@ __device__ __forceinline__ void hist1_tile(const uint32_t (&dw)[Stream<VEC>::SLO
             for (int hh = 0; hh < EPD; ++hh) {
                 const uint32_t d = key_of<VEC>(elem_of<VEC>(dw[e], hh)) >> SH1;
                 hot_count += static_cast<uint32_t>(__popcll(__ballot(d == hot)));
-                if (d != hot) atomicAdd(&h[d], 1u);
+                if (d != hot && d != 0) atomicAdd(&mine[d * HIST1_COPIES], 1u);
             }
-        if ((threadIdx.x & 63) == 0) atomicAdd(&h[hot], hot_count);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&mine[hot * HIST1_COPIES], hot_count);
         return;
     }
 #pragma unroll
     for (int e = 0; e < Stream<VEC>::SLOTS; ++e)
 #pragma unroll
-        for (int hh = 0; hh < EPD; ++hh)
-            if (FAST || ((valid[e] >> hh) & 1u))
-                atomicAdd(&h[key_of<VEC>(elem_of<VEC>(dw[e], hh)) >> SH1], 1u);
+        for (int hh = 0; hh < EPD; ++hh) {
+            const uint32_t d = key_of<VEC>(elem_of<VEC>(dw[e], hh)) >> SH1;
+            if ((FAST || ((valid[e] >> hh) & 1u)) && d != 0) atomicAdd(&mine[d * HIST1_COPIES], 1u);
+        }
 }
 
 // The full tiles of a chunk: `rem` tiles from element t0 on, which is advanced past them.
@@ -812,17 +818,23 @@ __device__ __forceinline__ void hist1_full_tiles(const void *x, int64_t &t0, int
 // more, contiguously: whoever comes next finds the bucket of the k-th key from the column sums of the rows.
 // acc becomes the workgroup's sum of it (in a fixed order); the two reductions share their barriers.  sm: 2 * NW words,
 // smd: NW doubles.  The counts are complete (the caller has synchronised); h is not written.
-template <int NB, int NC, bool SHARED>
-__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double &acc, double *smd) {
-    static_assert(NB == 4 * BLOCK && (NB / NC) % 4 == 0, "four counts per thread");
-    const uint4 c = reinterpret_cast<const uint4 *>(h)[threadIdx.x];
+// COPIES = 2: of every count there are two, next to each other.  all: the row's first entry, if not 0.
+template <int NB, int NC, bool SHARED, int COPIES = 1>
+__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double &acc, double *smd,
+                                           uint32_t all = 0) {
+    static_assert(NB == 4 * BLOCK && (NB / NC) % 4 == 0 && (COPIES == 1 || COPIES == 2), "four counts per thread");
+    uint4 c = reinterpret_cast<const uint4 *>(h)[threadIdx.x * COPIES];
+    if (COPIES == 2) {
+        const uint4 d = reinterpret_cast<const uint4 *>(h)[threadIdx.x * COPIES + 1];
+        c = make_uint4(c.x + c.y, c.z + c.w, d.x + d.y, d.z + d.w);
+    }
     uint32_t total;
     const uint32_t inc = block_incl_scan_and_sum(c.x + c.y + c.z + c.w, sm, &total, acc, smd);
     uint4 suffix;
     suffix.w = total - inc + c.w;
     suffix.z = suffix.w + c.z;
     suffix.y = suffix.z + c.y;
-    suffix.x = suffix.y + c.x;
+    suffix.x = all != 0 && threadIdx.x == 0 ? all : suffix.y + c.x;
     uint32_t *row = rows + static_cast<size_t>(g) * NB + 4 * threadIdx.x;
     if (SHARED) {
         store_agent(&row[0], suffix.x);
@@ -835,10 +847,10 @@ __device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, ui
     constexpr uint32_t PER_COARSE = NB / NC / 4;  // threads
     if (threadIdx.x % PER_COARSE == 0) store_count<SHARED>(&coarse[static_cast<size_t>(g) * NC + threadIdx.x / PER_COARSE], suffix.x);
 }
-template <int NB, int NC, bool SHARED>
-__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double *smd) {
+template <int NB, int NC, bool SHARED, int COPIES = 1>
+__device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double *smd, uint32_t all = 0) {
     double none = 0.0;
-    store_rows<NB, NC, SHARED>(h, rows, coarse, g, sm, none, smd);
+    store_rows<NB, NC, SHARED, COPIES>(h, rows, coarse, g, sm, none, smd, all);
 }
 
 // The histogram of one chunk.
@@ -847,7 +859,7 @@ __device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, 
     using St = Stream<VEC>;
     const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
     const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
-    for (int b = threadIdx.x; b < NB1; b += BLOCK) h[b] = 0;
+    for (int b = threadIdx.x; b < NB1 * HIST1_COPIES; b += BLOCK) h[b] = 0;
     __syncthreads();
 
     uint32_t cur[St::SLOTS], valid[St::SLOTS];
@@ -864,11 +876,11 @@ __device__ __forceinline__ void hist1_chunk(const Launch &a, const SegDesc &sg, 
     }
     __syncthreads();
 
-    store_rows<NB1, NC1, SHARED>(h, a.rows1, a.coarse1, g, sm, smd);
+    store_rows<NB1, NC1, SHARED, HIST1_COPIES>(h, a.rows1, a.coarse1, g, sm, smd, static_cast<uint32_t>(end > beg ? end - beg : 0));
 }
 
 template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
-    __shared__ __attribute__((aligned(16))) uint32_t h[NB1];
+    __shared__ __attribute__((aligned(16))) uint32_t h[NB1 * HIST1_COPIES];
     __shared__ uint32_t sm[2 * NW];
     __shared__ double smd[NW];
 
@@ -2550,7 +2562,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK, WIDE ? 2 : 4) void k_judge(Launch a) {
     __shared__ JudgeLds l;
     uint32_t *h = l.sl.smem;
-    static_assert(NBW + 1 <= SCAN_SMEM_WORDS && NCW + NBW / NCW <= SCAN_SMEM_WORDS, "shared scratch fits");
+    static_assert(NBW + 1 <= SCAN_SMEM_WORDS && NCW + NBW / NCW <= SCAN_SMEM_WORDS && NB1 * HIST1_COPIES <= SCAN_SMEM_WORDS, "shared scratch fits");
 
     const SegDesc &sg = a.seg[0];
     const uint32_t nchunks = static_cast<uint32_t>(sg.nchunks), kout = static_cast<uint32_t>(sg.k);
