@@ -1114,7 +1114,8 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
 // bound by instruction issue (two wavefronts per SIMD), so the work per sampled element is kept to a
 // handful of instructions: two for its bin's byte offset (the sign falls out of the shift), half of one each for the largest and
 // the smallest, one compare against a floor below which nothing needs counting, one add.  (With keys, a shift per use and
-// padded bins: 3.0 us from the sample's arrival to the window at 16 K fp32 values, now 2.1.)
+// padded bins it was 3.5 us from the sample's arrival to the window; this and the rows from registers took 1.3 us off a
+// compress and decompress of 393 K fp32 values, 24.2 -> 22.9.)
 // The bins holding the two ranks are found while the suffix sums are formed in registers.
 constexpr int SCAN_SMEM_WORDS = 2 * STAGE_CAP + NBW;  // k_scan's stage and window histogram; its prologue's scratch fits inside
 constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by up to this many run lengths
@@ -2245,7 +2246,7 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
 
 // k_emit.  Prologue -> threshold key T, tie quota q (threshold_f32 / threshold_16), then emit_part on the workgroup's
 // part.  Where there is room, one more workgroup for each tensor adds up its error norm (and writes its message's header): done by the
-// last part's workgroup as well, in front of its placing, the sum is what the launch ends with (6.5 M fp16 values 30.2 -> 28.6 us per
+// last part's workgroup as well, in front of its placing, the sum is what the launch ends with (6.5 M fp16 values 28.9 -> 28.0 us per
 // compress and decompress).
 template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(Launch a) {
     __shared__ uint32_t h[VEC == TAG_F32 ? 1 : NBW + 1];  // 16-bit types: the global suffix sums of the window bins up to Bw
@@ -2660,7 +2661,8 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
 // quota q, and the placing) works on the candidates, a few hundred of 8192 elements at 1 %.
 // Every wavefront owns a contiguous eighth of the tensor and a segment of the candidate list, so the candidates are
 // in index order without an exchange between the wavefronts; only their totals are added up before the placing.  (All
-// three digits and the placing over all elements: 12.1 us for 128 tensors of 1 to 8 K fp32 values.)
+// three digits and the placing over all elements, loads clamped and masked one by one: 12.2 us for 128 tensors of 1 to 8 K
+// fp32 values, now 7.0.)
 // Tensors beyond one register tile stay with the four-kernel path, which spreads them over many compute units.
 constexpr int SMALL_EPT = 128 / NW;            // elements per thread (16 with 512 threads)
 constexpr int SMALL_N = BLOCK * SMALL_EPT;     // largest tensor this path takes
@@ -3200,7 +3202,8 @@ inline int64_t chunk_target(int32_t S_batch) { return S_batch == 1 ? CTARGET_ONE
 // (an empty tensor still gets one chunk).  n(i), k(i): elements and kept elements.
 // All workgroups of a scan run at once, so it takes as long as the chunk with the most work: an element that is kept costs
 // SCAN_KEPT_COST times what reading one does (single fp32 tensors of 25 M: 20 us of streaming at 1 % kept, 28 at 10 %), and the tensors
-// of a batch keep anything from 0.1 to 20 %.  Tensors that need the exact passes beside ones that speculate have
+// of a batch keep anything from 0.1 to 20 % (24 x 33.5 MB: 454.7 us per compress and decompress with one length for all,
+// now 421.3).  Tensors that need the exact passes beside ones that speculate have
 // the chip to themselves in those two passes, so their chunks are cut finer: with m chunks for n elements of
 // either kind, n / m + 2 n' / m' is least at m' / m = sqrt(2 n' / n).
 constexpr double SCAN_KEPT_COST = 4.5;
