@@ -2658,11 +2658,13 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
 // two wavefronts per SIMD, and its time is the number of its instructions; so only two passes look at all elements: a
 // histogram of the top digit (LDS), and one that sets the candidates apart, the elements in the bucket of the k-th key or
 // above it, and sums the squares of the others.  What follows (two more digits, which fix the threshold key T and the tie
-// quota q, and the placing) works on the candidates, a few hundred of 8192 elements at 1 %.
-// Every wavefront owns a contiguous eighth of the tensor and a segment of the candidate list, so the candidates are
-// in index order without an exchange between the wavefronts; only their totals are added up before the placing.  (All
-// three digits and the placing over all elements, loads clamped and masked one by one: 12.2 us for 128 tensors of 1 to 8 K
-// fp32 values, now 7.0.)
+// quota q, and the placing: small_select) works on the candidates, a few hundred of 8192 elements at 1 %.  They lie in
+// index order in one list that is dealt out evenly, because in sorted tensors one wavefront has them all.  Where they are many (a large
+// keep share, equal keys) or the tensor is tiny they stay where they are: the same steps then go over all elements in registers.
+// 128 tensors of 8192 fp32 values, us, candidates always listed and left to the wavefront that found them / so: normal values 1 % kept 7.9 / 8.2,
+// 95 % 16.8 / 12.5, sorted 10 % 21.1 / 12.4, all equal 21.1 / 14.2.
+// (All three digits and the placing over all elements, loads clamped and masked one by one: 12.2 us for 128 tensors of 1 to 8 K
+// fp32 values, now 7.2.)
 // Tensors beyond one register tile stay with the four-kernel path, which spreads them over many compute units.
 constexpr int SMALL_EPT = 128 / NW;            // elements per thread (16 with 512 threads)
 constexpr int SMALL_N = BLOCK * SMALL_EPT;     // largest tensor this path takes
@@ -2683,12 +2685,20 @@ struct SmallLaunch {
 };
 static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments stay within 4 KB");
 static_assert(SMALL_N < 65536, "two 16-bit counts travel in one word");
+// Candidates are listed when at most a quarter of the tensor are some and it has more than two rows of 64 elements per wavefront.  Listed /
+// left in registers, us for 128 fp32 tensors: 1024 values at 1 % 6.0 / 5.8, 2000 values at 10 % 6.4 / 6.9, 3000 values at 50 % 10.3 / 9.0.
+constexpr uint32_t SMALL_LISTED = 4;
+constexpr int SMALL_UNLISTED_N = 2 * BLOCK;
+constexpr int SMALL_SEGMENT = 64 * SMALL_EPT;  // of the list, for one wavefront's candidates
 
-// The bucket of the krem-th largest (krem >= 1) of the counts h[NB] in LDS and the number of counts above it, found while
-// the suffix sums are formed in registers.  pick: two words of LDS.  Synchronises before it reads h and before it returns.
-template <int NB> __device__ __forceinline__ void small_pick(const uint32_t *h, uint32_t krem, uint32_t *sm, uint32_t *pick, uint32_t &B, uint32_t &above) {
+// The bucket of the krem-th largest (krem >= 1) of the counts h[NB] in LDS, the number of counts above it and its own count, found
+// while the suffix sums are formed in registers.  Synchronises before it reads h and before it returns.
+struct SmallPick {
+    uint32_t B, above, here;
+};
+template <int NB> __device__ __forceinline__ SmallPick small_pick(const uint32_t *h, uint32_t krem, uint32_t *sm, SmallPick *pick) {
     constexpr int PER = NB / BLOCK;
-    if (threadIdx.x == 0) pick[0] = pick[1] = 0;  // (counts that do not add up)
+    if (threadIdx.x == 0) *pick = SmallPick{0, 0, 0};  // (counts that do not add up)
     __syncthreads();
     uint32_t cnt[PER], own = 0;
 #pragma unroll
@@ -2701,15 +2711,96 @@ template <int NB> __device__ __forceinline__ void small_pick(const uint32_t *h, 
     uint32_t higher = total - inc;  // counts of the threads after this one
 #pragma unroll
     for (int j = PER - 1; j >= 0; --j) {
-        if (higher < krem && higher + cnt[j] >= krem) {
-            pick[0] = threadIdx.x * PER + j;
-            pick[1] = higher;
-        }
+        if (higher < krem && higher + cnt[j] >= krem) *pick = SmallPick{static_cast<uint32_t>(threadIdx.x * PER + j), higher, cnt[j]};
         higher += cnt[j];
     }
     __syncthreads();
-    B = pick[0];
-    above = pick[1];
+    return *pick;
+}
+
+// One digit of the tensor's elements that `in` names, into h.  Equal digits would serialise on one LDS word (64 lanes on one: 440
+// cycles): a wavefront half of whose first slot falls into the bin of a lane in its middle adds through hist_add, any other every lane
+// for itself.  (Of the first lane: in sorted tensors a bin often begins between it and the next.)  RUNS: nearly equal ones
+// are counted as a run; the code of that slows down tensors that do not use it, so it is not for the pass that they all make.
+template <bool RUNS, typename In, typename Bin> __device__ __forceinline__ void small_count(uint32_t *h, int slots, In &&in, Bin &&bin) {
+    const uint32_t first = bin(0);
+    const bool is = in(0);
+    const int alike = __popcll(__ballot(is & (first == static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(first), 31)))));
+    const bool skewed = alike >= 32;  // wave-uniform
+    if (RUNS && alike >= 56) {
+        BinRun run;
+#pragma unroll
+        for (int e = 0; e < SMALL_EPT; ++e)
+            if (e < slots) run.add(h, bin(e), in(e));
+        run.flush(h);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < SMALL_EPT; ++e)
+        if (e < slots) {  // wave-uniform
+            const uint32_t b = bin(e);
+            if (skewed) hist_add(h, b, in(e));
+            else if (in(e)) atomicAdd(&h[b], 1u);
+        }
+}
+
+// The rest of a small tensor's selection, over entries in index order (candidates in a list, or all elements in registers).
+// count(in, bin): the bins of the raw patterns that `in` names, into h.  each(f): f(index, raw pattern, whether there is such an entry)
+// slot by slot; the wavefronts' entries follow one another.  h is all zeros in its first NB2 words, which every thread sees.
+// top: the pick of the top digit; kout >= 1 keys are kept.  Returns this thread's share of the squares of the dropped entries.
+template <int VEC, typename Count, typename Each>
+__device__ __forceinline__ double small_select(Count &&count, Each &&each, const SmallPick &top, uint32_t kout, const OutPtrs &op, bool wide,
+                                               uint32_t *h, uint32_t *sm, SmallPick *s_pick) {
+    using R = typename Raw<VEC>::type;
+    static_assert(NB2 == 2 * BLOCK && NB3 == 2 * BLOCK, "two words per thread");
+    // T and the number of keys above it, from the digits below the first
+    count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH1 == top.B; }, [&](uint32_t raw) { return (key_of<VEC>(raw) >> SH2) & (NB2 - 1); });
+    const SmallPick second = small_pick<NB2>(h, kout - top.above, sm, s_pick);
+    uint32_t c_gt = top.above + second.above;
+    const uint32_t P = (top.B << BITS2) | second.B;
+    uint32_t T = P << BITS3;
+    if (VEC == TAG_F32) {  // (a 16-bit pattern ends within the second digit)
+        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);  // (read by everybody: small_pick synchronises behind that)
+        __syncthreads();
+        count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH2 == P; }, [&](uint32_t raw) { return key_of<VEC>(raw) & (NB3 - 1); });
+        const SmallPick third = small_pick<NB3>(h, kout - c_gt, sm, s_pick);
+        c_gt += third.above;
+        T |= third.B;
+    }
+    const uint32_t q = kout - c_gt;
+
+    // The placing: the wavefronts' counts above and equal to T, two 16-bit counts in a word (the sums in sm have been read).
+    uint32_t mine = 0;
+    each([&](uint32_t, uint32_t raw, bool in) {
+        const uint32_t key = key_of<VEC>(raw);
+        mine += static_cast<uint32_t>(__popcll(__ballot(in & (key > T)))) + (static_cast<uint32_t>(__popcll(__ballot(in & (key == T)))) << 16);
+    });
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    uint32_t before, all;
+    wave_counts(sm, before, all);
+    uint32_t run_eq = before >> 16, run = (before & 0xFFFFu) + (run_eq < q ? run_eq : q);  // equal to T, and kept, before this slot
+    double acc = 0.0;
+    each([&](uint32_t index, uint32_t raw, bool in) {
+        const uint32_t key = key_of<VEC>(raw);
+        bool keep = in & (key > T);  // (no && in these conditions: the compiler makes a branch of each)
+        const uint64_t be = __ballot(in & (key == T));
+        if (be != 0) {  // wave-uniform, one or two slots of a tensor without ties
+            keep = keep | (in & (key == T) & (lanes_below_plus(be, run_eq) < q));
+            run_eq += static_cast<uint32_t>(__popcll(be));
+        }
+        const uint64_t kept = __ballot(keep);
+        const uint32_t pos = lanes_below_plus(kept, run);
+        run += static_cast<uint32_t>(__popcll(kept));
+        if (keep & (pos < kout)) {
+            if (wide) *reinterpret_cast<int64_t *>(reinterpret_cast<char *>(op.i64) + pos * 8u) = static_cast<int64_t>(index);
+            else *reinterpret_cast<int32_t *>(reinterpret_cast<char *>(op.i32) + pos * 4u) = static_cast<int32_t>(index);
+            *reinterpret_cast<R *>(static_cast<char *>(op.val) + pos * static_cast<uint32_t>(sizeof(R))) = static_cast<R>(raw);
+        }
+        const double v = static_cast<double>((in & !keep) ? value_of<VEC>(raw) : 0.0f);
+        acc = fma(v, v, acc);
+    });
+    return acc;
 }
 
 template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallLaunch a) {
@@ -2717,149 +2808,103 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
     __shared__ __attribute__((aligned(16))) uint32_t h[NB1];
     __shared__ uint32_t sm[NW];
     __shared__ double smd[NW];
-    __shared__ uint32_t s_pick[2];
-    __shared__ uint2 candidates[SMALL_N];  // (index, raw pattern); the wavefronts' segments are SMALL_EPT * 64 long
+    __shared__ SmallPick s_pick;
+    __shared__ uint2 candidates[SMALL_N];  // (index, raw pattern); every wavefront has a segment
 
     const SmallDesc &sg = a.seg[blockIdx.x];
     const int n = static_cast<int>(a.nk[blockIdx.x] & 0xFFFFu);
     const uint32_t kout = a.nk[blockIdx.x] >> 16;
     const R *x = static_cast<const R *>(sg.x);
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slots = (n + BLOCK - 1) / BLOCK;      // element (slot e, lane) of wavefront w is i0 + 64 * e
-    const int i0 = w * slots * 64 + lane;
-    uint2 *mine = candidates + w * (SMALL_EPT * 64);
+    // The tensor's rows of 64 elements, dealt out to the wavefronts in runs: element (slot e, lane) of a wavefront is i0 + 64 * e < end.
+    const int rows = (n + 63) / 64, row0 = (w * rows) / NW, row1 = ((w + 1) * rows) / NW;
+    const int slots = row1 - row0, end = row1 * 64 < n ? row1 * 64 : n, whole = (end - row0 * 64) / 64;  // wave-uniform
+    const int i0 = row0 * 64 + lane;
 
-    // The whole tensor in one round of loads.  (The wavefront with the tensor's end without conditions, too, see ChunkSource:
-    // an element past the end reads the last one and is masked out.)
+    // One round of loads without conditions or clamps but for the tensor's last row, if it is a short one.  (Clamped and masked as a
+    // whole, the wavefront with the end made 5000 values take 1.7 us longer than 8192.)
     uint32_t raw[SMALL_EPT];
-#pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e) raw[e] = 0;
-    if ((w + 1) * slots * 64 <= n) {  // wave-uniform
+    {
         const R *own = x + i0;
 #pragma unroll
-        for (int e = 0; e < SMALL_EPT; ++e)
-            if (e < slots) raw[e] = static_cast<uint32_t>(own[64 * e]);
-    } else {
-#pragma unroll
-        for (int e = 0; e < SMALL_EPT; ++e)
-            if (e < slots) {  // uniform
-                const int i = i0 + 64 * e;
-                raw[e] = static_cast<uint32_t>(x[opaque(static_cast<uint32_t>(i < n ? i : n - 1))]) & keep_mask(i < n);
-            }
-    }
-
-    // the bucket of the k-th key on the top digit: keys from lo up are candidates
-    uint32_t lo = 0x80000000u, B1 = 0, above1 = 0;  // (k = 0: none)
-    if (kout != 0) {  // uniform
-        static_assert(NB1 == 4 * BLOCK, "four words per thread");
-        reinterpret_cast<uint4 *>(h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        // Equal keys would serialise on one LDS word: a wavefront half of whose first slot falls into one bucket adds
-        // through hist_add, any other every lane for itself.
-        const uint32_t first = key_of<VEC>(raw[0]) >> SH1;
-        const bool skewed = __popcll(__ballot(i0 < n && first == static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(first))))) >= 32;
-#pragma unroll
-        for (int e = 0; e < SMALL_EPT; ++e)
-            if (e < slots) {
-                const bool in = i0 + 64 * e < n;
-                const uint32_t bin = key_of<VEC>(raw[e]) >> SH1;
-                if (skewed) hist_add(h, bin, in);
-                else if (in) atomicAdd(&h[bin], 1u);
-            }
-        small_pick<NB1>(h, kout, sm, s_pick, B1, above1);
-        lo = B1 << SH1;
-    }
-
-    // the candidates, in index order, and the squares of all other elements
-    uint32_t count = 0;  // of this wavefront
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e)
-        if (e < slots) {
-            const bool keep = i0 + 64 * e < n && key_of<VEC>(raw[e]) >= lo;
-            const uint64_t m = __ballot(keep);
-            if (keep) mine[lanes_below_plus(m, count)] = make_uint2(static_cast<uint32_t>(i0 + 64 * e), raw[e]);
-            count += static_cast<uint32_t>(__popcll(m));
-            float xs = keep ? 0.0f : value_of<VEC>(raw[e]);  // (past the end: 0)
-            asm("" : "+v"(xs));                              // (see scan_tile)
-            const double xd = static_cast<double>(xs);
-            acc = fma(xd, xd, acc);
+        for (int e = 0; e < SMALL_EPT; ++e) {
+            raw[e] = 0;
+            if (e < whole) raw[e] = static_cast<uint32_t>(own[64 * e]);
         }
-
-    // f(candidate, whether there is one) for this wavefront's candidates, 64 at a time
-    auto each = [&](auto &&f) {
-#pragma unroll 1
-        for (uint32_t j0 = 0; j0 < count; j0 += 64) {
-            const uint32_t j = j0 + lane;
-            f(mine[j < count ? j : 0], j < count);
+        if (whole < slots) {  // wave-uniform; see ChunkSource: an element past the end reads the last one and is masked out
+            const int i = i0 + 64 * whole;
+            const uint32_t tail = static_cast<uint32_t>(x[opaque(static_cast<uint32_t>(i < n ? i : n - 1))]) & keep_mask(i < n);
+#pragma unroll
+            for (int e = 0; e < SMALL_EPT; ++e) raw[e] = e == whole ? tail : raw[e];
         }
-    };
-    // T and the number of keys above it, from the digits below the first
-    uint32_t T = 0xFFFFFFFFu, c_gt = 0;
-    if (kout != 0) {
-        uint32_t B2, above2;
-        static_assert(NB2 == 2 * BLOCK && NB3 == 2 * BLOCK, "two words per thread");
-        // (every thread has read what it needs of h: small_pick synchronises behind that)
-        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);
-        __syncthreads();
-        each([&](uint2 c, bool in) {
-            const uint32_t key = key_of<VEC>(c.y);
-            hist_add(h, (key >> SH2) & (NB2 - 1), in && key >> SH1 == B1);
-        });
-        small_pick<NB2>(h, kout - above1, sm, s_pick, B2, above2);
-        c_gt = above1 + above2;
-        const uint32_t P = (B1 << BITS2) | B2;
-        uint32_t B3 = 0, above3 = 0;
-        if (VEC == TAG_F32) {  // (a 16-bit pattern ends within the second digit)
-            reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);
-            __syncthreads();
-            each([&](uint2 c, bool in) {
-                const uint32_t key = key_of<VEC>(c.y);
-                hist_add(h, key & (NB3 - 1), in && key >> SH2 == P);
-            });
-            small_pick<NB3>(h, kout - c_gt, sm, s_pick, B3, above3);
-        }
-        c_gt += above3;
-        T = (P << BITS3) | B3;
     }
-    const uint32_t q = kout - c_gt;
-
-    // The placing: the wavefronts' counts above and equal to T (two 16-bit counts in a word), then the candidates once more.
-    uint32_t total = 0;
-    each([&](uint2 c, bool in) {
-        const uint32_t key = key_of<VEC>(c.y);
-        total += static_cast<uint32_t>(__popcll(__ballot(in && key > T))) + (static_cast<uint32_t>(__popcll(__ballot(in && key == T))) << 16);
-    });
-    __syncthreads();  // (the sums in sm have been read)
-    if (lane == 0) sm[w] = total;
-    __syncthreads();
-    uint32_t before, all;
-    wave_counts(sm, before, all);
-    uint32_t run_gt = before & 0xFFFFu, run_eq = before >> 16;
 
     const bool wide = a.idx64 != 0;
     const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, kout, wide, a.wire != 0, sizeof(R));
-    int32_t *oi = op.i32;
-    int64_t *oi64 = op.i64;
-    R *ov = static_cast<R *>(op.val);
-    each([&](uint2 c, bool in) {
-        const uint32_t key = key_of<VEC>(c.y);
-        const uint64_t bg = __ballot(in && key > T), be = __ballot(in && key == T);
-        const uint32_t gt_before = lanes_below_plus(bg, run_gt), eq_before = lanes_below_plus(be, run_eq);
-        run_gt += static_cast<uint32_t>(__popcll(bg));
-        run_eq += static_cast<uint32_t>(__popcll(be));
-        const bool keep = in && (key > T || (key == T && eq_before < q));
-        if (keep) {
-            const uint32_t pos = gt_before + (eq_before < q ? eq_before : q);
-            if (pos < kout) {
-                if (wide) oi64[pos] = static_cast<int64_t>(c.x);
-                else oi[pos] = static_cast<int32_t>(c.x);
-                ov[pos] = static_cast<R>(c.y);
+    double acc = 0.0;
+    SmallPick top{0, 0, 0};
+    if (kout != 0) {  // uniform
+        // the bucket of the k-th key on the top digit: its keys and those above are the candidates
+        static_assert(NB1 == 4 * BLOCK, "four words per thread");
+        reinterpret_cast<uint4 *>(h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        small_count<false>(h, slots, [&](int e) { return i0 + 64 * e < end; }, [&](int e) { return key_of<VEC>(raw[e]) >> SH1; });
+        top = small_pick<NB1>(h, kout, sm, &s_pick);
+        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);  // for small_select
+    }
+    const uint32_t ncand = top.above + top.here;
+    if (__builtin_expect(kout == 0 || (n > SMALL_UNLISTED_N && SMALL_LISTED * ncand <= static_cast<uint32_t>(n)), 1)) {  // uniform
+        // the candidates, in index order, into this wavefront's segment of the list, and the squares of all other elements
+        const uint32_t lo = kout != 0 ? top.B << SH1 : 0x80000000u;
+        uint2 *segment = candidates + w * SMALL_SEGMENT;
+        uint32_t count = 0;
+#pragma unroll
+        for (int e = 0; e < SMALL_EPT; ++e)
+            if (e < slots) {
+                const bool keep = (i0 + 64 * e < end) & (key_of<VEC>(raw[e]) >= lo);
+                const uint64_t m = __ballot(keep);
+                if (keep) segment[lanes_below_plus(m, count)] = make_uint2(static_cast<uint32_t>(i0 + 64 * e), raw[e]);
+                count += static_cast<uint32_t>(__popcll(m));
+                float xs = keep ? 0.0f : value_of<VEC>(raw[e]);  // (past the end: 0)
+                asm("" : "+v"(xs));                              // (see scan_tile)
+                const double xd = static_cast<double>(xs);
+                acc = fma(xd, xd, acc);
             }
+        if (kout != 0) {
+            if (lane == 0) sm[w] = count;
+            __syncthreads();
+            // Dealt out evenly: this wavefront takes `share` entries.  Entry i is in the last segment that begins at or before it.
+            uint32_t begin[NW];
+            begin[0] = 0;
+#pragma unroll
+            for (int v = 1; v < NW; ++v) begin[v] = begin[v - 1] + __builtin_amdgcn_readfirstlane(sm[v - 1]);
+            const uint32_t share = (ncand + BLOCK - 1) / BLOCK * 64, first = static_cast<uint32_t>(w) * share + lane;
+            auto each = [&](auto &&f) {
+#pragma unroll 1
+                for (uint32_t j = 0; j < share; j += 64) {
+                    const bool in = first + j < ncand;
+                    const uint32_t i = in ? first + j : 0u;
+                    uint32_t at = i;
+#pragma unroll
+                    for (int v = 1; v < NW; ++v) at = i >= begin[v] ? v * SMALL_SEGMENT + i - begin[v] : at;
+                    const uint2 c = candidates[at];
+                    f(c.x, c.y, in);
+                }
+            };
+            acc += small_select<VEC>([&](auto &&in, auto &&bin) { each([&](uint32_t, uint32_t r, bool is) { hist_add(h, bin(r), is & in(r)); }); }, each,
+                                     top, kout, op, wide, h, sm, &s_pick);
         }
-        const double v = static_cast<double>((in && !keep) ? value_of<VEC>(c.y) : 0.0f);
-        acc = fma(v, v, acc);
-    });
+    } else {
+        __syncthreads();
+        acc = small_select<VEC>(
+            [&](auto &&in, auto &&bin) { small_count<true>(h, slots, [&](int e) { return (i0 + 64 * e < end) & in(raw[e]); }, [&](int e) { return bin(raw[e]); }); },
+            [&](auto &&f) {
+#pragma unroll
+                for (int e = 0; e < SMALL_EPT; ++e)
+                    if (e < slots) f(static_cast<uint32_t>(i0 + 64 * e), raw[e], i0 + 64 * e < end);
+            },
+            top, kout, op, wide, h, sm, &s_pick);
+    }
     float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
     if (a.wire != 0) {
         write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, a.ratio[blockIdx.x]);

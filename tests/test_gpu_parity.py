@@ -605,3 +605,23 @@ def test_batch_of_tensors_without_lists(dtype, kind):
     assert np.array_equal(off, roff) and np.array_equal(gi, ri) and np.array_equal(H.bits(gv), H.bits(rv))
     assert all(H.same_err(ge[s], re[s], ERR_RTOL) for s in range(len(xs)))
     check_segmented_decompress(gi, gv, off, lens)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("kind", ["normal", "descending", "ascending", "all_equal", "sparse", "few_levels", "nonfinite"])
+def test_small_tensors_on_either_side_of_the_candidate_list(dtype, kind):
+    # one launch for all: lengths around whole rows of 64 elements and around the shortest tensor whose candidates are listed, keep counts
+    # whose candidates are a few, about a quarter of the tensor (listed up to there) and nearly all; sorted ones: in one wavefront
+    import gpu_harness as H
+
+    lens, ks = [], []
+    for n in (1, 63, 64, 65, 511, 513, 1023, 1024, 1025, 1088, 1600, 2047, 4097, 5000, 8129, 8191, 8192):
+        for k in (0, 1, n // 100, n // 9, n // 4 - n // 50, n // 4 + n // 50, n // 2, n - n // 20):
+            lens.append(n)
+            ks.append(min(max(k, 0), n))
+    xs = [wl.small_case(kind, n, seed=n + k, dtype=dtype) for n, k in zip(lens, ks)]
+    gi, gv, off, ge = H.gpu_compress_segmented(xs, ks)
+    for s, (x, k) in enumerate(zip(xs, ks)):
+        ri, rv, re = orc.compress(x, k)
+        assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), (lens[s], k)
+        assert H.same_err(ge[s], re, ERR_RTOL), (lens[s], k, ge[s], re)
