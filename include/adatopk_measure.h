@@ -48,9 +48,12 @@ void adatopk_measure_judge(int32_t missing_workgroups, int32_t wait_rounds);
  *   ADATOPK_MEASURE_CLAIMS        (a single tensor whose sample misled it) who worked: per chunk 1 + the number of the
  *                                 workgroup that took it, 0 if none had to (uint32)
  *   ADATOPK_MEASURE_CHUNK_COUNTS  per chunk its candidates, more than a quarter of the chunk's length: the chunk
- *                                 has no list (uint32) */
+ *                                 has no list (uint32)
+ *   ADATOPK_MEASURE_PART_COUNTS   (fp32) per part of a chunk's candidates how many lie above the k-th key's window bin; not
+ *                                 written for empty parts (uint32) */
 #define ADATOPK_MEASURE_CLAIMS 0
 #define ADATOPK_MEASURE_CHUNK_COUNTS 1
+#define ADATOPK_MEASURE_PART_COUNTS 2
 size_t adatopk_measure_workspace_offset(int32_t what, int64_t n_total, int32_t num_segments, adatopk_dtype dtype);
 
 /* Plain streaming kernels on `hip_stream`; all pointers are device memory, 16-byte

@@ -461,7 +461,7 @@ def measure_judge(missing_workgroups: int = 0, wait_rounds: int = -1) -> None:
     load_measure_library().adatopk_measure_judge(int(missing_workgroups), int(wait_rounds))
 
 
-MEASURE_CLAIMS, MEASURE_CHUNK_COUNTS = 0, 1
+MEASURE_CLAIMS, MEASURE_CHUNK_COUNTS, MEASURE_PART_COUNTS = 0, 1, 2
 
 
 def measure_workspace_offset(what: int, n_total: int, num_segments: int, dtype: torch.dtype) -> int:

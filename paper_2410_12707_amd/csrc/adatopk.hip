@@ -3373,7 +3373,7 @@ inline uint32_t norm_workgroups(uint32_t S) { return (S + XCDS - 1) / XCDS * XCD
 // The kernels of one launch.  With `speculate` the first full read of the input is the speculative
 // scan; the two exact passes behind it return at once for every tensor whose speculation held and
 // do the work for the others, so what reaches k_refine is complete either way.
-// `no_lists`: most elements belong to tensors without lists.
+// `no_lists`: most elements belong to tensors without lists, and nothing speculates; those tensors' chunks have one part each.
 template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, bool no_lists, hipStream_t st) {
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
@@ -3382,7 +3382,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         else launch(ST_SPEC, k_scan<VEC, true, 2>, grid, st, a);
     }
     const dim3 parts(a.parts);
-    const bool wide = (one_per_cu && parts.x == grid.x) || (no_lists && !speculate);  // one workgroup per chunk, at most one per compute unit: see Wide
+    const bool wide = (one_per_cu && parts.x == grid.x) || no_lists;  // see Wide
     // (a wide kernel has a compute unit's registers to itself: one workgroup too many waits for another one to end, 2 us)
     const uint32_t S = static_cast<uint32_t>(a.S);
     a.norms = (a.err_out != nullptr || a.wire) && (!wide || parts.x + S <= CTARGET_ONE) ? norm_workgroups(S) : 0u;
@@ -3580,7 +3580,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
         int64_t list_tiles = 0;
-        const bool no_lists = 2 * n_dense > n_batch;
+        const bool no_lists = nspec == 0 && 2 * n_dense > n_batch;  // (decided once: the cut into parts and the kernels' form go together)  // (decided once: the cut into parts and the kernels' form go together)
         uint32_t parts = 0;
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];
@@ -4049,7 +4049,8 @@ size_t adatopk_measure_workspace_offset(int32_t what, int64_t n_total, int32_t n
     int64_t max_chunks, list_slots;
     bounds_for(n_total, num_segments, &max_chunks, &list_slots);
     const Carve c = carve(max_chunks, list_slots, num_segments, dtype);
-    return what == ADATOPK_MEASURE_CLAIMS ? c.G3 + sizeof(uint32_t) * NB3 + offsetof(JudgeSync, claim) : c.cnt;
+    if (what == ADATOPK_MEASURE_CLAIMS) return c.G3 + sizeof(uint32_t) * NB3 + offsetof(JudgeSync, claim);
+    return what == ADATOPK_MEASURE_PART_COUNTS ? c.ldef : c.cnt;
 }
 
 adatopk_status adatopk_measure_copy(void *dst, const void *src, size_t bytes, void *hip_stream) {

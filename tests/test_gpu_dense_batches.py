@@ -1,0 +1,54 @@
+"""Batches with tensors that keep so much that their chunks have no lists and are placed from the input: the results against the
+oracle, and into how many parts the chunks were cut."""
+import numpy as np
+import pytest
+
+from oracle import adatopk_oracle as orc
+from paper_2410_12707_amd import workloads as wl
+from test_gpu_parity import ERR_RTOL, check_segmented_decompress
+
+pytestmark = pytest.mark.gpu
+
+
+def compress(xs, ks):
+    """Pairs, offsets, error norms and how many parts of chunks k_refine had something to do for (fp32)."""
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    ds = [H.to_device(x) for x in xs]
+    off = [0]
+    for k in ks:
+        off.append(off[-1] + k)
+    idx = torch.full((off[-1],), -7, dtype=torch.int32, device="cuda")
+    val = torch.zeros(off[-1], dtype=ds[0].dtype, device="cuda")
+    err = torch.full((len(xs),), -1.0, device="cuda")
+    n_total = sum(x.size for x in xs)
+    ws = B.new_workspace(n_total, len(xs), ds[0].dtype)
+    ws.fill_(255)
+    B.adatopk_compress_segmented(ds, ks, idx, val, off, err, ws)
+    torch.cuda.synchronize()
+    at = B.measure_workspace_offset(B.MEASURE_PART_COUNTS, n_total, len(xs), ds[0].dtype)
+    parts = int((ws[at:at + 4 * 8 * 512].view(torch.int32) != -1).sum()) if ds[0].dtype == torch.float32 else 0
+    return H.to_host(idx), H.to_host(val), off, H.to_host(err), parts
+
+
+def check(xs, ks):
+    import gpu_harness as H
+
+    gi, gv, off, ge, parts = compress(xs, ks)
+    refs = [orc.compress(x, k) for x, k in zip(xs, ks)]
+    for s, (ri, rv, re) in enumerate(refs):
+        assert np.array_equal(gi[off[s]:off[s + 1]], ri) and np.array_equal(H.bits(gv[off[s]:off[s + 1]]), H.bits(rv)), s
+        assert H.same_err(ge[s], re, ERR_RTOL), (s, ge[s], re)
+    check_segmented_decompress(gi, gv, off, [x.size for x in xs])
+    return parts, refs
+
+
+def test_dense_tensors_beside_speculating_ones_are_cut_into_parts():
+    # too few elements of either kind for launches of their own: the dense tensors' chunks go through the entry loop of the plain
+    # kernels, with several workgroups to a chunk
+    lens, shares = [8_400_003, 6_000_001, 3_000_000], [0.01, 0.6, 0.9]
+    xs = [wl.small_case("normal", n, seed=200 + i) for i, n in enumerate(lens)]
+    assert check(xs, [int(n * f) for n, f in zip(lens, shares)])[0] > 512
