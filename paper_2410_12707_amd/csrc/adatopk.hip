@@ -121,6 +121,15 @@ constexpr int64_t SPEC_NOT_FROM_F32 = 15 << 16, SPEC_AGAIN_FROM_F32 = 1 << 20;
 // 16 Mi 39.6 / 46.9 and 47.5 / 54.6; bf16 4 Mi 25.0 / 23.6 and 26.6 / 24.5, 8 Mi 26.8 / 26.5 and 30.3 / 28.6, 16 Mi 30.6 / 33.4 and
 // 36.5 / 39.0.
 constexpr int64_t SPEC_MIN_BATCH = 8 << 20;
+// Elements of a launch of tensors without lists from which the list kernels' wide form with one workgroup per chunk is the faster one.  Its
+// registers leave room for one workgroup per compute unit, so more than 256 chunks are two rounds; the plain form shares the units
+// among several, but waits for memory 8 KB at a time.  Compress, us, plain / wide, 55 and 90 % kept evenly spread, 90 % behind
+// zeros: 8 fp32 tensors, 8 Mi in all 61 / 79, 66 / 82 and 70 / 80, 24 Mi 135 / 155, 159 / 160 and 168 / 149, 28 Mi 157 / 174, 190 / 181 and
+// 196 / 167, 32 Mi 186 / 189, 217 / 197 and 224 / 181; a single one (at most 256 chunks), 1 Mi 31 / 31, 27 / 31 and 28 / 30, 4 Mi 46 / 49, 49 / 50 and
+// 50 / 43, 8 Mi 68 / 71, 70 / 71 and 67 / 61, 32 Mi 192 / 187, 223 / 191 and 197 / 152.  8 bf16 tensors, 30 and 90 % evenly spread, 30 % behind
+// zeros: 8 Mi 40 / 49, 50 / 54 and 42 / 50, 12 Mi 58 / 62, 69 / 68 and 59 / 60, 14 Mi 70 / 72, 85 / 78 and 66 / 59, 16 Mi 76 / 73, 91 / 80 and 76 / 71.  Sorted
+// values: within a tenth either way at these limits.
+constexpr int64_t WIDE_MIN_F32 = 28 << 20, WIDE_MIN_F32_ONE = 5 << 20, WIDE_MIN_16 = 13 << 20;
 constexpr double SPEC_MIN_EXPECTED = 32.0; // ... nor are keep counts that leave fewer than this many kept elements in the largest sample
 constexpr double SPEC_GOOD_EXPECTED = 96.0; // a smaller sample will do when it still expects this many (fp32)
 constexpr double SPEC_GOOD_EXPECTED_16 = 64.0; // 16-bit types: their sample costs twice the instructions per dword, and the wider window
@@ -3527,13 +3536,12 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     auto speculates = [&](int32_t s, uint32_t *ranks, uint32_t *batches) {
         return speculation_ranks(n_select(s), kept_whole(s) ? 0 : k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, ranks, batches);
     };
-    // Tensors whose chunks have no lists, mostly, and are placed from the input: a launch in which they hold the majority of the elements takes
-    // the list kernels' wide form, one workgroup per chunk.  With parts of 8 K entries and the plain form, us: four tensors of
-    // 8.4 M at 26, 50 and 90 % kept: bf16 149 / 161 / 173 -> 121 / 126 / 131, fp32 167 / 196 / 230 -> 180 / 189 / 199; 25 M fp32
-    // 140 / 151 / 178 -> 145 / 147 / 150.
+    // Tensors whose chunks have no lists, mostly, and are placed from the input.  A large enough launch in which they hold the majority
+    // of the elements takes the list kernels' wide form, one workgroup per chunk (see WIDE_MIN_F32).
     auto listless = [&](int32_t s) { return !kept_whole(s) && k[s] > n[s] / (dt == ADATOPK_F32 ? 2 : LIST_DIV); };
     // One launch of the kernels for the tensors `which[0 .. count)` of the call.
     auto select_group = [&](const int32_t *which, int32_t count, bool may_speculate) -> adatopk_status {
+        const int64_t wide_min = dt != ADATOPK_F32 ? WIDE_MIN_16 : (count == 1 ? WIDE_MIN_F32_ONE : WIDE_MIN_F32);
         Launch a{};
         a.S = count;
         // Chunk sizes of this launch: at most chunk_target() chunks in all, so that all workgroups are
@@ -3580,7 +3588,8 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.err_out = err_out ? err_out + which[0] : nullptr;  // (the slot in a tensor's flags counts from there)
         int32_t chunks = 0;
         int64_t list_tiles = 0;
-        const bool no_lists = nspec == 0 && 2 * n_dense > n_batch;  // (decided once: the cut into parts and the kernels' form go together)  // (decided once: the cut into parts and the kernels' form go together)
+        // (decided once: the cut into parts and the kernels' form go together)
+        const bool no_lists = nspec == 0 && 2 * n_dense > n_batch && n_batch >= wide_min;
         uint32_t parts = 0;
         for (int32_t i = 0; i < a.S; ++i) {
             SegDesc &d = a.seg[i];

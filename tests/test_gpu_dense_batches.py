@@ -30,7 +30,8 @@ def compress(xs, ks):
     B.adatopk_compress_segmented(ds, ks, idx, val, off, err, ws)
     torch.cuda.synchronize()
     at = B.measure_workspace_offset(B.MEASURE_PART_COUNTS, n_total, len(xs), ds[0].dtype)
-    parts = int((ws[at:at + 4 * 8 * 512].view(torch.int32) != -1).sum()) if ds[0].dtype == torch.float32 else 0
+    room = 8 * 512 if len(xs) > 1 else 4 * 256  # most parts per chunk, most chunks
+    parts = int((ws[at:at + 4 * room].view(torch.int32) != -1).sum()) if ds[0].dtype == torch.float32 else 0
     return H.to_host(idx), H.to_host(val), off, H.to_host(err), parts
 
 
@@ -52,3 +53,15 @@ def test_dense_tensors_beside_speculating_ones_are_cut_into_parts():
     lens, shares = [8_400_003, 6_000_001, 3_000_000], [0.01, 0.6, 0.9]
     xs = [wl.small_case("normal", n, seed=200 + i) for i, n in enumerate(lens)]
     assert check(xs, [int(n * f) for n, f in zip(lens, shares)])[0] > 512
+
+
+@pytest.mark.parametrize("dtype,tensors,n,keep", [("f32", 8, 1 << 20, 0.7), ("f32", 1, 4 << 20, 0.8), ("f32", 2, (14 << 20) - 8, 0.6),
+                                                  ("f32", 2, 14 << 20, 0.6), ("f32", 1, (5 << 20) - 1, 0.9), ("f32", 1, 5 << 20, 0.9),
+                                                  ("bf16", 1, 13 << 20, 0.3), ("bf16", 2, 13 << 19, 0.3), ("f16", 2, (13 << 19) - 4, 0.5)])
+def test_one_part_per_chunk_only_from_a_total_length_on(dtype, tensors, n, keep):
+    # either side of the lines between the list kernels' two forms; one workgroup per chunk where the wide one runs, several below
+    xs = [wl.small_case("normal", n, seed=230 + i, dtype=dtype) for i in range(tensors)]
+    written = check(xs, [int(n * keep)] * tensors)[0]
+    chunks = 512 if tensors > 1 else 256
+    if dtype == "f32":
+        assert (written <= chunks) == (n * tensors >= (28 if tensors > 1 else 5) << 20), written
