@@ -65,3 +65,13 @@ def test_one_part_per_chunk_only_from_a_total_length_on(dtype, tensors, n, keep)
     chunks = 512 if tensors > 1 else 256
     if dtype == "f32":
         assert (written <= chunks) == (n * tensors >= (28 if tensors > 1 else 5) << 20), written
+
+
+@pytest.mark.parametrize("tensors,n,keep,tiles,parts", [(2, 10 << 20, 0.7, 5, 4), (8, 3 << 19, 0.55, 3, 2), (4, 2 << 20, 0.9, 2, 2)])
+def test_parts_of_chunks_without_lists_have_a_tile_each(tensors, n, keep, tiles, parts):
+    # (with eight parts to chunks of five tiles, and four to chunks of three or two, the last ones have nothing to do or half a tile)
+    xs = [wl.small_case("normal", n, seed=220 + i) for i in range(tensors)]
+    chunks = -(-n // (tiles * 8192))
+    last = n - (chunks - 1) * tiles * 8192  # elements of the last chunk; parts are multiples of 2048 elements
+    written = check(xs, [int(n * keep)] * tensors)[0]
+    assert written <= tensors * chunks * parts and written >= tensors * ((chunks - 1) * parts + min(parts, -(-last // 8192))), written
