@@ -112,9 +112,6 @@ constexpr int CTARGET_ONE = 256;
 // 192 K 24.5 / 25.9, 22.6 / 26.1 and 22.3 / 25.3, 384 K 24.0 / 25.3, 22.6 / 25.4 and 22.4 / 26.1, 1 M 24.2 / 26.3,
 // 23.2 / 26.8 and 23.2 / 27.4; bf16 16 K 15.8 / 16.6, 14.8 / 16.9 and 15.6 / 17.2, 1 M 16.8 / 19.1, 16.1 / 19.4 and 16.6 / 19.7.
 constexpr int64_t SPEC_MIN_N_F32 = 3 << 16, SPEC_MIN_N_16 = 1 << 14;
-// (fp32 from 960 K to 1 M - 1 takes the exact passes all the same, 3 us slower: the check that every kernel of that path can be
-// timed, tests/test_gpu_graph_and_streams.py, makes a call of 1000003 values)
-constexpr int64_t SPEC_NOT_FROM_F32 = 15 << 16, SPEC_AGAIN_FROM_F32 = 1 << 20;
 // ... and elements of a launch of several tensors that could speculate, below which none of them does: there the speculative scan
 // saves a read and costs a launch with a sample, and the two exact passes are launched all the same.  Compress of four
 // tensors, us, speculative / exact, at 1 and 10 % kept: fp32 4 Mi in all 33.9 / 32.4 and 34.2 / 33.2, 8 Mi 35.5 / 36.9 and 39.8 / 39.4,
@@ -3444,9 +3441,7 @@ struct OutSpec {
 // of 25 M elements at k = 10 %).  The sample is the smallest of a quarter, half or all of
 // SAMPLE_ELEMS that expects SPEC_GOOD_EXPECTED kept elements, and the largest otherwise.
 bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
-    if (n < (dt == ADATOPK_F32 ? SPEC_MIN_N_F32 : SPEC_MIN_N_16) ||
-        (dt == ADATOPK_F32 && n >= SPEC_NOT_FROM_F32 && n < SPEC_AGAIN_FROM_F32))
-        return false;
+    if (n < (dt == ADATOPK_F32 ? SPEC_MIN_N_F32 : SPEC_MIN_N_16)) return false;
     if (!aligned16 || k <= 0 || k > n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
     const int epd = 4 / elem_size(dt);
     const int max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;

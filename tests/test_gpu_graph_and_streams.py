@@ -201,7 +201,7 @@ def test_measurement_hooks_do_what_the_benchmark_assumes():
     torch.cuda.synchronize()
     assert bool((dst[:1000] == 0).all()) and float(dst[1000]) == float(src[1000])
 
-    k = 10_000
+    k = 250_000  # a quarter: the exact passes by rule
     idx = torch.empty(k, dtype=torch.int32, device="cuda")
     val = torch.empty(k, device="cuda")
     ws = B.new_workspace(n, 1, torch.float32)
@@ -212,7 +212,7 @@ def test_measurement_hooks_do_what_the_benchmark_assumes():
     for name in ("k_hist1", "k_scan", "k_refine", "k_emit"):
         assert 0.0 < ms[name] < 5.0, (name, ms[name])  # milliseconds; each of these kernels takes microseconds here
     assert ms["k_merge"] < 0 and ms["k_small"] < 0  # not launched by this call
-    assert ms["k_scan_spec"] < 0  # a tensor of a million elements and a bit is not worth a speculative pass
+    assert ms["k_scan_spec"] < 0  # more than 21 % kept: no speculative pass
 
 
 def test_graph_capture_of_wire_and_segmented_calls():
