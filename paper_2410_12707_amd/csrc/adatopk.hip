@@ -1242,7 +1242,8 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     for (int j = 0; j < PER; ++j) own += cnt[j];
     uint32_t total;
     const uint32_t inc = block_incl_scan(own, sm, &total);
-    uint32_t above = total - inc;  // sampled (and counted) keys in the bins of the threads after this one
+    const uint32_t above_mine = total - inc;
+    uint32_t above = above_mine;  // sampled (and counted) keys in the bins of the threads after this one
     // (r_hi = 0: no bin holds it)
     if ((above < r_lo && above + own >= r_lo) || (above < r_hi && above + own >= r_hi)) {  // two threads of the workgroup
 #pragma unroll
@@ -1257,6 +1258,26 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     const uint32_t b_lo = __builtin_amdgcn_readfirstlane(s_pick[0]), b_hi = __builtin_amdgcn_readfirstlane(s_pick[1]);
     lo = b_lo < NSB ? b_lo << SAMPLE_SH : 0u;
     const uint32_t hi = b_hi < NSB ? (b_hi + 1u) << SAMPLE_SH : 0x80000000u;  // first key above the bracket
+    // fp32: a bracket wider than a window can span (keys that are thin around the k-th: a tensor that is mostly zeros, heavy tails at
+    // a small keep share).  The window then lies around the key at the expected rank; from the bracket's lower end up it ended
+    // below the k-th key, and tensors of 97 % zeros at 1 % kept missed in nine calls of ten, now in two.  (Not when the lower rank
+    // is a zero: then the k-th key may be one, too.  All keys of the branch are uniform.)
+    constexpr uint32_t SPAN = (NBW - 1) << BITS3;
+    if (VEC == TAG_F32 && b_lo < NSB && hi > lo && hi - lo > SPAN) {
+        const uint32_t rank = (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie SPEC_SIGMAS_LOW and SPEC_SIGMAS from it)
+        above = above_mine;
+        if (above < rank && above + own >= rank) {  // one thread: the rank is between the two that have been found
+#pragma unroll
+            for (int j = PER - 1; j >= 0; --j) {
+                const uint32_t with = above + cnt[j];
+                if (above < rank && with >= rank) s_pick[2] = threadIdx.x * PER + j;
+                above = with;
+            }
+        }
+        __syncthreads();
+        const uint32_t middle = (static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(s_pick[2])) << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
+        if (middle > lo + SPAN / 2) lo = middle - SPAN / 2;
+    }
     // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow, the least shift that makes NBW - 1 bins
     // span it.  16-bit types: a bin is one pattern (their keys have 16 zero bits below it), 2047 patterns upwards of lo, no last digit.
     const uint32_t width = hi > lo ? hi - lo : 1u;

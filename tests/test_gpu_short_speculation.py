@@ -18,3 +18,21 @@ def test_every_length_from_the_limit_on_speculates(dtype, n):
     c.run()
     assert c.held() == 1
     c.check(x)
+
+
+def holds(xs, k):
+    """How many of the calls find their window held; every result is checked."""
+    held = 0
+    for x in xs:
+        c = Call(x, k)
+        c.run()
+        held += c.held()
+        c.check(x)
+    return held
+
+
+@pytest.mark.parametrize("n,keep", [(200_000, 0.01), (393_216, 0.01), (900_001, 0.01), (1_300_000, 0.01)])
+def test_windows_hold_where_keys_are_thin(n, keep):
+    # 97 % zeros, a third of the others kept: the sample's bracket is wider than a window of fp32 keys can span
+    xs = [wl.small_case("sparse", n, seed=500 + i) for i in range(8)]
+    assert holds(xs, int(n * keep)) >= 5
