@@ -108,9 +108,10 @@ constexpr int CTARGET = 512;          // chunks of a launch of several tensors, 
 // sum; a batch of tensors with unequal keep counts wants the finer split, whose workgroups even out.
 constexpr int CTARGET_ONE = 256;
 // Tensors below this are not worth a speculative pass, even with a launch to themselves: one kernel less than the exact passes,
-// against the sample.  Compress alone, us, speculative / exact, at 0.2, 1 and 10 % kept: fp32 128 K 22.9 / 22.5, 21.6 / 22.9 and 22.9 / 23.6,
-// 192 K 24.5 / 25.9, 22.6 / 26.1 and 22.3 / 25.3, 384 K 24.0 / 25.3, 22.6 / 25.4 and 22.4 / 26.1, 1 M 24.2 / 26.3,
-// 23.2 / 26.8 and 23.2 / 27.4; bf16 16 K 15.8 / 16.6, 14.8 / 16.9 and 15.6 / 17.2, 1 M 16.8 / 19.1, 16.1 / 19.4 and 16.6 / 19.7.
+// against the sample, and both passes behind waits if the window misses.  Compress, us, held / exact passes / missed, at 1 % kept: fp32
+// 192 K 19.3 / 21.3 / 33 to 36 (128 K, an earlier version of the kernels: 21.6 / 22.9), 384 K 19.3 / 21.6 / 35 to 38, 768 K 19.7 / 22.4 / 37 to 40; bf16 16 K
+// 12.7 / 14.8, 128 K 13.5 / 15.7 / 28, 768 K 14.8 / 16.9 / 33; f16 16 K 12.4 / 14.8 / 26, 768 K 14.2 / 16.8 / 32 to 37.  So it pays while fewer than one
+// call in six misses: see SAMPLE_FINE_BELOW for how often windows hold.
 constexpr int64_t SPEC_MIN_N_F32 = 3 << 16, SPEC_MIN_N_16 = 1 << 14;
 // ... and elements of a launch of several tensors that could speculate, below which none of them does: there the speculative scan
 // saves a read and costs a launch with a sample, and the two exact passes are launched all the same.  Compress of four
@@ -1126,6 +1127,13 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
 // The bins holding the two ranks are found while the suffix sums are formed in registers.
 constexpr int SCAN_SMEM_WORDS = 2 * STAGE_CAP + NBW;  // k_scan's stage and window histogram; its prologue's scratch fits inside
 constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by up to this many run lengths
+// A sample of runs of 1 KB sees one row, channel or plane 256 times over and others not at all, and a window that misses costs a short
+// tensor four times what one that holds saves (SPEC_MIN_N_F32).  Below this length a run is spread over all that lies
+// between it and the next.  fp32 tensors of 192 K to 1 Mi, keep shares of 0.2, 1, 3, 10 and 20 %, windows held of 40, 1 KB runs / spread: a
+// scale exp(N(0, 0.5^2)) for each plane of 3136 values 30 34 20 25 32 / all, a tenth of the rows of 768 not zero
+// 38 17 9 11 38 / 40 40 34 23 40 (10 % is where the zeros begin), evenly spread values all.  Longer tensors as they were: 128-byte lines
+// for 64 bytes, 0.4 us for 4.9 M values, 1.5 for 25 M.
+constexpr int32_t SAMPLE_FINE_BELOW = 1 << 20;
 constexpr int SAMPLE_BATCH = 16;  // dword loads per thread and batch; the host picks 1, 2 or 4 batches (fp32: 8192 elements each)
 // Byte offset of the sample bin (4 * (key >> SAMPLE_SH)) of element hh of a dword.
 template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword, int hh) {
@@ -1147,10 +1155,14 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     constexpr int QUADS = SAMPLE_BATCH / 4;
     const int run_shift = __builtin_ctz(QUADS * NW) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
     const uint64_t nruns = (static_cast<uint64_t>(sg.n) / EPD) / 256;
-    // (the runs' offsets stay within what lies between two of them: short tensors, of which a good part is sampled)
-    const uint32_t apart = static_cast<uint32_t>(nruns >> run_shift);
-    const uint32_t skew = apart >= SAMPLE_SKEW ? SAMPLE_SKEW : (apart >= 1 ? 1u << (31 - __builtin_clz(apart)) : 1u);
-    const dword4 *x = static_cast<const dword4 *>(sg.x) + lane;
+    const bool fine = sg.n < SAMPLE_FINE_BELOW;  // uniform: a run's sixteen 64-byte pieces lie `spread` pieces apart
+    const uint32_t skew = fine ? 1u : SAMPLE_SKEW;
+    // (An odd number, and the runs are shifted by less than that many pieces: activations repeat their channels at even distances.  Run r
+    // begins at most at run nruns - 1 - (nruns - 1 >> run_shift), and with its shift it is at most as long as what follows there.)
+    const uint32_t between = static_cast<uint32_t>((nruns - 1) >> run_shift);
+    const uint32_t spread = fine && between > 1 ? (between - 1) | 1u : 1u;
+    const uint32_t shift_mask = fine ? (1u << (31 - __builtin_clz(spread))) - 1u : SAMPLE_SKEW - 1u, shift_by = fine ? 4u : 64u;
+    const dword4 *x = static_cast<const dword4 *>(sg.x) + (static_cast<uint32_t>(lane) / 4) * 4 * spread + (static_cast<uint32_t>(lane) & 3u);
     uint32_t v[MAXB][SAMPLE_BATCH];
 #pragma unroll
     for (int b = 0; b < MAXB; ++b)
@@ -1160,8 +1172,8 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                 // evenly spaced, plus a small run-dependent offset: an even spacing alone can put every
                 // run on the same memory channel
                 const uint32_t r = static_cast<uint32_t>(b * QUADS + j) * NW + w;
-                const uint64_t run = ((static_cast<uint64_t>(r) * (nruns - skew)) >> run_shift) + ((r * 37u) & (skew - 1));
-                const dword4 q = x[run * 64];
+                const uint64_t run = (static_cast<uint64_t>(r) * (nruns - skew)) >> run_shift;
+                const dword4 q = x[run * 64 + ((r * 37u) & shift_mask) * shift_by];
                 v[b][4 * j] = q.x;
                 v[b][4 * j + 1] = q.y;
                 v[b][4 * j + 2] = q.z;

@@ -360,20 +360,27 @@ def test_error_norm_is_optional(n):
     assert se is None and np.array_equal(si, qi) and np.array_equal(H.bits(sv), H.bits(qv))
 
 
-def _sampled_elements(n, esize):
+def _sampled_elements(n, esize, batches=None):
     """Element indices that the speculative scan may look at before it reads the tensor: runs of 1 KB,
-    evenly spaced with a small run-dependent shift, for each of its sample sizes (mirrors the kernel's
+    evenly spaced with a small run-dependent shift (below 2^20 elements in pieces of 64 bytes that are spread over
+    the space between two runs), for each of its sample sizes or the one given (mirrors the kernel's
     sampling on purpose: the test below plants values exactly there)."""
-    dwords = n * esize // 4
-    nruns = dwords // 256
+    nruns = n * esize // 4 // 256
+    fine = n < 1 << 20
+    skew = 1 if fine else 32
+    per16 = 16 // esize  # elements of one lane's load
+    lane = np.arange(64)
     idx = []
-    for nbatch in ((1, 2, 4) if esize == 4 else (1, 2)):
+    for nbatch in ([batches] if batches else (1, 2, 4) if esize == 4 else (1, 2)):
         runs = nbatch * 4 * 8
         shift = runs.bit_length() - 1
+        between = (nruns - 1) >> shift
+        spread = (between - 1) | 1 if fine and between > 1 else 1
+        mask, by = ((1 << (spread.bit_length() - 1)) - 1, 4) if fine else (31, 64)
         for r in range(runs):
-            run = ((r * (nruns - 32)) >> shift) + (r * 37) % 32
-            first = run * 1024 // esize
-            idx.append(np.arange(first, first + 1024 // esize))
+            at = ((r * (nruns - skew)) >> shift) * 64 + ((r * 37) & mask) * by + lane // 4 * 4 * spread + lane % 4
+            assert at.max() < nruns * 64
+            idx.append((at[:, None] * per16 + np.arange(per16)).ravel())
     return np.unique(np.concatenate(idx))
 
 
