@@ -114,11 +114,15 @@ constexpr int CTARGET_ONE = 256;
 // call in six misses: see SAMPLE_FINE_BELOW for how often windows hold.
 constexpr int64_t SPEC_MIN_N_F32 = 3 << 16, SPEC_MIN_N_16 = 1 << 14;
 // ... and elements of a launch of several tensors that could speculate, below which none of them does: there the speculative scan
-// saves a read and costs a launch with a sample, and the two exact passes are launched all the same.  Compress of four
-// tensors, us, speculative / exact, at 1 and 10 % kept: fp32 4 Mi in all 33.9 / 32.4 and 34.2 / 33.2, 8 Mi 35.5 / 36.9 and 39.8 / 39.4,
-// 16 Mi 39.6 / 46.9 and 47.5 / 54.6; bf16 4 Mi 25.0 / 23.6 and 26.6 / 24.5, 8 Mi 26.8 / 26.5 and 30.3 / 28.6, 16 Mi 30.6 / 33.4 and
-// 36.5 / 39.0.
-constexpr int64_t SPEC_MIN_BATCH = 8 << 20;
+// saves a read and costs a launch with a sample, and the two exact passes are launched all the same.  Where other tensors of the launch
+// need those passes, the scan of the speculating ones is a round of its own with part of the chip idle, so these have to be the larger part:
+// SPEC_MIN_SHARE times the others.  Compress, us, speculative / exact, four tensors at 1 and 10 % kept, in all: fp32 4 Mi 29.6 / 27.6 and
+// 30.5 / 30.0, 6 Mi 30.9 / 31.8 and 35.6 / 36.9, 8.5 Mi 32.6 / 34.6 and 37.9 / 40.9, 16 Mi 36.5 / 41.8 and 44.3 / 51.7; bf16 4 Mi 22.4 / 21.4 and
+// 25.3 / 23.0, 8.5 Mi 26.0 / 27.5 and 31.0 / 31.5, 16 Mi 28.6 / 32.2 and 35.0 / 37.6.  Beside them, 1 % kept: fp32 and four of 40 K values, 8.5 Mi 39.7 /
+// 34.5, 16 Mi 45.0 / 43.9, 24 Mi 50.0 / 53.2; and 5 Mi at 30 %, 8.5 Mi 73.4 / 62.5, 16 Mi 75.0 / 75.0, 24 Mi 79.7 / 88.0; and 10 Mi at 30 %,
+// 16 Mi 100.8 / 86.4, 20 Mi 95.2 / 92.1, 32 Mi 103.9 / 116.2; bf16 and four of 40 K, 8.5 Mi 25.8 / 27.9; and 5 Mi at 30 %, 12 Mi 57.8 / 55.4,
+// 20 Mi 65.8 / 76.8; and 10 Mi, 16 Mi 95.9 / 87.9, 24 Mi 99.8 / 103.7.
+constexpr int64_t SPEC_MIN_BATCH = 8 << 20, SPEC_MIN_SHARE = 2;
 // Elements of a launch of tensors without lists from which the list kernels' wide form with one workgroup per chunk is the faster one.  Its
 // registers leave room for one workgroup per compute unit, so more than 256 chunks are two rounds; the plain form shares the units
 // among several, but waits for memory 8 KB at a time.  Compress, us, plain / wide, 55 and 90 % kept evenly spread, 90 % behind
@@ -3714,7 +3718,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             if (rc == ADATOPK_OK) rc = select_group(exact, nexact, false);
         } else {
             for (int32_t i = 0; i < count; ++i) order[i] = s0 + i;
-            rc = select_group(order, count, count == 1 || n_spec >= SPEC_MIN_BATCH);
+            rc = select_group(order, count, count == 1 || (n_spec >= SPEC_MIN_BATCH && n_spec >= SPEC_MIN_SHARE * n_exact));
         }
         if (rc != ADATOPK_OK) return rc;
     }

@@ -1,9 +1,12 @@
 """Batches with tensors that keep so much that their chunks have no lists and are placed from the input: the results against the
-oracle, and into how many parts the chunks were cut."""
+oracle, as pairs and as wire messages, and into how many parts the chunks were cut."""
+import struct
+
 import numpy as np
 import pytest
 
 from oracle import adatopk_oracle as orc
+from oracle import wire_format as wf
 from paper_2410_12707_amd import workloads as wl
 from test_gpu_parity import ERR_RTOL, check_segmented_decompress
 
@@ -47,7 +50,7 @@ def check(xs, ks):
     return parts, refs
 
 
-def test_dense_tensors_beside_speculating_ones_are_cut_into_parts():
+def test_dense_tensors_beside_sparse_ones_are_cut_into_parts():
     # too few elements of either kind for launches of their own: the dense tensors' chunks go through the entry loop of the plain
     # kernels, with several workgroups to a chunk
     lens, shares = [8_400_003, 6_000_001, 3_000_000], [0.01, 0.6, 0.9]
@@ -75,3 +78,55 @@ def test_parts_of_chunks_without_lists_have_a_tile_each(tensors, n, keep, tiles,
     last = n - (chunks - 1) * tiles * 8192  # elements of the last chunk; parts are multiples of 2048 elements
     written = check(xs, [int(n * keep)] * tensors)[0]
     assert written <= tensors * chunks * parts and written >= tensors * ((chunks - 1) * parts + min(parts, -(-last // 8192))), written
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sparse,dense,held", [(9 << 20, 0, 1), (9 << 20, 4_000_003, 1), (9 << 20, 5_000_001, 0), (8 << 20, 70_001, 1),
+                                               ((8 << 20) - 8, 70_001, 0)])
+def test_a_batch_speculates_where_most_of_it_can(dtype, sparse, dense, held):
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    lens, shares = [sparse // 2, dense, sparse // 2], [0.01, 0.3, 0.02]
+    xs = [wl.small_case("normal", n, seed=240 + i, dtype=dtype) for i, n in enumerate(lens)]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    check(xs, ks)
+    ds = [H.to_device(x) for x in xs]
+    off = [0, ks[0], ks[0] + ks[1], sum(ks)]
+    ws = B.new_workspace(sum(lens), 3, ds[0].dtype)
+    B.adatopk_compress_segmented(ds, ks, torch.empty(off[3], dtype=torch.int32, device="cuda"),
+                                 torch.empty(off[3], dtype=ds[0].dtype, device="cuda"), off, None, ws)
+    torch.cuda.synchronize()
+    state = ws[:192].view(torch.int32).cpu()  # a record of 64 bytes per tensor, its seventh word the verdict
+    assert state[6] == held and state[32 + 6] == held
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_chunks_of_many_tiles_without_lists(dtype):
+    # more than 256 chunks of five tiles and more, and no workgroups for the error norms alone; ragged, and with a sparse and an empty
+    # tensor between them; as pairs and as wire messages
+    import torch
+
+    import gpu_harness as H
+    from paper_2410_12707_amd import binding as B
+
+    lens, shares = [9_000_011, 0, 11_000_003, 50_000, 10_000_001], [0.55, 0.0, 0.95, 0.02, 0.8]
+    xs = [wl.small_case("normal", n, seed=210 + i, dtype=dtype) for i, n in enumerate(lens)]
+    ks = [int(n * f) for n, f in zip(lens, shares)]
+    refs = check(xs, ks)[1]
+    ds = [H.to_device(x) for x in xs]
+    at, pos = [], 0
+    for k in ks:
+        at.append(pos)
+        pos += (wf.message_bytes(k, xs[0].dtype, 4) + 15) // 16 * 16
+    wire = torch.zeros(pos, dtype=torch.uint8, device="cuda")
+    B.adatopk_compress_wire_segmented(ds, ks, 4, None, wire, at, B.new_workspace(sum(lens), len(lens), ds[0].dtype))
+    torch.cuda.synchronize()
+    raw = wire.cpu().numpy().tobytes()
+    for s, (k, (ri, rv, re)) in enumerate(zip(ks, refs)):
+        ref = wf.pack(ri, rv, lens[s], float(re), lens[s] / k if k else 0.0, 4)
+        got = raw[at[s]:at[s] + len(ref)]
+        assert got[:12] == ref[:12] and got[16:] == ref[16:], s
+        assert H.same_err(struct.unpack("<f", got[12:16])[0], re, ERR_RTOL), s
