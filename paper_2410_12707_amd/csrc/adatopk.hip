@@ -33,8 +33,9 @@
 //   k_emit    prologue: G3 -> threshold key T and tie quota q (16-bit types: a window bin is one
 //             pattern, so T comes from the window rows and k_refine is not launched); output
 //             offsets from the rows of the earlier chunks.  Stable compaction into idx_out /
-//             val_out (key > T, plus the first q keys equal to T).  The tensor's last workgroup
-//             adds up the error norm from the partial sums the earlier kernels stored, in a fixed order
+//             val_out (key > T, plus the first q keys equal to T).  A workgroup of its own
+//             (the tensor's last one where every compute unit has one already) adds up the error norm from the partial sums the
+//             earlier kernels stored, in a fixed order
 // Cross-block order comes from counts that an EARLIER kernel stored and that every block
 // of the next kernel scans for itself: no block waits for another block (k_judge's exact passes aside, whose
 // waits end whatever workgroups are running), no block needs a release fence (on this chip an agent-scope fence writes back the L2 of its
@@ -146,7 +147,7 @@ constexpr size_t MERGE_SMALL_BYTES = static_cast<size_t>(32) << 20;
 constexpr size_t MERGE_MIN_SPAN = 16384;   // bytes; smaller outputs use fewer workgroups
 constexpr size_t MERGE_MAX_SPAN = 98304;   // bytes; larger outputs use more workgroups
 static_assert(NB1 % BLOCK == 0 && NBW % BLOCK == 0 && NB3 % BLOCK == 0 && NSB % BLOCK == 0, "bins split evenly over threads");
-static_assert(CTARGET <= BLOCK, "k_emit scans the chunks of a segment with one thread each");
+static_assert(CTARGET <= BLOCK, "the error norm of 16-bit types asks for a chunk's sum with one thread each");
 static_assert(BLOCK % 64 == 0, "whole wavefronts");
 static_assert(TILE % (LIST_DIV * BLOCK * LU) == 0, "a chunk's list capacity is whole list tiles");
 
@@ -1624,7 +1625,8 @@ template <int VEC> __device__ __forceinline__ void load_raw(const ChunkSource<VE
 // constant tensor), and far less when only a few are (sorted data: the chunks at one end).  With one
 // workgroup per compute unit nothing else hides the round trips.  The list kernels therefore come
 // in two forms.  WIDE, for a launch with one workgroup per chunk and at most one per compute unit
-// (a single tensor, lists of one part): a part from the input is read as tiles of U 16-byte loads
+// (a single tensor, lists of one part), and for long launches of tensors without lists, up to 512 chunks of many tiles
+// (WIDE_MIN_F32): a part from the input is read as tiles of U 16-byte loads
 // per thread (thread t takes the t-th, (BLOCK + t)-th ... 16 bytes of the tile) with the next tiles'
 // loads in flight; what is left after the last whole tile goes through the entry loop.  Needs the
 // part to start on a 16-byte boundary (chunks are whole tiles, so this is the alignment of the

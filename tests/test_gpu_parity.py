@@ -465,13 +465,22 @@ def test_misled_samples_on_several_streams_at_once(n, k, scale, dtype):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_midsize_tensors_value_structures_and_boundaries(dtype):
-    # between the one-launch path for small tensors and the sizes at which a sample of the tensor is taken
-    # first (2^20 elements): the exact two-pass select with tens to hundreds of chunks, around powers of two,
-    # with value structures whose candidate lists overflow (constant, few levels), keep counts of 0 and 1
+    # tens to hundreds of chunks, around powers of two, with value structures whose candidate lists overflow (constant,
+    # few levels), keep counts of 0 and 1: the exact two-pass select for fp32 below 192 K and 16-bit types at the smallest keep counts,
+    # the sample and the kernel that judges it otherwise (all of them through the exact select: the next test)
     for n, k in ((65_535, 600), (65_536, 655), (65_537, 1), (300_000, 6144), (300_000, 6145), (1_048_575, 6000),
                  (1_048_576, 6000), (1_048_577, 6000), (524_288, 0), (200_001, 2000)):
         for kind in ("normal", "few_levels", "all_equal", "sparse", "descending", "nonfinite"):
             check_one(wl.small_case(kind, n, seed=n % 1000 + k, dtype=dtype), k, label="%s %s n=%d k=%d" % (kind, dtype, n, k))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_midsize_tensors_off_the_16_byte_grid(dtype):
+    # nothing is sampled there: the exact two-pass select, at the lengths and for the value structures of the test above
+    for n, k in ((65_537, 655), (200_001, 2000), (300_000, 6144), (524_288, 0), (1_048_575, 6000), (1_048_577, 200_000)):
+        for kind in ("normal", "few_levels", "all_equal", "sparse", "descending", "nonfinite"):
+            check_one(wl.small_case(kind, n, seed=n % 1000 + k, dtype=dtype), k, offset_elems=2 if dtype == "f32" else 4,
+                      label="%s %s n=%d k=%d" % (kind, dtype, n, k))
 
 
 def test_midsize_tensors_in_one_segmented_call():
@@ -581,7 +590,7 @@ def test_decompress_of_as_many_tensors_as_a_launch_holds_and_one_more(tensors):
 @pytest.mark.parametrize("scale", [1, 2])
 def test_tensors_of_one_launch_have_chunks_of_their_own_length(dtype, scale):
     # unequal keep shares and lengths: chunks of dense tensors and of those that need the exact passes are shorter; with
-    # scale 1 none speculates (less than 8 Mi elements could), with 2 four of the seven do
+    # scale 1 none speculates (less than 8 Mi elements could), with 2 three of the seven fp32 tensors do and four of the 16-bit ones
     import gpu_harness as H
 
     lens = [n * scale for n in (1_000_003, 35_000, 2_600_000, 0, 1_700_001, 4_500, 750_000)]
