@@ -317,27 +317,40 @@ __device__ __forceinline__ void write_header(void *messages, int64_t idx_at, int
 }
 
 // Streaming layout of the two full-input kernels.  A tile is TILE consecutive elements; wave w
-// of the workgroup owns the w-th contiguous 1/NW of it and reads it as SLOTS dword loads of
-// 64 consecutive dwords each (256 contiguous bytes per wave-level load).  Index order inside
-// a wave is therefore: slot, then lane, then half-word - which makes the lane mask of a
-// per-slot compare a bitmap in index order.
-template <int VEC> struct Stream {
+// of the workgroup owns the w-th contiguous 1/NW of it and reads it as GROUPS loads, one after the other, of GE consecutive
+// elements per lane (fp32: 16 bytes, 16-bit types: 8).  Index order inside a wave is therefore: group, then lane, then
+// element.  The candidates of a group are ranked and stored together while no lane holds two of them; with
+// one element per lane and load, those of each of the 16 were (25 M fp32 at 1 % kept 60.4 -> 59.5 us per compress and decompress, 24 tensors of
+// 8.4 M 395.5 -> 391.4).
+template <int VEC, int NT = BLOCK> struct Stream {
+    static constexpr int EL = TILE / NT;       // elements per thread per tile
     static constexpr int EPD = VEC / 4;        // elements per dword
-    static constexpr int SLOTS = EPT / EPD;    // dword loads per thread per tile
-    // first element of (wave, slot, lane) in the tile that starts at element t0
-    static __device__ __forceinline__ int64_t first_elem(int64_t t0, int slot) {
+    static constexpr int SLOTS = EL / EPD;     // dwords per thread per tile
+    static constexpr int GE = 4;               // elements per lane and load
+    static constexpr int GROUPS = EL / GE;     // loads per thread per tile
+    static constexpr int GD = GE / EPD;        // dwords per load
+    // (a vector type for loads at any dword: the tensor's base need not lie on the 16-byte grid)
+    typedef uint32_t Group __attribute__((ext_vector_type(GD), aligned(4)));
+    // first element of (wave, group, lane) in the tile that starts at element t0
+    static __device__ __forceinline__ int64_t first_elem(int64_t t0, int group) {
         const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        return t0 + (static_cast<int64_t>(w * SLOTS + slot) * 64 + lane) * EPD;
+        return t0 + (static_cast<int64_t>(w * GROUPS + group) * 64 + lane) * GE;
     }
-    // whole tile in range, base 4-byte aligned: dword loads, nontemporal.  The input is streamed
+    // element e of group j, as the raw pattern of one element
+    static __device__ __forceinline__ uint32_t elem(const uint32_t (&dw)[SLOTS], int j, int e) { return elem_of<VEC>(dw[j * GD + e / EPD], e % EPD); }
+    // whole tile in range, base 4-byte aligned: nontemporal loads.  The input is streamed
     // through twice and is as large as the caches or larger; loaded nontemporally it does not
     // displace what the call does reuse (the per-chunk rows, the candidate list) nor the output of
     // the previous call that is still draining to memory (measured: 83.7 -> 76.6 us per step on
     // the 100 MB tensor, 636 -> 554 us on the 805 MB batch).
     static __device__ __forceinline__ void load_fast(const void *x, int64_t t0, uint32_t (&dw)[SLOTS]) {
-        const uint32_t *p = static_cast<const uint32_t *>(x) + first_elem(t0, 0) / EPD;
+        const Group *p = reinterpret_cast<const Group *>(static_cast<const uint32_t *>(x) + first_elem(t0, 0) / EPD);
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) dw[e] = __builtin_nontemporal_load(p + e * 64);
+        for (int j = 0; j < GROUPS; ++j) {
+            const Group v = __builtin_nontemporal_load(p + j * 64);
+#pragma unroll
+            for (int d = 0; d < GD; ++d) dw[j * GD + d] = v[d];
+        }
     }
     // The same tile with 16-byte loads, thread t taking the t-th, (BLOCK + t)-th ... 16 bytes: for a
     // kernel that does not care which lane holds which element (the histogram).  Base 16-byte aligned.
@@ -353,15 +366,15 @@ template <int VEC> struct Stream {
             dw[4 * j + 3] = v.w;
         }
     }
-    // ragged tile or misaligned bf16 base: element-wise, guarded; valid[e] has bit h set when
-    // element h of slot e is below `end`
+    // ragged tile or misaligned bf16 base: element-wise, guarded; valid[d] has bit h set when
+    // element h of dword d is below `end`
     static __device__ __forceinline__ void load_slow(const void *x, int64_t t0, int64_t end, uint32_t (&dw)[SLOTS],
                                                      uint32_t (&valid)[SLOTS]) {
         using R = typename Raw<VEC>::type;
         const R *p = static_cast<const R *>(x);
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) {
-            const int64_t i0 = first_elem(t0, e);
+        for (int s = 0; s < SLOTS; ++s) {
+            const int64_t i0 = first_elem(t0, s / GD) + (s % GD) * EPD;
             uint32_t d = 0, v = 0;
 #pragma unroll
             for (int h = 0; h < EPD; ++h)
@@ -369,8 +382,8 @@ template <int VEC> struct Stream {
                     d |= static_cast<uint32_t>(p[i0 + h]) << (16 * h);
                     v |= 1u << h;
                 }
-            dw[e] = d;
-            valid[e] = v;
+            dw[s] = d;
+            valid[s] = v;
         }
     }
 };
@@ -424,21 +437,21 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {  // lane:
 template <int DPP_CTRL> __device__ __forceinline__ uint32_t row_shr_add(uint32_t v) {
     return v + static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), DPP_CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ void wave_counts(const uint32_t *cnt, uint32_t &before, uint32_t &total) {
-    static_assert(NW <= 16, "the scan stays inside one row of 16 lanes");
+template <int WAVES = NW> __device__ __forceinline__ void wave_counts(const uint32_t *cnt, uint32_t &before, uint32_t &total) {
+    static_assert(WAVES <= 16, "the scan stays inside one row of 16 lanes");
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint32_t v = cnt[threadIdx.x & (NW - 1)];
-    v = row_shr_add<0x111>(v);                // row_shr:1
-    if (NW > 2) v = row_shr_add<0x112>(v);    // row_shr:2
-    if (NW > 4) v = row_shr_add<0x114>(v);    // row_shr:4
-    if (NW > 8) v = row_shr_add<0x118>(v);    // row_shr:8
-    total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), NW - 1));
+    uint32_t v = cnt[threadIdx.x & (WAVES - 1)];
+    v = row_shr_add<0x111>(v);                   // row_shr:1
+    if (WAVES > 2) v = row_shr_add<0x112>(v);    // row_shr:2
+    if (WAVES > 4) v = row_shr_add<0x114>(v);    // row_shr:4
+    if (WAVES > 8) v = row_shr_add<0x118>(v);    // row_shr:8
+    total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), WAVES - 1));
     const uint32_t prev = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), w ? w - 1 : 0));
     before = w ? prev : 0u;
 }
 
-// Inclusive prefix sum over the block in thread order; *total = block sum.  sm holds NW words.
-__device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t *sm, uint32_t *total) {
+// Inclusive prefix sum over the block in thread order; *total = block sum.  sm holds WAVES words.
+template <int WAVES = NW> __device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t *sm, uint32_t *total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t inc = wave_incl_scan(v);
     __syncthreads();
@@ -446,7 +459,7 @@ __device__ __forceinline__ uint32_t block_incl_scan(uint32_t v, uint32_t *sm, ui
     __syncthreads();
     uint32_t pre = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
+    for (int i = 0; i < WAVES; ++i) {
         const uint32_t t = sm[i];
         pre += (i < w) ? t : 0u;
         tot += t;
@@ -479,6 +492,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double *sm) {
 }
 
 // Both at once: the prefix sum of v and, in acc, the block sum of it.
+template <int WAVES = NW>
 __device__ __forceinline__ uint32_t block_incl_scan_and_sum(uint32_t v, uint32_t *sm, uint32_t *total, double &acc, double *smd) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t inc = wave_incl_scan(v);
@@ -492,7 +506,7 @@ __device__ __forceinline__ uint32_t block_incl_scan_and_sum(uint32_t v, uint32_t
     uint32_t pre = 0, tot = 0;
     double sum = 0.0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
+    for (int i = 0; i < WAVES; ++i) {
         const uint32_t t = sm[i];
         pre += (i < w) ? t : 0u;
         tot += t;
@@ -622,12 +636,12 @@ struct NoPrefetch {
     __device__ __forceinline__ void operator()() const {}
 };
 // `after_step_a` is called when every thread has its step-A loads and before step B issues any.
-template <int NB, int NC, int UA = 8, typename Prefetch = NoPrefetch, typename Between = NoPrefetch>
+template <int NB, int NC, int UA = 8, int NT = BLOCK, typename Prefetch = NoPrefetch, typename Between = NoPrefetch>
 __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const uint32_t *coarse, int nrows, uint32_t krem, uint32_t *red,
                                                   Prefetch after_first_loads = Prefetch(), Between after_step_a = Between()) {
     constexpr int FINE = NB / NC;
-    static_assert(NC <= 64 && FINE <= 64 && NC % 4 == 0 && FINE % 4 == 0 && BLOCK % (NC / 4) == 0 &&
-                      BLOCK % (FINE / 4) == 0 && NC + FINE <= BLOCK,
+    static_assert(NC <= 64 && FINE <= 64 && NC % 4 == 0 && FINE % 4 == 0 && NT % (NC / 4) == 0 &&
+                      NT % (FINE / 4) == 0 && NC + FINE <= NT,
                   "column_pick geometry");
     uint32_t *redA = red, *redB = red + NC;
     ColumnPick r{static_cast<uint32_t>(NB), 0u};
@@ -636,7 +650,7 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
     __syncthreads();
     const int lane = threadIdx.x & 63;
     {
-        constexpr int Q = NC / 4, G = BLOCK / Q;
+        constexpr int Q = NC / 4, G = NT / Q;
         const int q = threadIdx.x % Q;
         const uint4 *co = reinterpret_cast<const uint4 *>(coarse) + q;
         uint4 sum = make_uint4(0, 0, 0, 0);
@@ -671,7 +685,7 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
     if (krem != 0 && okA != 0) {                                            // uniform over the workgroup
         const int J = 63 - __builtin_clzll(okA);
         {
-            constexpr int Q = FINE / 4, G = BLOCK / Q;
+            constexpr int Q = FINE / 4, G = NT / Q;
             const int q = threadIdx.x % Q;
             const uint4 *col = reinterpret_cast<const uint4 *>(rows + J * FINE) + q;
             uint4 all = make_uint4(0, 0, 0, 0);
@@ -832,33 +846,37 @@ __device__ __forceinline__ void hist1_full_tiles(const void *x, int64_t &t0, int
 // acc becomes the workgroup's sum of it (in a fixed order); the two reductions share their barriers.  sm: 2 * NW words,
 // smd: NW doubles.  The counts are complete (the caller has synchronised); h is not written.
 // COPIES = 2: of every count there are two, next to each other.  all: the row's first entry, if not 0.
-template <int NB, int NC, bool SHARED, int COPIES = 1>
+template <int NB, int NC, bool SHARED, int COPIES = 1, int NT = BLOCK>
 __device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double &acc, double *smd,
                                            uint32_t all = 0) {
-    static_assert(NB == 4 * BLOCK && (NB / NC) % 4 == 0 && (COPIES == 1 || COPIES == 2), "four counts per thread");
-    uint4 c = reinterpret_cast<const uint4 *>(h)[threadIdx.x * COPIES];
-    if (COPIES == 2) {
-        const uint4 d = reinterpret_cast<const uint4 *>(h)[threadIdx.x * COPIES + 1];
-        c = make_uint4(c.x + c.y, c.z + c.w, d.x + d.y, d.z + d.w);
+    constexpr int PER = NB / NT;  // counts per thread
+    static_assert((PER == 4 || PER == 2) && (NB / NC) % PER == 0 && (COPIES == 1 || COPIES == 2), "one store of up to 16 bytes per thread");
+    typedef uint32_t Counts __attribute__((ext_vector_type(PER)));
+    Counts c = reinterpret_cast<const Counts *>(h)[threadIdx.x * COPIES];
+    if constexpr (COPIES == 2) {
+        const Counts d = reinterpret_cast<const Counts *>(h)[threadIdx.x * COPIES + 1];
+        c = Counts{c.x + c.y, c.z + c.w, d.x + d.y, d.z + d.w};
     }
+    uint32_t own = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) own += c[j];
     uint32_t total;
-    const uint32_t inc = block_incl_scan_and_sum(c.x + c.y + c.z + c.w, sm, &total, acc, smd);
-    uint4 suffix;
-    suffix.w = total - inc + c.w;
-    suffix.z = suffix.w + c.z;
-    suffix.y = suffix.z + c.y;
-    suffix.x = all != 0 && threadIdx.x == 0 ? all : suffix.y + c.x;
-    uint32_t *row = rows + static_cast<size_t>(g) * NB + 4 * threadIdx.x;
+    const uint32_t inc = block_incl_scan_and_sum<NT / 64>(own, sm, &total, acc, smd);
+    Counts suffix;
+    uint32_t above = total - inc;
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) suffix[j] = above += c[j];
+    if (all != 0 && threadIdx.x == 0) suffix[0] = all;
+    uint32_t *row = rows + static_cast<size_t>(g) * NB + PER * threadIdx.x;
     if (SHARED) {
-        store_agent(&row[0], suffix.x);
-        store_agent(&row[1], suffix.y);
-        store_agent(&row[2], suffix.z);
-        store_agent(&row[3], suffix.w);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) store_agent(&row[j], static_cast<uint32_t>(suffix[j]));
     } else {
-        *reinterpret_cast<uint4 *>(row) = suffix;
+        *reinterpret_cast<Counts *>(row) = suffix;
     }
-    constexpr uint32_t PER_COARSE = NB / NC / 4;  // threads
-    if (threadIdx.x % PER_COARSE == 0) store_count<SHARED>(&coarse[static_cast<size_t>(g) * NC + threadIdx.x / PER_COARSE], suffix.x);
+    constexpr uint32_t PER_COARSE = NB / NC / PER;  // threads
+    if (threadIdx.x % PER_COARSE == 0)
+        store_count<SHARED>(&coarse[static_cast<size_t>(g) * NC + threadIdx.x / PER_COARSE], static_cast<uint32_t>(suffix[0]));
 }
 template <int NB, int NC, bool SHARED, int COPIES = 1>
 __device__ __forceinline__ void store_rows(const uint32_t *h, uint32_t *rows, uint32_t *coarse, int g, uint32_t *sm, double *smd, uint32_t all = 0) {
@@ -937,10 +955,10 @@ constexpr int STAGE_CAP = 2048;
 
 // Writes list slots [from, to) of the chunk from the stage to memory and counts their window bins.
 // stage[0] is list slot `from`.
-template <int VEC>
+template <int VEC, int NT>
 __device__ __forceinline__ void flush_stage(const uint2 *stage, uint32_t from, uint32_t to, uint32_t cap, uint32_t lo,
                                             uint32_t shw, uint32_t *hw, int32_t *Li, typename Raw<VEC>::type *Lv) {
-    for (uint32_t i = from + threadIdx.x; i < to; i += BLOCK) {
+    for (uint32_t i = from + threadIdx.x; i < to; i += NT) {
         const uint2 pr = stage[i - from];
         if (i < cap) {
             Li[i] = static_cast<int32_t>(pr.x);
@@ -950,18 +968,18 @@ __device__ __forceinline__ void flush_stage(const uint2 *stage, uint32_t from, u
     }
 }
 
-template <int VEC, bool FAST, bool RUNS>
-__device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOTS],
-                                          const uint32_t (&valid)[Stream<VEC>::SLOTS], int64_t t0, uint32_t lo,
+template <int VEC, bool FAST, bool RUNS, int NT>
+__device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::SLOTS],
+                                          const uint32_t (&valid)[Stream<VEC, NT>::SLOTS], int64_t t0, uint32_t lo,
                                           uint32_t shw, uint32_t *hw, uint32_t *wcnt, uint2 *stage, uint32_t &running,
                                           uint32_t &flushed, uint32_t &cap, int32_t *Li,
                                           typename Raw<VEC>::type *Lv, double &acc) {  // cap: 0 once the list is given up
-    using St = Stream<VEC>;
+    using St = Stream<VEC, NT>;
     using R = typename Raw<VEC>::type;
     constexpr int EPD = St::EPD, SLOTS = St::SLOTS;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint64_t m[SLOTS][EPD];
-    bool keep[SLOTS][EPD];  // lives as the compare's lane mask, i.e. the same registers as m
+    uint64_t m[St::GROUPS][St::GE];
+    bool keep[St::GROUPS][St::GE];  // lives as the compare's lane mask, i.e. the same registers as m
     uint32_t wc = 0;
     if (VEC != TAG_F32 && FAST) {
         // Two 16-bit elements per dword, handled as a pair: one AND clears both signs, each half is
@@ -975,13 +993,15 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
         float part = 0.0f;
 #pragma unroll
         for (int e = 0; e < SLOTS; ++e) {
+            constexpr int GD = St::GD;
+            const int j = e / GD, h = e % GD * EPD;  // elements h and h + 1 of group j
             const uint32_t k2 = dw[e] & 0x7FFF7FFFu;
             const uint32_t k_lo = k2 & 0xFFFFu, k_hi = k2 >> 16;
-            keep[e][0] = k_lo >= thr16;
-            keep[e][EPD - 1] = k_hi >= thr16;
-            m[e][0] = __ballot(keep[e][0]);
-            m[e][EPD - 1] = __ballot(keep[e][EPD - 1]);
-            wc += __popcll(m[e][0]) + __popcll(m[e][EPD - 1]);
+            keep[j][h] = k_lo >= thr16;
+            keep[j][h + EPD - 1] = k_hi >= thr16;
+            m[j][h] = __ballot(keep[j][h]);
+            m[j][h + EPD - 1] = __ballot(keep[j][h + EPD - 1]);
+            wc += __popcll(m[j][h]) + __popcll(m[j][h + EPD - 1]);
             float x_lo, x_hi;  // magnitudes: the signs are gone, the squares do not care
             if (VEC == TAG_F16) {
                 x_lo = __half2float(__ushort_as_half(static_cast<unsigned short>(k_lo)));
@@ -990,8 +1010,8 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
                 x_lo = __uint_as_float(k2 << 16);
                 x_hi = __uint_as_float(k2 & 0xFFFF0000u);
             }
-            x_lo = keep[e][0] ? 0.0f : x_lo;
-            x_hi = keep[e][EPD - 1] ? 0.0f : x_hi;
+            x_lo = keep[j][h] ? 0.0f : x_lo;
+            x_hi = keep[j][h + EPD - 1] ? 0.0f : x_hi;
             if (VEC == TAG_F16) {
                 part = fmaf(x_lo, x_lo, part);
                 part = fmaf(x_hi, x_hi, part);
@@ -1006,15 +1026,15 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
         acc += static_cast<double>(part);
     } else {
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e)
+        for (int j = 0; j < St::GROUPS; ++j)
 #pragma unroll
-            for (int hh = 0; hh < EPD; ++hh) {
-                const uint32_t raw = elem_of<VEC>(dw[e], hh);
-                const bool ok = FAST || ((valid[e] >> hh) & 1u);
-                keep[e][hh] = ok && key_of<VEC>(raw) >= lo;
-                m[e][hh] = __ballot(keep[e][hh]);
-                wc += __popcll(m[e][hh]);
-                float xs = (ok && !keep[e][hh]) ? value_of<VEC>(raw) : 0.0f;
+            for (int e = 0; e < St::GE; ++e) {
+                const uint32_t raw = St::elem(dw, j, e);
+                const bool ok = FAST || ((valid[j * St::GD + e / EPD] >> (e % EPD)) & 1u);
+                keep[j][e] = ok && key_of<VEC>(raw) >= lo;
+                m[j][e] = __ballot(keep[j][e]);
+                wc += __popcll(m[j][e]);
+                float xs = (ok && !keep[j][e]) ? value_of<VEC>(raw) : 0.0f;
                 // The empty statement pins the select to the 32-bit value: left alone, the compiler widens
                 // first and then selects both halves of the double (one more instruction per element in a
                 // loop whose time follows its instruction count: 24.0 -> 22.7 us on the 100 MB tensor).
@@ -1026,10 +1046,10 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
     if (lane == 0) wcnt[w] = wc;
     __syncthreads();
     uint32_t before, tot;  // wave-uniform, in scalar registers: the branches below are scalar
-    wave_counts(wcnt, before, tot);
+    wave_counts<NT / 64>(wcnt, before, tot);
     if (tot == 0) return;  // uniform over the workgroup
     if (running + tot - flushed > STAGE_CAP) {  // uniform: make room
-        flush_stage<VEC>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
+        flush_stage<VEC, NT>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
         __syncthreads();
         flushed = running;
     }
@@ -1039,28 +1059,35 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
     if (!direct) {
         uint2 *dst = stage - flushed;
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) {
-            uint64_t any = 0;
-#pragma unroll
-            for (int hh = 0; hh < EPD; ++hh) any |= m[e][hh];
+        for (int j = 0; j < St::GROUPS; ++j) {
+            const uint64_t m0 = m[j][0], m1 = m[j][1], m2 = m[j][2], m3 = m[j][3];
+            const uint64_t first = m0 | m1, second = m2 | m3, any = first | second;
             if (any == 0) continue;  // wave-uniform
-            uint32_t pos = slot_base;
-#pragma unroll
-            for (int hh = 0; hh < EPD; ++hh) pos = lanes_below_plus(m[e][hh], pos);
-            if constexpr (EPD == 2) {
-                // (a lane's two halves are neighbours in the list: one address, the second eight bytes on if the first is kept)
-                char *p = reinterpret_cast<char *>(dst + pos);
-                const uint32_t i0 = i_lane + e * 64 * EPD;
-                if (keep[e][0]) *reinterpret_cast<uint2 *>(p) = make_uint2(i0, elem_of<VEC>(dw[e], 0));
-                p += keep[e][0] ? sizeof(uint2) : 0;
-                if (keep[e][1]) *reinterpret_cast<uint2 *>(p) = make_uint2(i0 + 1, elem_of<VEC>(dw[e], 1));
-                slot_base += __popcll(m[e][0]) + __popcll(m[e][1]);
+            const uint32_t i = i_lane + j * 64 * St::GE;
+            if (((m0 & m1) | (m2 & m3) | (first & second)) == 0) {  // wave-uniform: one candidate per lane at most
+                const uint32_t pos = lanes_below_plus(any, slot_base);
+                const bool front = keep[j][0] | keep[j][1], odd = keep[j][1] | keep[j][3];
+                uint32_t raw;
+                if constexpr (EPD == 2) {
+                    const uint32_t d = front ? dw[j * St::GD] : dw[j * St::GD + 1];
+                    raw = odd ? d >> 16 : d & 0xFFFFu;
+                } else {
+                    const uint32_t a = keep[j][0] ? dw[j * 4] : dw[j * 4 + 1], b = keep[j][2] ? dw[j * 4 + 2] : dw[j * 4 + 3];
+                    raw = front ? a : b;
+                }
+                if (front | keep[j][2] | keep[j][3]) dst[pos] = make_uint2(i + (front ? 0u : 2u) + (odd ? 1u : 0u), raw);
+                slot_base += __popcll(any);
             } else {
+                uint32_t pos = slot_base;
 #pragma unroll
-                for (int hh = 0; hh < EPD; ++hh) {
-                    if (keep[e][hh]) dst[pos] = make_uint2(i_lane + e * 64 * EPD + hh, elem_of<VEC>(dw[e], hh));
-                    pos += keep[e][hh] ? 1u : 0u;
-                    slot_base += __popcll(m[e][hh]);
+                for (int e = 0; e < St::GE; ++e) pos = lanes_below_plus(m[j][e], pos);
+                // (a lane's candidates are neighbours in the list: one address, eight bytes further behind each that is kept)
+                char *p = reinterpret_cast<char *>(dst + pos);
+#pragma unroll
+                for (int e = 0; e < St::GE; ++e) {
+                    if (keep[j][e]) *reinterpret_cast<uint2 *>(p) = make_uint2(i + e, St::elem(dw, j, e));
+                    p += keep[j][e] ? sizeof(uint2) : 0;
+                    slot_base += __popcll(m[j][e]);
                 }
             }
         }
@@ -1080,32 +1107,31 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC>::SLOT
         } else {
             BinRun run;
 #pragma unroll
-            for (int e = 0; e < SLOTS; ++e)
+            for (int j = 0; j < St::GROUPS; ++j)
 #pragma unroll
-                for (int hh = 0; hh < EPD; ++hh)
-                    run.add(hw, window_bin(key_of<VEC>(elem_of<VEC>(dw[e], hh)), lo, shw), keep[e][hh]);
+                for (int e = 0; e < St::GE; ++e) run.add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e]);
             run.flush(hw);
         }
     } else {
         // (the variant with two workgroups per compute unit has no register to spare for a list that
         // ends early: it stores while the list has room)
 #pragma unroll
-        for (int e = 0; e < SLOTS; ++e) {
+        for (int j = 0; j < St::GROUPS; ++j) {
             uint32_t pos = slot_base;
 #pragma unroll
-            for (int hh = 0; hh < EPD; ++hh) pos = lanes_below_plus(m[e][hh], pos);
+            for (int e = 0; e < St::GE; ++e) pos = lanes_below_plus(m[j][e], pos);
 #pragma unroll
-            for (int hh = 0; hh < EPD; ++hh) {
-                if (keep[e][hh]) {
-                    const uint32_t raw = elem_of<VEC>(dw[e], hh);
+            for (int e = 0; e < St::GE; ++e) {
+                if (keep[j][e]) {
+                    const uint32_t raw = St::elem(dw, j, e);
                     if (pos < cap) {
-                        Li[pos] = static_cast<int32_t>(i_lane + e * 64 * EPD + hh);
+                        Li[pos] = static_cast<int32_t>(i_lane + j * 64 * St::GE + e);
                         Lv[pos] = static_cast<R>(raw);
                     }
                     hist_add(hw, window_bin(key_of<VEC>(raw), lo, shw), true);
                     ++pos;
                 }
-                slot_base += __popcll(m[e][hh]);
+                slot_base += __popcll(m[j][e]);
             }
         }
     }
@@ -1139,26 +1165,27 @@ constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by
 // 38 17 9 11 38 / 40 40 34 23 40 (10 % is where the zeros begin), evenly spread values all.  Longer tensors as they were: 128-byte lines
 // for 64 bytes, 0.4 us for 4.9 M values, 1.5 for 25 M.
 constexpr int32_t SAMPLE_FINE_BELOW = 1 << 20;
-constexpr int SAMPLE_BATCH = 16;  // dword loads per thread and batch; the host picks 1, 2 or 4 batches (fp32: 8192 elements each)
+constexpr int SAMPLE_BATCH = 16;  // dwords per thread and batch with BLOCK threads; the host picks 1, 2 or 4 batches (fp32: 8192 elements each)
 // Byte offset of the sample bin (4 * (key >> SAMPLE_SH)) of element hh of a dword.
 template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword, int hh) {
     static_assert(SAMPLE_SH == 19, "the shifts below");
     constexpr uint32_t MASK = (NSB - 1) * 4;
     return (VEC == TAG_F32 || hh == 1 ? dword >> 17 : dword >> 1) & MASK;
 }
-template <int VEC, typename Prefetch>
+template <int VEC, int NT, typename Prefetch>
 __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, uint32_t *s_pick,
                                               Prefetch after_loads, uint32_t &lo, uint32_t &shw) {
     constexpr int EPD = VEC / 4;
-    constexpr int MAXB = SAMPLE_ELEMS / BLOCK / EPD / SAMPLE_BATCH;  // batches at the full sample size
-    constexpr int PER = NSB / BLOCK;                                 // bins per thread in the search
+    constexpr int BATCH = SAMPLE_BATCH * BLOCK / NT, WAVES = NT / 64;
+    constexpr int MAXB = SAMPLE_ELEMS / NT / EPD / BATCH;  // batches at the full sample size
+    constexpr int PER = NSB / NT;                          // bins per thread in the search
     static_assert(MAXB == 4 || MAXB == 2, "sample batches");
     const int lane = threadIdx.x & 63;
     const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));  // in a scalar register
     const int nbatch = static_cast<int>((sg.flags >> FLAG_SAMPLE_SHIFT) & 15u);  // uniform; 1 .. MAXB
-    // 16-byte loads: a run is 64 lanes x 16 bytes = 1 KB; nbatch * (SAMPLE_BATCH / 4) * NW runs, a power of two
-    constexpr int QUADS = SAMPLE_BATCH / 4;
-    const int run_shift = __builtin_ctz(QUADS * NW) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
+    // 16-byte loads: a run is 64 lanes x 16 bytes = 1 KB; nbatch * QUADS * WAVES runs, a power of two
+    constexpr int QUADS = BATCH / 4;
+    const int run_shift = __builtin_ctz(QUADS * WAVES) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
     const uint64_t nruns = (static_cast<uint64_t>(sg.n) / EPD) / 256;
     const bool fine = sg.n < SAMPLE_FINE_BELOW;  // uniform: a run's sixteen 64-byte pieces lie `spread` pieces apart
     const uint32_t skew = fine ? 1u : SAMPLE_SKEW;
@@ -1168,7 +1195,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     const uint32_t spread = fine && between > 1 ? (between - 1) | 1u : 1u;
     const uint32_t shift_mask = fine ? (1u << (31 - __builtin_clz(spread))) - 1u : SAMPLE_SKEW - 1u, shift_by = fine ? 4u : 64u;
     const dword4 *x = static_cast<const dword4 *>(sg.x) + (static_cast<uint32_t>(lane) / 4) * 4 * spread + (static_cast<uint32_t>(lane) & 3u);
-    uint32_t v[MAXB][SAMPLE_BATCH];
+    uint32_t v[MAXB][BATCH];
 #pragma unroll
     for (int b = 0; b < MAXB; ++b)
         if (b < nbatch) {
@@ -1176,7 +1203,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
             for (int j = 0; j < QUADS; ++j) {
                 // evenly spaced, plus a small run-dependent offset: an even spacing alone can put every
                 // run on the same memory channel
-                const uint32_t r = static_cast<uint32_t>(b * QUADS + j) * NW + w;
+                const uint32_t r = static_cast<uint32_t>(b * QUADS + j) * WAVES + w;
                 const uint64_t run = (static_cast<uint64_t>(r) * (nruns - skew)) >> run_shift;
                 const dword4 q = x[run * 64 + ((r * 37u) & shift_mask) * shift_by];
                 v[b][4 * j] = q.x;
@@ -1188,17 +1215,17 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     __builtin_amdgcn_sched_barrier(0);
     after_loads();
     __builtin_amdgcn_sched_barrier(0);
-    static_assert(NSB == 2 * 4 * BLOCK && PER == 8, "two 16-byte accesses per thread");
+    static_assert(PER == 8 || PER == 4, "16-byte accesses");
     uint4 *hs4 = reinterpret_cast<uint4 *>(hs);
-    hs4[threadIdx.x] = make_uint4(0, 0, 0, 0);
-    hs4[BLOCK + threadIdx.x] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < PER / 4; ++j) hs4[j * NT + threadIdx.x] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x == 0) {
         s_pick[0] = NSB;  // what stays when no bin holds the rank
         s_pick[1] = NSB;
     }
     // Only the largest few per cent of the sample decide the two ranks.  Every thread's largest bin
-    // is at least `floor` = the smallest of the threads' largest bins, so at least BLOCK sampled keys
-    // are in it or above: when the lower rank is within BLOCK, bins below it need not be counted at all.
+    // is at least `floor` = the smallest of the threads' largest bins, so at least NT sampled keys
+    // are in it or above: when the lower rank is within NT, bins below it need not be counted at all.
     // Bin 0 (zeros and the smallest denormals) is never counted: a rank that falls into it is not
     // found, which puts the window's lower end at key 0 just the same, and a tensor that is mostly
     // zeros does not pile its lanes onto one word.
@@ -1207,7 +1234,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     for (int b = 0; b < MAXB; ++b)
         if (b < nbatch) {
 #pragma unroll
-            for (int j = 0; j < SAMPLE_BATCH; ++j)
+            for (int j = 0; j < BATCH; ++j)
 #pragma unroll
                 for (int hh = 0; hh < EPD; ++hh) {
                     const uint32_t bin = sample_bin<VEC>(v[b][j], hh);
@@ -1228,21 +1255,21 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     if (lane == 0) sm[w] = floor_bin;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NW; ++i) floor_bin = sm[i] < floor_bin ? sm[i] : floor_bin;
+    for (int i = 0; i < WAVES; ++i) floor_bin = sm[i] < floor_bin ? sm[i] : floor_bin;
     const uint32_t r_lo = sg.ranks & 0xFFFFu, r_hi = sg.ranks >> 16;
-    if (r_lo > BLOCK) floor_bin = 0;
+    if (r_lo > NT) floor_bin = 0;
     floor_bin = floor_bin < 4 ? 4 : floor_bin;
     auto count = [&](uint32_t bin, uint32_t c) { atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hs) + bin), c); };
     // A thread whose sampled keys all lie in one bin (a constant tensor) adds them with one add:
     // element by element the whole sample would go to one LDS word, one key after the other.
     if (least == most) {
-        if (most >= floor_bin) count(most, static_cast<uint32_t>(nbatch * SAMPLE_BATCH * EPD));
+        if (most >= floor_bin) count(most, static_cast<uint32_t>(nbatch * BATCH * EPD));
     } else {
 #pragma unroll
         for (int b = 0; b < MAXB; ++b)
             if (b < nbatch) {
 #pragma unroll
-                for (int j = 0; j < SAMPLE_BATCH; ++j)
+                for (int j = 0; j < BATCH; ++j)
 #pragma unroll
                     for (int hh = 0; hh < EPD; ++hh) {
                         const uint32_t bin = VEC == TAG_F32 ? v[b][j] : sample_bin<VEC>(v[b][j], hh);
@@ -1252,13 +1279,19 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     }
     __syncthreads();
     // thread t owns bins [t * PER, (t + 1) * PER); higher bins hold larger keys
-    const uint4 c_lo = hs4[2 * threadIdx.x], c_hi = hs4[2 * threadIdx.x + 1];
-    const uint32_t cnt[PER] = {c_lo.x, c_lo.y, c_lo.z, c_lo.w, c_hi.x, c_hi.y, c_hi.z, c_hi.w};
-    uint32_t own = 0;
+    uint32_t cnt[PER], own = 0;
+#pragma unroll
+    for (int j = 0; j < PER / 4; ++j) {
+        const uint4 c = hs4[PER / 4 * threadIdx.x + j];
+        cnt[4 * j] = c.x;
+        cnt[4 * j + 1] = c.y;
+        cnt[4 * j + 2] = c.z;
+        cnt[4 * j + 3] = c.w;
+    }
 #pragma unroll
     for (int j = 0; j < PER; ++j) own += cnt[j];
     uint32_t total;
-    const uint32_t inc = block_incl_scan(own, sm, &total);
+    const uint32_t inc = block_incl_scan<WAVES>(own, sm, &total);
     const uint32_t above_mine = total - inc;
     uint32_t above = above_mine;  // sampled (and counted) keys in the bins of the threads after this one
     // (r_hi = 0: no bin holds it)
@@ -1312,14 +1345,19 @@ struct JudgeSync {
 static_assert(sizeof(JudgeSync) <= sizeof(uint32_t) * NB3 * (MAXSEG - 1), "fits behind tensor 0's histogram");
 __device__ __forceinline__ JudgeSync *judge_sync(const Launch &a) { return reinterpret_cast<JudgeSync *>(a.G3 + NB3); }
 
+// Threads of a scan with a compute unit to itself.  A wavefront issues one instruction in about 2 ns, vector or scalar, whatever the
+// others do, and a tile is some 400 of them per wavefront of eight: with four wavefronts per SIMD instead of two the same tile is shared by twice as
+// many (what they issue in all is still below what the SIMDs take), and so is the sample.  512 / 1024 threads, us per compress and decompress: 25 M fp32 at
+// 1 % 59.5 / 58.0, at 10 % 80.5 / 75.9, 26 M bf16 41.0 / 37.6, 4.9 M wire message 30.9 / 30.4, 393 K fp32 22.0 to 22.9 either way.
+constexpr int SCAN_THREADS = 1024, SCAN_WAVES = SCAN_THREADS / 64;
 // LDS of a scan.
 struct ScanLds {
     // 24 KB used in turn as: the sample histogram or the bucket search's scratch (prologue), then the
     // stage (STAGE_CAP pairs) followed by the window histogram
     __attribute__((aligned(16))) uint32_t smem[SCAN_SMEM_WORDS];
-    uint32_t wcnt[2][NW];
-    uint32_t sm[2 * NW];
-    double smd[NW];
+    uint32_t wcnt[2][SCAN_WAVES];
+    uint32_t sm[2 * SCAN_WAVES];
+    double smd[SCAN_WAVES];
     uint32_t s_pick[4];
 };
 
@@ -1336,23 +1374,21 @@ __device__ __forceinline__ const Launch &args_again() {
 }
 
 // DEPTH = register buffers of one tile each that the streaming loop rotates through, i.e. DEPTH - 1
-// tiles of loads in flight while one is processed.  The loop waits for memory, not for instructions
-// (one workgroup per compute unit with one tile ahead keeps 32 KB per compute unit in flight, which at
-// the latency of a load under this traffic sustains about 4.8 TB/s), so a single tensor, whose launch has
-// one workgroup per compute unit and twice the registers to spend, runs two tiles ahead.  A batch of
-// tensors is launched with two workgroups per compute unit (four wavefronts per SIMD), which needs the
-// kernel to stay within 128 vector registers: one tile ahead.
+// tiles of loads in flight while one is processed.  One workgroup per compute unit with one tile ahead keeps 32 KB per compute
+// unit in flight, which at the latency of a load under this traffic sustains about 4.8 TB/s, so a single tensor, whose launch has
+// one workgroup of SCAN_THREADS per compute unit, runs two tiles ahead (half as long per thread).  A batch of
+// tensors is launched with two workgroups of BLOCK threads per compute unit (four wavefronts per SIMD as well): one tile ahead.
 //
 // One chunk with the window (lo, shw); `cur` holds the chunk's first tile if it has a full one.  PAIR: leave
 // the two counts by which k_hist1 judges a speculative window.  `room`: the list's capacity, or 0 for no list, if the chunk's candidates
 // are known (listed_room) not to fit one; a speculative scan knows nothing yet.
-template <int VEC, bool PAIR, int DEPTH, bool SHARED>
+template <int VEC, bool PAIR, int DEPTH, bool SHARED, int NT>
 __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32_t lo, uint32_t shw, uint32_t room,
-                                           uint32_t (&cur)[Stream<VEC>::SLOTS], ScanLds &l) {
+                                           uint32_t (&cur)[Stream<VEC, NT>::SLOTS], ScanLds &l) {
     static_assert(DEPTH == 2 || DEPTH == 3, "one or two tiles ahead");
     const SegDesc &sg = a.seg[s];
     using R = typename Raw<VEC>::type;
-    using St = Stream<VEC>;
+    using St = Stream<VEC, NT>;
     const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
     const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
@@ -1367,7 +1403,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32
     uint2 *stage = reinterpret_cast<uint2 *>(l.smem);
     uint32_t *hw = l.smem + 2 * STAGE_CAP;
     __syncthreads();
-    for (int b = threadIdx.x; b < NBW; b += BLOCK) hw[b] = 0;
+    for (int b = threadIdx.x; b < NBW; b += NT) hw[b] = 0;
     __syncthreads();
 
     double acc = 0.0;
@@ -1378,7 +1414,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32
     int64_t t0 = beg;
     int64_t rem = ntiles;
     auto tile = [&](const uint32_t(&dw)[St::SLOTS]) {
-        scan_tile<VEC, true, DEPTH == 3>(dw, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+        scan_tile<VEC, true, DEPTH == 3, NT>(dw, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
         t0 += TILE;
         wb ^= 1;
     };
@@ -1430,16 +1466,16 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32
     }
     for (; t0 < end; t0 += TILE, wb ^= 1) {
         St::load_slow(sg.x, t0, end, cur, valid);
-        scan_tile<VEC, false, DEPTH == 3>(cur, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+        scan_tile<VEC, false, DEPTH == 3, NT>(cur, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
     }
     __syncthreads();
-    flush_stage<VEC>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
+    flush_stage<VEC, NT>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
 
     const Launch &again = args_again();  // (what the end of the chunk needs of them does not take up registers in the tile loop)
     const uint32_t capacity = list_cap(again.seg[s]);
     __syncthreads();
     // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
-    store_rows<NBW, NCW, SHARED>(hw, again.rowsW, again.coarseW, g, l.sm, acc, l.smd);
+    store_rows<NBW, NCW, SHARED, 1, NT>(hw, again.rowsW, again.coarseW, g, l.sm, acc, l.smd);
     if (threadIdx.x == 0) {
         store_count<SHARED>(&again.chunk_err[g], acc);
         // more than the list holds = "read this chunk from the input", also for a list that was given up
@@ -1462,8 +1498,9 @@ template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Lau
 }
 
 template <int VEC, bool SPEC, int DEPTH>
-__global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
-    using St = Stream<VEC>;
+__global__ __launch_bounds__(DEPTH == 2 ? BLOCK : SCAN_THREADS, 4) void k_scan(Launch a) {
+    constexpr int NT = DEPTH == 2 ? BLOCK : SCAN_THREADS;
+    using St = Stream<VEC, NT>;
     __shared__ ScanLds l;
     static_assert(NSB <= SCAN_SMEM_WORDS && NC1 + FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
 
@@ -1489,11 +1526,11 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
 
     uint32_t lo, shw, room = 0;
     if (SPEC) {
-        sample_window<VEC>(sg, l.smem, l.sm, l.s_pick, first_tile, lo, shw);
+        sample_window<VEC, NT>(sg, l.smem, l.sm, l.s_pick, first_tile, lo, shw);
         if (c == 0) {  // the accumulators of the kernels that follow
-            for (int b = threadIdx.x; b < NB3; b += BLOCK) a.G3[s * NB3 + b] = 0;
+            for (int b = threadIdx.x; b < NB3; b += NT) a.G3[s * NB3 + b] = 0;
             if (a.S == 1)
-                for (uint32_t b = threadIdx.x; b < sizeof(JudgeSync) / 4; b += BLOCK) reinterpret_cast<uint32_t *>(judge_sync(a))[b] = 0;
+                for (uint32_t b = threadIdx.x; b < sizeof(JudgeSync) / 4; b += NT) reinterpret_cast<uint32_t *>(judge_sync(a))[b] = 0;
             if (threadIdx.x == 0) {
                 a.state[s].loA = lo;
                 a.state[s].shwA = shw;
@@ -1503,7 +1540,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
     } else {
         // The same in every workgroup of the tensor: bucket B1 of the k-th key from the rows of k_hist1
         // is the window, its 2^20 keys in the first 1024 bins.
-        const ColumnPick p1 = column_pick<NB1, NC1, 16>(a.rows1 + static_cast<size_t>(sg.chunk_begin) * NB1,
+        const ColumnPick p1 = column_pick<NB1, NC1, 16 * BLOCK / NT, NT>(a.rows1 + static_cast<size_t>(sg.chunk_begin) * NB1,
                                                         a.coarse1 + static_cast<size_t>(sg.chunk_begin) * NC1, sg.nchunks,
                                                         static_cast<uint32_t>(sg.k), l.smem, first_tile);
         // (asked only where many chunks can be in question: the answer costs a short tensor a memory round trip)
@@ -1515,7 +1552,7 @@ __global__ __launch_bounds__(BLOCK, DEPTH == 2 ? 4 : 2) void k_scan(Launch a) {
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, DEPTH, false>(a, s, g, lo, shw, room, cur, l);
+    scan_chunk<VEC, SPEC, DEPTH, false, NT>(a, s, g, lo, shw, room, cur, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -2563,7 +2600,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
-                scan_chunk<VEC, false, DEPTH, true>(a, 0, ci, lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), cur, l.sl);
+                scan_chunk<VEC, false, DEPTH, true, BLOCK>(a, 0, ci, lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), cur, l.sl);
             }
             __syncthreads();
         }))
@@ -3394,17 +3431,17 @@ int32_t g_judge_missing = 0;  // workgroups that k_judge is launched without
 int32_t g_judge_rounds = -1;  // its rounds of waiting, if not negative
 #endif
 
-template <typename K, typename... Args>
+template <int NT = BLOCK, typename K, typename... Args>
 inline void launch(int stage, K kernel, dim3 grid, hipStream_t st, Args... args) {
 #ifdef ADATOPK_MEASURE_BUILD
     if (g_measure) {
-        hipExtLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, g_start[stage], g_stop[stage], 0, args...);
+        hipExtLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, g_start[stage], g_stop[stage], 0, args...);
         g_ran[stage] = true;
         return;
     }
 #endif
     (void)stage;
-    hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, args...);
+    hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, args...);
 }
 
 // Workgroups in front of those of the parts that S error norms take.  Workgroups are dealt out over the eight XCDs in turn, and what the
@@ -3423,7 +3460,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
     if (speculate) {
-        if (one_per_cu) launch(ST_SPEC, k_scan<VEC, true, 3>, grid, st, a);
+        if (one_per_cu) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, 3>, grid, st, a);
         else launch(ST_SPEC, k_scan<VEC, true, 2>, grid, st, a);
     }
     const dim3 parts(a.parts);
@@ -3441,7 +3478,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         else if constexpr (VEC == TAG_F32) launch(ST_JUDGE, k_judge<VEC, false>, judges, st, a);
     } else {
         launch(ST_HIST1, k_hist1<VEC>, grid, st, a);
-        if (one_per_cu) launch(ST_SCAN, k_scan<VEC, false, 3>, grid, st, a);
+        if (one_per_cu) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, 3>, grid, st, a);
         else launch(ST_SCAN, k_scan<VEC, false, 2>, grid, st, a);
         if constexpr (VEC == TAG_F32) {  // the 16-bit types have no last digit to refine
             if (wide) launch(ST_REFINE, k_refine<VEC, true>, parts, st, a);
