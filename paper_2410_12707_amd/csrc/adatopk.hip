@@ -61,6 +61,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "adatopk.h"
 #include "wire_layout.h"
@@ -364,6 +365,29 @@ template <int VEC, int NT = BLOCK> struct Stream {
             dw[4 * j + 1] = v.y;
             dw[4 * j + 2] = v.z;
             dw[4 * j + 3] = v.w;
+        }
+    }
+    // The first `bytes` bytes (whole dwords) behind a 4-byte aligned address, the same in all lanes: what is asked for beyond them reads as
+    // zeros and moves nothing.  So a loop can ask for the tile some iterations ahead without knowing whether there is one.
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t bounded(const void *chunk, uint32_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(chunk), static_cast<short>(0), static_cast<int>(bytes), 0x00020000);
+    }
+    // tile `tile` of it, nontemporal like load_fast
+    static __device__ __forceinline__ void load_bounded(__amdgpu_buffer_rsrc_t chunk, uint32_t tile, uint32_t (&dw)[SLOTS]) {
+        constexpr uint32_t GROUP = GE * (4 / EPD);  // bytes per lane and load
+        constexpr int NONTEMPORAL = 2;
+        const uint32_t at = tile * (TILE * (4 / EPD)) + ((threadIdx.x >> 6) * GROUPS * 64 + (threadIdx.x & 63)) * GROUP;
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j) {
+            if constexpr (GD == 4) {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(chunk, static_cast<int>(at + j * 64 * GROUP), 0, NONTEMPORAL);
+#pragma unroll
+                for (int d = 0; d < GD; ++d) dw[j * GD + d] = v[d];
+            } else {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(chunk, static_cast<int>(at + j * 64 * GROUP), 0, NONTEMPORAL);
+#pragma unroll
+                for (int d = 0; d < GD; ++d) dw[j * GD + d] = v[d];
+            }
         }
     }
     // ragged tile or misaligned bf16 base: element-wise, guarded; valid[d] has bit h set when
@@ -1149,13 +1173,12 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
 // beyond the sample's size puts the lower end at key 0; rank 0 leaves the upper end open.  All
 // integer work on the same data: every workgroup gets the same window.
 //
-// The histogram lives in LDS; a thread reads its eight consecutive bins with two 16-byte loads.  The whole prologue is
-// bound by instruction issue (two wavefronts per SIMD), so the work per sampled element is kept to a
+// The histogram lives in LDS.  The whole prologue is
+// bound by instruction issue, so the work per sampled element is kept to a
 // handful of instructions: two for its bin's byte offset (the sign falls out of the shift), half of one each for the largest and
 // the smallest, one compare against a floor below which nothing needs counting, one add.  (With keys, a shift per use and
 // padded bins it was 3.5 us from the sample's arrival to the window; this and the rows from registers took 1.3 us off a
 // compress and decompress of 393 K fp32 values, 24.2 -> 22.9.)
-// The bins holding the two ranks are found while the suffix sums are formed in registers.
 constexpr int SCAN_SMEM_WORDS = 2 * STAGE_CAP + NBW;  // k_scan's stage and window histogram; its prologue's scratch fits inside
 constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by up to this many run lengths
 // A sample of runs of 1 KB sees one row, channel or plane 256 times over and others not at all, and a window that misses costs a short
@@ -1172,13 +1195,15 @@ template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword
     constexpr uint32_t MASK = (NSB - 1) * 4;
     return (VEC == TAG_F32 || hh == 1 ? dword >> 17 : dword >> 1) & MASK;
 }
+// after_sample is called when the sample has arrived: what is asked for there does not delay it.  (The chunk's first tile asked for right behind the
+// sample's own loads, us per compress and decompress: 25 M fp32 56.4, so 55.9; 4.9 M wire message 28.1, 27.9; two tiles there: 55.6 and 28.7.)
+// sm: 2 * NT / 64 words.  No wavefront has read hs to the end before it returns, but every one has before the caller's next barrier.
 template <int VEC, int NT, typename Prefetch>
-__device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, uint32_t *s_pick,
-                                              Prefetch after_loads, uint32_t &lo, uint32_t &shw) {
+__device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, Prefetch after_sample, uint32_t &lo, uint32_t &shw) {
     constexpr int EPD = VEC / 4;
     constexpr int BATCH = SAMPLE_BATCH * BLOCK / NT, WAVES = NT / 64;
     constexpr int MAXB = SAMPLE_ELEMS / NT / EPD / BATCH;  // batches at the full sample size
-    constexpr int PER = NSB / NT;                          // bins per thread in the search
+    constexpr int PER = NSB / NT;                          // bins per thread
     static_assert(MAXB == 4 || MAXB == 2, "sample batches");
     const int lane = threadIdx.x & 63;
     const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));  // in a scalar register
@@ -1212,23 +1237,10 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                 v[b][4 * j + 3] = q.w;
             }
         }
-    __builtin_amdgcn_sched_barrier(0);
-    after_loads();
-    __builtin_amdgcn_sched_barrier(0);
     static_assert(PER == 8 || PER == 4, "16-byte accesses");
     uint4 *hs4 = reinterpret_cast<uint4 *>(hs);
 #pragma unroll
     for (int j = 0; j < PER / 4; ++j) hs4[j * NT + threadIdx.x] = make_uint4(0, 0, 0, 0);
-    if (threadIdx.x == 0) {
-        s_pick[0] = NSB;  // what stays when no bin holds the rank
-        s_pick[1] = NSB;
-    }
-    // Only the largest few per cent of the sample decide the two ranks.  Every thread's largest bin
-    // is at least `floor` = the smallest of the threads' largest bins, so at least NT sampled keys
-    // are in it or above: when the lower rank is within NT, bins below it need not be counted at all.
-    // Bin 0 (zeros and the smallest denormals) is never counted: a rank that falls into it is not
-    // found, which puts the window's lower end at key 0 just the same, and a tensor that is mostly
-    // zeros does not pile its lanes onto one word.
     uint32_t most = 0, least = 0xFFFFFFFFu;
 #pragma unroll
     for (int b = 0; b < MAXB; ++b)
@@ -1243,22 +1255,51 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
                     if (VEC == TAG_F32) v[b][j] = bin;  // (16-bit types: two to a dword, formed again below)
                 }
         }
-    uint32_t floor_bin = most;
-    auto lower = [&](uint32_t o) { floor_bin = o < floor_bin ? o : floor_bin; };
-    lower(dpp<DPP_SHR1>(floor_bin, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR2>(floor_bin, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR4>(floor_bin, 0xFFFFFFFFu));
-    lower(dpp<DPP_SHR8>(floor_bin, 0xFFFFFFFFu));
-    lower(dpp<DPP_BCAST15>(floor_bin, 0xFFFFFFFFu));
-    lower(dpp<DPP_BCAST31>(floor_bin, 0xFFFFFFFFu));
-    floor_bin = lane_value(floor_bin, 63);  // the wavefront's
-    if (lane == 0) sm[w] = floor_bin;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < WAVES; ++i) floor_bin = sm[i] < floor_bin ? sm[i] : floor_bin;
+    __builtin_amdgcn_sched_barrier(0);
+    after_sample();
+    __builtin_amdgcn_sched_barrier(0);
+    // Only the largest few per cent of the sample decide the two ranks.  The threads are taken in groups; every group's largest bin
+    // is at least `floor` = the smallest of the groups' largest bins, so at least as many sampled keys as there are groups
+    // are in it or above: when the lower rank is within that number, bins below it need not be counted at all.  The larger the groups,
+    // the fewer keys are: of 16 K normal values in 1024 threads a third with every thread for itself, an eighth with eight together.
+    // Bin 0 (zeros and the smallest denormals) is never counted: a rank that falls into it is not
+    // found, which puts the window's lower end at key 0 just the same, and a tensor that is mostly
+    // zeros does not pile its lanes onto one word.
     const uint32_t r_lo = sg.ranks & 0xFFFFu, r_hi = sg.ranks >> 16;
-    if (r_lo > NT) floor_bin = 0;
-    floor_bin = floor_bin < 4 ? 4 : floor_bin;
+    auto larger = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
+    auto smaller = [](uint32_t x, uint32_t y) { return x < y ? x : y; };
+    uint32_t floor_bin = most, top_bin = most;
+    constexpr int DPP_PAIRS = 0xB1, DPP_QUADS = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROWS = 0xF;
+    auto exchanged = [&](auto ctrl) {  // with the lane that the control names, all of them in the same row
+        return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(floor_bin), decltype(ctrl)::value, DPP_ROWS, 0xF, true));
+    };
+    if (r_lo <= NT / 2) floor_bin = larger(floor_bin, exchanged(std::integral_constant<int, DPP_PAIRS>()));
+    if (r_lo <= NT / 4) floor_bin = larger(floor_bin, exchanged(std::integral_constant<int, DPP_QUADS>()));
+    if (r_lo <= NT / 8) floor_bin = larger(floor_bin, exchanged(std::integral_constant<int, DPP_HALF_MIRROR>()));
+    auto reduce = [&](auto ctrl) {
+        floor_bin = smaller(floor_bin, dpp<decltype(ctrl)::value>(floor_bin, 0xFFFFFFFFu));
+        top_bin = larger(top_bin, dpp<decltype(ctrl)::value>(top_bin, 0u));
+    };
+    reduce(std::integral_constant<int, DPP_SHR1>());
+    reduce(std::integral_constant<int, DPP_SHR2>());
+    reduce(std::integral_constant<int, DPP_SHR4>());
+    reduce(std::integral_constant<int, DPP_SHR8>());
+    reduce(std::integral_constant<int, DPP_BCAST15>());
+    reduce(std::integral_constant<int, DPP_BCAST31>());
+    if (lane == 63) {
+        sm[w] = floor_bin;
+        sm[WAVES + w] = top_bin;
+    }
+    __syncthreads();
+    floor_bin = sm[lane & (WAVES - 1)];
+    top_bin = sm[WAVES + (lane & (WAVES - 1))];
+    static_assert(WAVES == 8 || WAVES == 16, "one row of 16 lanes");
+    reduce(std::integral_constant<int, DPP_SHR1>());
+    reduce(std::integral_constant<int, DPP_SHR2>());
+    reduce(std::integral_constant<int, DPP_SHR4>());
+    if (WAVES == 16) reduce(std::integral_constant<int, DPP_SHR8>());
+    floor_bin = r_lo <= NT ? larger(lane_value(floor_bin, WAVES - 1), 4u) : 4u;
+    const uint32_t top = lane_value(top_bin, WAVES - 1) / 4;
     auto count = [&](uint32_t bin, uint32_t c) { atomicAdd(reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(hs) + bin), c); };
     // A thread whose sampled keys all lie in one bin (a constant tensor) adds them with one add:
     // element by element the whole sample would go to one LDS word, one key after the other.
@@ -1278,54 +1319,43 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
             }
     }
     __syncthreads();
-    // thread t owns bins [t * PER, (t + 1) * PER); higher bins hold larger keys
-    uint32_t cnt[PER], own = 0;
-#pragma unroll
-    for (int j = 0; j < PER / 4; ++j) {
-        const uint4 c = hs4[PER / 4 * threadIdx.x + j];
-        cnt[4 * j] = c.x;
-        cnt[4 * j + 1] = c.y;
-        cnt[4 * j + 2] = c.z;
-        cnt[4 * j + 3] = c.w;
-    }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) own += cnt[j];
-    uint32_t total;
-    const uint32_t inc = block_incl_scan<WAVES>(own, sm, &total);
-    const uint32_t above_mine = total - inc;
-    uint32_t above = above_mine;  // sampled (and counted) keys in the bins of the threads after this one
-    // (r_hi = 0: no bin holds it)
-    if ((above < r_lo && above + own >= r_lo) || (above < r_hi && above + own >= r_hi)) {  // two threads of the workgroup
-#pragma unroll
-        for (int j = PER - 1; j >= 0; --j) {
-            const uint32_t with = above + cnt[j];  // suffix sum at this bin
-            if (above < r_lo && with >= r_lo) s_pick[0] = threadIdx.x * PER + j;
-            if (above < r_hi && with >= r_hi) s_pick[1] = threadIdx.x * PER + j;
-            above = with;
+    // The bins that hold two ranks, the first one the larger number, or NSB (also for rank 0).  Every wavefront looks for itself, four bins to
+    // a lane, from the largest sampled key downwards: 256 bins are 16 binades, so it rarely looks twice, and nobody waits for a
+    // barrier (block-wide suffix sums and the two threads that found a rank took 0.9 us, this 0.3).
+    struct Bins {
+        uint32_t lo, hi;
+    };
+    auto find = [&](uint32_t rank_lo, uint32_t rank_hi) {
+        Bins found = {NSB, NSB};
+        uint32_t above = 0;  // counted keys in the bins looked at so far
+        for (uint32_t base = top & ~255u;; base -= 256) {
+            const uint4 c = hs4[base / 4 + lane];
+            const uint32_t own = c.x + c.y + c.z + c.w, inc = wave_incl_scan(own), total = lane_value(inc, 63);
+            const uint32_t higher = above + total - inc;  // ... and in those of the lanes after this one
+            auto pick = [&](uint32_t rank, uint32_t &bin) {
+                const uint64_t here = __ballot(higher < rank && higher + own >= rank);
+                if (here == 0) return;  // uniform
+                const int l = __builtin_ctzll(here);
+                const uint32_t w3 = lane_value(higher, l) + lane_value(c.w, l), w2 = w3 + lane_value(c.z, l), w1 = w2 + lane_value(c.y, l);
+                bin = base + 4 * l + (w3 >= rank ? 3u : (w2 >= rank ? 2u : (w1 >= rank ? 1u : 0u)));
+            };
+            pick(rank_lo, found.lo);
+            pick(rank_hi, found.hi);
+            above += total;
+            if (above >= rank_lo || base * 4 <= floor_bin) return found;
         }
-    }
-    __syncthreads();
-    const uint32_t b_lo = __builtin_amdgcn_readfirstlane(s_pick[0]), b_hi = __builtin_amdgcn_readfirstlane(s_pick[1]);
-    lo = b_lo < NSB ? b_lo << SAMPLE_SH : 0u;
-    const uint32_t hi = b_hi < NSB ? (b_hi + 1u) << SAMPLE_SH : 0x80000000u;  // first key above the bracket
+    };
+    const Bins bins = find(r_lo, r_hi);
+    lo = bins.lo < NSB ? bins.lo << SAMPLE_SH : 0u;
+    const uint32_t hi = bins.hi < NSB ? (bins.hi + 1u) << SAMPLE_SH : 0x80000000u;  // first key above the bracket
     // fp32: a bracket wider than a window can span (keys that are thin around the k-th: a tensor that is mostly zeros, heavy tails at
     // a small keep share).  The window then lies around the key at the expected rank; from the bracket's lower end up it ended
     // below the k-th key, and tensors of 97 % zeros at 1 % kept missed in nine calls of ten, now in two.  (Not when the lower rank
     // is a zero: then the k-th key may be one, too.  All keys of the branch are uniform.)
     constexpr uint32_t SPAN = (NBW - 1) << BITS3;
-    if (VEC == TAG_F32 && b_lo < NSB && hi > lo && hi - lo > SPAN) {
-        const uint32_t rank = (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie SPEC_SIGMAS_LOW and SPEC_SIGMAS from it)
-        above = above_mine;
-        if (above < rank && above + own >= rank) {  // one thread: the rank is between the two that have been found
-#pragma unroll
-            for (int j = PER - 1; j >= 0; --j) {
-                const uint32_t with = above + cnt[j];
-                if (above < rank && with >= rank) s_pick[2] = threadIdx.x * PER + j;
-                above = with;
-            }
-        }
-        __syncthreads();
-        const uint32_t middle = (static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(s_pick[2])) << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
+    if (VEC == TAG_F32 && bins.lo < NSB && hi > lo && hi - lo > SPAN) {
+        const uint32_t rank = (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie SPEC_SIGMAS_LOW and SPEC_SIGMAS from it, and both have been found)
+        const uint32_t middle = (find(rank, 0).lo << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
         if (middle > lo + SPAN / 2) lo = middle - SPAN / 2;
     }
     // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow, the least shift that makes NBW - 1 bins
@@ -1358,7 +1388,6 @@ struct ScanLds {
     uint32_t wcnt[2][SCAN_WAVES];
     uint32_t sm[2 * SCAN_WAVES];
     double smd[SCAN_WAVES];
-    uint32_t s_pick[4];
 };
 
 // The launch's arguments once more, as if from another address: what is read through the result is read again where it
@@ -1373,26 +1402,36 @@ __device__ __forceinline__ const Launch &args_again() {
     return *(const Launch *)p;
 }
 
-// DEPTH = register buffers of one tile each that the streaming loop rotates through, i.e. DEPTH - 1
-// tiles of loads in flight while one is processed.  One workgroup per compute unit with one tile ahead keeps 32 KB per compute
-// unit in flight, which at the latency of a load under this traffic sustains about 4.8 TB/s, so a single tensor, whose launch has
-// one workgroup of SCAN_THREADS per compute unit, runs two tiles ahead (half as long per thread).  A batch of
-// tensors is launched with two workgroups of BLOCK threads per compute unit (four wavefronts per SIMD as well): one tile ahead.
-//
-// One chunk with the window (lo, shw); `cur` holds the chunk's first tile if it has a full one.  PAIR: leave
+// A chunk of a tensor as a scan reads it.
+template <int VEC, int NT> struct Chunk {
+    using St = Stream<VEC, NT>;
+    int64_t beg, end;             // its elements
+    __amdgpu_buffer_rsrc_t bytes; // its whole dwords, or nothing if loads of dwords are not possible
+    __device__ __forceinline__ Chunk(const SegDesc &sg, int c) {
+        beg = static_cast<int64_t>(c) * sg.E;
+        end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
+        using R = typename Raw<VEC>::type;
+        const int64_t len = (sg.flags & FLAG_ALIGNED4) && end > beg ? end - beg : 0;
+        bytes = St::bounded(static_cast<const R *>(sg.x) + beg, static_cast<uint32_t>(len * static_cast<int64_t>(sizeof(R))) & ~3u);
+    }
+    __device__ __forceinline__ void load(uint32_t tile, uint32_t (&dw)[St::SLOTS]) const { St::load_bounded(bytes, tile, dw); }
+};
+
+// One chunk with the window (lo, shw); the loads of its first tile into buf[0] are under way.  Two register buffers: the next tile's loads are in
+// flight while one is processed.  (With more buffers the scan is no faster, with four wavefronts per SIMD: two / three / four / five / seven of them, us per
+// compress and decompress: 25 M fp32 at 1 % 56.3 / 56.0 / 56.5 / 56.9 / 58, 26 M bf16 35.8 / 35.8 / 36.0 / 38 / 75.)
+// CLEARED: the window histogram is zero, and a barrier lies
+// between that and this (and all are done with the stage's LDS at the next one, the first tile's).  PAIR: leave
 // the two counts by which k_hist1 judges a speculative window.  `room`: the list's capacity, or 0 for no list, if the chunk's candidates
 // are known (listed_room) not to fit one; a speculative scan knows nothing yet.
-template <int VEC, bool PAIR, int DEPTH, bool SHARED, int NT>
-__device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32_t lo, uint32_t shw, uint32_t room,
-                                           uint32_t (&cur)[Stream<VEC, NT>::SLOTS], ScanLds &l) {
-    static_assert(DEPTH == 2 || DEPTH == 3, "one or two tiles ahead");
+template <int VEC, bool PAIR, bool RUNS, bool SHARED, bool CLEARED, int NT>
+__device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const Chunk<VEC, NT> &chunk, uint32_t lo, uint32_t shw, uint32_t room,
+                                           uint32_t (&buf)[2][Stream<VEC, NT>::SLOTS], ScanLds &l) {
     const SegDesc &sg = a.seg[s];
     using R = typename Raw<VEC>::type;
     using St = Stream<VEC, NT>;
-    const int64_t beg = static_cast<int64_t>(g - sg.chunk_begin) * sg.E;
-    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
-    const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
-    uint32_t nxt[St::SLOTS], far[St::SLOTS], valid[St::SLOTS];  // far: DEPTH 3 only
+    const int64_t beg = chunk.beg, end = chunk.end;
+    uint32_t valid[St::SLOTS];
     // Becomes 0 also when a dense tile makes the scan give the chunk's list up.  (Every speculating tensor has a sample: the
     // condition only keeps this count apart from the capacity.  Left equal to it at the start, the compiler spills a dozen
     // scalar registers more in the tile loop of the 16-bit scan: 26 M bf16 41.5 -> 42.3 us per compress and decompress.)
@@ -1402,71 +1441,44 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, uint32
 
     uint2 *stage = reinterpret_cast<uint2 *>(l.smem);
     uint32_t *hw = l.smem + 2 * STAGE_CAP;
-    __syncthreads();
-    for (int b = threadIdx.x; b < NBW; b += NT) hw[b] = 0;
-    __syncthreads();
+    if (!CLEARED) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < NBW; b += NT) hw[b] = 0;
+        __syncthreads();
+    }
 
     double acc = 0.0;
     uint32_t running = 0, flushed = 0;
     int wb = 0;
-    // Full tiles, the register buffers used in turn, unconditional loads in the loop, peeled tail (see
-    // hist1_full_tiles).
+    // The tiles, whole ones and the chunk's last: what lies behind its end reads as zeros, which are dropped and add nothing unless the
+    // window begins at key 0.  The register buffers are used in turn, with loads whatever the tile and no copies between them.
     int64_t t0 = beg;
-    int64_t rem = ntiles;
-    auto tile = [&](const uint32_t(&dw)[St::SLOTS]) {
-        scan_tile<VEC, true, DEPTH == 3, NT>(dw, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
-        t0 += TILE;
-        wb ^= 1;
-    };
-    if (DEPTH == 3) {
-        // cur holds the tile at t0; nxt the one behind it; far the one behind that
-        if (rem >= 2) St::load_fast(sg.x, t0 + TILE, nxt);
-        while (rem >= 5) {
-            St::load_fast(sg.x, t0 + 2 * static_cast<int64_t>(TILE), far);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(cur);
-            St::load_fast(sg.x, t0 + 2 * static_cast<int64_t>(TILE), cur);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(nxt);
-            St::load_fast(sg.x, t0 + 2 * static_cast<int64_t>(TILE), nxt);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(far);
-            rem -= 3;
-        }
-        if (rem >= 1) {  // one to four tiles left: cur is loaded, nxt is if there are two
-            if (rem >= 3) St::load_fast(sg.x, t0 + 2 * static_cast<int64_t>(TILE), far);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(cur);
-            if (rem >= 2) {
-                if (rem >= 4) St::load_fast(sg.x, t0 + 2 * static_cast<int64_t>(TILE), cur);
+    const uint32_t len = end > beg && (sg.flags & FLAG_ALIGNED4) ? static_cast<uint32_t>(end - beg) : 0u;
+    const uint32_t tiles = lo != 0 ? (len + TILE - 1) / TILE : len / TILE;
+    if (tiles != 0) {  // uniform
+        uint32_t t = 0;
+        for (bool more = true; more;) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                if (!more) break;
+                chunk.load(t + 1, buf[1 - b]);
                 __builtin_amdgcn_sched_barrier(0);
-                tile(nxt);
-                if (rem >= 3) tile(far);
-                if (rem >= 4) tile(cur);
+                if (St::EPD == 2 && t + 1 == tiles && (len & 1u)) {  // uniform: half a dword is left behind the whole ones
+                    const uint32_t last = static_cast<uint32_t>(static_cast<const R *>(sg.x)[end - 1]);
+#pragma unroll
+                    for (int e = 0; e < St::SLOTS; ++e)
+                        if (St::first_elem(t0, e / St::GD) + (e % St::GD) * St::EPD == end - 1) buf[b][e] = last;
+                }
+                scan_tile<VEC, true, RUNS, NT>(buf[b], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+                t0 += TILE;
+                wb ^= 1;
+                more = ++t != tiles;
             }
-        }
-    } else if (rem > 0) {
-        while (rem > 2) {
-            St::load_fast(sg.x, t0 + TILE, nxt);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(cur);
-            St::load_fast(sg.x, t0 + TILE, cur);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(nxt);
-            rem -= 2;
-        }
-        if (rem == 2) {
-            St::load_fast(sg.x, t0 + TILE, nxt);
-            __builtin_amdgcn_sched_barrier(0);
-            tile(cur);
-            tile(nxt);
-        } else {
-            tile(cur);
         }
     }
     for (; t0 < end; t0 += TILE, wb ^= 1) {
-        St::load_slow(sg.x, t0, end, cur, valid);
-        scan_tile<VEC, false, DEPTH == 3, NT>(cur, valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+        St::load_slow(sg.x, t0, end, buf[0], valid);
+        scan_tile<VEC, false, RUNS, NT>(buf[0], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
     }
     __syncthreads();
     flush_stage<VEC, NT>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
@@ -1497,9 +1509,9 @@ template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Lau
     return B < NB1 && candidates > list_cap(sg) ? 0u : list_cap(sg);  // (B = NB1: nothing is kept, nothing reaches the window)
 }
 
-template <int VEC, bool SPEC, int DEPTH>
-__global__ __launch_bounds__(DEPTH == 2 ? BLOCK : SCAN_THREADS, 4) void k_scan(Launch a) {
-    constexpr int NT = DEPTH == 2 ? BLOCK : SCAN_THREADS;
+template <int VEC, bool SPEC, bool ALONE>
+__global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch a) {
+    constexpr int NT = ALONE ? SCAN_THREADS : BLOCK;
     using St = Stream<VEC, NT>;
     __shared__ ScanLds l;
     static_assert(NSB <= SCAN_SMEM_WORDS && NC1 + FINE1 <= SCAN_SMEM_WORDS, "shared scratch fits");
@@ -1508,34 +1520,34 @@ __global__ __launch_bounds__(DEPTH == 2 ? BLOCK : SCAN_THREADS, 4) void k_scan(L
     const int s = find_segment(a, g);
     const SegDesc &sg = a.seg[s];
     const int c = g - sg.chunk_begin;
-    const int64_t beg = static_cast<int64_t>(c) * sg.E;
-    const int64_t end = (beg + sg.E < sg.n) ? beg + sg.E : sg.n;
     if (SPEC) {
         if (!(sg.flags & FLAG_SPEC)) return;  // this tensor goes straight to the exact passes
     } else {
         if (a.state[s].spec_held) return;     // the speculative pass did the work already
     }
 
-    // The first tile does not depend on the prologue: its loads are put in flight inside it, behind
-    // the prologue's first loads.
-    uint32_t cur[St::SLOTS];
-    const int64_t ntiles = (sg.flags & FLAG_ALIGNED4) ? (end - beg) / TILE : 0;
-    auto first_tile = [&]() {
-        if (ntiles > 0) St::load_fast(sg.x, beg, cur);
-    };
+    // The first tile does not depend on the prologue: its loads are put in flight inside it.
+    const Chunk<VEC, NT> chunk(sg, c);
+    uint32_t buf[2][St::SLOTS];
+    auto first_tile = [&]() { chunk.load(0, buf[0]); };
 
     uint32_t lo, shw, room = 0;
     if (SPEC) {
-        sample_window<VEC, NT>(sg, l.smem, l.sm, l.s_pick, first_tile, lo, shw);
-        if (c == 0) {  // the accumulators of the kernels that follow
-            for (int b = threadIdx.x; b < NB3; b += NT) a.G3[s * NB3 + b] = 0;
-            if (a.S == 1)
-                for (uint32_t b = threadIdx.x; b < sizeof(JudgeSync) / 4; b += NT) reinterpret_cast<uint32_t *>(judge_sync(a))[b] = 0;
-            if (threadIdx.x == 0) {
-                a.state[s].loA = lo;
-                a.state[s].shwA = shw;
-                a.state[s].failed = 0u;
+        static_assert(NSB <= 2 * STAGE_CAP, "the sample's histogram ends before the window's");
+        for (int b = threadIdx.x; b < NBW; b += NT) l.smem[2 * STAGE_CAP + b] = 0;
+        auto first_tile_and_clear = [&]() {
+            first_tile();
+            if (c == 0) {  // the accumulators of the kernels that follow
+                for (int b = threadIdx.x; b < NB3; b += NT) a.G3[s * NB3 + b] = 0;
+                if (a.S == 1)
+                    for (uint32_t b = threadIdx.x; b < sizeof(JudgeSync) / 4; b += NT) reinterpret_cast<uint32_t *>(judge_sync(a))[b] = 0;
             }
+        };
+        sample_window<VEC, NT>(sg, l.smem, l.sm, first_tile_and_clear, lo, shw);
+        if (c == 0 && threadIdx.x == 0) {
+            a.state[s].loA = lo;
+            a.state[s].shwA = shw;
+            a.state[s].failed = 0u;
         }
     } else {
         // The same in every workgroup of the tensor: bucket B1 of the k-th key from the rows of k_hist1
@@ -1552,7 +1564,7 @@ __global__ __launch_bounds__(DEPTH == 2 ? BLOCK : SCAN_THREADS, 4) void k_scan(L
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, DEPTH, false, NT>(a, s, g, lo, shw, room, cur, l);
+    scan_chunk<VEC, SPEC, ALONE, false, SPEC, NT>(a, s, g, chunk, lo, shw, room, buf, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -2446,7 +2458,7 @@ __device__ __forceinline__ bool exact_pass(int pass, uint32_t nchunks, Owned &o,
     uint32_t from = 0;
     for (uint32_t round = 0; round < args_again().wait_rounds; ++round) {
         const uint32_t to = o.count;  // uniform
-        for (uint32_t i = from; i < to; ++i) work(static_cast<uint32_t>(o.chunk[i]));
+        for (uint32_t i = from; i < to; ++i) work(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(o.chunk[i]))));
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every thread's stores have arrived ...
         __syncthreads();
         JudgeSync *sync = judge_sync(args_again());
@@ -2551,7 +2563,6 @@ struct JudgeLds {
 template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(JudgeLds &l, bool above) {
     const Launch &a0 = args_again();
     using St = Stream<VEC>;
-    constexpr int DEPTH = WIDE ? 3 : 2;  // see scan_chunk
     uint32_t *h = l.sl.smem;
     const uint32_t nchunks = static_cast<uint32_t>(a0.seg[0].nchunks);
     const uint32_t lo_list = a0.state[0].loA;  // where the lists start
@@ -2580,13 +2591,8 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
         }))
         return gave_up();
     // (the first tile of the first chunk does not depend on the bucket search: see k_scan)
-    uint32_t cur[St::SLOTS];
-    auto first_tile = [&](uint32_t c) {
-        const Launch &a = args_again();
-        const SegDesc &sg = a.seg[0];
-        const int64_t beg = static_cast<int64_t>(c) * sg.E;
-        if ((sg.flags & FLAG_ALIGNED4) && (beg + sg.E < sg.n ? sg.E : sg.n - beg) >= TILE) St::load_fast(sg.x, beg, cur);
-    };
+    uint32_t buf[2][St::SLOTS];
+    auto first_tile = [&](uint32_t c) { Chunk<VEC, BLOCK>(args_again().seg[0], static_cast<int>(c)).load(0, buf[0]); };
     const uint32_t first_chunk = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(l.own.chunk[0])));
     const Launch &a1 = args_again();
     const ColumnPick p1 = column_pick<NB1, NC1, 16>(a1.rows1, a1.coarse1, a1.seg[0].nchunks, static_cast<uint32_t>(a1.seg[0].k), h, [&]() { first_tile(first_chunk); });
@@ -2600,7 +2606,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
-                scan_chunk<VEC, false, DEPTH, true, BLOCK>(a, 0, ci, lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), cur, l.sl);
+                scan_chunk<VEC, false, WIDE, true, false, BLOCK>(a, 0, ci, Chunk<VEC, BLOCK>(a.seg[0], ci), lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), buf, l.sl);
             }
             __syncthreads();
         }))
@@ -3460,8 +3466,8 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
     if (speculate) {
-        if (one_per_cu) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, 3>, grid, st, a);
-        else launch(ST_SPEC, k_scan<VEC, true, 2>, grid, st, a);
+        if (one_per_cu) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, true>, grid, st, a);
+        else launch(ST_SPEC, k_scan<VEC, true, false>, grid, st, a);
     }
     const dim3 parts(a.parts);
     const bool wide = (one_per_cu && parts.x == grid.x) || no_lists;  // see Wide
@@ -3478,8 +3484,8 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         else if constexpr (VEC == TAG_F32) launch(ST_JUDGE, k_judge<VEC, false>, judges, st, a);
     } else {
         launch(ST_HIST1, k_hist1<VEC>, grid, st, a);
-        if (one_per_cu) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, 3>, grid, st, a);
-        else launch(ST_SCAN, k_scan<VEC, false, 2>, grid, st, a);
+        if (one_per_cu) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, true>, grid, st, a);
+        else launch(ST_SCAN, k_scan<VEC, false, false>, grid, st, a);
         if constexpr (VEC == TAG_F32) {  // the 16-bit types have no last digit to refine
             if (wide) launch(ST_REFINE, k_refine<VEC, true>, parts, st, a);
             else launch(ST_REFINE, k_refine<VEC, false>, parts, st, a);
