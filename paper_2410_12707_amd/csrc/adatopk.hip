@@ -48,7 +48,7 @@
 // the pairs into an existing tensor.
 //
 // Tensors of at most one register tile (8192 elements) skip all of the above: k_small selects
-// and writes one tensor per workgroup in a single launch.
+// and writes one tensor per workgroup in a single launch.  So does k_mid for up to 64 K elements, with a compute unit for each tensor.
 //
 // Outputs can be laid out as one wire message (header, indices, values); indices are stored as
 // int32 or, for the paper's own accounting (Sec. 5.2), int64.
@@ -449,6 +449,17 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     v += dpp<DPP_BCAST31>(v, 0u);
     return v;
 }
+// The largest of the wavefront, in lane 63.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    auto with = [&](uint32_t o) { v = o > v ? o : v; };
+    with(dpp<DPP_SHR1>(v, 0u));
+    with(dpp<DPP_SHR2>(v, 0u));
+    with(dpp<DPP_SHR4>(v, 0u));
+    with(dpp<DPP_SHR8>(v, 0u));
+    with(dpp<DPP_BCAST15>(v, 0u));
+    with(dpp<DPP_BCAST31>(v, 0u));
+    return v;
+}
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {  // lane: the same in all lanes
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
 }
@@ -502,8 +513,8 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     v += dpp<DPP_BCAST31>(v);
     return v;
 }
-// Block sum of doubles in a fixed order (same grouping every run).  sm holds NW doubles.
-__device__ __forceinline__ double block_sum_f64(double v, double *sm) {
+// Block sum of doubles in a fixed order (same grouping every run).  sm holds WAVES doubles.
+template <int WAVES = NW> __device__ __forceinline__ double block_sum_f64(double v, double *sm) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     v = wave_sum_f64(v);
     __syncthreads();
@@ -511,7 +522,7 @@ __device__ __forceinline__ double block_sum_f64(double v, double *sm) {
     __syncthreads();
     double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) s += sm[i];
+    for (int i = 0; i < WAVES; ++i) s += sm[i];
     return s;
 }
 
@@ -1189,6 +1200,34 @@ constexpr uint32_t SAMPLE_SKEW = 32;   // runs: the sample's runs are shifted by
 // for 64 bytes, 0.4 us for 4.9 M values, 1.5 for 25 M.
 constexpr int32_t SAMPLE_FINE_BELOW = 1 << 20;
 constexpr int SAMPLE_BATCH = 16;  // dwords per thread and batch with BLOCK threads; the host picks 1, 2 or 4 batches (fp32: 8192 elements each)
+// The bins of h[NSB] in LDS that hold two ranks counted from the largest key, the first rank not below the second; NSB: no bin does (as for rank 0).
+// Only bins `lowest` to `top` have counts.  Every wavefront looks for itself, four bins to
+// a lane, from the top downwards: 256 bins are 16 binades, so it rarely looks twice, and nobody waits for a
+// barrier (block-wide suffix sums and the two threads that found a rank took 0.9 us, this 0.3).
+struct RankedBins {
+    uint32_t lo, hi;
+};
+__device__ __forceinline__ RankedBins ranked_bins(const uint32_t *h, uint32_t top, uint32_t lowest, uint32_t rank_lo, uint32_t rank_hi) {
+    RankedBins found = {NSB, NSB};
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t above = 0;  // counted keys in the bins looked at so far
+    for (uint32_t base = top & ~255u;; base -= 256) {
+        const uint4 c = reinterpret_cast<const uint4 *>(h)[base / 4 + lane];
+        const uint32_t own = c.x + c.y + c.z + c.w, inc = wave_incl_scan(own), total = lane_value(inc, 63);
+        const uint32_t higher = above + total - inc;  // ... and in those of the lanes after this one
+        auto pick = [&](uint32_t rank, uint32_t &bin) {
+            const uint64_t here = __ballot(higher < rank && higher + own >= rank);
+            if (here == 0) return;  // uniform
+            const int l = __builtin_ctzll(here);
+            const uint32_t w3 = lane_value(higher, l) + lane_value(c.w, l), w2 = w3 + lane_value(c.z, l), w1 = w2 + lane_value(c.y, l);
+            bin = base + 4 * l + (w3 >= rank ? 3u : (w2 >= rank ? 2u : (w1 >= rank ? 1u : 0u)));
+        };
+        pick(rank_lo, found.lo);
+        pick(rank_hi, found.hi);
+        above += total;
+        if (above >= rank_lo || base <= lowest) return found;
+    }
+}
 // Byte offset of the sample bin (4 * (key >> SAMPLE_SH)) of element hh of a dword.
 template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword, int hh) {
     static_assert(SAMPLE_SH == 19, "the shifts below");
@@ -1319,33 +1358,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
             }
     }
     __syncthreads();
-    // The bins that hold two ranks, the first one the larger number, or NSB (also for rank 0).  Every wavefront looks for itself, four bins to
-    // a lane, from the largest sampled key downwards: 256 bins are 16 binades, so it rarely looks twice, and nobody waits for a
-    // barrier (block-wide suffix sums and the two threads that found a rank took 0.9 us, this 0.3).
-    struct Bins {
-        uint32_t lo, hi;
-    };
-    auto find = [&](uint32_t rank_lo, uint32_t rank_hi) {
-        Bins found = {NSB, NSB};
-        uint32_t above = 0;  // counted keys in the bins looked at so far
-        for (uint32_t base = top & ~255u;; base -= 256) {
-            const uint4 c = hs4[base / 4 + lane];
-            const uint32_t own = c.x + c.y + c.z + c.w, inc = wave_incl_scan(own), total = lane_value(inc, 63);
-            const uint32_t higher = above + total - inc;  // ... and in those of the lanes after this one
-            auto pick = [&](uint32_t rank, uint32_t &bin) {
-                const uint64_t here = __ballot(higher < rank && higher + own >= rank);
-                if (here == 0) return;  // uniform
-                const int l = __builtin_ctzll(here);
-                const uint32_t w3 = lane_value(higher, l) + lane_value(c.w, l), w2 = w3 + lane_value(c.z, l), w1 = w2 + lane_value(c.y, l);
-                bin = base + 4 * l + (w3 >= rank ? 3u : (w2 >= rank ? 2u : (w1 >= rank ? 1u : 0u)));
-            };
-            pick(rank_lo, found.lo);
-            pick(rank_hi, found.hi);
-            above += total;
-            if (above >= rank_lo || base * 4 <= floor_bin) return found;
-        }
-    };
-    const Bins bins = find(r_lo, r_hi);
+    const RankedBins bins = ranked_bins(hs, top, floor_bin / 4, r_lo, r_hi);
     lo = bins.lo < NSB ? bins.lo << SAMPLE_SH : 0u;
     const uint32_t hi = bins.hi < NSB ? (bins.hi + 1u) << SAMPLE_SH : 0x80000000u;  // first key above the bracket
     // fp32: a bracket wider than a window can span (keys that are thin around the k-th: a tensor that is mostly zeros, heavy tails at
@@ -1355,7 +1368,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     constexpr uint32_t SPAN = (NBW - 1) << BITS3;
     if (VEC == TAG_F32 && bins.lo < NSB && hi > lo && hi - lo > SPAN) {
         const uint32_t rank = (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie SPEC_SIGMAS_LOW and SPEC_SIGMAS from it, and both have been found)
-        const uint32_t middle = (find(rank, 0).lo << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
+        const uint32_t middle = (ranked_bins(hs, top, floor_bin / 4, rank, 0).lo << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
         if (middle > lo + SPAN / 2) lo = middle - SPAN / 2;
     }
     // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow, the least shift that makes NBW - 1 bins
@@ -2756,7 +2769,7 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_keep_all(Launch a)
 // 95 % 16.8 / 12.5, sorted 10 % 21.1 / 12.4, all equal 21.1 / 14.2.
 // (All three digits and the placing over all elements, loads clamped and masked one by one: 12.2 us for 128 tensors of 1 to 8 K
 // fp32 values, now 7.2.)
-// Tensors beyond one register tile stay with the four-kernel path, which spreads them over many compute units.
+// Tensors beyond one register tile: k_mid below, or the four-kernel path, which spreads them over many compute units.
 constexpr int SMALL_EPT = 128 / NW;            // elements per thread (16 with 512 threads)
 constexpr int SMALL_N = BLOCK * SMALL_EPT;     // largest tensor this path takes
 constexpr int SMALL_MAXSEG = 128;              // tensors per launch (the table travels as kernel arguments)
@@ -2787,8 +2800,8 @@ constexpr int SMALL_SEGMENT = 64 * SMALL_EPT;  // of the list, for one wavefront
 struct SmallPick {
     uint32_t B, above, here;
 };
-template <int NB> __device__ __forceinline__ SmallPick small_pick(const uint32_t *h, uint32_t krem, uint32_t *sm, SmallPick *pick) {
-    constexpr int PER = NB / BLOCK;
+template <int NB, int NT = BLOCK> __device__ __forceinline__ SmallPick small_pick(const uint32_t *h, uint32_t krem, uint32_t *sm, SmallPick *pick) {
+    constexpr int PER = NB / NT;
     if (threadIdx.x == 0) *pick = SmallPick{0, 0, 0};  // (counts that do not add up)
     __syncthreads();
     uint32_t cnt[PER], own = 0;
@@ -2798,7 +2811,7 @@ template <int NB> __device__ __forceinline__ SmallPick small_pick(const uint32_t
         own += cnt[j];
     }
     uint32_t total;
-    const uint32_t inc = block_incl_scan(own, sm, &total);
+    const uint32_t inc = block_incl_scan<NT / 64>(own, sm, &total);
     uint32_t higher = total - inc;  // counts of the threads after this one
 #pragma unroll
     for (int j = PER - 1; j >= 0; --j) {
@@ -2813,7 +2826,7 @@ template <int NB> __device__ __forceinline__ SmallPick small_pick(const uint32_t
 // cycles): a wavefront half of whose first slot falls into the bin of a lane in its middle adds through hist_add, any other every lane
 // for itself.  (Of the first lane: in sorted tensors a bin often begins between it and the next.)  RUNS: nearly equal ones
 // are counted as a run; the code of that slows down tensors that do not use it, so it is not for the pass that they all make.
-template <bool RUNS, typename In, typename Bin> __device__ __forceinline__ void small_count(uint32_t *h, int slots, In &&in, Bin &&bin) {
+template <bool RUNS, int SLOTS = SMALL_EPT, typename In, typename Bin> __device__ __forceinline__ void small_count(uint32_t *h, int slots, In &&in, Bin &&bin) {
     const uint32_t first = bin(0);
     const bool is = in(0);
     const int alike = __popcll(__ballot(is & (first == static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(first), 31)))));
@@ -2821,13 +2834,13 @@ template <bool RUNS, typename In, typename Bin> __device__ __forceinline__ void 
     if (RUNS && alike >= 56) {
         BinRun run;
 #pragma unroll
-        for (int e = 0; e < SMALL_EPT; ++e)
+        for (int e = 0; e < SLOTS; ++e)
             if (e < slots) run.add(h, bin(e), in(e));
         run.flush(h);
         return;
     }
 #pragma unroll
-    for (int e = 0; e < SMALL_EPT; ++e)
+    for (int e = 0; e < SLOTS; ++e)
         if (e < slots) {  // wave-uniform
             const uint32_t b = bin(e);
             if (skewed) hist_add(h, b, in(e));
@@ -2835,32 +2848,12 @@ template <bool RUNS, typename In, typename Bin> __device__ __forceinline__ void 
         }
 }
 
-// The rest of a small tensor's selection, over entries in index order (candidates in a list, or all elements in registers).
-// count(in, bin): the bins of the raw patterns that `in` names, into h.  each(f): f(index, raw pattern, whether there is such an entry)
-// slot by slot; the wavefronts' entries follow one another.  h is all zeros in its first NB2 words, which every thread sees.
-// top: the pick of the top digit; kout >= 1 keys are kept.  Returns this thread's share of the squares of the dropped entries.
-template <int VEC, typename Count, typename Each>
-__device__ __forceinline__ double small_select(Count &&count, Each &&each, const SmallPick &top, uint32_t kout, const OutPtrs &op, bool wide,
-                                               uint32_t *h, uint32_t *sm, SmallPick *s_pick) {
+// The placing of entries in index order: those with a key above T, and the first q of those equal to T, of which there are kout in all.  each: see
+// small_select.  sm: WAVES words that nobody reads any more.  Returns this thread's share of the squares of the dropped entries.
+template <int VEC, int WAVES = NW, typename Each>
+__device__ __forceinline__ double place_entries(Each &&each, uint32_t T, uint32_t q, uint32_t kout, const OutPtrs &op, bool wide, uint32_t *sm) {
     using R = typename Raw<VEC>::type;
-    static_assert(NB2 == 2 * BLOCK && NB3 == 2 * BLOCK, "two words per thread");
-    // T and the number of keys above it, from the digits below the first
-    count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH1 == top.B; }, [&](uint32_t raw) { return (key_of<VEC>(raw) >> SH2) & (NB2 - 1); });
-    const SmallPick second = small_pick<NB2>(h, kout - top.above, sm, s_pick);
-    uint32_t c_gt = top.above + second.above;
-    const uint32_t P = (top.B << BITS2) | second.B;
-    uint32_t T = P << BITS3;
-    if (VEC == TAG_F32) {  // (a 16-bit pattern ends within the second digit)
-        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);  // (read by everybody: small_pick synchronises behind that)
-        __syncthreads();
-        count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH2 == P; }, [&](uint32_t raw) { return key_of<VEC>(raw) & (NB3 - 1); });
-        const SmallPick third = small_pick<NB3>(h, kout - c_gt, sm, s_pick);
-        c_gt += third.above;
-        T |= third.B;
-    }
-    const uint32_t q = kout - c_gt;
-
-    // The placing: the wavefronts' counts above and equal to T, two 16-bit counts in a word (the sums in sm have been read).
+    // the wavefronts' counts above and equal to T, two 16-bit counts in a word
     uint32_t mine = 0;
     each([&](uint32_t, uint32_t raw, bool in) {
         const uint32_t key = key_of<VEC>(raw);
@@ -2869,7 +2862,7 @@ __device__ __forceinline__ double small_select(Count &&count, Each &&each, const
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = mine;
     __syncthreads();
     uint32_t before, all;
-    wave_counts(sm, before, all);
+    wave_counts<WAVES>(sm, before, all);
     uint32_t run_eq = before >> 16, run = (before & 0xFFFFu) + (run_eq < q ? run_eq : q);  // equal to T, and kept, before this slot
     double acc = 0.0;
     each([&](uint32_t index, uint32_t raw, bool in) {
@@ -2892,6 +2885,33 @@ __device__ __forceinline__ double small_select(Count &&count, Each &&each, const
         acc = fma(v, v, acc);
     });
     return acc;
+}
+
+// The rest of a small tensor's selection, over entries in index order (candidates in a list, or all elements in registers).
+// count(in, bin): the bins of the raw patterns that `in` names, into h.  each(f): f(index, raw pattern, whether there is such an entry)
+// slot by slot; the wavefronts' entries follow one another.  h is all zeros in its first NB2 words, which every thread sees.
+// top: the pick of the top digit; kout >= 1 keys are kept.  Returns this thread's share of the squares of the dropped entries.
+template <int VEC, typename Count, typename Each>
+__device__ __forceinline__ double small_select(Count &&count, Each &&each, const SmallPick &top, uint32_t kout, const OutPtrs &op, bool wide,
+                                               uint32_t *h, uint32_t *sm, SmallPick *s_pick) {
+    static_assert(NB2 == 2 * BLOCK && NB3 == 2 * BLOCK, "two words per thread");
+    // T and the number of keys above it, from the digits below the first
+    count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH1 == top.B; }, [&](uint32_t raw) { return (key_of<VEC>(raw) >> SH2) & (NB2 - 1); });
+    const SmallPick second = small_pick<NB2>(h, kout - top.above, sm, s_pick);
+    uint32_t c_gt = top.above + second.above;
+    const uint32_t P = (top.B << BITS2) | second.B;
+    uint32_t T = P << BITS3;
+    if (VEC == TAG_F32) {  // (a 16-bit pattern ends within the second digit)
+        reinterpret_cast<uint2 *>(h)[threadIdx.x] = make_uint2(0, 0);  // (read by everybody: small_pick synchronises behind that)
+        __syncthreads();
+        count([&](uint32_t raw) { return key_of<VEC>(raw) >> SH2 == P; }, [&](uint32_t raw) { return key_of<VEC>(raw) & (NB3 - 1); });
+        const SmallPick third = small_pick<NB3>(h, kout - c_gt, sm, s_pick);
+        c_gt += third.above;
+        T |= third.B;
+    }
+    const uint32_t q = kout - c_gt;
+
+    return place_entries<VEC>(each, T, q, kout, op, wide, sm);
 }
 
 template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallLaunch a) {
@@ -3004,6 +3024,505 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
     }
     if (err != nullptr) {
         const double tot = block_sum_f64(acc, smd);
+        if (threadIdx.x == 0) *err = static_cast<float>(sqrt(tot));
+    }
+}
+
+// ------------------------------------------------------------------ tensors of up to 64 K elements: one launch
+// Four dependent launches, each of a few microseconds whatever the size, are what such a tensor takes on the path for larger ones.
+// Here one workgroup of 1024 threads does the whole selection, the tensor in its registers, up to 64 elements per thread; every tensor of the launch has a
+// compute unit.  What bounds it is the number of instructions per element (one compute unit issues 2 ns of them per 64 elements), so only two passes look
+// at all:
+//   - the largest of every thread's elements (or of 4 or 16 parts of them, where more is kept).  The k-th largest of these maxima bounds the
+//     k-th key from below, whatever the values are, and closely: of 65 536 normal values at 1 % kept 1.6 % reach it.  It is found
+//     in a histogram of the maxima, to a sixteenth of a binade;
+//   - the candidates, which reach the bound, into a list in LDS, a segment for each wavefront, in index order, and into a histogram over their keys; the
+//     squares of the others.
+// The k-th key's bin holds a few candidates, which are compared with one another, or settled by further digits if they are more.  Where a segment is
+// too short (sorted values, equal keys, a large keep share), keys are much alike or fewer than k elements are not zero, the elements are read again,
+// and one list without segments is made: of the same candidates, or of those that reach a closer bound, or of the keys above the threshold and enough
+// of those equal to it.
+constexpr int MID_THREADS = 1024, MID_WAVES = MID_THREADS / 64, MID_GROUPS = 16, MID_GE = 4;  // groups per wavefront, elements per lane and group
+constexpr int MID_N = MID_THREADS * MID_GE * MID_GROUPS;  // largest tensor this path takes
+constexpr uint32_t MID_SEGMENT = 1024;                    // candidates of a wavefront that have room in its part of the list
+constexpr uint32_t MID_LIST = MID_WAVES * MID_SEGMENT;
+constexpr int MID_FIRST_BITS = 11, MID_FIRST = 1 << MID_FIRST_BITS;  // bins over the candidates' keys
+constexpr int MID_DIGIT_BITS = 12, MID_DIGIT = 1 << MID_DIGIT_BITS;  // further digits
+constexpr int MID_MAXSEG = 96;                            // tensors per launch (the table travels as kernel arguments)
+// Which tensors take this path.  It takes about 6 us, 0.1 for 1024 elements more and 1.4 for 1024 kept ones; the launches of the path for larger tensors 18 to 20
+// whatever the sizes, and more for a batch that fills the chip.  Where the list is made a second time (sorted values, equal keys) it is 5 to 16 us more,
+// for tensors whose keys are all within a few per cent of each other 40, so short calls stay well below the limit where the two cross.  GPU us of a compress call,
+// larger tensors' path / so: one fp32 tensor, 1 % kept, 9000 values 18.2 / 6.6, 32 768 18.6 / 8.7, 65 536 19.0 / 12.3 (sorted 19.6 / 27.8, equal 21.7 / 25.0);
+// 20 % kept, 9000 18.9 / 9.3, 32 768 19.4 / 17.6; 64 of 8 to 64 K at 1 % 21.7 / 13.1, 64 of 64 K 27.8 / 13.4, 24 of 60 000 at 5 % 21.2 / 18.0, 256 of 30 000 at 2 %
+// 99 / 32; bf16, one of 9000 14.5 / 6.6, two of 40 000 16.5 / 9.8.  (A single 16-bit tensor that speculates takes two launches, 12 us, and stays there.)
+constexpr int64_t MID_WORK = 1 << 17, MID_WORK_SHORT = 1 << 16, MID_SHORT_CALL = 1 << 20;
+inline bool mid_takes(int64_t n, int64_t k, int64_t n_total) {
+    return n <= MID_N && k <= n / 4 && n + 13 * k <= (n_total < MID_SHORT_CALL ? MID_WORK_SHORT : MID_WORK);
+}
+static_assert(MID_WORK / 13 + 64 * MID_GE * MID_GROUPS <= MID_LIST, "k and the ties of a wavefront fit the list");
+struct MidDesc {
+    const void *x;
+    int64_t out_off;
+    double ratio;  // wire mode: goes into the message's header
+    uint32_t n, k;
+};
+struct MidLaunch {
+    MidDesc seg[MID_MAXSEG];
+    SegState *state;
+    void *idx_out;
+    void *val_out;
+    float *err_out;
+    uint32_t idx64;
+    uint32_t wire;
+};
+static_assert(sizeof(MidLaunch) <= 4096, "kernel arguments stay within 4 KB");
+
+// Keys in this path: the bits without the sign, 15 of them for the 16-bit types.
+template <int VEC> __device__ __forceinline__ uint32_t mid_key(uint32_t raw) { return raw & (VEC == TAG_F32 ? 0x7FFFFFFFu : 0x7FFFu); }
+
+// The krem-th largest key of those in [base, base + 2^bits), digit by digit, and the number of keys above it in there.  count(base, bits, shift) adds
+// the keys of that range to the bins (key - base) >> shift of h.
+struct MidPick {
+    uint32_t T, above;
+};
+template <typename Count>
+__device__ __forceinline__ MidPick mid_digits(Count &&count, uint32_t base, uint32_t bits, uint32_t krem, uint32_t *h, uint32_t *sm, SmallPick *s_pick) {
+    static_assert(MID_DIGIT == 4 * MID_THREADS && MID_DIGIT == NSB, "four bins per thread");
+    uint32_t above = 0;
+    while (bits != 0) {  // uniform
+        const uint32_t shift = bits > MID_DIGIT_BITS ? bits - MID_DIGIT_BITS : 0;
+        reinterpret_cast<uint4 *>(h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        count(base, bits, shift);
+        const SmallPick p = small_pick<MID_DIGIT, MID_THREADS>(h, krem - above, sm, s_pick);
+        base += p.B << shift;
+        above += p.above;
+        bits = shift;
+    }
+    return MidPick{base, above};
+}
+
+struct MidLds {
+    __attribute__((aligned(16))) uint32_t h[NSB];        // of the maxima, then of a digit
+    __attribute__((aligned(16))) uint32_t first[MID_FIRST];  // of the candidates' keys
+    uint2 list[MID_WAVES][MID_SEGMENT];                  // (index, raw pattern)
+    uint32_t sm[3][MID_WAVES];
+    double smd[MID_WAVES];
+    uint32_t few[64], nfew;                              // the keys of one bin
+    SmallPick s_pick;
+};
+
+template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const MidLaunch a) {
+    using R = typename Raw<VEC>::type;
+    constexpr int EPD = VEC / 4, GD = MID_GE / EPD;  // elements per dword, dwords per lane and group
+    constexpr uint32_t SH = VEC == TAG_F32 ? SAMPLE_SH : SAMPLE_SH - 16;  // key >> SH: the bin of a maximum
+    __shared__ MidLds l;
+
+    const MidDesc &sg = a.seg[blockIdx.x];
+    const uint32_t n = sg.n, kout = sg.k;
+    const R *x = static_cast<const R *>(sg.x);
+    const uint32_t lane = threadIdx.x & 63, w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    // The tensor's groups of 256 elements, four to a lane, dealt out to the wavefronts in runs.
+    constexpr uint32_t GROUP = 64 * MID_GE;
+    const uint32_t all_groups = (n + GROUP - 1) / GROUP, g0 = w * all_groups / MID_WAVES, groups = (w + 1) * all_groups / MID_WAVES - g0;
+    const uint32_t i0 = g0 * GROUP + lane * MID_GE;  // this lane's first element; that of its group j is i0 + j * GROUP
+
+    // Behind the tensor's last whole dword there are zeros (Stream::bounded).
+    const __amdgpu_buffer_rsrc_t bytes = Stream<VEC>::bounded(x, static_cast<uint32_t>(n * sizeof(R)) & ~3u);
+    auto load = [&](uint32_t i, uint32_t(&d)[GD]) {  // elements i .. i + 3
+        if constexpr (GD == 4) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b128(bytes, static_cast<int>(i * sizeof(R)), 0, 0);
+#pragma unroll
+            for (int h = 0; h < GD; ++h) d[h] = q[h];
+        } else {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(bytes, static_cast<int>(i * sizeof(R)), 0, 0);
+#pragma unroll
+            for (int h = 0; h < GD; ++h) d[h] = q[h];
+        }
+    };
+    auto with_last = [&](uint32_t i, uint32_t(&d)[GD], uint32_t last) {  // half a dword is left
+#pragma unroll
+        for (int h = 0; h < GD; ++h) d[h] = i + h * EPD == n - 1 ? last : d[h];
+    };
+    const bool half_left = EPD == 2 && (n & 1u);  // uniform
+    // One round of loads.
+    uint32_t v[MID_GROUPS][GD];
+#pragma unroll
+    for (uint32_t j = 0; j < MID_GROUPS; ++j)
+        if (j < groups) {  // wave-uniform
+            load(i0 + j * GROUP, v[j]);
+        } else {
+#pragma unroll
+            for (int d = 0; d < GD; ++d) v[j][d] = 0;
+        }
+    if (half_left) {
+        const uint32_t last = static_cast<uint32_t>(x[n - 1]);
+#pragma unroll
+        for (uint32_t j = 0; j < MID_GROUPS; ++j)
+            if (j < groups) with_last(i0 + j * GROUP, v[j], last);
+    }
+    auto raw = [&](int j, int e) { return elem_of<VEC>(v[j][e / EPD], e % EPD); };
+    reinterpret_cast<uint4 *>(l.h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+    reinterpret_cast<uint2 *>(l.first)[threadIdx.x] = make_uint2(0, 0);
+    static_assert(NSB == 4 * MID_THREADS && MID_FIRST == 2 * MID_THREADS, "four bins per thread, and two");
+    if (threadIdx.x == 0) l.nfew = 0;
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.state[0].spec_held = a.state[0].failed = 0u;  // (no window was guessed)
+
+    const bool wide = a.idx64 != 0;
+    const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, kout, wide, a.wire != 0, sizeof(R));
+    double acc = 0.0;
+    // The bound: of `parts` maxima per thread.  With a part's elements alike in number, a share s of the maxima that reach it leaves about
+    // -ln(1 - s) / s times k candidates.
+    uint32_t lo = 0xFFFFFFFFu, largest = 0;
+    bool skewed = false;
+    if (kout != 0) {  // uniform
+        uint32_t m[MID_GROUPS];  // the largest of each group's four
+#pragma unroll
+        for (int j = 0; j < MID_GROUPS; ++j) {
+            m[j] = mid_key<VEC>(raw(j, 0));
+#pragma unroll
+            for (int e = 1; e < MID_GE; ++e) {
+                const uint32_t key = mid_key<VEC>(raw(j, e));
+                m[j] = key > m[j] ? key : m[j];
+            }
+        }
+        uint32_t quarter[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            quarter[j] = m[j];
+#pragma unroll
+            for (int i = j + 4; i < MID_GROUPS; i += 4) quarter[j] = m[i] > quarter[j] ? m[i] : quarter[j];
+            largest = quarter[j] > largest ? quarter[j] : largest;
+        }
+        // (64 lanes that count on one word take 440 cycles: a wavefront half of whose keys are alike takes those together, and nothing is listed in segments)
+        skewed = __popcll(__ballot(m[0] >> SH == lane_value(m[0], 31) >> SH)) >= 32 && groups != 0;
+        auto count = [&](uint32_t key) {
+            if (skewed) hist_add(l.h, key >> SH, key >> SH != 0);  // (zeros need not be counted)
+            else if (key >> SH) atomicAdd(&l.h[key >> SH], 1u);
+        };
+        if (kout <= MID_THREADS * 5 / 8) {  // uniform
+            count(largest);
+        } else if (kout <= 4 * MID_THREADS * 5 / 8) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) count(quarter[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < MID_GROUPS; ++j)
+                if (j < static_cast<int>(groups)) count(m[j]);
+        }
+        largest = wave_max(largest);
+        if (lane == 63) {
+            l.sm[0][w] = largest;
+            l.sm[2][w] = skewed ? 1u : 0u;
+        }
+        __syncthreads();
+        skewed = __ballot(l.sm[2][lane & (MID_WAVES - 1)] != 0) != 0;  // uniform from here on: any wavefront's
+        largest = l.sm[0][lane & (MID_WAVES - 1)];
+        largest = wave_max(largest);
+        largest = lane_value(largest, 63);
+        const uint32_t bin = ranked_bins(l.h, largest >> SH, 0, kout, 0).lo;
+        lo = bin < NSB ? bin << SH : 1u;  // (fewer than k maxima that are not zero)
+    }
+
+    // The candidates.  (What lies behind the tensor's end is zero, no candidate, and adds nothing.)
+    const uint32_t bits = largest > lo ? 32u - static_cast<uint32_t>(__builtin_clz(largest - lo)) : 0u;  // (not used if nothing is kept)
+    const uint32_t shift = bits > MID_FIRST_BITS ? bits - MID_FIRST_BITS : 0u;
+    uint2 *segment = l.list[w];
+    uint32_t own = 0;  // of this wavefront
+    uint32_t before = 0, candidates = 0;
+    constexpr uint32_t NO_ROOM = 1u << 20;  // beyond the number of elements
+    if (__builtin_expect(!skewed, 1)) {
+#pragma unroll
+        for (int j = 0; j < MID_GROUPS; ++j)
+            if (j < static_cast<int>(groups)) {  // wave-uniform
+                const uint32_t i = i0 + j * GROUP;
+                bool keep[MID_GE];
+                uint64_t b[MID_GE];
+#pragma unroll
+                for (int e = 0; e < MID_GE; ++e) {
+                    keep[e] = mid_key<VEC>(raw(j, e)) >= lo;
+                    b[e] = __ballot(keep[e]);
+                    float xs = keep[e] ? 0.0f : value_of<VEC>(raw(j, e));
+                    asm("" : "+v"(xs));  // (see scan_tile)
+                    const double xd = static_cast<double>(xs);
+                    acc = fma(xd, xd, acc);
+                }
+                auto put = [&](uint32_t pos, uint32_t index, uint32_t r) {
+                    segment[pos] = make_uint2(index, r);
+                    atomicAdd(&l.first[(mid_key<VEC>(r) - lo) >> shift], 1u);
+                };
+                const uint64_t first = b[0] | b[1], second = b[2] | b[3], any = first | second;
+                if (any == 0) continue;                                         // wave-uniform, as what follows
+                if (((b[0] & b[1]) | (b[2] & b[3]) | (first & second)) == 0) {  // one per lane at most (see scan_tile)
+                    const bool front = keep[0] | keep[1], odd = keep[1] | keep[3];
+                    const uint32_t r = front ? (keep[0] ? raw(j, 0) : raw(j, 1)) : (keep[2] ? raw(j, 2) : raw(j, 3));
+                    const uint32_t more = static_cast<uint32_t>(__popcll(any));
+                    if (own + more <= MID_SEGMENT && (front | keep[2] | keep[3])) put(lanes_below_plus(any, own), i + (front ? 0u : 2u) + (odd ? 1u : 0u), r);
+                    own += more;
+                } else {
+                    uint32_t pos = own;
+#pragma unroll
+                    for (int e = 0; e < MID_GE; ++e) {
+                        pos = lanes_below_plus(b[e], pos);
+                        own += static_cast<uint32_t>(__popcll(b[e]));
+                    }
+                    if (own <= MID_SEGMENT) {
+#pragma unroll
+                        for (int e = 0; e < MID_GE; ++e) {
+                            if (keep[e]) put(pos, i + e, raw(j, e));
+                            pos += keep[e] ? 1u : 0u;
+                        }
+                    }
+                }
+            }
+        if (lane == 0) l.sm[1][w] = own <= MID_SEGMENT ? own : own | NO_ROOM;
+        __syncthreads();
+        wave_counts<MID_WAVES>(l.sm[1], before, candidates);
+    }
+    const bool segments = !skewed && candidates < NO_ROOM;
+    before &= NO_ROOM - 1;
+    candidates &= NO_ROOM - 1;
+    if (__builtin_expect(kout != 0 && (!segments || candidates < kout), 0)) {  // uniform
+        // The elements once more, GROUPS of a lane's at a time: f(first index, raw patterns) group by group.  (Read again: kept, they and what the passes
+        // derive from them take more registers than there are.)
+        constexpr uint32_t AT_ONCE = 8;
+        auto each_group = [&](auto &&f) {
+#pragma unroll 1
+            for (uint32_t j0 = 0; j0 < groups; j0 += AT_ONCE) {
+                uint32_t d[AT_ONCE][GD];
+#pragma unroll
+                for (uint32_t j = 0; j < AT_ONCE; ++j) load(i0 + (j0 + j) * GROUP, d[j]);
+#pragma unroll
+                for (uint32_t j = 0; j < AT_ONCE; ++j)
+                    if (j0 + j < groups) {  // wave-uniform
+                        const uint32_t i = i0 + (j0 + j) * GROUP;
+                        if (half_left) with_last(i, d[j], static_cast<uint32_t>(x[n - 1]));
+                        uint32_t r[MID_GE];
+#pragma unroll
+                        for (int e = 0; e < MID_GE; ++e) r[e] = elem_of<VEC>(d[j][e / EPD], e % EPD);
+                        f(i, r);
+                    }
+            }
+        };
+        uint2 *list = l.list[0];
+        uint32_t total = candidates, from = lo;
+        MidPick t{0, candidates};
+        // (the same candidates; the threshold is to be found among them)
+        bool digits = !skewed && candidates >= kout && candidates <= MID_LIST;
+        if (!digits) {
+            // Equal keys, sorted values: an element of every fourth group in all lanes says what the k-th key may be, and a bound that is closer.
+            uint32_t guess = 0, bound = 0;  // (fewer than k are not zero: then zero is the threshold)
+            if (skewed || candidates >= kout) {
+                constexpr int EACH = 4;
+                uint32_t *sample = reinterpret_cast<uint32_t *>(list) + threadIdx.x;
+                uint32_t taken = 0;  // by this wavefront, per lane
+#pragma unroll
+                for (int j = 0; j < MID_GROUPS; j += EACH)
+                    if (j < static_cast<int>(groups)) {
+                        uint32_t d[GD];
+                        load(i0 + j * GROUP, d);
+                        sample[taken * MID_THREADS] = mid_key<VEC>(elem_of<VEC>(d[0], 0));
+                        ++taken;
+                    }
+                __syncthreads();  // (all are done with h and sm)
+                reinterpret_cast<uint4 *>(l.h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+                if (threadIdx.x == 0) l.few[0] = 0;
+                if (lane == 0) l.sm[0][w] = taken;
+                __syncthreads();
+#pragma unroll 1
+                for (uint32_t i = 0; i < taken; ++i) {
+                    const uint32_t bin = sample[i * MID_THREADS] >> SH;
+                    hist_add(l.h, bin, bin != 0);
+                }
+                uint32_t unused, rows;
+                wave_counts<MID_WAVES>(l.sm[0], unused, rows);
+                __syncthreads();
+                const uint32_t expected = static_cast<uint32_t>((static_cast<uint64_t>(kout) * rows * 64 + n - 1) / n);
+                const RankedBins at = ranked_bins(l.h, largest >> SH, 0, expected + static_cast<uint32_t>(4.0f * sqrtf(static_cast<float>(expected))) + 2, expected);
+                uint32_t most = 0;
+#pragma unroll 1
+                for (uint32_t i = 0; i < taken; ++i) {
+                    const uint32_t key = sample[i * MID_THREADS];
+                    most = key >> SH == at.hi && key > most ? key : most;
+                }
+                most = wave_max(most);
+                if (lane == 63 && most != 0) atomicMax(&l.few[0], most);
+                __syncthreads();
+                guess = l.few[0];
+                bound = at.lo < NSB ? at.lo << SH : 1u;
+            }
+            for (;;) {
+                uint32_t gt = 0, eq = 0, ge = 0;
+                each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
+#pragma unroll
+                    for (int e = 0; e < MID_GE; ++e) {
+                        const uint32_t key = mid_key<VEC>(r[e]);
+                        gt += key > guess ? 1u : 0u;
+                        eq += ((key == guess) & (i + e < n)) ? 1u : 0u;
+                        ge += key >= bound ? 1u : 0u;
+                    }
+                });
+                gt = lane_value(wave_incl_scan(gt), 63);
+                eq = lane_value(wave_incl_scan(eq), 63);
+                ge = lane_value(wave_incl_scan(ge), 63);
+                __syncthreads();
+                if (lane == 0) {
+                    l.sm[0][w] = gt;
+                    l.sm[1][w] = eq;
+                    l.sm[2][w] = ge;
+                }
+                __syncthreads();
+                const uint32_t of = lane & (MID_WAVES - 1), its_gt = l.sm[0][of], its_ties = l.sm[1][of], its_ge = l.sm[2][of];
+                auto row_scan = [](uint32_t v) {  // over 16 lanes
+                    v = row_shr_add<DPP_SHR1>(v);
+                    v = row_shr_add<DPP_SHR2>(v);
+                    v = row_shr_add<DPP_SHR4>(v);
+                    return row_shr_add<DPP_SHR8>(v);
+                };
+                const uint32_t ties_to = row_scan(its_ties), ge_to = row_scan(its_ge), all_gt = lane_value(row_scan(its_gt), MID_WAVES - 1);
+                const uint32_t all_ge = lane_value(ge_to, MID_WAVES - 1);
+                if (all_gt < kout && kout <= all_gt + lane_value(ties_to, MID_WAVES - 1)) {  // uniform, as what follows: it is the k-th key
+                    t = MidPick{guess, all_gt};
+                    // (a wavefront before which the quota of ties is used up lists none of its own)
+                    const uint32_t q = kout - all_gt, lists = its_gt + (ties_to - its_ties < q ? its_ties : 0u), up_to = row_scan(lists);
+                    total = lane_value(up_to, MID_WAVES - 1);
+                    before = lane_value(up_to - lists, static_cast<int>(w));
+                    from = lane_value(ties_to - its_ties, static_cast<int>(w)) < q ? guess : guess + 1;
+                    break;
+                }
+                if (bound != 0 && all_ge >= kout && all_ge <= MID_LIST) {
+                    digits = true;
+                    total = all_ge;
+                    before = lane_value(ge_to - its_ge, static_cast<int>(w));
+                    from = bound;
+                    break;
+                }
+                guess = mid_digits(
+                            [&](uint32_t base, uint32_t width, uint32_t by) {
+                                each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
+#pragma unroll
+                                    for (int e = 0; e < MID_GE; ++e) {
+                                        const uint32_t d = mid_key<VEC>(r[e]) - base;
+                                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), (i + e < n) & (d >> (width - 1) >> 1 == 0));
+                                    }
+                                });
+                            },
+                            0, largest != 0 ? 32u - static_cast<uint32_t>(__builtin_clz(largest)) : 0u, kout, l.h, l.sm[0], &l.s_pick)
+                            .T;
+                bound = 0;
+            }
+        }
+        acc = 0.0;
+        uint32_t to = before;
+        each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
+            bool keep[MID_GE];
+            uint32_t pos = to;
+#pragma unroll
+            for (int e = 0; e < MID_GE; ++e) {
+                keep[e] = (mid_key<VEC>(r[e]) >= from) & (i + e < n);
+                const uint64_t b = __ballot(keep[e]);
+                pos = lanes_below_plus(b, pos);
+                to += static_cast<uint32_t>(__popcll(b));
+                const double xd = static_cast<double>(keep[e] ? 0.0f : value_of<VEC>(r[e]));
+                acc = fma(xd, xd, acc);
+            }
+#pragma unroll
+            for (int e = 0; e < MID_GE; ++e) {
+                if (keep[e] & (pos < MID_LIST)) list[pos] = make_uint2(i + e, r[e]);
+                pos += keep[e] ? 1u : 0u;
+            }
+        });
+        total = total < MID_LIST ? total : MID_LIST;
+        __syncthreads();
+        const uint32_t share = (total + MID_THREADS - 1) / MID_THREADS * 64, mine = w * share + lane;  // entries of a wavefront
+        auto each = [&](auto &&f) {
+#pragma unroll 1
+            for (uint32_t j = 0; j < share; j += 64) {
+                const bool in = mine + j < total;
+                const uint2 c = list[in ? mine + j : 0u];
+                f(c.x, c.y, in);
+            }
+        };
+        if (digits)
+            t = mid_digits(
+                [&](uint32_t base, uint32_t width, uint32_t by) {
+                    each([&](uint32_t, uint32_t r, bool in) {
+                        const uint32_t d = mid_key<VEC>(r) - base;
+                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), in & (d >> (width - 1) >> 1 == 0));
+                    });
+                },
+                from, largest > from ? 32u - static_cast<uint32_t>(__builtin_clz(largest - from)) : 0u, kout, l.h, l.sm[0], &l.s_pick);
+        __syncthreads();  // (the counts in sm have been read)
+        acc += place_entries<VEC, MID_WAVES>(each, VEC == TAG_F32 ? t.T : t.T << 16, kout - t.above, kout, op, wide, l.sm[0]);
+    } else if (kout != 0) {
+        auto each = [&](auto &&f) {
+#pragma unroll 1
+            for (uint32_t j = 0; j < own; j += 64) {
+                const bool in = j + lane < own;
+                const uint2 c = segment[in ? j + lane : 0u];
+                f(c.x, c.y, in);
+            }
+        };
+        // The bin of the k-th key, looked for from the bound upwards, where it is: `below` candidates are in the bins before it.  Every wavefront for
+        // itself, four bins to a lane.
+        uint32_t B = 0, here = 0, below = 0;
+        const uint32_t from_below = candidates - kout + 1;
+        for (uint32_t base = 0; base < MID_FIRST; base += 256) {
+            const uint4 c = reinterpret_cast<const uint4 *>(l.first)[base / 4 + lane];
+            const uint32_t sum = c.x + c.y + c.z + c.w, inc = wave_incl_scan(sum), total = lane_value(inc, 63);
+            if (below + total < from_below) {  // uniform
+                below += total;
+                continue;
+            }
+            const int in = __builtin_ctzll(__ballot(below + inc >= from_below));
+            below += lane_value(inc - sum, in);
+            const uint32_t n0 = lane_value(c.x, in), n1 = lane_value(c.y, in), n2 = lane_value(c.z, in), n3 = lane_value(c.w, in);
+            B = base + 4 * in;
+            here = n0;
+            if (below + here < from_below) below += here, here = n1, ++B;
+            if (below + here < from_below) below += here, here = n2, ++B;
+            if (below + here < from_below) below += here, here = n3, ++B;
+            break;
+        }
+        uint32_t T = lo + (B << shift), above = candidates - below - here;
+        if (shift != 0 && here <= 64) {  // uniform
+            each([&](uint32_t, uint32_t r, bool in) {
+                if (in & ((mid_key<VEC>(r) - lo) >> shift == B)) l.few[atomicAdd(&l.nfew, 1u)] = mid_key<VEC>(r);
+            });
+            __syncthreads();
+            const uint32_t key = lane < here ? l.few[lane] : 0u, krem = kout - above;
+            uint32_t larger = 0, not_smaller = 0;
+            for (uint32_t i = 0; i < here; ++i) {
+                const uint32_t other = lane_value(key, static_cast<int>(i));
+                larger += other > key ? 1u : 0u;
+                not_smaller += other >= key ? 1u : 0u;
+            }
+            const int is = __builtin_ctzll(__ballot(lane < here && larger < krem && krem <= not_smaller) | 1ull << 63);
+            T = lane_value(key, is);
+            above += lane_value(larger, is);
+        } else if (shift != 0) {
+            const MidPick t = mid_digits(
+                [&](uint32_t base, uint32_t width, uint32_t by) {
+                    each([&](uint32_t, uint32_t r, bool in) {
+                        const uint32_t d = mid_key<VEC>(r) - base;
+                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), in & (d >> (width - 1) >> 1 == 0));
+                    });
+                },
+                T, shift, kout - above, l.h, l.sm[0], &l.s_pick);
+            T = t.T;
+            above += t.above;
+        }
+        acc += place_entries<VEC, MID_WAVES>(each, VEC == TAG_F32 ? T : T << 16, kout - above, kout, op, wide, l.sm[0]);
+    }
+    float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
+    if (a.wire != 0) {
+        write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, sg.ratio);
+        err = reinterpret_cast<float *>(static_cast<char *>(a.idx_out) + sg.out_off - sizeof(adatopk_wire_header) +
+                                        offsetof(adatopk_wire_header, err_norm));
+    }
+    if (err != nullptr) {
+        const double tot = block_sum_f64<MID_WAVES>(acc, l.smd);
         if (threadIdx.x == 0) *err = static_cast<float>(sqrt(tot));
     }
 }
@@ -3424,11 +3943,11 @@ void bounds_for(int64_t n_total, int32_t S, int64_t *max_chunks, int64_t *list_s
 // library), which gives every launch start / stop events carrying the timestamps of the dispatch
 // itself, as a profiler sees it; the product build launches plainly and keeps no state.
 enum Stage {
-    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_SMALL, ST_ALL, NSTAGE
+    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_SMALL, ST_ALL, ST_MID, NSTAGE
 };
 #ifdef ADATOPK_MEASURE_BUILD
 const char *const kStageNames[NSTAGE] = {"k_scan_spec", "k_judge", "k_hist1", "k_scan", "k_refine", "k_emit",
-                                         "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all"};
+                                         "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all", "k_mid"};
 bool g_measure = false;
 bool g_events_made = false;
 hipEvent_t g_start[NSTAGE], g_stop[NSTAGE];
@@ -3601,6 +4120,31 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             if (dt == ADATOPK_F32) launch(ST_SMALL, k_small<TAG_F32>, dim3(cnt), st, sl);
             else if (dt == ADATOPK_BF16) launch(ST_SMALL, k_small<TAG_BF16>, dim3(cnt), st, sl);
             else launch(ST_SMALL, k_small<TAG_F16>, dim3(cnt), st, sl);
+            if (hipGetLastError() != hipSuccess) return ADATOPK_ERUNTIME;
+        }
+        return ADATOPK_OK;
+    }
+
+    // Tensors of up to 64 K elements, which can be read by dwords: one launch as well.
+    bool all_mid = S != 1 || dt == ADATOPK_F32 || n[0] < SPEC_MIN_N_16;
+    for (int32_t s = 0; s < S; ++s) all_mid = all_mid && mid_takes(n[s], k[s], n_total) && reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
+    if (all_mid) {
+        for (int32_t s0 = 0; s0 < S; s0 += MID_MAXSEG) {
+            MidLaunch m{};
+            const int32_t cnt = (S - s0 < MID_MAXSEG) ? S - s0 : MID_MAXSEG;
+            for (int32_t i = 0; i < cnt; ++i) {
+                const int32_t s = s0 + i;
+                m.seg[i] = MidDesc{dense[s], out_offset[s] + header, out.wire ? ratio_of(s) : 0.0, static_cast<uint32_t>(n[s]), static_cast<uint32_t>(k[s])};
+            }
+            m.state = reinterpret_cast<SegState *>(ws + cv.state);
+            m.idx_out = idx_out;
+            m.idx64 = idx_bytes == 8 ? 1u : 0u;
+            m.wire = out.wire ? 1u : 0u;
+            m.val_out = val_out;
+            m.err_out = err_out ? err_out + s0 : nullptr;
+            if (dt == ADATOPK_F32) launch<MID_THREADS>(ST_MID, k_mid<TAG_F32>, dim3(cnt), st, m);
+            else if (dt == ADATOPK_BF16) launch<MID_THREADS>(ST_MID, k_mid<TAG_BF16>, dim3(cnt), st, m);
+            else launch<MID_THREADS>(ST_MID, k_mid<TAG_F16>, dim3(cnt), st, m);
             if (hipGetLastError() != hipSuccess) return ADATOPK_ERUNTIME;
         }
         return ADATOPK_OK;
