@@ -36,6 +36,8 @@
 //             val_out (key > T, plus the first q keys equal to T).  A workgroup of its own
 //             (the tensor's last one where every compute unit has one already) adds up the error norm from the partial sums the
 //             earlier kernels stored, in a fixed order
+//   k_place_dense  (tensors of a large batch that keep more than 21 %) their speculative scan lists the keys within the window's bins
+//             alone and counts those above; this reads the input a second time and places what is above T
 // Cross-block order comes from counts that an EARLIER kernel stored and that every block
 // of the next kernel scans for itself: no block waits for another block (k_judge's exact passes aside, whose
 // waits end whatever workgroups are running), no block needs a release fence (on this chip an agent-scope fence writes back the L2 of its
@@ -141,6 +143,13 @@ constexpr double SPEC_GOOD_EXPECTED_16 = 64.0; // 16-bit types: their sample cos
 constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket in standard deviations, upper side
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
+// Tensors of a batch that keep more than that speculate as well, in launches of their own, if they hold as many elements as the list kernels' wide form asks
+// for (five launches more beside other tensors).  Compress, us, exact passes / so: 8 fp32 tensors of 8.4 M, 25 % kept 343 / 189, 50 % 349 / 213, 90 % 383 / 263, 99 %
+// 403 / 371 (thin keys, windows miss); four at 30 % 164 / 112; bf16 30 % 204 / 157.  Below SPEC_MAX_KEEP_PERCENT lists of all that is kept are the better way: 18 % 138, so 174.
+// Where the window's bins hold most of a chunk (equal keys, zeros) its list overflows and the input is read a third time: values behind a ReLU, 70 %
+// kept 418 / 355, one key throughout 338 / 352.  A window that misses costs the exact passes on top: behind a ReLU with about as many kept as are not zero, 48 to 52 %, 396 / 502.
+constexpr int64_t DENSE_MIN_N = 1 << 20, DENSE_MIN_F32 = WIDE_MIN_F32, DENSE_MIN_16 = WIDE_MIN_16;
+constexpr double DENSE_MAX_KEEP = 0.995;
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
 constexpr uint32_t MERGE_DENSE_SHIFT = 6;        // k > n / 64 takes the LDS-built variant of the one-kernel decompress ...
 constexpr uint32_t MERGE_DENSE_SHIFT_SMALL = 5;  // ... for outputs up to MERGE_SMALL_BYTES n / 32, and any large output takes it (merge_dense)
@@ -176,6 +185,7 @@ __device__ __forceinline__ SegStateWords read_state(const SegState *st) {
 
 constexpr uint32_t FLAG_ALIGNED4 = 1u;  // tensor base is 4-byte aligned (always for fp32): dword loads allowed
 constexpr uint32_t FLAG_SPEC = 2u;      // the speculative pass runs for this tensor
+constexpr uint32_t FLAG_DENSE = 4u;     // ... and lists the keys within the window's bins alone, those above are counted (k_place_dense)
 constexpr int FLAG_SAMPLE_SHIFT = 4;    // four bits from here up: the sample's size in batches of SAMPLE_BATCH dword loads per thread
 constexpr int FLAG_SUB_SHIFT = 8;       // four bits: workgroups per chunk in the list kernels, the logarithm
 constexpr int FLAG_SLOT_SHIFT = 12;     // bits from here up: the tensor's entry of err_out
@@ -752,22 +762,22 @@ __device__ __forceinline__ ColumnPick column_pick(const uint32_t *rows, const ui
 }
 
 // ------------------------------------------------------------------ which scan pass counts
-// Sums of two counters over the workgroup.  sm holds 2 * NW words.
-__device__ __forceinline__ void block_sum2_u32(uint32_t &a, uint32_t &b, uint32_t *sm) {
+// Sums of two counters over the workgroup.  sm holds 2 * WAVES words.
+template <int WAVES = NW> __device__ __forceinline__ void block_sum2_u32(uint32_t &a, uint32_t &b, uint32_t *sm) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     a = wave_incl_scan(a);
     b = wave_incl_scan(b);
     __syncthreads();
     if (lane == 63) {
         sm[w] = a;
-        sm[NW + w] = b;
+        sm[WAVES + w] = b;
     }
     __syncthreads();
     uint32_t sa = 0, sb = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
+    for (int i = 0; i < WAVES; ++i) {
         sa += sm[i];
-        sb += sm[NW + i];
+        sb += sm[WAVES + i];
     }
     a = sa;
     b = sb;
@@ -1003,12 +1013,13 @@ __device__ __forceinline__ void flush_stage(const uint2 *stage, uint32_t from, u
     }
 }
 
-template <int VEC, bool FAST, bool RUNS, int NT>
+template <int VEC, bool FAST, bool RUNS, bool DENSE, int NT>
 __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::SLOTS],
                                           const uint32_t (&valid)[Stream<VEC, NT>::SLOTS], int64_t t0, uint32_t lo,
                                           uint32_t shw, uint32_t *hw, uint32_t *wcnt, uint2 *stage, uint32_t &running,
                                           uint32_t &flushed, uint32_t &cap, int32_t *Li,
-                                          typename Raw<VEC>::type *Lv, double &acc) {  // cap: 0 once the list is given up
+                                          typename Raw<VEC>::type *Lv, double &acc, uint32_t &reached) {
+    // cap: 0 once the list is given up.  reached (DENSE): this wavefront's elements with keys >= lo, the candidates among them.
     using St = Stream<VEC, NT>;
     using R = typename Raw<VEC>::type;
     constexpr int EPD = St::EPD, SLOTS = St::SLOTS;
@@ -1047,6 +1058,15 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
             }
             x_lo = keep[j][h] ? 0.0f : x_lo;
             x_hi = keep[j][h + EPD - 1] ? 0.0f : x_hi;
+            if (DENSE) {  // the window's bins are one pattern each
+                reached += __popcll(m[j][h]) + __popcll(m[j][h + EPD - 1]);
+                wc -= __popcll(m[j][h]) + __popcll(m[j][h + EPD - 1]);
+                keep[j][h] = k_lo - thr16 < NBW - 1;
+                keep[j][h + EPD - 1] = k_hi - thr16 < NBW - 1;
+                m[j][h] = __ballot(keep[j][h]);
+                m[j][h + EPD - 1] = __ballot(keep[j][h + EPD - 1]);
+                wc += __popcll(m[j][h]) + __popcll(m[j][h + EPD - 1]);
+            }
             if (VEC == TAG_F16) {
                 part = fmaf(x_lo, x_lo, part);
                 part = fmaf(x_hi, x_hi, part);
@@ -1067,9 +1087,13 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
                 const uint32_t raw = St::elem(dw, j, e);
                 const bool ok = FAST || ((valid[j * St::GD + e / EPD] >> (e % EPD)) & 1u);
                 keep[j][e] = ok && key_of<VEC>(raw) >= lo;
+                float xs = (ok && !keep[j][e]) ? value_of<VEC>(raw) : 0.0f;
+                if (DENSE) {
+                    reached += __popcll(__ballot(keep[j][e]));
+                    keep[j][e] = keep[j][e] & (key_of<VEC>(raw) - lo < static_cast<uint32_t>(NBW - 1) << shw);
+                }
                 m[j][e] = __ballot(keep[j][e]);
                 wc += __popcll(m[j][e]);
-                float xs = (ok && !keep[j][e]) ? value_of<VEC>(raw) : 0.0f;
                 // The empty statement pins the select to the 32-bit value: left alone, the compiler widens
                 // first and then selects both halves of the double (one more instruction per element in a
                 // loop whose time follows its instruction count: 24.0 -> 22.7 us on the 100 MB tensor).
@@ -1437,7 +1461,7 @@ template <int VEC, int NT> struct Chunk {
 // between that and this (and all are done with the stage's LDS at the next one, the first tile's).  PAIR: leave
 // the two counts by which k_hist1 judges a speculative window.  `room`: the list's capacity, or 0 for no list, if the chunk's candidates
 // are known (listed_room) not to fit one; a speculative scan knows nothing yet.
-template <int VEC, bool PAIR, bool RUNS, bool SHARED, bool CLEARED, int NT>
+template <int VEC, bool PAIR, bool RUNS, bool SHARED, bool CLEARED, bool DENSE, int NT>
 __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const Chunk<VEC, NT> &chunk, uint32_t lo, uint32_t shw, uint32_t room,
                                            uint32_t (&buf)[2][Stream<VEC, NT>::SLOTS], ScanLds &l) {
     const SegDesc &sg = a.seg[s];
@@ -1461,7 +1485,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const 
     }
 
     double acc = 0.0;
-    uint32_t running = 0, flushed = 0;
+    uint32_t running = 0, flushed = 0, reached = 0;
     int wb = 0;
     // The tiles, whole ones and the chunk's last: what lies behind its end reads as zeros, which are dropped and add nothing unless the
     // window begins at key 0.  The register buffers are used in turn, with loads whatever the tile and no copies between them.
@@ -1482,7 +1506,7 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const 
                     for (int e = 0; e < St::SLOTS; ++e)
                         if (St::first_elem(t0, e / St::GD) + (e % St::GD) * St::EPD == end - 1) buf[b][e] = last;
                 }
-                scan_tile<VEC, true, RUNS, NT>(buf[b], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+                scan_tile<VEC, true, RUNS, DENSE, NT>(buf[b], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc, reached);
                 t0 += TILE;
                 wb ^= 1;
                 more = ++t != tiles;
@@ -1491,14 +1515,19 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const 
     }
     for (; t0 < end; t0 += TILE, wb ^= 1) {
         St::load_slow(sg.x, t0, end, buf[0], valid);
-        scan_tile<VEC, false, RUNS, NT>(buf[0], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc);
+        scan_tile<VEC, false, RUNS, DENSE, NT>(buf[0], valid, t0, lo, shw, hw, l.wcnt[wb], stage, running, flushed, cap, Li, Lv, acc, reached);
     }
     __syncthreads();
     flush_stage<VEC, NT>(stage, flushed, running, cap, lo, shw, hw, Li, Lv);
 
     const Launch &again = args_again();  // (what the end of the chunk needs of them does not take up registers in the tile loop)
     const uint32_t capacity = list_cap(again.seg[s]);
+    if (DENSE && (threadIdx.x & 63) == 0) atomicAdd(&hw[NBW - 1], reached);  // (less the candidates, below: no candidate lies in that bin)
     __syncthreads();
+    if (DENSE) {
+        if (threadIdx.x == 0) hw[NBW - 1] -= running;
+        __syncthreads();
+    }
     // window-bin counts of this chunk's candidates, as a row of suffix sums (no global atomics)
     store_rows<NBW, NCW, SHARED, 1, NT>(hw, again.rowsW, again.coarseW, g, l.sm, acc, l.smd);
     if (threadIdx.x == 0) {
@@ -1506,7 +1535,8 @@ __device__ __forceinline__ void scan_chunk(const Launch &a, int s, int g, const 
         // more than the list holds = "read this chunk from the input", also for a list that was given up
         store_count<SHARED>(&again.cnt[g], (cap == 0 && running <= capacity) ? capacity + 1 : running);
     }
-    if (PAIR && again.S != 1 && threadIdx.x == 0) again.cpairA[g] = make_uint2(running, hw[NBW - 1]);  // (k_judge reads the rows)
+    // (k_judge reads the rows)
+    if (PAIR && (DENSE || again.S != 1) && threadIdx.x == 0) again.cpairA[g] = make_uint2(DENSE ? running + hw[NBW - 1] : running, hw[NBW - 1]);
 }
 
 // The exact scan knows a chunk's candidates beforehand: the keys of the bucket B of the k-th key and of those above, which
@@ -1522,7 +1552,7 @@ template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Lau
     return B < NB1 && candidates > list_cap(sg) ? 0u : list_cap(sg);  // (B = NB1: nothing is kept, nothing reaches the window)
 }
 
-template <int VEC, bool SPEC, bool ALONE>
+template <int VEC, bool SPEC, bool ALONE, bool DENSE = false>
 __global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch a) {
     constexpr int NT = ALONE ? SCAN_THREADS : BLOCK;
     using St = Stream<VEC, NT>;
@@ -1577,7 +1607,7 @@ __global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, ALONE, false, SPEC, NT>(a, s, g, chunk, lo, shw, room, buf, l);
+    scan_chunk<VEC, SPEC, ALONE, false, SPEC, DENSE, NT>(a, s, g, chunk, lo, shw, room, buf, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -1629,6 +1659,15 @@ __device__ __forceinline__ uint32_t part_entries(const SegDesc &sg, int g, uint3
     const uint64_t first = static_cast<uint64_t>(per) * part;
     if (first >= entries) return 0u;
     return (first + per < entries) ? per : entries - static_cast<uint32_t>(first);
+}
+
+// Whether a tensor's window held and its lists are those of the window's bins alone: then a list is one part, whatever the tensor's parts per
+// chunk (which serve where the window missed or a list overflowed), and the keys above the bins are the last entry of the chunk's row.
+__device__ __forceinline__ bool dense_held(const SegDesc &sg, bool spec_held) { return (sg.flags & FLAG_DENSE) != 0 && spec_held; }
+__device__ __forceinline__ bool one_part(const SegDesc &sg, uint32_t count, bool dense) { return dense && count <= list_cap(sg); }
+// Whether a part has stored its counts.
+__device__ __forceinline__ bool part_counted(const SegDesc &sg, int g, uint32_t count, uint32_t part, uint32_t sl, bool dense) {
+    return one_part(sg, count, dense) ? part == 0 : part_entries(sg, g, count, part, sl) != 0;
 }
 
 // Part `part` of 1 << sl of chunk g's candidates: the entries are cut into that many runs of whole list
@@ -1869,10 +1908,10 @@ __device__ __attribute__((noinline)) DenseCounts refine_wide_tiles(const ChunkSo
 // position inside the bin is counted, globally (G3) and as a row of suffix sums of the part; candidates in
 // higher bins are counted (kept whatever the last digit is), the squares of those in lower bins are summed
 // (dropped whatever it is).  `first`: the first LU entries of every thread.  `slot`: the part's place in the
-// arrays of the parts.  h: NB3 words of LDS, sm: 2 * NW, smd: NW doubles.
+// arrays of the parts.  above_all: further elements above bin Bw.  h: NB3 words of LDS, sm: 2 * NW, smd: NW doubles.
 template <int VEC, bool WIDE>
 __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkSource<VEC> &src, size_t slot, uint32_t Bw, uint32_t lo,
-                                            uint32_t shw, const uint32_t (&first)[LU], uint32_t *h, uint32_t *sm, double *smd) {
+                                            uint32_t shw, const uint32_t (&first)[LU], uint32_t *h, uint32_t *sm, double *smd, uint32_t above_all = 0) {
     const uint32_t shl = VEC == TAG_F32 ? 0u : 16u;
     uint32_t *h3 = h;
     for (int b = threadIdx.x; b < NB3; b += BLOCK) h3[b] = 0;
@@ -1936,7 +1975,7 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
     const uint32_t above = total - up_to;  // counts of the threads after this one
     reinterpret_cast<uint2 *>(a.rows3 + slot * NB3)[threadIdx.x] = make_uint2(above + mine.y + mine.x, above + mine.y);
     if (threadIdx.x == 0) {
-        a.ldef[slot] = deftot;
+        a.ldef[slot] = deftot + above_all;
         a.lerr[slot] = below;
     }
 }
@@ -1956,8 +1995,15 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(
     const bool spec = stw.spec_held != 0;
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
-    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, a.cnt[g], part, sl, lo);
-    if (src.len == 0 && !(c == 0 && part == 0)) return;  // an empty part (the tensor's first part still reports Bw)
+    const uint32_t count = a.cnt[g];
+    const bool one = one_part(sg, count, dense_held(sg, spec));
+    // (Not always the chunk's first workgroup: every eighth of the grid is on the same XCD.  Six tensors of 8.4 M, eight parts to a chunk: 36 us, so 15.)
+    if (one && part != (static_cast<uint32_t>(c) & ((1u << sl) - 1))) return;
+    const size_t slot = one ? a.part_begin[s] + (static_cast<uint32_t>(c) << sl) : blockIdx.x;
+    const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, count, one ? 0u : part, one ? 0u : sl, lo);
+    if (src.len == 0 && !(c == 0 && part == 0) && !one) return;  // an empty part (the tensor's first part still reports Bw)
+    // (an overflowed list is the input, with the keys above the window's bins in it)
+    const uint32_t above_all = one ? a.rowsW[static_cast<size_t>(g) * NBW + NBW - 1] : 0u;
 
     // The first LU entries of every thread do not depend on the prologue: their loads are in flight
     // while it runs (a typical chunk has no more than these), issued behind its first loads.
@@ -1970,7 +2016,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_refine(
         a.state[s].Bw = pw.B;  // NBW when nothing is kept
         a.state[s].c_gtw = pw.above;
     }
-    refine_part<VEC, WIDE>(a, s, src, blockIdx.x, pw.B, lo, shw, first, h, sm, smd);
+    refine_part<VEC, WIDE>(a, s, src, slot, pw.B, lo, shw, first, h, sm, smd, above_all);
 }
 
 // k_emit's placing over the whole dense tiles of a part read from the input; returns the counts of
@@ -2075,10 +2121,11 @@ struct Threshold {
 
 // fp32: the last digit B3 of the k-th key from its histogram (my_bins: the bins [threadIdx.x * NB3 / BLOCK, ...)
 // of G3), hence T and q.  All candidates of one last-digit bin share one key.
-__device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32_t (&my_bins)[NB3 / BLOCK], uint32_t kout,
+template <int NT = BLOCK>
+__device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32_t (&my_bins)[NB3 / NT], uint32_t kout,
                                                    uint32_t Bw, uint32_t c_gtw, uint32_t lo, uint32_t shw, uint32_t *sm,
                                                    uint32_t *s_pick) {
-    constexpr int PER = NB3 / BLOCK;
+    constexpr int PER = NB3 / NT;
     const uint32_t krem = kout - c_gtw;
     if (threadIdx.x == 0) {  // what stays when no bin holds the rank: nothing to keep
         s_pick[0] = NB3;
@@ -2088,8 +2135,8 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 #pragma unroll
     for (int j = 0; j < PER; ++j) own += my_bins[j];
     uint32_t total;
-    const uint32_t inc = block_incl_scan(own, sm, &total);  // (synchronises)
-    uint32_t higher = total - inc;                          // counts of the threads after this one
+    const uint32_t inc = block_incl_scan<NT / 64>(own, sm, &total);  // (synchronises)
+    uint32_t higher = total - inc;                                   // counts of the threads after this one
 #pragma unroll
     for (int j = PER - 1; j >= 0; --j) {
         if (higher < krem && higher + my_bins[j] >= krem) {
@@ -2115,7 +2162,7 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
 // ones of a bin add count * value^2.  Fixed summation order.
 // dropped_below: this thread's share of the first two.
-__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t first_part) {
+__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t first_part, bool dense) {
     double sum = 0.0;
     const uint32_t sl = sub_log(sg);
     const uint32_t nparts = static_cast<uint32_t>(sg.nchunks) << sl;
@@ -2124,7 +2171,7 @@ __device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &
         const uint32_t count = a.cnt[sg.chunk_begin + cc];
         const double below_bin = a.lerr[first_part + e], below_window = a.chunk_err[sg.chunk_begin + cc];
         if (pp == 0) sum += below_window;
-        if (part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl) != 0) sum += below_bin;  // (an empty part stored nothing)
+        if (part_counted(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl, dense)) sum += below_bin;  // (an empty part stored nothing)
     }
     return sum;
 }
@@ -2271,7 +2318,7 @@ __device__ __forceinline__ void emit_part(const Launch &a, const SegDesc &sg, co
             const uint32_t count = a.cnt[sg.chunk_begin + cc];
             const uint32_t here = r[t.t_bin], next = r[t.t_bin + 1 < t.row_len ? t.t_bin + 1 : t.t_bin];
             const uint32_t extra = t.extra_gt != nullptr ? t.extra_gt[stored] : 0u;
-            const bool any = part_entries(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl) != 0;  // else nothing is stored for it
+            const bool any = part_counted(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl, false);  // else nothing is stored for it
             const uint32_t above = t.t_bin + 1 < t.row_len ? next : 0u;
             const uint32_t g1 = any ? extra + above : 0u, e1 = any ? here - above : 0u;
             if (e < me) {
@@ -2374,6 +2421,8 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, norm_only ? 0u : a.cnt[g], part, sl, lo);
+    const bool dense = dense_held(sg, spec);
+    if (dense && !norm) return;  // k_place_dense places its pairs
     if (norm && a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
     if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
         if (norm && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
@@ -2382,7 +2431,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     // what the error norm's workgroup needs of the chunks arrives behind the prologue
     double below_t = 0.0;
     if (norm) {
-        if (VEC == TAG_F32) below_t = dropped_below(a, sg, first_part);
+        if (VEC == TAG_F32) below_t = dropped_below(a, sg, first_part, dense);
         else if (static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
     }
 
@@ -2408,8 +2457,141 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         t = threshold_16(a, pw, kout, lo, shw);
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
-    if (norm_only) return;
+    if (norm_only || dense) return;
     emit_part<VEC, WIDE>(a, sg, src, first_part, c, part, t, raw, id, l);
+}
+
+// k_place_dense.  The pairs of a tensor that keeps a large share and whose window held: the input is read a second time, and every element
+// above T goes out, the first q equal to T with them.  (With the exact passes such a tensor was read four times: the top digits, the window's counts, a
+// part's counts and the placing.  24 tensors of 8.4 M with planned keep counts, six of them so: 804 us per compress and decompress, now 684; the placing of
+// those six, 201 MB read and 203 MB written, 76 us, what a copy takes.)  One workgroup per chunk, which knows its
+// first output slot from the earlier chunks' counts; a wavefront reads rows of 64 consecutive elements, so its stores are contiguous, and the wavefronts exchange
+// one count each per tile.
+constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / 64, PLACE_ROWS = TILE / PLACE_THREADS;
+template <int VEC> __global__ __launch_bounds__(PLACE_THREADS, 8) void k_place_dense(Launch a) {
+    using R = typename Raw<VEC>::type;
+    __shared__ uint32_t sm[2 * PLACE_WAVES], s_pick[2], s_counts[2][PLACE_WAVES];
+    __shared__ uint32_t red[NCW + NBW / NCW];
+    const int g = blockIdx.x;
+    const int s = find_segment(a, g);
+    const SegDesc &sg = a.seg[s];
+    const SegStateWords stw = read_state(&a.state[s]);
+    if (!dense_held(sg, stw.spec_held != 0)) return;  // k_emit has placed its pairs
+    const int c = g - sg.chunk_begin;
+    const uint32_t kout = static_cast<uint32_t>(sg.k), lo = stw.loA, shw = stw.shwA, sl = sub_log(sg), lane = threadIdx.x & 63;
+    const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
+    const int64_t beg = static_cast<int64_t>(c) * sg.E;
+    const uint32_t len = static_cast<uint32_t>(beg + sg.E < sg.n ? sg.E : sg.n - beg);
+    // the rows: element e of the chunk is row e / 64 in lane e % 64; what is asked for behind the chunk's end reads as zeros
+    const __amdgpu_buffer_rsrc_t bytes = Stream<VEC>::bounded(static_cast<const R *>(sg.x) + beg, len * static_cast<uint32_t>(sizeof(R)));
+    auto load = [&](uint32_t tile, uint32_t(&v)[PLACE_ROWS]) {
+        const uint32_t at = (tile * TILE + w * (PLACE_ROWS * 64) + lane) * static_cast<uint32_t>(sizeof(R));
+        constexpr int NONTEMPORAL = 2;
+#pragma unroll
+        for (int r = 0; r < PLACE_ROWS; ++r) {
+            if constexpr (VEC == TAG_F32) v[r] = __builtin_amdgcn_raw_buffer_load_b32(bytes, static_cast<int>(at + r * 64 * sizeof(R)), 0, NONTEMPORAL);
+            else v[r] = __builtin_amdgcn_raw_buffer_load_b16(bytes, static_cast<int>(at + r * 64 * sizeof(R)), 0, NONTEMPORAL);
+        }
+    };
+    uint32_t buf[2][PLACE_ROWS];
+    Threshold t;
+    if constexpr (VEC == TAG_F32) {
+        uint32_t my_bins[NB3 / PLACE_THREADS];
+        my_bins[0] = a.G3[s * NB3 + threadIdx.x];
+        load(0, buf[0]);
+        t = threshold_f32<PLACE_THREADS>(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, sm, s_pick);
+    } else {
+        const ColumnPick pw = column_pick<NBW, NCW, 4, PLACE_THREADS>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW,
+                                                                      a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW, sg.nchunks, kout, red,
+                                                                      [&]() { load(0, buf[0]); });
+        t = threshold_16(a, pw, kout, lo, shw);
+    }
+    // sums over the earlier chunks of (#keys above T, #keys equal to T)
+    uint32_t gt = 0, eq = 0;
+    static_assert(CTARGET <= PLACE_THREADS, "a chunk per thread");
+    if (t.any_kept && static_cast<int>(threadIdx.x) < c) {
+        const int before = sg.chunk_begin + static_cast<int>(threadIdx.x);
+        const uint32_t count = a.cnt[before];
+        const bool one = VEC != TAG_F32 || one_part(sg, count, true);
+        const size_t first = VEC == TAG_F32 ? a.part_begin[s] + (threadIdx.x << sl) : static_cast<uint32_t>(before);
+        for (uint32_t part = 0; part < (one ? 1u : 1u << sl); ++part) {
+            if (!one && !part_counted(sg, before, count, part, sl, true)) continue;
+            const uint32_t *r = t.rows + (first + part) * t.row_len;
+            const uint32_t above = t.t_bin + 1 < t.row_len ? r[t.t_bin + 1] : 0u;
+            gt += above + (t.extra_gt != nullptr ? t.extra_gt[first + part] : 0u);
+            eq += r[t.t_bin] - above;
+        }
+    }
+    block_sum2_u32<PLACE_WAVES>(gt, eq, sm);
+    if (!t.any_kept) return;  // uniform
+    const uint32_t T = t.T, q = t.q, first_pos = gt + (eq < q ? eq : q);
+    uint32_t run_eq = eq, run = 0;  // equal to T so far in the tensor; kept so far of the chunk
+    const bool wide = a.idx64 != 0;
+    const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, kout, wide, a.wire != 0, sizeof(R));
+    char *const oi = wide ? reinterpret_cast<char *>(op.i64 + first_pos) : reinterpret_cast<char *>(op.i32 + first_pos);
+    char *const ov = static_cast<char *>(op.val) + static_cast<size_t>(first_pos) * sizeof(R);
+    const uint32_t room = kout - first_pos;
+    const uint32_t tiles = (len + TILE - 1) / TILE;
+    int b = 0;
+    auto tile = [&](uint32_t at, const uint32_t(&v)[PLACE_ROWS]) {
+        const uint32_t row0 = at * TILE + w * (PLACE_ROWS * 64);  // first element of the wavefront's first row, in the chunk
+        uint64_t mg[PLACE_ROWS], me[PLACE_ROWS];
+        uint32_t counts = 0;
+#pragma unroll
+        for (int r = 0; r < PLACE_ROWS; ++r) {
+            const uint32_t key = key_of<VEC>(v[r]);
+            mg[r] = __ballot(key > T);
+            me[r] = __ballot(key == T);
+        }
+        if (T == 0 && at + 1 == tiles) {  // uniform; the zeros behind the end are no ties
+#pragma unroll
+            for (int r = 0; r < PLACE_ROWS; ++r) {
+                const uint32_t i = row0 + r * 64, left = i < len ? len - i : 0u;
+                me[r] &= left >= 64 ? ~0ull : (1ull << left) - 1ull;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < PLACE_ROWS; ++r) counts += static_cast<uint32_t>(__popcll(mg[r])) + (static_cast<uint32_t>(__popcll(me[r])) << 16);
+        if (lane == 0) s_counts[b][w] = counts;
+        __syncthreads();
+        uint32_t before, total;
+        wave_counts<PLACE_WAVES>(s_counts[b], before, total);
+        b ^= 1;
+        uint32_t eq_at = run_eq + (before >> 16), ties_before = (eq_at < q ? eq_at : q) - (run_eq < q ? run_eq : q);
+        uint32_t pos0 = run + (before & 0xFFFFu) + ties_before;
+#pragma unroll
+        for (int r = 0; r < PLACE_ROWS; ++r) {
+            uint64_t kept = mg[r];
+            if (me[r] != 0) {  // wave-uniform
+                const uint32_t ties = static_cast<uint32_t>(__popcll(me[r]));
+                if (eq_at + ties <= q) kept |= me[r];
+                else if (eq_at < q) kept |= __ballot(((me[r] >> lane) & 1u) != 0 && lanes_below(me[r]) < q - eq_at);
+                eq_at += ties;
+            }
+            const uint32_t pos = lanes_below_plus(kept, pos0);
+            if (((kept >> lane) & 1u) != 0 && pos < room) {
+                const int32_t index = static_cast<int32_t>(static_cast<uint32_t>(beg) + row0 + r * 64 + lane);
+                if (wide) *reinterpret_cast<int64_t *>(oi + pos * 8u) = index;
+                else *reinterpret_cast<int32_t *>(oi + pos * 4u) = index;
+                *reinterpret_cast<R *>(ov + pos * static_cast<uint32_t>(sizeof(R))) = static_cast<R>(v[r]);
+            }
+            pos0 += static_cast<uint32_t>(__popcll(kept));
+        }
+        const uint32_t all_eq = run_eq + (total >> 16);
+        run += (total & 0xFFFFu) + (all_eq < q ? all_eq : q) - (run_eq < q ? run_eq : q);
+        run_eq = all_eq;
+    };
+    uint32_t at = 0;
+    for (bool more = tiles != 0; more;) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (!more) break;
+            load(at + 1, buf[1 - i]);
+            __builtin_amdgcn_sched_barrier(0);
+            tile(at, buf[i]);
+            more = ++at != tiles;
+        }
+    }
 }
 
 // ------------------------------------------------------------------ k_judge
@@ -2619,7 +2801,7 @@ template <int VEC, bool WIDE> __device__ __forceinline__ void judge_missed(Judge
                 rewindow_candidates<VEC>(a, chunk_source<VEC>(a, a.seg[0], ci, listed, 0, 0, lo_list), ci, lo, shw, h, l.sl.sm, l.sl.smd);
             } else {
                 if (c != first_chunk) first_tile(c);
-                scan_chunk<VEC, false, WIDE, true, false, BLOCK>(a, 0, ci, Chunk<VEC, BLOCK>(a.seg[0], ci), lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), buf, l.sl);
+                scan_chunk<VEC, false, WIDE, true, false, false, BLOCK>(a, 0, ci, Chunk<VEC, BLOCK>(a.seg[0], ci), lo, shw, listed_room<true>(a, a.seg[0], ci, p1.B), buf, l.sl);
             }
             __syncthreads();
         }))
@@ -3943,11 +4125,11 @@ void bounds_for(int64_t n_total, int32_t S, int64_t *max_chunks, int64_t *list_s
 // library), which gives every launch start / stop events carrying the timestamps of the dispatch
 // itself, as a profiler sees it; the product build launches plainly and keeps no state.
 enum Stage {
-    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_SMALL, ST_ALL, ST_MID, NSTAGE
+    ST_SPEC, ST_JUDGE, ST_HIST1, ST_SCAN, ST_REFINE, ST_EMIT, ST_FILL, ST_SCATTER, ST_MERGE, ST_SMALL, ST_ALL, ST_MID, ST_PLACE, NSTAGE
 };
 #ifdef ADATOPK_MEASURE_BUILD
 const char *const kStageNames[NSTAGE] = {"k_scan_spec", "k_judge", "k_hist1", "k_scan", "k_refine", "k_emit",
-                                         "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all", "k_mid"};
+                                         "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all", "k_mid", "k_place_dense"};
 bool g_measure = false;
 bool g_events_made = false;
 hipEvent_t g_start[NSTAGE], g_stop[NSTAGE];
@@ -3981,10 +4163,13 @@ inline uint32_t norm_workgroups(uint32_t S) { return (S + XCDS - 1) / XCDS * XCD
 // scan; the two exact passes behind it return at once for every tensor whose speculation held and
 // do the work for the others, so what reaches k_refine is complete either way.
 // `no_lists`: most elements belong to tensors without lists, and nothing speculates; those tensors' chunks have one part each.
-template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, bool no_lists, hipStream_t st) {
+// `dense`: the tensors that speculate are FLAG_DENSE.
+template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, bool no_lists, bool dense, hipStream_t st) {
     const dim3 grid(total_chunks);
     const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
-    if (speculate) {
+    if (dense) {
+        launch(ST_SPEC, k_scan<VEC, true, false, true>, grid, st, a);
+    } else if (speculate) {
         if (one_per_cu) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, true>, grid, st, a);
         else launch(ST_SPEC, k_scan<VEC, true, false>, grid, st, a);
     }
@@ -3994,7 +4179,8 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     const uint32_t S = static_cast<uint32_t>(a.S);
     a.norms = (a.err_out != nullptr || a.wire) && (!wide || parts.x + S <= CTARGET_ONE) ? norm_workgroups(S) : 0u;
     const dim3 parts_and_norms(parts.x + a.norms);
-    if (speculate && a.S == 1) {
+    const bool judge = speculate && a.S == 1 && !dense;
+    if (judge) {
         dim3 judges = VEC == TAG_F32 ? parts : parts_and_norms;
 #ifdef ADATOPK_MEASURE_BUILD
         if (g_judge_missing > 0 && static_cast<uint32_t>(g_judge_missing) < parts.x) judges.x -= static_cast<uint32_t>(g_judge_missing);
@@ -4010,10 +4196,11 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
             else launch(ST_REFINE, k_refine<VEC, false>, parts, st, a);
         }
     }
-    if (VEC == TAG_F32 || !(speculate && a.S == 1)) {
+    if (VEC == TAG_F32 || !judge) {
         if (wide) launch(ST_EMIT, k_emit<VEC, true>, parts_and_norms, st, a);
         else launch(ST_EMIT, k_emit<VEC, false>, parts_and_norms, st, a);
     }
+    if (dense) launch<PLACE_THREADS>(ST_PLACE, k_place_dense<VEC>, grid, st, a);
     return hipGetLastError() == hipSuccess ? ADATOPK_OK : ADATOPK_ERUNTIME;
 }
 
@@ -4058,6 +4245,22 @@ bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, u
     const double lo = ceil(mu + SPEC_SIGMAS_LOW * sqrt(mu) + 2.0), hi = floor(mu - margin);
     static_assert(SAMPLE_ELEMS < 65536, "a rank fits 16 bits");
     *ranks = static_cast<uint32_t>(lo) | (hi < 1.0 ? 0u : static_cast<uint32_t>(hi) << 16);  // (lo: well below the sample's size, k being at most 21 %)
+    *batches = static_cast<uint32_t>(nb);
+    return true;
+}
+
+// The same for a tensor of a batch that keeps more (DENSE_MAX_KEEP of it, at most): of the sampled elements, mu lie among the k largest with a standard
+// deviation of sqrt(mu (1 - k / n)), so a sample of a quarter will do until few are dropped, whose keys are thin against what a window spans.
+bool dense_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
+    if (n < DENSE_MIN_N || !aligned16 || k <= n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
+    const double share = static_cast<double>(k) / static_cast<double>(n);
+    if (share > DENSE_MAX_KEEP) return false;
+    const int epd = 4 / elem_size(dt), max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;
+    int nb = share > 0.9 ? 4 : (share > 0.75 ? 2 : 1);
+    if (nb > max_batches) nb = max_batches;
+    const double ns = static_cast<double>(nb) * SAMPLE_BATCH * BLOCK * epd, mu = share * ns, sigma = sqrt(mu * (1.0 - share));
+    const double lo = ceil(mu + SPEC_SIGMAS_LOW * sigma + 2.0), hi = floor(mu - SPEC_SIGMAS * sigma - 2.0);
+    *ranks = static_cast<uint32_t>(lo < ns ? lo : ns) | (hi < 1.0 ? 0u : static_cast<uint32_t>(hi) << 16);
     *batches = static_cast<uint32_t>(nb);
     return true;
 }
@@ -4160,8 +4363,11 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     // Tensors whose chunks have no lists, mostly, and are placed from the input.  A large enough launch in which they hold the majority
     // of the elements takes the list kernels' wide form, one workgroup per chunk (see WIDE_MIN_F32).
     auto listless = [&](int32_t s) { return !kept_whole(s) && k[s] > n[s] / (dt == ADATOPK_F32 ? 2 : LIST_DIV); };
-    // One launch of the kernels for the tensors `which[0 .. count)` of the call.
-    auto select_group = [&](const int32_t *which, int32_t count, bool may_speculate) -> adatopk_status {
+    auto speculates_dense = [&](int32_t s, uint32_t *ranks, uint32_t *batches) {
+        return !kept_whole(s) && dense_ranks(n[s], k[s], dt, reinterpret_cast<uintptr_t>(dense[s]) % 16 == 0, ranks, batches);
+    };
+    // One launch of the kernels for the tensors `which[0 .. count)` of the call.  `dense_group`: all of them are dense ones that speculate.
+    auto select_group = [&](const int32_t *which, int32_t count, bool may_speculate, bool dense_group) -> adatopk_status {
         const int64_t wide_min = dt != ADATOPK_F32 ? WIDE_MIN_16 : (count == 1 ? WIDE_MIN_F32_ONE : WIDE_MIN_F32);
         Launch a{};
         a.S = count;
@@ -4177,10 +4383,10 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             n_batch += n_select(s);
             if (listless(s)) n_dense += n[s];
             whole += kept_whole(s) ? 1 : 0;
-            spec[i] = may_speculate && speculates(s, &ranks[i], &batches[i]);
+            spec[i] = dense_group ? speculates_dense(s, &ranks[i], &batches[i]) : may_speculate && speculates(s, &ranks[i], &batches[i]);
             nspec += spec[i] ? 1 : 0;
         }
-        const int64_t target = chunk_target(a.S);
+        const int64_t target = dense_group ? CTARGET : chunk_target(a.S);
         int64_t E[MAXSEG];
         plan_chunks(a.S, target, list_slots, [&](int32_t i) { return n_select(which[i]); },
                     [&](int32_t i) { return kept_whole(which[i]) ? 0 : k[which[i]]; }, spec, n_batch, E);
@@ -4228,7 +4434,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             const bool aligned4 = reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
             d.flags = (aligned4 ? FLAG_ALIGNED4 : 0u) | (static_cast<uint32_t>(s - which[0]) << FLAG_SLOT_SHIFT);
             if (spec[i]) {
-                d.flags |= FLAG_SPEC | (batches[i] << FLAG_SAMPLE_SHIFT);
+                d.flags |= FLAG_SPEC | (dense_group ? FLAG_DENSE : 0u) | (batches[i] << FLAG_SAMPLE_SHIFT);
                 d.ranks = ranks[i];
             }
             chunks += d.nchunks;
@@ -4254,9 +4460,9 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         a.parts = parts;
         if (chunks > max_chunks || list_tiles * (TILE / LIST_DIV) > list_slots) return ADATOPK_ERUNTIME;  // planner invariant
         if (whole < a.S) {  // something to select
-            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, no_lists, st)
-                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, nspec > 0, no_lists, st)
-                                                             : launch_batch<TAG_F16>(a, chunks, nspec > 0, no_lists, st);
+            const adatopk_status rc = (dt == ADATOPK_F32)    ? launch_batch<TAG_F32>(a, chunks, nspec > 0, no_lists, dense_group, st)
+                                      : (dt == ADATOPK_BF16) ? launch_batch<TAG_BF16>(a, chunks, nspec > 0, no_lists, dense_group, st)
+                                                             : launch_batch<TAG_F16>(a, chunks, nspec > 0, no_lists, dense_group, st);
             if (rc != ADATOPK_OK) return rc;
         }
         if (whole > 0) {
@@ -4289,26 +4495,34 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     // 32 Mi 237 / 260 (365 / 344); bf16 8 Mi 81 / 75, 16 Mi 140 / 111.
     for (int32_t s0 = 0; s0 < S; s0 += MAXSEG) {
         const int32_t count = (S - s0 < MAXSEG) ? S - s0 : MAXSEG;
-        int32_t order[MAXSEG], nspec = 0, nexact = 0;
-        int64_t n_spec = 0, n_exact = 0;
-        int32_t exact[MAXSEG];
+        int32_t order[MAXSEG], nspec = 0, nexact = 0, ndense = 0;
+        int64_t n_spec = 0, n_exact = 0, n_dense = 0;
+        int32_t exact[MAXSEG], dense_ones[MAXSEG], others[MAXSEG], nothers = 0;
+        uint32_t ranks, batches;
+        for (int32_t i = 0; i < count; ++i)
+            if (speculates_dense(s0 + i, &ranks, &batches)) n_dense += n[s0 + i];
+        const bool with_dense = S > 1 && n_dense >= (dt == ADATOPK_F32 ? DENSE_MIN_F32 : DENSE_MIN_16);
         for (int32_t i = 0; i < count; ++i) {
             const int32_t s = s0 + i;
-            uint32_t ranks, batches;
+            if (with_dense && speculates_dense(s, &ranks, &batches)) {
+                dense_ones[ndense++] = s;
+                continue;
+            }
+            others[nothers++] = s;
             const bool spec = speculates(s, &ranks, &batches);
             if (spec) n_spec += n[s];
             else n_exact += n_select(s);
             if (spec || n_select(s) == 0) order[nspec++] = s;  // (what is not selected from goes with either)
             else exact[nexact++] = s;
         }
-        adatopk_status rc;
+        adatopk_status rc = ADATOPK_OK;
         if (n_spec >= SPLIT_MIN_N && n_exact >= SPLIT_MIN_N) {
-            rc = select_group(order, nspec, true);
-            if (rc == ADATOPK_OK) rc = select_group(exact, nexact, false);
-        } else {
-            for (int32_t i = 0; i < count; ++i) order[i] = s0 + i;
-            rc = select_group(order, count, count == 1 || (n_spec >= SPEC_MIN_BATCH && n_spec >= SPEC_MIN_SHARE * n_exact));
+            rc = select_group(order, nspec, true, false);
+            if (rc == ADATOPK_OK) rc = select_group(exact, nexact, false, false);
+        } else if (nothers > 0) {
+            rc = select_group(others, nothers, count == 1 || (n_spec >= SPEC_MIN_BATCH && n_spec >= SPEC_MIN_SHARE * n_exact), false);
         }
+        if (rc == ADATOPK_OK && ndense > 0) rc = select_group(dense_ones, ndense, true, true);
         if (rc != ADATOPK_OK) return rc;
     }
     return ADATOPK_OK;
