@@ -140,7 +140,17 @@ def _declare(lib: ctypes.CDLL) -> ctypes.CDLL:
     lib.adatopk_plan_keep_counts.restype = i32
     lib.adatopk_compress_noalloc.argtypes = [p, i64, i32, i64, p, p, p, p]
     lib.adatopk_compress_noalloc.restype = i32
+    lib.address = _Addresses(lib)
     return lib
+
+
+class _Addresses:
+    """Where the functions are that the _marshal extension calls for itself."""
+
+    def __init__(self, lib: ctypes.CDLL):
+        for name in ("compress", "decompress", "decompress_sorted", "decompress_accumulate", "decompress_segmented", "compress_wire",
+                     "compress_wire_segmented", "decompress_wire", "compress_segmented"):
+            setattr(self, name, ctypes.cast(getattr(lib, "adatopk_" + name), ctypes.c_void_p).value)
 
 
 def _check(status: int, where: str) -> None:
@@ -200,22 +210,33 @@ def _check_pairs(dtype: torch.dtype, k_total: int, idx: torch.Tensor, val: torch
         raise ValueError("val must have the dense tensor's dtype (%s) and at least %d entries" % (dtype, k_total))
 
 
-_marshal = None  # the extension that reads the arguments of the segmented calls; False: there is none
+_marshal = None  # the extension that reads the arguments and makes the calls; False: there is none
 
 
 def _load_marshal():
     """The extension, or None where it is not built (for this Python): Python then reads the arguments itself, with the
-    same result, half a microsecond per tensor and call slower."""
+    same result, microseconds per call and half a microsecond per tensor slower."""
     global _marshal
     if _marshal is None:
         try:
             from . import _marshal as m
+            if _raw_stream is not None:
+                m.streams(torch.cuda.current_device, _raw_stream)
         except ImportError as e:
-            warnings.warn("segmented calls go without the _marshal extension (%s): run `python -m paper_2410_12707_amd.build`" % e,
+            warnings.warn("calls go without the _marshal extension (%s): run `python -m paper_2410_12707_amd.build`" % e,
                           RuntimeWarning, stacklevel=3)
             m = False
         _marshal = m
     return _marshal or None
+
+
+def _done(status: Optional[int], where: str) -> bool:
+    """Whether the extension has made the call (None: its arguments are left to Python)."""
+    if status is None:
+        return False
+    if status != OK:
+        raise AdaTopKError(status, where)
+    return True
 
 
 def _segments(tensors: Sequence[torch.Tensor]):
@@ -257,6 +278,9 @@ def adatopk_compress(dense: torch.Tensor, k: int, idx_out: torch.Tensor, val_out
                      err_norm_out: Optional[torch.Tensor], workspace: torch.Tensor) -> None:
     """Enqueues compress of one tensor on the current stream; outputs are written in place."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.compress(lib.address.compress, dense, k, idx_out, val_out, err_norm_out, workspace), "adatopk_compress"):
+        return
     _check_outputs(dense.dtype, int(k), idx_out, val_out, err_norm_out, 1)
     err_ptr = _dev(err_norm_out) if err_norm_out is not None else None
     _check(lib.adatopk_compress(_dev(dense), dense.numel(), _dtype_code(dense.dtype), int(k), _dev(idx_out),
@@ -276,6 +300,9 @@ def adatopk_compress_noalloc(dense: torch.Tensor, k: int, idx_out: torch.Tensor,
 
 def adatopk_decompress(idx: torch.Tensor, val: torch.Tensor, k: int, dense_out: torch.Tensor) -> None:
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.decompress(lib.address.decompress, idx, val, k, dense_out), "adatopk_decompress"):
+        return
     _check_pairs(dense_out.dtype, int(k), idx, val)
     _check(lib.adatopk_decompress(_dev(idx), _dev(val), int(k), _dtype_code(dense_out.dtype), _dev(dense_out),
                                   dense_out.numel(), _stream()), "adatopk_decompress")
@@ -284,6 +311,9 @@ def adatopk_decompress(idx: torch.Tensor, val: torch.Tensor, k: int, dense_out: 
 def adatopk_decompress_sorted(idx: torch.Tensor, val: torch.Tensor, k: int, dense_out: torch.Tensor) -> None:
     """Decompress for strictly ascending idx (what adatopk_compress produces)."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.decompress(lib.address.decompress_sorted, idx, val, k, dense_out), "adatopk_decompress_sorted"):
+        return
     _check_pairs(dense_out.dtype, int(k), idx, val)
     _check(lib.adatopk_decompress_sorted(_dev(idx), _dev(val), int(k), _dtype_code(dense_out.dtype),
                                          _dev(dense_out), dense_out.numel(), _stream()), "adatopk_decompress_sorted")
@@ -292,6 +322,9 @@ def adatopk_decompress_sorted(idx: torch.Tensor, val: torch.Tensor, k: int, dens
 def adatopk_decompress_accumulate(idx: torch.Tensor, val: torch.Tensor, k: int, dense_inout: torch.Tensor) -> None:
     """dense_inout[idx[j]] += val[j] for unique indices; every other entry is left alone."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.decompress(lib.address.decompress_accumulate, idx, val, k, dense_inout), "adatopk_decompress_accumulate"):
+        return
     _check_pairs(dense_inout.dtype, int(k), idx, val)
     _check(lib.adatopk_decompress_accumulate(_dev(idx), _dev(val), int(k), _dtype_code(dense_inout.dtype),
                                              _dev(dense_inout), dense_inout.numel(), _stream()),
@@ -302,6 +335,9 @@ def adatopk_decompress_segmented(idx: torch.Tensor, val: torch.Tensor, out_offse
                                  dense_out: Sequence[torch.Tensor]) -> None:
     """Decompress of S tensors from the concatenated, per-tensor ascending pairs in few launches."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.decompress_segmented(lib.address.decompress_segmented, idx, val, out_offset, dense_out), "adatopk_decompress_segmented"):
+        return
     S = len(dense_out)
     segments = _segments(dense_out)
     dtype = segments[2] if segments else dense_out[0].dtype if S else torch.float32
@@ -346,6 +382,9 @@ def adatopk_compress_wire(dense: torch.Tensor, k: int, index_bytes: int, ratio: 
     """adatopk_compress writing one wire message into the uint8 tensor wire_out (device memory, or pinned
     host memory: the message then needs no copy before the host can send it)."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.compress_wire(lib.address.compress_wire, dense, k, index_bytes, ratio, wire_out, workspace), "adatopk_compress_wire"):
+        return
     _check(lib.adatopk_compress_wire(_dev(dense), dense.numel(), _dtype_code(dense.dtype), int(k), int(index_bytes),
                                      float(ratio), _dev_or_pinned(wire_out), wire_out.numel() * wire_out.element_size(),
                                      _dev(workspace), workspace.numel(), _stream()), "adatopk_compress_wire")
@@ -356,6 +395,9 @@ def adatopk_compress_wire_segmented(dense: Sequence[torch.Tensor], ks: Sequence[
                                     wire_offset: Sequence[int], workspace: torch.Tensor) -> None:
     """One wire message per tensor, message s at byte wire_offset[s] of the uint8 tensor wire_out."""
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.compress_wire_segmented(lib.address.compress_wire_segmented, dense, ks, index_bytes, ratios, wire_out, wire_offset, workspace), "adatopk_compress_wire_segmented"):
+        return
     S = len(dense)
     segments = _segments(dense)
     dt = _dtype_code(segments[2] if segments else dense[0].dtype) if S else F32
@@ -373,6 +415,9 @@ def adatopk_compress_wire_segmented(dense: Sequence[torch.Tensor], ks: Sequence[
 def adatopk_decompress_wire(wire: torch.Tensor, wire_bytes: int, index_bytes: int, dense: torch.Tensor,
                             accumulate: bool = False) -> None:
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.decompress_wire(lib.address.decompress_wire, wire, wire_bytes, index_bytes, dense, accumulate), "adatopk_decompress_wire"):
+        return
     _check(lib.adatopk_decompress_wire(_dev(wire), int(wire_bytes), _dtype_code(dense.dtype), int(index_bytes),
                                        dense.numel(), 1 if accumulate else 0, _dev(dense), _stream()),
            "adatopk_decompress_wire")
@@ -382,6 +427,9 @@ def adatopk_compress_segmented(dense: Sequence[torch.Tensor], ks: Sequence[int],
                                val_out: torch.Tensor, out_offset: Sequence[int],
                                err_norm_out: Optional[torch.Tensor], workspace: torch.Tensor) -> None:
     lib = load_library()
+    m = _marshal or _load_marshal()
+    if m and _done(m.compress_segmented(lib.address.compress_segmented, dense, ks, idx_out, val_out, out_offset, err_norm_out, workspace), "adatopk_compress_segmented"):
+        return
     S = len(dense)
     segments = _segments(dense)
     dtype = segments[2] if segments else dense[0].dtype if S else torch.float32

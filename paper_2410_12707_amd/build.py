@@ -2,7 +2,7 @@
 libadatopk_measure.so: the same sources compiled with ADATOPK_MEASURE_BUILD, which adds the
 benchmark-only hooks of include/adatopk_measure.h (per-kernel dispatch timing, plain streaming
 kernels).  The product library carries none of them.  _marshal is the Python extension that reads
-the arguments of the segmented calls (marshal.cpp, host code only); the package works without it."""
+the arguments and makes the calls (marshal.cpp, host code only); the package works without it."""
 from __future__ import annotations
 
 import os
@@ -42,14 +42,14 @@ def build_measure_library(verbose: bool = False) -> str:
 
 
 def build_marshal(verbose: bool = False) -> str:
-    """The Python extension that reads the arguments of the segmented calls (host code only)."""
+    """The Python extension that reads the arguments and makes the calls (host code only)."""
     import torch
 
     base = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
-           "-isystem", sysconfig.get_paths()["include"], "-Wall", "-Wextra", "-o", MARSHAL_LIB, MARSHAL_SOURCE,
+           "-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-Wall", "-Wextra", "-o", MARSHAL_LIB, MARSHAL_SOURCE,
            "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
