@@ -3247,9 +3247,9 @@ constexpr int MID_FIRST_BITS = 11, MID_FIRST = 1 << MID_FIRST_BITS;  // bins ove
 constexpr int MID_DIGIT_BITS = 12, MID_DIGIT = 1 << MID_DIGIT_BITS;  // further digits
 constexpr int MID_MAXSEG = 96;                            // tensors per launch (the table travels as kernel arguments)
 // Which tensors take this path.  It takes about 6 us, 0.1 for 1024 elements more and 1.4 for 1024 kept ones; the launches of the path for larger tensors 18 to 20
-// whatever the sizes, and more for a batch that fills the chip.  Where the list is made a second time (sorted values, equal keys) it is 5 to 16 us more,
+// whatever the sizes, and more for a batch that fills the chip.  Where the list is made a second time (sorted values, equal keys) it is 5 to 14 us more,
 // for tensors whose keys are all within a few per cent of each other 40, so short calls stay well below the limit where the two cross.  GPU us of a compress call,
-// larger tensors' path / so: one fp32 tensor, 1 % kept, 9000 values 18.2 / 6.6, 32 768 18.6 / 8.7, 65 536 19.0 / 12.3 (sorted 19.6 / 27.8, equal 21.7 / 25.0);
+// larger tensors' path / so: one fp32 tensor, 1 % kept, 9000 values 18.2 / 6.6, 32 768 18.6 / 8.7, 65 536 19.0 / 12.3 (sorted 19.6 / 29, equal 21.7 / 25.5), four of 50 000 at 2 % sorted 21.4 / 25.7;
 // 20 % kept, 9000 18.9 / 9.3, 32 768 19.4 / 17.6; 64 of 8 to 64 K at 1 % 21.7 / 13.1, 64 of 64 K 27.8 / 13.4, 24 of 60 000 at 5 % 21.2 / 18.0, 256 of 30 000 at 2 %
 // 99 / 32; bf16, one of 9000 14.5 / 6.6, two of 40 000 16.5 / 9.8.  (A single 16-bit tensor that speculates takes two launches, 12 us, and stays there.)
 constexpr int64_t MID_WORK = 1 << 17, MID_WORK_SHORT = 1 << 16, MID_SHORT_CALL = 1 << 20;
@@ -3393,7 +3393,9 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
             largest = quarter[j] > largest ? quarter[j] : largest;
         }
         // (64 lanes that count on one word take 440 cycles: a wavefront half of whose keys are alike takes those together, and nothing is listed in segments)
-        skewed = __popcll(__ballot(m[0] >> SH == lane_value(m[0], 31) >> SH)) >= 32 && groups != 0;
+        // (Zeros are not counted, and no candidates: 20 fp32 tensors of 30 K of which 3 % are not zero 19.0 us when they passed for alike, now 9.1.)
+        const uint32_t middle = lane_value(m[0], 31) >> SH;
+        skewed = __popcll(__ballot(m[0] >> SH == middle)) >= 32 && middle != 0;
         auto count = [&](uint32_t key) {
             if (skewed) hist_add(l.h, key >> SH, key >> SH != 0);  // (zeros need not be counted)
             else if (key >> SH) atomicAdd(&l.h[key >> SH], 1u);
@@ -3508,7 +3510,9 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
         // (the same candidates; the threshold is to be found among them)
         bool digits = !skewed && candidates >= kout && candidates <= MID_LIST;
         if (!digits) {
-            // Equal keys, sorted values: an element of every fourth group in all lanes says what the k-th key may be, and a bound that is closer.
+            // Equal keys, sorted values: every sixteenth element says what the k-th key may be, and a bound that is closer.  (An element of
+            // every lane in every fourth group missed the k largest of sorted values: 20 fp32 tensors of 30 K at 1 %
+            // 40.0 us, so 18.6.)
             uint32_t guess = 0, bound = 0;  // (fewer than k are not zero: then zero is the threshold)
             if (skewed || candidates >= kout) {
                 constexpr int EACH = 4;
@@ -3517,25 +3521,24 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
 #pragma unroll
                 for (int j = 0; j < MID_GROUPS; j += EACH)
                     if (j < static_cast<int>(groups)) {
+                        const uint32_t its = j + lane / (64 / EACH);  // sixteen lanes to a group
                         uint32_t d[GD];
-                        load(i0 + j * GROUP, d);
+                        load(its < groups ? (g0 + its) * GROUP + lane % (64 / EACH) * (GROUP * EACH / 64) : n + MID_GE, d);  // (behind the end: zeros)
                         sample[taken * MID_THREADS] = mid_key<VEC>(elem_of<VEC>(d[0], 0));
                         ++taken;
                     }
                 __syncthreads();  // (all are done with h and sm)
                 reinterpret_cast<uint4 *>(l.h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
                 if (threadIdx.x == 0) l.few[0] = 0;
-                if (lane == 0) l.sm[0][w] = taken;
                 __syncthreads();
 #pragma unroll 1
                 for (uint32_t i = 0; i < taken; ++i) {
                     const uint32_t bin = sample[i * MID_THREADS] >> SH;
                     hist_add(l.h, bin, bin != 0);
                 }
-                uint32_t unused, rows;
-                wave_counts<MID_WAVES>(l.sm[0], unused, rows);
                 __syncthreads();
-                const uint32_t expected = static_cast<uint32_t>((static_cast<uint64_t>(kout) * rows * 64 + n - 1) / n);
+                constexpr uint32_t ONE_IN = GROUP * EACH / 64;
+                const uint32_t expected = (kout + ONE_IN - 1) / ONE_IN;
                 const RankedBins at = ranked_bins(l.h, largest >> SH, 0, expected + static_cast<uint32_t>(4.0f * sqrtf(static_cast<float>(expected))) + 2, expected);
                 uint32_t most = 0;
 #pragma unroll 1
