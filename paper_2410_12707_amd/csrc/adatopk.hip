@@ -50,7 +50,8 @@
 // the pairs into an existing tensor.
 //
 // Tensors of at most one register tile (8192 elements) skip all of the above: k_small selects
-// and writes one tensor per workgroup in a single launch.  So does k_mid for up to 64 K elements, with a compute unit for each tensor.
+// and writes one tensor per workgroup in a single launch.  So does k_mid for up to 64 K elements, with a compute unit for each tensor, and for
+// fp32 calls whose longest tensor is not far below k_small's limit.
 //
 // Outputs can be laid out as one wire message (header, indices, values); indices are stored as
 // int32 or, for the paper's own accounting (Sec. 5.2), int64.
@@ -3245,7 +3246,7 @@ constexpr uint32_t MID_SEGMENT = 1024;                    // candidates of a wav
 constexpr uint32_t MID_LIST = MID_WAVES * MID_SEGMENT;
 constexpr int MID_FIRST_BITS = 11, MID_FIRST = 1 << MID_FIRST_BITS;  // bins over the candidates' keys
 constexpr int MID_DIGIT_BITS = 12, MID_DIGIT = 1 << MID_DIGIT_BITS;  // further digits
-constexpr int MID_MAXSEG = 96;                            // tensors per launch (the table travels as kernel arguments)
+constexpr int MID_MAXSEG = 128;                           // tensors per launch (the table travels as kernel arguments)
 // Which tensors take this path.  It takes about 6 us, 0.1 for 1024 elements more and 1.4 for 1024 kept ones; the launches of the path for larger tensors 18 to 20
 // whatever the sizes, and more for a batch that fills the chip.  Where the list is made a second time (sorted values, equal keys) it is 5 to 14 us more,
 // for tensors whose keys are all within a few per cent of each other 40, so short calls stay well below the limit where the two cross.  GPU us of a compress call,
@@ -3256,16 +3257,22 @@ constexpr int64_t MID_WORK = 1 << 17, MID_WORK_SHORT = 1 << 16, MID_SHORT_CALL =
 inline bool mid_takes(int64_t n, int64_t k, int64_t n_total) {
     return n <= MID_N && k <= n / 4 && n + 13 * k <= (n_total < MID_SHORT_CALL ? MID_WORK_SHORT : MID_WORK);
 }
+// ... also where k_small could do it: fp32 tensors the longest of which, whose time the call's is, has more elements than this.  k_small / k_mid, us, 64 tensors:
+// 4100 values at 1 % 7.2 / 6.7, at 20 % 8.0 / 8.1, 8192 at 1 % 8.0 / 6.9, at 20 % 10.3 / 9.3, 7000 behind a ReLU at 2 % 10.7 / 7.1, equal ones 13.1 / 10.6, sorted
+// 10.0 / 12.9; 128 of 1 to 8 K at 1 % 7.8 / 6.9; 3000 at 10 % 6.9 / 7.0.  16-bit types: 7000 at 5 % 7.2 / 7.3, f16 at 20 % 8.5 / 9.3.
+constexpr int64_t SMALL_LONG = 4096;
 static_assert(MID_WORK / 13 + 64 * MID_GE * MID_GROUPS <= MID_LIST, "k and the ties of a wavefront fit the list");
+constexpr int MID_K_SHIFT = 17;
+static_assert(MID_N < 1 << MID_K_SHIFT && MID_N / 4 < 1 << (32 - MID_K_SHIFT), "two counts travel in one word");
 struct MidDesc {
     const void *x;
     int64_t out_off;
-    double ratio;  // wire mode: goes into the message's header
-    uint32_t n, k;
 };
 struct MidLaunch {
     MidDesc seg[MID_MAXSEG];
-    SegState *state;
+    double ratio[MID_MAXSEG];  // wire mode: goes into the message's header
+    uint32_t nk[MID_MAXSEG];   // elements, and kept elements from bit MID_K_SHIFT up
+    SegState *state;           // nullptr: tensors that use no workspace
     void *idx_out;
     void *val_out;
     float *err_out;
@@ -3316,7 +3323,7 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
     __shared__ MidLds l;
 
     const MidDesc &sg = a.seg[blockIdx.x];
-    const uint32_t n = sg.n, kout = sg.k;
+    const uint32_t n = a.nk[blockIdx.x] & ((1u << MID_K_SHIFT) - 1u), kout = a.nk[blockIdx.x] >> MID_K_SHIFT;
     const R *x = static_cast<const R *>(sg.x);
     const uint32_t lane = threadIdx.x & 63, w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     // The tensor's groups of 256 elements, four to a lane, dealt out to the wavefronts in runs.
@@ -3364,7 +3371,7 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
     static_assert(NSB == 4 * MID_THREADS && MID_FIRST == 2 * MID_THREADS, "four bins per thread, and two");
     if (threadIdx.x == 0) l.nfew = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.state[0].spec_held = a.state[0].failed = 0u;  // (no window was guessed)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && a.state != nullptr) a.state[0].spec_held = a.state[0].failed = 0u;  // (no window was guessed)
 
     const bool wide = a.idx64 != 0;
     const OutPtrs op = out_ptrs(a.idx_out, a.val_out, sg.out_off, kout, wide, a.wire != 0, sizeof(R));
@@ -3717,7 +3724,7 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
     }
     float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
     if (a.wire != 0) {
-        write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, sg.ratio);
+        write_header<VEC>(a.idx_out, sg.out_off, n, kout, wide, a.ratio[blockIdx.x]);
         err = reinterpret_cast<float *>(static_cast<char *>(a.idx_out) + sg.out_off - sizeof(adatopk_wire_header) +
                                         offsetof(adatopk_wire_header, err_norm));
     }
@@ -4332,9 +4339,14 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
         return out.ratio ? out.ratio[s] : (k[s] > 0 ? static_cast<double>(n[s]) / static_cast<double>(k[s]) : 0.0);
     };
     // Only small tensors: one launch, one workgroup per tensor, no workspace traffic.
-    bool all_small = true;
-    for (int32_t s = 0; s < S; ++s) all_small = all_small && n[s] <= SMALL_N;
-    if (all_small) {
+    bool all_small = true, all_mid = true;
+    int64_t longest = 0;
+    for (int32_t s = 0; s < S; ++s) {
+        all_small = all_small && n[s] <= SMALL_N;
+        all_mid = all_mid && mid_takes(n[s], k[s], n_total) && reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
+        longest = n[s] > longest ? n[s] : longest;
+    }
+    if (all_small && !(all_mid && dt == ADATOPK_F32 && longest > SMALL_LONG)) {
         for (int32_t s0 = 0; s0 < S; s0 += SMALL_MAXSEG) {
             SmallLaunch sl{};
             const int32_t cnt = (S - s0 < SMALL_MAXSEG) ? S - s0 : SMALL_MAXSEG;
@@ -4358,17 +4370,17 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     }
 
     // Tensors of up to 64 K elements, which can be read by dwords: one launch as well.
-    bool all_mid = S != 1 || dt == ADATOPK_F32 || n[0] < SPEC_MIN_N_16;
-    for (int32_t s = 0; s < S; ++s) all_mid = all_mid && mid_takes(n[s], k[s], n_total) && reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
-    if (all_mid) {
+    if (all_mid && (S != 1 || dt == ADATOPK_F32 || n[0] < SPEC_MIN_N_16)) {
         for (int32_t s0 = 0; s0 < S; s0 += MID_MAXSEG) {
             MidLaunch m{};
             const int32_t cnt = (S - s0 < MID_MAXSEG) ? S - s0 : MID_MAXSEG;
             for (int32_t i = 0; i < cnt; ++i) {
                 const int32_t s = s0 + i;
-                m.seg[i] = MidDesc{dense[s], out_offset[s] + header, out.wire ? ratio_of(s) : 0.0, static_cast<uint32_t>(n[s]), static_cast<uint32_t>(k[s])};
+                m.seg[i] = MidDesc{dense[s], out_offset[s] + header};
+                m.nk[i] = static_cast<uint32_t>(n[s]) | static_cast<uint32_t>(k[s]) << MID_K_SHIFT;
+                if (out.wire) m.ratio[i] = ratio_of(s);
             }
-            m.state = reinterpret_cast<SegState *>(ws + cv.state);
+            m.state = all_small ? nullptr : reinterpret_cast<SegState *>(ws + cv.state);
             m.idx_out = idx_out;
             m.idx64 = idx_bytes == 8 ? 1u : 0u;
             m.wire = out.wire ? 1u : 0u;

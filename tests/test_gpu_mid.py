@@ -48,3 +48,17 @@ def test_more_tensors_than_one_launch_holds(dtype):
     ri, rv, _, re = orc.compress_segmented(xs, ks)
     assert np.array_equal(gi, ri) and np.array_equal(H.bits(gv), H.bits(rv))
     assert all(H.same_err(a, b) for a, b in zip(ge, re))
+
+
+@pytest.mark.parametrize("longest", [4096, 4097, 4100, 5121, 8191, 8192])  # the last length of the other kernel, and this one's
+def test_calls_of_small_tensors(longest):
+    # beside tensors of which most wavefronts, or most lanes of the last one, have no element; the call uses no workspace
+    lens = [longest, 0, 4, 5, 63, 64, 65, 255, 256, 257, 600, 1023, 4095, longest - 1]
+    for kind in KINDS:
+        xs = [values(kind, max(n, 1), longest + i, "f32")[:n] for i, n in enumerate(lens)]
+        for share in (0.0, 0.003, 0.25):
+            ks = [int(n * share) for n in lens]
+            gi, gv, _, ge = H.gpu_compress_segmented(xs, ks)
+            ri, rv, _, re = orc.compress_segmented(xs, ks)
+            assert np.array_equal(gi, ri) and np.array_equal(H.bits(gv), H.bits(rv)), (kind, share)
+            assert all(H.same_err(a, b) for a, b in zip(ge, re)), (kind, share)
