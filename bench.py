@@ -111,7 +111,7 @@ def input_passes(stage_us, input_bytes: int, judged: int) -> int:
     """Full reads of the input in a step: the passes that ran, and what the judging kernel read.  A pass over the input
     that finishes faster than the peak allows did not read it (the exact passes return at once when the
     speculative pass held, and the other way round)."""
-    ran = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small")
+    ran = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small", "k_mid")
               if nm in stage_us and input_bytes / stage_us[nm] / 1e3 <= HBM_PEAK_GBS)
     return ran + (judged if "k_judge" in stage_us else 0)
 
@@ -252,7 +252,8 @@ class Bench:
             "k_hist1": b * n,                    # exact passes (when they do not return at once): one read of the input ...
             "k_scan": b * n + (4 + b) * k,       # ... and another, with the candidate pairs written
             "k_merge": b * n + (4 + b) * k,      # one write of the dense output + the pairs read
-            "k_small": b * n + (4 + b) * k,      # one-launch path: one read of the input + the pairs
+            "k_small": b * n + (4 + b) * k,      # one-launch paths: one read of the input + the pairs
+            "k_mid": b * n + (4 + b) * k,
         }
 
     def step_bytes(self, input_reads: int) -> int:

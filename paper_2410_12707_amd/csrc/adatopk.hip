@@ -1766,8 +1766,8 @@ template <int VEC> struct Wide {
 };
 // That is k_refine's form, which only counts (WIDE_U loads per thread and tile, two tiles ahead).
 // k_emit also places what it keeps, and 16-byte loads would leave a wavefront's store with four
-// bytes every sixteen, in sixteen cache lines: its wide tiles (DENSE_SLOTS elements per thread) use
-// the streaming layout of the scan instead: a wavefront owns a contiguous eighth of the tile and
+// bytes every sixteen, in sixteen cache lines: in its wide tiles (DENSE_SLOTS elements per thread)
+// a wavefront owns a contiguous eighth of the tile and
 // reads it 64 consecutive elements at a time, so consecutive lanes place consecutive elements, and
 // only the wavefronts' totals are exchanged per tile; two tiles ahead, so that a tile's loads are
 // issued before the stores of the tile two before it (one counter, in order: a wait for loads lets
@@ -1778,7 +1778,7 @@ constexpr uint32_t DENSE_ELEMS = BLOCK * DENSE_SLOTS;
 // f(tile, registers of the tile) for tiles [0, t_end) in order, with two tiles of loads in flight behind
 // the one worked on: three register buffers of N loads used in turn, the loop body written out per buffer
 // so that none is ever copied (a copy would wait for its loads); load(tile, buffer) fills one.  b0 holds
-// tile 0 already.  Same shape as the streaming loop of the scan.  For a loop that also stores: the loads
+// tile 0 already.  For a loop that also stores: the loads
 // of a tile are issued before the stores of the tile two before it, so the wait for them does not have to
 // let those stores drain first.
 template <typename E, int N, typename L, typename F>
@@ -2625,7 +2625,8 @@ template <int VEC> __global__ __launch_bounds__(PLACE_THREADS, 8) void k_place_d
 // missed 81 / 87; 4.9 M held 33 / 25, missed 42 / 48; 25 M at 10 % (lists in two parts, one workgroup of the two
 // makes the exact passes) held 65 / 59, missed 103 / 121.  Values with a scale per run of 1600, standard deviation
 // 0.5 of its logarithm, miss in three calls of eight and come out at 62 / 52 us on average; with 1.0 they miss in seven,
-// 91 / 88.  (Taking k_emit in as well, behind a third wait, costs an fp32 tensor 3 us more than its launch does.)
+// 91 / 88.  (Taking k_emit in as well, behind a third wait, costs an fp32 tensor 3 us more than its launch does.  Without one, every workgroup ranking the
+// few keys of the k-th key's bin for itself, 393 K at 1 % gained 0.7 us, 786 K at 5 % lost 2.8, few levels 3.6 and more.)
 //
 // The exact passes are separated by waits for the other workgroups' stores instead of kernel boundaries:
 //   - what one workgroup hands to another goes through store_agent / atomics; a workgroup lets its stores
