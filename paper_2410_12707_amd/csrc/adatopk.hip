@@ -4185,11 +4185,13 @@ inline void launch(int stage, K kernel, dim3 grid, hipStream_t st, Args... args)
 constexpr uint32_t XCDS = 8;
 inline uint32_t norm_workgroups(uint32_t S) { return (S + XCDS - 1) / XCDS * XCDS; }
 
-// Whether the exact scan has something to do for 1024 threads: chunks of more than one tile.  A single tile is counted and listed at once, and what is left is
-// the bucket search in front and the rows behind, which the smaller workgroup's fewer wavefronts are through sooner.  512 / 1024 threads,
-// compress, us: one tile, 1 Mi fp32 at 30 % 28.3 / 29.2, four bf16 tensors of 180 K at 30 % 21.3 / 22.0; two tiles and more, fp32 3 M at 60 % 41.6 / 39.7,
-// 25 M at 25 % 133.8 / 120.3, 12 M bf16 at 25 % 62.9 / 59.5.
-inline bool exact_alone(const Launch &a) {
+// Whether a scan with a compute unit to itself has something to do for 1024 threads: chunks of more than one tile, or the largest sample.  A single tile is
+// counted and listed at once, and what is left is the prologue in front and the rows behind, which the smaller workgroup's fewer wavefronts are through
+// sooner.  512 / 1024 threads, compress, us: one tile, exact, 1 Mi fp32 at 30 % 28.3 / 29.2, four bf16 tensors of 180 K at 30 % 21.3 / 22.0; from a sample, 786 K fp32 at
+// 5 % 17.9 / 18.5, at 0.3 % (32 K samples) 19.4 / 19.0, 2 M bf16 at 1 % 13.0 / 13.5, 786 K f16 at 20 % 13.8 / 14.2; two tiles and more, fp32 3 M at 60 %
+// 41.6 / 39.7, 25 M at 25 % 133.8 / 120.3, 12 M bf16 at 25 % 62.9 / 59.5.
+inline bool scan_alone(const Launch &a, bool sampled, int elems_per_dword) {
+    if (sampled && a.S == 1 && static_cast<int>(a.seg[0].flags >> FLAG_SAMPLE_SHIFT & 15u) * SAMPLE_BATCH * BLOCK * elems_per_dword >= SAMPLE_ELEMS) return true;
     int32_t longest = 0;
     for (int32_t s = 0; s < a.S; ++s) longest = a.seg[s].E > longest ? a.seg[s].E : longest;
     return longest > TILE;
@@ -4206,7 +4208,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     if (dense) {
         launch(ST_SPEC, k_scan<VEC, true, false, true>, grid, st, a);
     } else if (speculate) {
-        if (one_per_cu) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, true>, grid, st, a);
+        if (one_per_cu && scan_alone(a, true, VEC / 4)) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, true>, grid, st, a);
         else launch(ST_SPEC, k_scan<VEC, true, false>, grid, st, a);
     }
     const dim3 parts(a.parts);
@@ -4225,7 +4227,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
         else if constexpr (VEC == TAG_F32) launch(ST_JUDGE, k_judge<VEC, false>, judges, st, a);
     } else {
         launch(ST_HIST1, k_hist1<VEC>, grid, st, a);
-        if (one_per_cu && exact_alone(a)) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, true>, grid, st, a);
+        if (one_per_cu && scan_alone(a, false, VEC / 4)) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, true>, grid, st, a);
         else launch(ST_SCAN, k_scan<VEC, false, false>, grid, st, a);
         if constexpr (VEC == TAG_F32) {  // the 16-bit types have no last digit to refine
             if (dense) launch(ST_REFINE, k_refine<VEC, false, true>, parts, st, a);
