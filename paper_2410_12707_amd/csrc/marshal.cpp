@@ -118,8 +118,16 @@ PyObject *streams(PyObject *, PyObject *const *args, Py_ssize_t nargs) {
 }
 
 struct Call {
-    bool plain = true;  // so far
+    bool plain = true;    // so far
+    bool raised = false;  // Python code that was called has raised an exception
 
+    // Whether an object is true.
+    int truth(PyObject *o) {
+        const int is = plain ? PyObject_IsTrue(o) : 0;
+        raised = raised || is < 0;
+        plain = plain && is >= 0;
+        return is;
+    }
     // A plain tensor in contiguous device memory, or nullptr.
     const at::Tensor *tensor(PyObject *o) {
         if (!plain || !THPVariable_CheckExact(o)) {
@@ -184,6 +192,7 @@ struct Call {
         PyObject *device = PyObject_CallNoArgs(g_current_device);
         PyObject *raw = device != nullptr ? PyObject_CallOneArg(g_raw_stream, device) : nullptr;
         void *handle = raw != nullptr ? PyLong_AsVoidPtr(raw) : nullptr;
+        raised = raw == nullptr;
         plain = raw != nullptr && !PyErr_Occurred();
         Py_XDECREF(device);
         Py_XDECREF(raw);
@@ -192,7 +201,8 @@ struct Call {
 };
 
 // The body of a call: `f` reads the arguments and returns the status; what it throws (a wrapper of functorch, a tensor without storage)
-// and what is not plain is left to Python.
+// and what is not plain is left to Python.  An exception out of Python code, that of a signal among them (an interrupt while the stream is asked for),
+// is the call's: nothing has been enqueued.
 template <typename F> PyObject *call(Py_ssize_t nargs, Py_ssize_t expected, F &&f) {
     if (nargs != expected) {
         PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
@@ -201,6 +211,7 @@ template <typename F> PyObject *call(Py_ssize_t nargs, Py_ssize_t expected, F &&
     try {
         Call c;
         const long status = f(c);
+        if (c.raised) return nullptr;
         if (c.plain && !PyErr_Occurred()) return PyLong_FromLong(status);
     } catch (...) {
     }
@@ -258,9 +269,9 @@ PyObject *decompress_wire(PyObject *, PyObject *const *a, Py_ssize_t nargs) {
         if (wire == nullptr || y == nullptr) return 0;
         const int64_t bytes = c.number(a[2]), ib = c.number(a[3]);
         const adatopk_dtype dt = c.dtype(y->scalar_type());
-        const int accumulate = PyObject_IsTrue(a[5]);
+        c.plain = c.plain && bytes >= 0 && (ib == 4 || ib == 8);
+        const int accumulate = c.truth(a[5]);
         void *stream = c.stream();
-        c.plain = c.plain && accumulate >= 0 && bytes >= 0 && (ib == 4 || ib == 8);
         if (!c.plain) return 0;
         return without_gil<decltype(&adatopk_decompress_wire)>(c, a[0], static_cast<const void *>(c.address(wire)), static_cast<size_t>(bytes), dt,
                                                                static_cast<int32_t>(ib), y->numel(), accumulate, c.address(y), stream);

@@ -78,3 +78,35 @@ def test_calls_with_and_without_the_extension(monkeypatch):
     monkeypatch.setattr(B, "_marshal", False)
     without, refused_without = everything(), refused()
     assert all(torch.equal(a, b) for a, b in zip(with_it, without)) and refused_with == refused_without
+
+
+@pytest.mark.gpu
+def test_exceptions_of_python_code_end_the_call():
+    m = B._load_marshal()
+    x, idx, val, ws = torch.ones(64, device="cuda"), torch.zeros(8, dtype=torch.int32, device="cuda"), torch.zeros(8, device="cuda"), B.new_workspace(64, 1, torch.float32)
+    wire = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    calls = [lambda: B.adatopk_compress(x, 8, idx, val, None, ws), lambda: B.adatopk_decompress(idx, val, 8, x),
+             lambda: B.adatopk_compress_wire(x, 8, 4, 8.0, wire, ws), lambda: B.adatopk_decompress_wire(wire, 128, 4, x),
+             lambda: B.adatopk_compress_segmented([x], [8], idx, val, [0, 8], None, ws), lambda: B.adatopk_decompress_segmented(idx, val, [0, 8], [x]),
+             lambda: B.adatopk_compress_wire_segmented([x], [8], 4, None, wire, [0], ws)]
+
+    def interrupted(*_):  # as a signal's handler does while the stream is asked for
+        raise KeyboardInterrupt
+
+    for ways in ((interrupted, B._raw_stream), (torch.cuda.current_device, interrupted)):
+        m.streams(*ways)
+        try:
+            for call in calls:
+                with pytest.raises(KeyboardInterrupt):
+                    call()
+        finally:
+            m.streams(torch.cuda.current_device, B._raw_stream)
+
+    class Neither:
+        def __bool__(self):
+            raise ZeroDivisionError
+
+    with pytest.raises(ZeroDivisionError):
+        B.adatopk_decompress_wire(wire, 128, 4, x, accumulate=Neither())
+    torch.cuda.synchronize()
+    assert not idx.any() and not val.any() and not wire.any() and bool((x == 1).all())
