@@ -211,15 +211,20 @@ def _check_pairs(dtype: torch.dtype, k_total: int, idx: torch.Tensor, val: torch
 
 
 _marshal = None  # the extension that reads the arguments and makes the calls; False: there is none
+_MARSHAL_NAMES = ("tensors", "int64s", "streams", "compress", "decompress", "compress_wire", "decompress_wire", "compress_segmented",
+                  "decompress_segmented", "compress_wire_segmented")
 
 
 def _load_marshal():
-    """The extension, or None where it is not built (for this Python): Python then reads the arguments itself, with the
+    """The extension, or None where it is not built (for this Python, or from an older source): Python then reads the arguments itself, with the
     same result, microseconds per call and half a microsecond per tensor slower."""
     global _marshal
     if _marshal is None:
         try:
             from . import _marshal as m
+            missing = [name for name in _MARSHAL_NAMES if not hasattr(m, name)]
+            if missing:
+                raise ImportError("built from an older source, without %s" % ", ".join(missing))
             if _raw_stream is not None:
                 m.streams(torch.cuda.current_device, _raw_stream)
         except ImportError as e:

@@ -110,3 +110,21 @@ def test_exceptions_of_python_code_end_the_call():
         B.adatopk_decompress_wire(wire, 128, 4, x, accumulate=Neither())
     torch.cuda.synchronize()
     assert not idx.any() and not val.any() and not wire.any() and bool((x == 1).all())
+
+
+def test_an_older_extension_is_gone_without(monkeypatch):
+    import sys
+    import types
+
+    import paper_2410_12707_amd as package
+
+    older = types.ModuleType(package.__name__ + "._marshal")  # it read the arrays of the segmented calls and made no call
+    older.tensors = older.int64s = lambda *_: None
+    monkeypatch.setitem(sys.modules, older.__name__, older)
+    monkeypatch.setattr(package, "_marshal", older, raising=False)
+    monkeypatch.setattr(B, "_marshal", None)
+    x, idx, val, ws = torch.zeros(64), torch.zeros(8, dtype=torch.int32), torch.zeros(8), torch.zeros(256, dtype=torch.uint8)
+    with pytest.warns(RuntimeWarning, match="older source"):
+        with pytest.raises(ValueError):  # what the call in Python says of host memory
+            B.adatopk_compress(x, 8, idx, val, None, ws)
+    assert B._marshal is False
