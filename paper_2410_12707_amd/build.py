@@ -17,6 +17,7 @@ MEASURE_LIB = os.path.join(HERE, "libadatopk_measure.so")
 # (the suffix names the Python it is built for: another one does not load it)
 MARSHAL_LIB = os.path.join(HERE, "_marshal" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
+HEADER = os.path.join(ROOT, "include", "adatopk.h")
 SOURCES = [os.path.join(CSRC, "adatopk.hip"), os.path.join(CSRC, "adatopk_host.cpp")]
 
 HIPCC_FLAGS = [
@@ -61,13 +62,15 @@ def library_is_stale() -> bool:
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = SOURCES + [os.path.join(ROOT, "include", "adatopk.h"), os.path.join(ROOT, "include", "adatopk_measure.h"),
-                      os.path.join(CSRC, "wire_layout.h")]
+    deps = SOURCES + [HEADER, os.path.join(ROOT, "include", "adatopk_measure.h"), os.path.join(CSRC, "wire_layout.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
 def marshal_is_stale() -> bool:
-    return not os.path.exists(MARSHAL_LIB) or os.path.getmtime(MARSHAL_SOURCE) > os.path.getmtime(MARSHAL_LIB)
+    if not os.path.exists(MARSHAL_LIB):
+        return True
+    t = os.path.getmtime(MARSHAL_LIB)
+    return any(os.path.getmtime(d) > t for d in (MARSHAL_SOURCE, HEADER))  # (it calls the library's functions by address, as the header declares them)
 
 
 if __name__ == "__main__":

@@ -127,3 +127,16 @@ def test_bench_counts_the_judging_kernels_reads_of_the_input():
     assert bench.input_passes(dict(hit, k_judge=57.0), 100_663_296, 2) == 3
     assert bench.input_passes({"k_hist1": 17.0, "k_scan": 24.0, "k_refine": 6.0}, 100_663_296, 0) == 2
     assert bench.input_passes({"k_scan_spec": 24.0, "k_hist1": 3.9, "k_scan": 4.0}, 100_663_296, 0) == 1  # returned at once
+
+
+def test_extension_is_rebuilt_after_a_change_of_the_header(tmp_path, monkeypatch):
+    from paper_2410_12707_amd import build as b
+
+    paths = [tmp_path / name for name in ("marshal.cpp", "adatopk.h", "_marshal.so")]
+    for path, attribute, time in zip(paths, ("MARSHAL_SOURCE", "HEADER", "MARSHAL_LIB"), (1, 1, 2)):
+        path.write_text("")
+        os.utime(path, (time, time))
+        monkeypatch.setattr(b, attribute, str(path), raising=False)
+    assert not b.marshal_is_stale()
+    os.utime(paths[1], (3, 3))
+    assert b.marshal_is_stale()
