@@ -144,9 +144,10 @@ constexpr double SPEC_GOOD_EXPECTED_16 = 64.0; // 16-bit types: their sample cos
 constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket in standard deviations, upper side
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
-// Tensors of a batch that keep more than that speculate as well, in launches of their own, if they hold as many elements as the list kernels' wide form asks
+// Tensors of a batch that keep more than that (16-bit types: more than a list holds) speculate as well, in launches of their own, if they hold as many elements as the list kernels' wide form asks
 // for (five launches more beside other tensors).  Compress, us, exact passes / so: 8 fp32 tensors of 8.4 M, 25 % kept 343 / 189, 50 % 349 / 213, 90 % 383 / 263, 99 %
-// 403 / 371 (thin keys, windows miss); four at 30 % 164 / 112; bf16 30 % 204 / 157.  Below SPEC_MAX_KEEP_PERCENT lists of all that is kept are the better way: 18 % 138, so 174.
+// 403 / 371 (thin keys, windows miss); four at 30 % 164 / 112; bf16 30 % 204 / 157.  Below SPEC_MAX_KEEP_PERCENT lists of all that is kept are the better way: 18 % 138, so 174.  So they are for the 16-bit types
+// up to a quarter, unless most keys are in the k-th key's binade: 22 %, bf16 behind a ReLU 70 / 89, f16 50 / 64, bf16 normal 150 / 92.
 // Where the window's bins hold most of a chunk (equal keys, zeros) its list overflows and the input is read a third time: values behind a ReLU, 70 %
 // kept 418 / 355, one key throughout 338 / 352.  A window that misses costs the exact passes on top: behind a ReLU with about as many kept as are not zero, 48 to 52 %, 396 / 502.
 constexpr int64_t DENSE_MIN_N = 1 << 20, DENSE_MIN_F32 = WIDE_MIN_F32, DENSE_MIN_16 = WIDE_MIN_16;
@@ -4291,7 +4292,7 @@ bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, u
 // The same for a tensor of a batch that keeps more (DENSE_MAX_KEEP of it, at most): of the sampled elements, mu lie among the k largest with a standard
 // deviation of sqrt(mu (1 - k / n)), so a sample of a quarter will do until few are dropped, whose keys are thin against what a window spans.
 bool dense_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
-    if (n < DENSE_MIN_N || !aligned16 || k <= n / 100 * SPEC_MAX_KEEP_PERCENT) return false;
+    if (n < DENSE_MIN_N || !aligned16 || k <= (dt == ADATOPK_F32 ? n / 100 * SPEC_MAX_KEEP_PERCENT : n / LIST_DIV)) return false;
     const double share = static_cast<double>(k) / static_cast<double>(n);
     if (share > DENSE_MAX_KEEP) return false;
     const int epd = 4 / elem_size(dt), max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;

@@ -1,0 +1,55 @@
+"""What a batch of tensors that keep more than a fifth costs where its windows do not hold, and when they do.  Times are the least of several, of one
+kernel or call against another."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_12707_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+TYPES = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+
+
+def normal(n, seed):
+    return torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed))
+
+
+class Batch:
+    def __init__(self, xs, share):
+        self.xs, self.ks = xs, [int(x.numel() * share) for x in xs]
+        self.off = np.concatenate([[0], np.cumsum(self.ks)]).tolist()
+        self.idx = torch.empty(self.off[-1], dtype=torch.int32, device="cuda")
+        self.val = torch.empty(self.off[-1], dtype=xs[0].dtype, device="cuda")
+        self.err = torch.empty(len(xs), device="cuda")
+        self.ws = B.new_workspace(sum(x.numel() for x in xs), len(xs), xs[0].dtype)
+
+    def compress(self):
+        B.adatopk_compress_segmented(self.xs, self.ks, self.idx, self.val, self.off, self.err, self.ws)
+
+    def stages(self):
+        times = {}
+        with B.measuring():
+            for _ in range(6):
+                self.compress()
+                torch.cuda.synchronize()
+                for name, t in zip(B.measure_stage_names(), B.measure_read()):
+                    if t > 0:
+                        times[name] = min(t, times.get(name, t))
+        return times
+
+    def time(self):
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            self.compress()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times[2:])
+
+
+@pytest.mark.parametrize("dtype,share,dense", [("f32", 0.2, False), ("f32", 0.22, True), ("bf16", 0.22, False), ("f16", 0.25, False), ("bf16", 0.26, True)])
+def test_lists_are_for_shares_that_fit_them(dtype, share, dense):
+    batch = Batch([normal(8 << 20, i).to(TYPES[dtype]) for i in range(4)], share)
+    assert ("k_place_dense" in batch.stages()) == dense
