@@ -37,7 +37,7 @@
 //             (the tensor's last one where every compute unit has one already) adds up the error norm from the partial sums the
 //             earlier kernels stored, in a fixed order
 //   k_place_dense  (tensors of a large batch that keep more than 21 %) their speculative scan lists the keys within the window's bins
-//             alone and counts those above; this reads the input a second time and places what is above T
+//             alone and counts those above; this reads the input once more, whether the window held or not, places what is above T and adds up the error norms
 // Cross-block order comes from counts that an EARLIER kernel stored and that every block
 // of the next kernel scans for itself: no block waits for another block (k_judge's exact passes aside, whose
 // waits end whatever workgroups are running), no block needs a release fence (on this chip an agent-scope fence writes back the L2 of its
@@ -145,11 +145,11 @@ constexpr double SPEC_SIGMAS = 5.0;        // width of the sample's rank bracket
 constexpr double SPEC_SIGMAS_LOW = 3.5;    // ... and lower side: every key down to there is a candidate, so this one costs
 constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k and the bracket's margin) may not fit a quarter of a chunk
 // Tensors of a batch that keep more than that (16-bit types: more than a list holds) speculate as well, in launches of their own, if they hold as many elements as the list kernels' wide form asks
-// for (five launches more beside other tensors).  Compress, us, exact passes / so: 8 fp32 tensors of 8.4 M, 25 % kept 343 / 189, 50 % 349 / 213, 90 % 383 / 263, 99 %
-// 403 / 371 (thin keys, windows miss); four at 30 % 164 / 112; bf16 30 % 204 / 157.  Below SPEC_MAX_KEEP_PERCENT lists of all that is kept are the better way: 18 % 138, so 174.  So they are for the 16-bit types
-// up to a quarter, unless most keys are in the k-th key's binade: 22 %, bf16 behind a ReLU 70 / 89, f16 50 / 64, bf16 normal 150 / 92.
+// for (four launches more beside other tensors).  Compress, us, exact passes / so: 8 fp32 tensors of 8.4 M, 25 % kept 344 / 194, 50 % 344 / 208, 90 % 391 / 267, 99 %
+// 410 / 361; four at 35 % 164 / 114; bf16 30 % 206 / 154.  Below SPEC_MAX_KEEP_PERCENT lists of all that is kept are the better way: 18 % 138, so 174.  So they are for the 16-bit types
+// up to a quarter, unless most keys are in the k-th key's binade: 22 %, bf16 behind a ReLU 70 / 95, f16 50 / 68, bf16 normal 150 / 102.
 // Where the window's bins hold most of a chunk (equal keys, zeros) its list overflows and the input is read a third time: values behind a ReLU, 70 %
-// kept 418 / 355, one key throughout 338 / 352.  A window that misses costs the exact passes on top: behind a ReLU with about as many kept as are not zero, 48 to 52 %, 396 / 502.
+// kept 427 / 354.
 constexpr int64_t DENSE_MIN_N = 1 << 20, DENSE_MIN_F32 = WIDE_MIN_F32, DENSE_MIN_16 = WIDE_MIN_16;
 constexpr double DENSE_MAX_KEEP = 0.995;
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
@@ -1677,13 +1677,14 @@ __device__ __forceinline__ uint32_t part_entries(const SegDesc &sg, int g, uint3
     return (first + per < entries) ? per : entries - static_cast<uint32_t>(first);
 }
 
-// Whether a tensor's window held and its lists are those of the window's bins alone: then a list is one part, whatever the tensor's parts per
-// chunk (which serve where the window missed or a list overflowed), and the keys above the bins are the last entry of the chunk's row.
-__device__ __forceinline__ bool dense_held(const SegDesc &sg, bool spec_held) { return (sg.flags & FLAG_DENSE) != 0 && spec_held; }
-__device__ __forceinline__ bool one_part(const SegDesc &sg, uint32_t count, bool dense) { return dense && count <= list_cap(sg); }
+// Whether a chunk of a dense tensor (FLAG_DENSE) whose window held is one part, whatever the tensor's parts per chunk: its list is that of the window's
+// bins alone, and the keys above the bins are the last entry of the chunk's row.  (The parts serve where the window missed or a list overflowed.)
+__device__ __forceinline__ bool one_part(const SegDesc &sg, uint32_t count, bool spec_held) {
+    return (sg.flags & FLAG_DENSE) != 0 && spec_held && count <= list_cap(sg);
+}
 // Whether a part has stored its counts.
-__device__ __forceinline__ bool part_counted(const SegDesc &sg, int g, uint32_t count, uint32_t part, uint32_t sl, bool dense) {
-    return one_part(sg, count, dense) ? part == 0 : part_entries(sg, g, count, part, sl) != 0;
+__device__ __forceinline__ bool part_counted(const SegDesc &sg, int g, uint32_t count, uint32_t part, uint32_t sl, bool spec_held) {
+    return one_part(sg, count, spec_held) ? part == 0 : part_entries(sg, g, count, part, sl) != 0;
 }
 
 // Part `part` of 1 << sl of chunk g's candidates: the entries are cut into that many runs of whole list
@@ -1925,7 +1926,7 @@ __device__ __attribute__((noinline)) DenseCounts refine_wide_tiles(const ChunkSo
 // higher bins are counted (kept whatever the last digit is), the squares of those in lower bins are summed
 // (dropped whatever it is).  `first`: the first LU entries of every thread.  `slot`: the part's place in the
 // arrays of the parts.  above_all: further elements above bin Bw.  h: NB3 words of LDS, sm: 2 * NW, smd: NW doubles.
-template <int VEC, bool WIDE>
+template <int VEC, bool WIDE, bool DENSE = false>
 __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkSource<VEC> &src, size_t slot, uint32_t Bw, uint32_t lo,
                                             uint32_t shw, const uint32_t (&first)[LU], uint32_t *h, uint32_t *sm, double *smd, uint32_t above_all = 0) {
     const uint32_t shl = VEC == TAG_F32 ? 0u : 16u;
@@ -1959,6 +1960,20 @@ __device__ __forceinline__ void refine_part(const Launch &a, int s, const ChunkS
     for (uint32_t i0 = i_next; i0 < src.len; i0 += LU * BLOCK) {
         uint32_t more[LU];
         load_raw<VEC>(src, i0, more);
+        if (DENSE && src.from_input && whole_wave<VEC>(src, i0)) {  // wave-uniform
+            const uint32_t raw0 = lane_value(more[0], 0);
+            uint32_t other = 0;
+#pragma unroll
+            for (int j = 0; j < LU; ++j) other |= more[j] ^ raw0;
+            if (__ballot(other != 0) == 0) {  // wave-uniform: one key, counted once
+                const uint32_t key = key_of<VEC>(raw0), bin = window_bin(key, lo, shw);
+                if (key >= lo && bin > Bw) def += LU;
+                if (key >= lo && bin == Bw && (threadIdx.x & 63) == 0) atomicAdd(&h3[((key - lo) & ((1u << shw) - 1u)) >> shl], 64u * LU);
+                const double xd = key >= lo && bin < Bw ? static_cast<double>(value_of<VEC>(raw0)) : 0.0;
+                acc = fma(static_cast<double>(LU) * xd, xd, acc);
+                continue;
+            }
+        }
 #pragma unroll
         for (int j = 0; j < LU; ++j) count_entry(list_entry(i0) + 64 * j, more[j]);
     }
@@ -2013,7 +2028,7 @@ template <int VEC, bool WIDE, bool DENSE = false> __global__ __launch_bounds__(B
     const uint32_t lo = spec ? stw.loA : stw.loB;
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
     const uint32_t count = a.cnt[g];
-    const bool one = DENSE && one_part(sg, count, dense_held(sg, spec));
+    const bool one = DENSE && one_part(sg, count, spec);
     // (Not always the chunk's first workgroup: every eighth of the grid is on the same XCD.  Six tensors of 8.4 M, eight parts to a chunk: 36 us, so 15.)
     if (one && part != (static_cast<uint32_t>(c) & ((1u << sl) - 1))) return;
     const size_t slot = one ? a.part_begin[s] + (static_cast<uint32_t>(c) << sl) : blockIdx.x;
@@ -2033,7 +2048,7 @@ template <int VEC, bool WIDE, bool DENSE = false> __global__ __launch_bounds__(B
         a.state[s].Bw = pw.B;  // NBW when nothing is kept
         a.state[s].c_gtw = pw.above;
     }
-    refine_part<VEC, WIDE>(a, s, src, slot, pw.B, lo, shw, first, h, sm, smd, above_all);
+    refine_part<VEC, WIDE, DENSE>(a, s, src, slot, pw.B, lo, shw, first, h, sm, smd, above_all);
 }
 
 // k_emit's placing over the whole dense tiles of a part read from the input; returns the counts of
@@ -2179,7 +2194,7 @@ __device__ __forceinline__ Threshold threshold_f32(const Launch &a, const uint32
 // the candidates below bin Bw (refine_part), and the counts of the candidates in bin Bw by last digit: the dropped
 // ones of a bin add count * value^2.  Fixed summation order.
 // dropped_below: this thread's share of the first two.
-__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t first_part, bool dense) {
+__device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &sg, uint32_t first_part, bool spec_held) {
     double sum = 0.0;
     const uint32_t sl = sub_log(sg);
     const uint32_t nparts = static_cast<uint32_t>(sg.nchunks) << sl;
@@ -2188,7 +2203,7 @@ __device__ __forceinline__ double dropped_below(const Launch &a, const SegDesc &
         const uint32_t count = a.cnt[sg.chunk_begin + cc];
         const double below_bin = a.lerr[first_part + e], below_window = a.chunk_err[sg.chunk_begin + cc];
         if (pp == 0) sum += below_window;
-        if (part_counted(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl, dense)) sum += below_bin;  // (an empty part stored nothing)
+        if (part_counted(sg, sg.chunk_begin + static_cast<int>(cc), count, pp, sl, spec_held)) sum += below_bin;  // (an empty part stored nothing)
     }
     return sum;
 }
@@ -2438,8 +2453,6 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     const uint32_t shw = spec ? stw.shwA : stw.shwB;
     const uint32_t kout = static_cast<uint32_t>(sg.k);
     const ChunkSource<VEC> src = chunk_source<VEC>(a, sg, g, norm_only ? 0u : a.cnt[g], part, sl, lo);
-    const bool dense = dense_held(sg, spec);
-    if (dense && !norm) return;  // k_place_dense places its pairs
     if (norm && a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
     if (VEC == TAG_F32 && stw.failed != 0) {  // uniform; k_judge gave up (nothing that follows is set)
         if (norm && threadIdx.x == 0) *err_ptr(a, sg) = __uint_as_float(QUIET_NAN);
@@ -2448,7 +2461,7 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
     // what the error norm's workgroup needs of the chunks arrives behind the prologue
     double below_t = 0.0;
     if (norm) {
-        if (VEC == TAG_F32) below_t = dropped_below(a, sg, first_part, dense);
+        if (VEC == TAG_F32) below_t = dropped_below(a, sg, first_part, spec);
         else if (static_cast<int>(threadIdx.x) < sg.nchunks) below_t = a.chunk_err[sg.chunk_begin + threadIdx.x];
     }
 
@@ -2474,28 +2487,59 @@ template <int VEC, bool WIDE> __global__ __launch_bounds__(BLOCK) void k_emit(La
         t = threshold_16(a, pw, kout, lo, shw);
         if (norm) error_norm_16<VEC>(a, sg, t, lo, shw, below_t, h, l.smd);
     }
-    if (norm_only || dense) return;
+    if (norm_only) return;
     emit_part<VEC, WIDE>(a, sg, src, first_part, c, part, t, raw, id, l);
 }
 
-// k_place_dense.  The pairs of a tensor that keeps a large share and whose window held: the input is read a second time, and every element
-// above T goes out, the first q equal to T with them.  (With the exact passes such a tensor was read four times: the top digits, the window's counts, a
+// A dense tensor's error norm (and its message's header), by a workgroup of BLOCK threads.  h: NBW + 1 words of LDS (16-bit types), sm: 2 * NW.
+template <int VEC>
+__device__ __forceinline__ void sum_error_norm(const Launch &a, int s, const SegStateWords &stw, uint32_t *h, uint32_t *sm, uint32_t *s_pick, double *smd) {
+    const SegDesc &sg = a.seg[s];
+    const bool held = stw.spec_held != 0;
+    const uint32_t kout = static_cast<uint32_t>(sg.k), lo = held ? stw.loA : stw.loB, shw = held ? stw.shwA : stw.shwB;
+    if (a.wire != 0) write_header<VEC>(a.idx_out, sg.out_off, sg.n, sg.k, a.idx64 != 0, sg.ratio);
+    if constexpr (VEC == TAG_F32) {
+        uint32_t my_bins[NB3 / BLOCK];
+#pragma unroll
+        for (int j = 0; j < NB3 / BLOCK; ++j) my_bins[j] = a.G3[s * NB3 + threadIdx.x * (NB3 / BLOCK) + j];
+        const double below_t = dropped_below(a, sg, a.part_begin[s], held);
+        const Threshold t = threshold_f32(a, my_bins, kout, stw.Bw, stw.c_gtw, lo, shw, sm, s_pick);
+        error_norm_f32<VEC>(a, sg, t, lo + (stw.Bw << shw), my_bins, below_t, smd);
+    } else {
+        const double below_t = static_cast<int>(threadIdx.x) < sg.nchunks ? a.chunk_err[sg.chunk_begin + threadIdx.x] : 0.0;
+        const ColumnPick pw = column_pick<NBW, NCW>(a.rowsW + static_cast<size_t>(sg.chunk_begin) * NBW, a.coarseW + static_cast<size_t>(sg.chunk_begin) * NCW,
+                                                    sg.nchunks, kout, h);
+        error_norm_16<VEC>(a, sg, threshold_16(a, pw, kout, lo, shw), lo, shw, below_t, h, smd);
+    }
+}
+
+// k_place_dense.  The pairs of a tensor that keeps a large share: the input is read once more, and every element
+// above T goes out, the first q equal to T with them.  (With the exact passes alone such a tensor was read four times: the top digits, the window's counts, a
 // part's counts and the placing.  24 tensors of 8.4 M with planned keep counts, six of them so: 804 us per compress and decompress, now 684; the placing of
-// those six, 201 MB read and 203 MB written, 76 us, what a copy takes.)  One workgroup per chunk, which knows its
+// those six, 201 MB read and 203 MB written, 76 us, what a copy takes.)  Also where the window missed: k_emit's reads of a part without a list, one workgroup per chunk and no tile ahead, were
+// what a call then ended with (8 bf16 tensors of 8.4 M behind a ReLU at 50 %, exact passes / window missed, k_emit / so: 283 / 447 / 270; fp32 402 / 488 / 431).
+// One workgroup per chunk, which knows its
 // first output slot from the earlier chunks' counts; a wavefront reads rows of 64 consecutive elements, so its stores are contiguous, and the wavefronts exchange
-// one count each per tile.
+// one count each per tile.  The error norms are added up by workgroups in front of the others (a launch of k_emit for that took 4 to 6 us).
 constexpr int PLACE_THREADS = 1024, PLACE_WAVES = PLACE_THREADS / 64, PLACE_ROWS = TILE / PLACE_THREADS;
 template <int VEC> __global__ __launch_bounds__(PLACE_THREADS, 8) void k_place_dense(Launch a) {
     using R = typename Raw<VEC>::type;
     __shared__ uint32_t sm[2 * PLACE_WAVES], s_pick[2], s_counts[2][PLACE_WAVES];
-    __shared__ uint32_t red[NCW + NBW / NCW];
-    const int g = blockIdx.x;
-    const int s = find_segment(a, g);
+    __shared__ uint32_t red[VEC == TAG_F32 ? 1 : NBW + 1];  // of a bucket search; 16-bit types' error norm: as in k_emit
+    const bool norm = blockIdx.x < a.norms;  // uniform
+    const int g = static_cast<int>(blockIdx.x - a.norms);
+    if (norm && (blockIdx.x >= static_cast<uint32_t>(a.S) || threadIdx.x >= BLOCK)) return;  // (whole wavefronts: barriers wait for those that are left)
+    const int s = norm ? static_cast<int>(blockIdx.x) : find_segment(a, g);
     const SegDesc &sg = a.seg[s];
     const SegStateWords stw = read_state(&a.state[s]);
-    if (!dense_held(sg, stw.spec_held != 0)) return;  // k_emit has placed its pairs
+    if (norm) {
+        __shared__ double smd[NW];
+        sum_error_norm<VEC>(a, s, stw, red, sm, s_pick, smd);
+        return;
+    }
+    const bool held = stw.spec_held != 0;
     const int c = g - sg.chunk_begin;
-    const uint32_t kout = static_cast<uint32_t>(sg.k), lo = stw.loA, shw = stw.shwA, sl = sub_log(sg), lane = threadIdx.x & 63;
+    const uint32_t kout = static_cast<uint32_t>(sg.k), lo = held ? stw.loA : stw.loB, shw = held ? stw.shwA : stw.shwB, sl = sub_log(sg), lane = threadIdx.x & 63;
     const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     const int64_t beg = static_cast<int64_t>(c) * sg.E;
     const uint32_t len = static_cast<uint32_t>(beg + sg.E < sg.n ? sg.E : sg.n - beg);
@@ -2529,10 +2573,10 @@ template <int VEC> __global__ __launch_bounds__(PLACE_THREADS, 8) void k_place_d
     if (t.any_kept && static_cast<int>(threadIdx.x) < c) {
         const int before = sg.chunk_begin + static_cast<int>(threadIdx.x);
         const uint32_t count = a.cnt[before];
-        const bool one = VEC != TAG_F32 || one_part(sg, count, true);
+        const bool one = VEC != TAG_F32 || one_part(sg, count, held);
         const size_t first = VEC == TAG_F32 ? a.part_begin[s] + (threadIdx.x << sl) : static_cast<uint32_t>(before);
         for (uint32_t part = 0; part < (one ? 1u : 1u << sl); ++part) {
-            if (!one && !part_counted(sg, before, count, part, sl, true)) continue;
+            if (!one && !part_counted(sg, before, count, part, sl, held)) continue;
             const uint32_t *r = t.rows + (first + part) * t.row_len;
             const uint32_t above = t.t_bin + 1 < t.row_len ? r[t.t_bin + 1] : 0u;
             gt += above + (t.extra_gt != nullptr ? t.extra_gt[first + part] : 0u);
@@ -4216,7 +4260,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     const bool wide = (one_per_cu && parts.x == grid.x) || no_lists;  // see Wide
     // (a wide kernel has a compute unit's registers to itself: one workgroup too many waits for another one to end, 2 us)
     const uint32_t S = static_cast<uint32_t>(a.S);
-    a.norms = (a.err_out != nullptr || a.wire) && (!wide || parts.x + S <= CTARGET_ONE) ? norm_workgroups(S) : 0u;
+    a.norms = (a.err_out != nullptr || a.wire) && (dense || !wide || parts.x + S <= CTARGET_ONE) ? norm_workgroups(S) : 0u;
     const dim3 parts_and_norms(parts.x + a.norms);
     const bool judge = speculate && a.S == 1 && !dense;
     if (judge) {
@@ -4236,11 +4280,12 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
             else launch(ST_REFINE, k_refine<VEC, false>, parts, st, a);
         }
     }
-    if (VEC == TAG_F32 || !judge) {
+    if (dense) {
+        launch<PLACE_THREADS>(ST_PLACE, k_place_dense<VEC>, dim3(total_chunks + a.norms), st, a);
+    } else if (VEC == TAG_F32 || !judge) {
         if (wide) launch(ST_EMIT, k_emit<VEC, true>, parts_and_norms, st, a);
         else launch(ST_EMIT, k_emit<VEC, false>, parts_and_norms, st, a);
     }
-    if (dense) launch<PLACE_THREADS>(ST_PLACE, k_place_dense<VEC>, grid, st, a);
     return hipGetLastError() == hipSuccess ? ADATOPK_OK : ADATOPK_ERUNTIME;
 }
 

@@ -53,3 +53,11 @@ class Batch:
 def test_lists_are_for_shares_that_fit_them(dtype, share, dense):
     batch = Batch([normal(8 << 20, i).to(TYPES[dtype]) for i in range(4)], share)
     assert ("k_place_dense" in batch.stages()) == dense
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_a_window_that_misses_costs_little(dtype):
+    # behind a ReLU, as many kept as are not zero or a few more or less; tensors off the 16-byte grid take the exact passes at once
+    xs = [torch.relu(normal((8 << 20) + 8, i)).to(TYPES[dtype]) for i in range(4)]
+    once = Batch([x[2:2 - 8] for x in xs], 0.5).time()
+    assert Batch([x[:-8] for x in xs], 0.5).time() < 1.25 * once
