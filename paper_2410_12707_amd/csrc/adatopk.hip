@@ -152,6 +152,15 @@ constexpr int64_t SPEC_MAX_KEEP_PERCENT = 21;  // beyond this the candidates (k 
 // kept 427 / 354.
 constexpr int64_t DENSE_MIN_N = 1 << 20, DENSE_MIN_F32 = WIDE_MIN_F32, DENSE_MIN_16 = WIDE_MIN_16;
 constexpr double DENSE_MAX_KEEP = 0.995;
+// A window that misses costs a scan on top of the exact passes, which the placing by k_place_dense makes up for in part, and all of the passes' time if one tensor of
+// eight misses.  So the bracket is wider than for tensors that keep less, and the sample is taken in pieces of 64 bytes: values with a scale for every 1600, standard deviation 0.5 of
+// its logarithm, 50 % kept, exact passes / runs of 1 KB, 3.5 deviations / so: fp32 349 / 321 / 211, bf16 30 % 210 / 376 / 159; deviation 1.0, fp32 350 / 420 / 210.
+// 16-bit types: 8 deviations, a list that is a little longer costs nothing there (a window's bins are 16 binades).
+// And the scan is not made where the sample says that a window is not worth it: the k-th key is zero or not, as it happens; it is among keys so thin
+// that a bracket of DENSE_SPANS windows holds it; or all but one in DENSE_ALIKE keys are in its bin, and the lists would overflow.  Behind a ReLU, about as many kept as are not zero, exact passes /
+// scan and passes / so: 48 % 348 / 405 / 322, 50 % 405 / 431 / 384, bf16 50 % 282 / 270 / 237; one key throughout, 50 % 338 / 353 / 334, 25 % 315 / 330 / 349, 70 % 320 / 374 / 361.
+constexpr double DENSE_SIGMAS_F32 = 5.0, DENSE_SIGMAS_16 = 8.0;
+constexpr uint32_t DENSE_SPANS = 6, DENSE_ALIKE = 8;
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
 constexpr uint32_t MERGE_DENSE_SHIFT = 6;        // k > n / 64 takes the LDS-built variant of the one-kernel decompress ...
 constexpr uint32_t MERGE_DENSE_SHIFT_SMALL = 5;  // ... for outputs up to MERGE_SMALL_BYTES n / 32, and any large output takes it (merge_dense)
@@ -1246,26 +1255,33 @@ constexpr int SAMPLE_BATCH = 16;  // dwords per thread and batch with BLOCK thre
 // barrier (block-wide suffix sums and the two threads that found a rank took 0.9 us, this 0.3).
 struct RankedBins {
     uint32_t lo, hi;
+    uint32_t above_lo;  // counted keys in the bins above lo
+    uint32_t seen;      // ... in the bins looked at; all there are if no bin holds the first rank
 };
 __device__ __forceinline__ RankedBins ranked_bins(const uint32_t *h, uint32_t top, uint32_t lowest, uint32_t rank_lo, uint32_t rank_hi) {
-    RankedBins found = {NSB, NSB};
+    RankedBins found = {NSB, NSB, 0, 0};
     const uint32_t lane = threadIdx.x & 63;
     uint32_t above = 0;  // counted keys in the bins looked at so far
     for (uint32_t base = top & ~255u;; base -= 256) {
         const uint4 c = reinterpret_cast<const uint4 *>(h)[base / 4 + lane];
         const uint32_t own = c.x + c.y + c.z + c.w, inc = wave_incl_scan(own), total = lane_value(inc, 63);
         const uint32_t higher = above + total - inc;  // ... and in those of the lanes after this one
-        auto pick = [&](uint32_t rank, uint32_t &bin) {
+        auto pick = [&](uint32_t rank, uint32_t &bin, uint32_t &above_it) {
             const uint64_t here = __ballot(higher < rank && higher + own >= rank);
             if (here == 0) return;  // uniform
             const int l = __builtin_ctzll(here);
-            const uint32_t w3 = lane_value(higher, l) + lane_value(c.w, l), w2 = w3 + lane_value(c.z, l), w1 = w2 + lane_value(c.y, l);
+            const uint32_t w4 = lane_value(higher, l), w3 = w4 + lane_value(c.w, l), w2 = w3 + lane_value(c.z, l), w1 = w2 + lane_value(c.y, l);
             bin = base + 4 * l + (w3 >= rank ? 3u : (w2 >= rank ? 2u : (w1 >= rank ? 1u : 0u)));
+            above_it = w3 >= rank ? w4 : (w2 >= rank ? w3 : (w1 >= rank ? w2 : w1));
         };
-        pick(rank_lo, found.lo);
-        pick(rank_hi, found.hi);
+        uint32_t above_hi;
+        pick(rank_lo, found.lo, found.above_lo);
+        pick(rank_hi, found.hi, above_hi);
         above += total;
-        if (above >= rank_lo || base <= lowest) return found;
+        if (above >= rank_lo || base <= lowest) {
+            found.seen = above;
+            return found;
+        }
     }
 }
 // Byte offset of the sample bin (4 * (key >> SAMPLE_SH)) of element hh of a dword.
@@ -1277,8 +1293,9 @@ template <int VEC> __device__ __forceinline__ uint32_t sample_bin(uint32_t dword
 // after_sample is called when the sample has arrived: what is asked for there does not delay it.  (The chunk's first tile asked for right behind the
 // sample's own loads, us per compress and decompress: 25 M fp32 56.4, so 55.9; 4.9 M wire message 28.1, 27.9; two tiles there: 55.6 and 28.7.)
 // sm: 2 * NT / 64 words.  No wavefront has read hs to the end before it returns, but every one has before the caller's next barrier.
-template <int VEC, int NT, typename Prefetch>
-__device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, Prefetch after_sample, uint32_t &lo, uint32_t &shw) {
+// DENSE: returns whether the scan is worth it, the same in every workgroup (see DENSE_SIGMAS_F32).
+template <int VEC, int NT, bool DENSE, typename Prefetch>
+__device__ __forceinline__ bool sample_window(const SegDesc &sg, uint32_t *hs, uint32_t *sm, Prefetch after_sample, uint32_t &lo, uint32_t &shw) {
     constexpr int EPD = VEC / 4;
     constexpr int BATCH = SAMPLE_BATCH * BLOCK / NT, WAVES = NT / 64;
     constexpr int MAXB = SAMPLE_ELEMS / NT / EPD / BATCH;  // batches at the full sample size
@@ -1291,7 +1308,7 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     constexpr int QUADS = BATCH / 4;
     const int run_shift = __builtin_ctz(QUADS * WAVES) + (nbatch >= 4 ? 2 : (nbatch >= 2 ? 1 : 0));
     const uint64_t nruns = (static_cast<uint64_t>(sg.n) / EPD) / 256;
-    const bool fine = sg.n < SAMPLE_FINE_BELOW;  // uniform: a run's sixteen 64-byte pieces lie `spread` pieces apart
+    const bool fine = DENSE || sg.n < SAMPLE_FINE_BELOW;  // uniform: a run's sixteen 64-byte pieces lie `spread` pieces apart
     const uint32_t skew = fine ? 1u : SAMPLE_SKEW;
     // (An odd number, and the runs are shifted by less than that many pieces: activations repeat their channels at even distances.  Run r
     // begins at most at run nruns - 1 - (nruns - 1 >> run_shift), and with its shift it is at most as long as what follows there.)
@@ -1407,8 +1424,11 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     // is a zero: then the k-th key may be one, too.  All keys of the branch are uniform.)
     constexpr uint32_t SPAN = (NBW - 1) << BITS3;
     if (VEC == TAG_F32 && bins.lo < NSB && hi > lo && hi - lo > SPAN) {
-        const uint32_t rank = (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie SPEC_SIGMAS_LOW and SPEC_SIGMAS from it, and both have been found)
-        const uint32_t middle = (ranked_bins(hs, top, floor_bin / 4, rank, 0).lo << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
+        const uint32_t rank = DENSE ? (r_lo + r_hi) / 2 : (r_lo * 10 + r_hi * 7) / 17;  // (the ranks lie the bracket's standard deviations from it, and both have been found)
+        const RankedBins at = ranked_bins(hs, top, floor_bin / 4, rank, 0);
+        uint32_t middle = (at.lo << SAMPLE_SH) + (1u << (SAMPLE_SH - 1));
+        if (DENSE)  // (as far into its bin as the rank is: thin keys, three or four bins to the window)
+            middle = (at.lo << SAMPLE_SH) + static_cast<uint32_t>((1.0f - (static_cast<float>(rank - at.above_lo) - 0.5f) / static_cast<float>(hs[at.lo])) * (1 << SAMPLE_SH));
         if (middle > lo + SPAN / 2) lo = middle - SPAN / 2;
     }
     // fp32: bins as fine as the bracket and a last digit of BITS3 bits allow, the least shift that makes NBW - 1 bins
@@ -1417,6 +1437,14 @@ __device__ __forceinline__ void sample_window(const SegDesc &sg, uint32_t *hs, u
     const uint32_t keys_per_bin = (width - 1) / (NBW - 1) + 1;
     const uint32_t shift = keys_per_bin > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(keys_per_bin - 1)) : 0u;
     shw = VEC != TAG_F32 ? 16u : (shift < static_cast<uint32_t>(BITS3) ? shift : static_cast<uint32_t>(BITS3));
+    if constexpr (DENSE) {
+        constexpr uint32_t ALL = BATCH * EPD * NT;  // sampled elements of a batch
+        if (bins.lo == NSB) return bins.seen < (r_lo * 5 + r_hi * 11) / 16 && bins.seen * DENSE_ALIKE >= static_cast<uint32_t>(nbatch) * ALL;
+        if (hi - (bins.lo << SAMPLE_SH) > (VEC == TAG_F32 ? DENSE_SPANS * SPAN : static_cast<uint32_t>(NBW - 1) << 16)) return false;
+        const uint32_t most_alike = larger(hs[bins.lo], hs[bins.hi < NSB ? bins.hi : bins.lo]);
+        return most_alike + static_cast<uint32_t>(nbatch) * (ALL / DENSE_ALIKE) <= static_cast<uint32_t>(nbatch) * ALL;
+    }
+    return true;
 }
 
 // What the workgroups of k_judge (further down) share, cleared by the scan in front of it: in the last-digit
@@ -1602,11 +1630,15 @@ __global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch
                     for (uint32_t b = threadIdx.x; b < sizeof(JudgeSync) / 4; b += NT) reinterpret_cast<uint32_t *>(judge_sync(a))[b] = 0;
             }
         };
-        sample_window<VEC, NT>(sg, l.smem, l.sm, first_tile_and_clear, lo, shw);
+        const bool worth = sample_window<VEC, NT, DENSE>(sg, l.smem, l.sm, first_tile_and_clear, lo, shw);
         if (c == 0 && threadIdx.x == 0) {
             a.state[s].loA = lo;
             a.state[s].shwA = shw;
             a.state[s].failed = 0u;
+        }
+        if (DENSE && !worth) {  // uniform over the tensor's workgroups
+            if (threadIdx.x == 0) a.cpairA[g] = make_uint2(0, 0);
+            return;
         }
     } else {
         // The same in every workgroup of the tensor: bucket B1 of the k-th key from the rows of k_hist1
@@ -4335,16 +4367,17 @@ bool speculation_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, u
 }
 
 // The same for a tensor of a batch that keeps more (DENSE_MAX_KEEP of it, at most): of the sampled elements, mu lie among the k largest with a standard
-// deviation of sqrt(mu (1 - k / n)), so a sample of a quarter will do until few are dropped, whose keys are thin against what a window spans.
+// deviation of sqrt(mu (1 - k / n)), so a sample of half the size will do until few are dropped, whose keys are thin against what a window spans (16-bit
+// types, whose window spans more: the smallest one).  A quarter in fp32: 4 tensors of 8.4 M behind a ReLU at 35 % 168 to 183 us, as windows missed, so 106.
 bool dense_ranks(int64_t n, int64_t k, adatopk_dtype dt, bool aligned16, uint32_t *ranks, uint32_t *batches) {
     if (n < DENSE_MIN_N || !aligned16 || k <= (dt == ADATOPK_F32 ? n / 100 * SPEC_MAX_KEEP_PERCENT : n / LIST_DIV)) return false;
     const double share = static_cast<double>(k) / static_cast<double>(n);
     if (share > DENSE_MAX_KEEP) return false;
     const int epd = 4 / elem_size(dt), max_batches = SAMPLE_ELEMS / BLOCK / epd / SAMPLE_BATCH;
-    int nb = share > 0.9 ? 4 : (share > 0.75 ? 2 : 1);
+    int nb = dt != ADATOPK_F32 ? 1 : (share > 0.75 ? 4 : 2);
     if (nb > max_batches) nb = max_batches;
     const double ns = static_cast<double>(nb) * SAMPLE_BATCH * BLOCK * epd, mu = share * ns, sigma = sqrt(mu * (1.0 - share));
-    const double lo = ceil(mu + SPEC_SIGMAS_LOW * sigma + 2.0), hi = floor(mu - SPEC_SIGMAS * sigma - 2.0);
+    const double sigmas = dt == ADATOPK_F32 ? DENSE_SIGMAS_F32 : DENSE_SIGMAS_16, lo = ceil(mu + sigmas * sigma + 2.0), hi = floor(mu - sigmas * sigma - 2.0);
     *ranks = static_cast<uint32_t>(lo < ns ? lo : ns) | (hi < 1.0 ? 0u : static_cast<uint32_t>(hi) << 16);
     *batches = static_cast<uint32_t>(nb);
     return true;

@@ -61,3 +61,25 @@ def test_a_window_that_misses_costs_little(dtype):
     xs = [torch.relu(normal((8 << 20) + 8, i)).to(TYPES[dtype]) for i in range(4)]
     once = Batch([x[2:2 - 8] for x in xs], 0.5).time()
     assert Batch([x[:-8] for x in xs], 0.5).time() < 1.25 * once
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("share", [0.3, 0.5])
+def test_windows_hold_where_the_scale_varies(dtype, share):
+    n = 8 << 20
+    xs = []
+    for i in range(4):
+        scale = torch.exp(0.5 * normal(n // 1600 + 1, 100 + i)).repeat_interleave(1600)[:n]
+        xs.append((normal(n, i) * scale).to(TYPES[dtype]))
+    batch = Batch(xs, share)
+    batch.compress()
+    torch.cuda.synchronize()
+    assert batch.ws[:64 * len(xs)].view(torch.int32).cpu()[6::16].tolist() == [1] * len(xs)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_no_scan_for_a_window_that_is_not_worth_it(dtype):
+    xs = [normal(8 << 20, i).to(TYPES[dtype]) for i in range(4)]
+    scan = Batch(xs, 0.5).stages()["k_scan_spec"]
+    for alike in ([torch.relu(x) for x in xs], [torch.ones_like(x) for x in xs], [torch.zeros_like(x) for x in xs]):
+        assert Batch(alike, 0.5).stages()["k_scan_spec"] < 0.5 * scan
