@@ -3314,31 +3314,40 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_small(const SmallL
 //     in a histogram of the maxima, to a sixteenth of a binade;
 //   - the candidates, which reach the bound, into a list in LDS, a segment for each wavefront, in index order, and into a histogram over their keys; the
 //     squares of the others.
-// The k-th key's bin holds a few candidates, which are compared with one another, or settled by further digits if they are more.  Where a segment is
-// too short (sorted values, equal keys, a large keep share), keys are much alike or fewer than k elements are not zero, the elements are read again,
-// and one list without segments is made: of the same candidates, or of those that reach a closer bound, or of the keys above the threshold and enough
-// of those equal to it.
+// The k-th key's bin holds a few candidates, which are compared with one another, equal ones, or more, which further digits settle. Where a segment is
+// too short (sorted values, equal keys, an uneven tensor), keys are much alike or fewer than k elements are not zero, one list without segments is made from the
+// registers in another pass: of the same candidates, or of those that reach a closer bound, or of the keys above the threshold and enough
+// of those equal to it.  The closer bound and a guess at the threshold come from every sixteenth element; a pass that counts what reaches them says whether they will do.
+// (With the elements read again for every pass and a guess no finer than a sixteenth of a binade, keys within 3 % of each other took 67 us in 64 K tensors
+// and 18 in 8 K, sorted ones 30 and 13, so 23 and 12, 23 and 10.  16 K elements fit the segments whatever they are.)
 constexpr int MID_THREADS = 1024, MID_WAVES = MID_THREADS / 64, MID_GROUPS = 16, MID_GE = 4;  // groups per wavefront, elements per lane and group
 constexpr int MID_N = MID_THREADS * MID_GE * MID_GROUPS;  // largest tensor this path takes
 constexpr uint32_t MID_SEGMENT = 1024;                    // candidates of a wavefront that have room in its part of the list
 constexpr uint32_t MID_LIST = MID_WAVES * MID_SEGMENT;
+constexpr uint32_t MID_LOOSE = 1024;                      // ... that are listed rather than counted, beyond twice what is kept
+constexpr int MID_SAMPLE_BITS = 10;                       // bins over the sample's keys
+static_assert(1 << MID_SAMPLE_BITS == MID_THREADS, "a bin per thread");
 constexpr int MID_FIRST_BITS = 11, MID_FIRST = 1 << MID_FIRST_BITS;  // bins over the candidates' keys
 constexpr int MID_DIGIT_BITS = 12, MID_DIGIT = 1 << MID_DIGIT_BITS;  // further digits
 constexpr int MID_MAXSEG = 128;                           // tensors per launch (the table travels as kernel arguments)
 // Which tensors take this path.  It takes about 6 us, 0.1 for 1024 elements more and 1.4 for 1024 kept ones; the launches of the path for larger tensors 18 to 20
-// whatever the sizes, and more for a batch that fills the chip.  Where the list is made a second time (sorted values, equal keys) it is 5 to 14 us more,
-// for tensors whose keys are all within a few per cent of each other 40, so short calls stay well below the limit where the two cross.  GPU us of a compress call,
-// larger tensors' path / so: one fp32 tensor, 1 % kept, 9000 values 18.2 / 6.6, 32 768 18.6 / 8.7, 65 536 19.0 / 12.3 (sorted 19.6 / 29, equal 21.7 / 25.5), four of 50 000 at 2 % sorted 21.4 / 25.7;
-// 20 % kept, 9000 18.9 / 9.3, 32 768 19.4 / 17.6; 64 of 8 to 64 K at 1 % 21.7 / 13.1, 64 of 64 K 27.8 / 13.4, 24 of 60 000 at 5 % 21.2 / 18.0, 256 of 30 000 at 2 %
-// 99 / 32; bf16, one of 9000 14.5 / 6.6, two of 40 000 16.5 / 9.8.  (A single 16-bit tensor that speculates takes two launches, 12 us, and stays there.)
-constexpr int64_t MID_WORK = 1 << 17, MID_WORK_SHORT = 1 << 16, MID_SHORT_CALL = 1 << 20;
-inline bool mid_takes(int64_t n, int64_t k, int64_t n_total) {
-    return n <= MID_N && k <= n / 4 && n + 13 * k <= (n_total < MID_SHORT_CALL ? MID_WORK_SHORT : MID_WORK);
+// whatever the sizes (16-bit types 15 to 17), and more for a batch that fills the chip.  Where the list is made in another pass it is 3 to 10 us more: the limits lie where that
+// is no loss.  GPU us of a compress call, larger tensors' path / so (sorted; all keys equal): one fp32 tensor, 1 % kept, 9000 values 18.2 / 6.8 (19.7 / 8.5; 21.7 / 12.2), 32 768
+// 18.5 / 9.0 (20.1 / 14.9; 21.1 / 14.5), 57 000 18.9 / 11.9 (21.2 / 20.1; 27.3 / 20.0); four of 50 000 at 2 % 20.1 / 12.3 (21.9 / 21.0; 23.8 / 19.7); 64 of 8 to 64 K at 1 % 21.7 / 13.0
+// (23.3 / 23.0; 24.9 / 22.6), 64 of 64 K 26.2 / 13.1 (30.0 / 23.3; 39.0 / 22.8); beyond the limit 24 of 60 000 at 5 % 20.8 / 18.2 (23.5 / 28.6; uneven 21.1 / 25.2).  bf16: one of 9000
+// 14.6 / 6.8 (14.8 / 7.9; 17.8 / 12.6), two of 40 000 at 2 % 17.0 / 10.9 (19.1 / 16.9; 22.6 / 17.6); beyond, 24 of 65 536 at 1 % 15.6 / 13.2 (16.9 / 23.3; 19.3 / 23.9).
+// (A single 16-bit tensor of SPEC_MIN_N_16 elements and more stays with the other path, which takes two launches and 12 us where it speculates.)
+constexpr int64_t MID_WORK = 83 << 10, MID_WORK_SHORT = 1 << 16, MID_WORK_16 = 52 << 10, MID_SHORT_CALL = 1 << 20;
+inline bool mid_takes(int64_t n, int64_t k, int64_t n_total, bool f32) {
+    return n <= MID_N && k <= n / 4 && n + 13 * k <= (!f32 ? MID_WORK_16 : (n_total < MID_SHORT_CALL ? MID_WORK_SHORT : MID_WORK));
 }
-// ... also where k_small could do it: fp32 tensors the longest of which, whose time the call's is, has more elements than this.  k_small / k_mid, us, 64 tensors:
-// 4100 values at 1 % 7.2 / 6.7, at 20 % 8.0 / 8.1, 8192 at 1 % 8.0 / 6.9, at 20 % 10.3 / 9.3, 7000 behind a ReLU at 2 % 10.7 / 7.1, equal ones 13.1 / 10.6, sorted
-// 10.0 / 12.9; 128 of 1 to 8 K at 1 % 7.8 / 6.9; 3000 at 10 % 6.9 / 7.0.  16-bit types: 7000 at 5 % 7.2 / 7.3, f16 at 20 % 8.5 / 9.3.
-constexpr int64_t SMALL_LONG = 4096;
+// ... also where k_small could do it: fp32 calls by the longest tensor, whose time the call's is, and what is kept of it.  k_small / k_mid, us, 64 tensors of normal values (behind
+// a ReLU; multiples of 1/32, many to a key): 8192, 1 % 8.0 / 7.1 (11.1 / 7.0; 8.0 / 7.6), 20 % 10.4 / 9.3 (13.4 / 9.3; 10.5 / 9.6); 7000, 1 % 7.9 / 7.1, 5 % 7.9 / 7.6 (10.7 / 7.6; 8.0 / 9.3),
+// 20 % 9.9 / 9.3 (12.3 / 9.2; 10.3 / 12.4); 6000, 1 % 7.6 / 7.0 (10.2 / 7.0; 7.6 / 7.4), 5 % 7.7 / 7.6 (10.1 / 7.6; 7.7 / 9.2); 4100, 1 % 7.2 / 6.9, 20 % 8.8 / 8.4 (9.7 / 8.3; 8.1 / 11.3).
+constexpr int64_t SMALL_LONG = 4096, SMALL_LONG_KEPT = 8, SMALL_LONGER = 7168;
+inline bool mid_takes_small(int64_t longest, int64_t its_k, bool f32) {
+    return f32 && (longest > SMALL_LONGER || longest > SMALL_LONG + SMALL_LONG_KEPT * its_k);
+}
 static_assert(MID_WORK / 13 + 64 * MID_GE * MID_GROUPS <= MID_LIST, "k and the ties of a wavefront fit the list");
 constexpr int MID_K_SHIFT = 17;
 static_assert(MID_N < 1 << MID_K_SHIFT && MID_N / 4 < 1 << (32 - MID_K_SHIFT), "two counts travel in one word");
@@ -3391,6 +3400,7 @@ struct MidLds {
     uint32_t sm[3][MID_WAVES];
     double smd[MID_WAVES];
     uint32_t few[64], nfew;                              // the keys of one bin
+    uint32_t least_not, most;                            // their least, inverted, and largest
     SmallPick s_pick;
 };
 
@@ -3398,6 +3408,7 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
     using R = typename Raw<VEC>::type;
     constexpr int EPD = VEC / 4, GD = MID_GE / EPD;  // elements per dword, dwords per lane and group
     constexpr uint32_t SH = VEC == TAG_F32 ? SAMPLE_SH : SAMPLE_SH - 16;  // key >> SH: the bin of a maximum
+    constexpr uint32_t SH_NEAR = VEC == TAG_F16 ? SH + 3 : SH;                          // ... 16 to the binade in every type
     __shared__ MidLds l;
 
     const MidDesc &sg = a.seg[blockIdx.x];
@@ -3443,11 +3454,40 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
         for (uint32_t j = 0; j < MID_GROUPS; ++j)
             if (j < groups) with_last(i0 + j * GROUP, v[j], last);
     }
+    // The elements once more, one group at a time from memory: f(first index, raw patterns).
+    auto each_group = [&](auto &&f) {
+#pragma unroll 1
+        for (uint32_t j = 0; j < groups; ++j) {
+            uint32_t d[GD], r[MID_GE];
+            load(i0 + j * GROUP, d);
+            if (half_left) with_last(i0 + j * GROUP, d, static_cast<uint32_t>(x[n - 1]));
+#pragma unroll
+            for (int e = 0; e < MID_GE; ++e) r[e] = elem_of<VEC>(d[e / EPD], e % EPD);
+            f(i0 + j * GROUP, r);
+        }
+    };
     auto raw = [&](int j, int e) { return elem_of<VEC>(v[j][e / EPD], e % EPD); };
+    // A further pass: f(group) for the wavefront's groups, four behind one branch.  (What is derived from the elements is formed again: kept from pass to pass, or for several groups at once, it takes
+    // more registers than there are.)
+    auto pass = [&](auto &&f) {
+        uint32_t unsigned_bits = mid_key<VEC>(0xFFFFFFFFu);
+        uint32_t its_groups = groups;
+        asm volatile("" : "+s"(unsigned_bits), "+s"(its_groups));
+#pragma unroll
+        for (int q = 0; q < MID_GROUPS; q += 4)
+            if (q < static_cast<int>(its_groups)) {  // wave-uniform
+#pragma unroll
+                for (int j = q; j < q + 4; ++j)
+                    if (j < static_cast<int>(its_groups)) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        f(j, unsigned_bits);
+                    }
+            }
+    };
     reinterpret_cast<uint4 *>(l.h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
     reinterpret_cast<uint2 *>(l.first)[threadIdx.x] = make_uint2(0, 0);
     static_assert(NSB == 4 * MID_THREADS && MID_FIRST == 2 * MID_THREADS, "four bins per thread, and two");
-    if (threadIdx.x == 0) l.nfew = 0;
+    if (threadIdx.x == 0) l.nfew = l.least_not = l.most = 0;
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.state != nullptr) a.state[0].spec_held = a.state[0].failed = 0u;  // (no window was guessed)
 
@@ -3477,10 +3517,11 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
             for (int i = j + 4; i < MID_GROUPS; i += 4) quarter[j] = m[i] > quarter[j] ? m[i] : quarter[j];
             largest = quarter[j] > largest ? quarter[j] : largest;
         }
-        // (64 lanes that count on one word take 440 cycles: a wavefront half of whose keys are alike takes those together, and nothing is listed in segments)
+        // (64 lanes that count on one word take 440 cycles: a wavefront half of whose keys are alike takes those together.  Nothing is listed in segments then, nor where
+        // most of them lie within three sixteenths of a binade, as in sorted values.)
         // (Zeros are not counted, and no candidates: 20 fp32 tensors of 30 K of which 3 % are not zero 19.0 us when they passed for alike, now 9.1.)
         const uint32_t middle = lane_value(m[0], 31) >> SH;
-        skewed = __popcll(__ballot(m[0] >> SH == middle)) >= 32 && middle != 0;
+        skewed = (__popcll(__ballot(m[0] >> SH == middle)) >= 32 || __popcll(__ballot((m[0] >> SH_NEAR) - (middle >> (SH_NEAR - SH)) + 1 <= 2)) >= 48) && middle != 0;
         auto count = [&](uint32_t key) {
             if (skewed) hist_add(l.h, key >> SH, key >> SH != 0);  // (zeros need not be counted)
             else if (key >> SH) atomicAdd(&l.h[key >> SH], 1u);
@@ -3516,289 +3557,332 @@ template <int VEC> __global__ __launch_bounds__(MID_THREADS) void k_mid(const Mi
     uint32_t own = 0;  // of this wavefront
     uint32_t before = 0, candidates = 0;
     constexpr uint32_t NO_ROOM = 1u << 20;  // beyond the number of elements
-    if (__builtin_expect(!skewed, 1)) {
+    const bool roomy = n <= MID_LIST;  // (four groups fit a wavefront's part of the list, whatever they hold)
+    auto list_in_segment = [&](auto some_alike, uint32_t i, const uint32_t(&el)[MID_GE]) {  // (alike keys: see hist_add)
+        constexpr bool ALIKE = decltype(some_alike)::value;
+        bool keep[MID_GE];
+        uint64_t b[MID_GE];
 #pragma unroll
-        for (int j = 0; j < MID_GROUPS; ++j)
-            if (j < static_cast<int>(groups)) {  // wave-uniform
-                const uint32_t i = i0 + j * GROUP;
-                bool keep[MID_GE];
-                uint64_t b[MID_GE];
+        for (int e = 0; e < MID_GE; ++e) {
+            keep[e] = mid_key<VEC>(el[e]) >= lo;
+            b[e] = __ballot(keep[e]);
+            float xs = keep[e] ? 0.0f : value_of<VEC>(el[e]);
+            asm("" : "+v"(xs));  // (see scan_tile)
+            const double xd = static_cast<double>(xs);
+            acc = fma(xd, xd, acc);
+        }
+        auto put = [&](uint32_t pos, uint32_t index, uint32_t r) {
+            segment[pos] = make_uint2(index, r);
+            if (ALIKE) hist_add(l.first, (mid_key<VEC>(r) - lo) >> shift, true);
+            else atomicAdd(&l.first[(mid_key<VEC>(r) - lo) >> shift], 1u);
+        };
+        const uint64_t first = b[0] | b[1], second = b[2] | b[3], any = first | second;
+        if (any == 0) return;                                           // wave-uniform, as what follows
+        if (((b[0] & b[1]) | (b[2] & b[3]) | (first & second)) == 0) {  // one per lane at most (see scan_tile)
+            const bool front = keep[0] | keep[1], odd = keep[1] | keep[3];
+            const uint32_t r = front ? (keep[0] ? el[0] : el[1]) : (keep[2] ? el[2] : el[3]);
+            const uint32_t more = static_cast<uint32_t>(__popcll(any));
+            if (own + more <= MID_SEGMENT && (front | keep[2] | keep[3])) put(lanes_below_plus(any, own), i + (front ? 0u : 2u) + (odd ? 1u : 0u), r);
+            own += more;
+        } else {
+            uint32_t pos = own;
+#pragma unroll
+            for (int e = 0; e < MID_GE; ++e) {
+                pos = lanes_below_plus(b[e], pos);
+                own += static_cast<uint32_t>(__popcll(b[e]));
+            }
+            if (own <= MID_SEGMENT) {
 #pragma unroll
                 for (int e = 0; e < MID_GE; ++e) {
-                    keep[e] = mid_key<VEC>(raw(j, e)) >= lo;
-                    b[e] = __ballot(keep[e]);
-                    float xs = keep[e] ? 0.0f : value_of<VEC>(raw(j, e));
-                    asm("" : "+v"(xs));  // (see scan_tile)
-                    const double xd = static_cast<double>(xs);
-                    acc = fma(xd, xd, acc);
-                }
-                auto put = [&](uint32_t pos, uint32_t index, uint32_t r) {
-                    segment[pos] = make_uint2(index, r);
-                    atomicAdd(&l.first[(mid_key<VEC>(r) - lo) >> shift], 1u);
-                };
-                const uint64_t first = b[0] | b[1], second = b[2] | b[3], any = first | second;
-                if (any == 0) continue;                                         // wave-uniform, as what follows
-                if (((b[0] & b[1]) | (b[2] & b[3]) | (first & second)) == 0) {  // one per lane at most (see scan_tile)
-                    const bool front = keep[0] | keep[1], odd = keep[1] | keep[3];
-                    const uint32_t r = front ? (keep[0] ? raw(j, 0) : raw(j, 1)) : (keep[2] ? raw(j, 2) : raw(j, 3));
-                    const uint32_t more = static_cast<uint32_t>(__popcll(any));
-                    if (own + more <= MID_SEGMENT && (front | keep[2] | keep[3])) put(lanes_below_plus(any, own), i + (front ? 0u : 2u) + (odd ? 1u : 0u), r);
-                    own += more;
-                } else {
-                    uint32_t pos = own;
-#pragma unroll
-                    for (int e = 0; e < MID_GE; ++e) {
-                        pos = lanes_below_plus(b[e], pos);
-                        own += static_cast<uint32_t>(__popcll(b[e]));
-                    }
-                    if (own <= MID_SEGMENT) {
-#pragma unroll
-                        for (int e = 0; e < MID_GE; ++e) {
-                            if (keep[e]) put(pos, i + e, raw(j, e));
-                            pos += keep[e] ? 1u : 0u;
-                        }
-                    }
+                    if (keep[e]) put(pos, i + e, el[e]);
+                    pos += keep[e] ? 1u : 0u;
                 }
             }
+        }
+    };
+    if (__builtin_expect(!skewed || roomy, 1)) {
+        if (__builtin_expect(!skewed, 1)) {
+#pragma unroll
+            for (int j = 0; j < MID_GROUPS; ++j)
+                if (j < static_cast<int>(groups)) {  // wave-uniform
+                    const uint32_t r[MID_GE] = {raw(j, 0), raw(j, 1), raw(j, 2), raw(j, 3)};
+                    list_in_segment(std::false_type(), i0 + j * GROUP, r);
+                }
+        } else {
+            each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) { list_in_segment(std::true_type(), i, r); });
+        }
         if (lane == 0) l.sm[1][w] = own <= MID_SEGMENT ? own : own | NO_ROOM;
         __syncthreads();
         wave_counts<MID_WAVES>(l.sm[1], before, candidates);
     }
-    const bool segments = !skewed && candidates < NO_ROOM;
+    const bool segments = (!skewed || roomy) && candidates < NO_ROOM;
     before &= NO_ROOM - 1;
     candidates &= NO_ROOM - 1;
-    if (__builtin_expect(kout != 0 && (!segments || candidates < kout), 0)) {  // uniform
-        // The elements once more, GROUPS of a lane's at a time: f(first index, raw patterns) group by group.  (Read again: kept, they and what the passes
-        // derive from them take more registers than there are.)
-        constexpr uint32_t AT_ONCE = 8;
-        auto each_group = [&](auto &&f) {
-#pragma unroll 1
-            for (uint32_t j0 = 0; j0 < groups; j0 += AT_ONCE) {
-                uint32_t d[AT_ONCE][GD];
-#pragma unroll
-                for (uint32_t j = 0; j < AT_ONCE; ++j) load(i0 + (j0 + j) * GROUP, d[j]);
-#pragma unroll
-                for (uint32_t j = 0; j < AT_ONCE; ++j)
-                    if (j0 + j < groups) {  // wave-uniform
-                        const uint32_t i = i0 + (j0 + j) * GROUP;
-                        if (half_left) with_last(i, d[j], static_cast<uint32_t>(x[n - 1]));
-                        uint32_t r[MID_GE];
-#pragma unroll
-                        for (int e = 0; e < MID_GE; ++e) r[e] = elem_of<VEC>(d[j][e / EPD], e % EPD);
-                        f(i, r);
-                    }
-            }
-        };
-        uint2 *list = l.list[0];
-        uint32_t total = candidates, from = lo;
-        MidPick t{0, candidates};
-        // (the same candidates; the threshold is to be found among them)
-        bool digits = !skewed && candidates >= kout && candidates <= MID_LIST;
-        if (!digits) {
-            // Equal keys, sorted values: every sixteenth element says what the k-th key may be, and a bound that is closer.  (An element of
-            // every lane in every fourth group missed the k largest of sorted values: 20 fp32 tensors of 30 K at 1 %
-            // 40.0 us, so 18.6.)
-            uint32_t guess = 0, bound = 0;  // (fewer than k are not zero: then zero is the threshold)
-            if (skewed || candidates >= kout) {
-                constexpr int EACH = 4;
-                uint32_t *sample = reinterpret_cast<uint32_t *>(list) + threadIdx.x;
-                uint32_t taken = 0;  // by this wavefront, per lane
-#pragma unroll
-                for (int j = 0; j < MID_GROUPS; j += EACH)
-                    if (j < static_cast<int>(groups)) {
-                        const uint32_t its = j + lane / (64 / EACH);  // sixteen lanes to a group
-                        uint32_t d[GD];
-                        load(its < groups ? (g0 + its) * GROUP + lane % (64 / EACH) * (GROUP * EACH / 64) : n + MID_GE, d);  // (behind the end: zeros)
-                        sample[taken * MID_THREADS] = mid_key<VEC>(elem_of<VEC>(d[0], 0));
-                        ++taken;
-                    }
-                __syncthreads();  // (all are done with h and sm)
-                reinterpret_cast<uint4 *>(l.h)[threadIdx.x] = make_uint4(0, 0, 0, 0);
-                if (threadIdx.x == 0) l.few[0] = 0;
-                __syncthreads();
-#pragma unroll 1
-                for (uint32_t i = 0; i < taken; ++i) {
-                    const uint32_t bin = sample[i * MID_THREADS] >> SH;
-                    hist_add(l.h, bin, bin != 0);
-                }
-                __syncthreads();
-                constexpr uint32_t ONE_IN = GROUP * EACH / 64;
-                const uint32_t expected = (kout + ONE_IN - 1) / ONE_IN;
-                const RankedBins at = ranked_bins(l.h, largest >> SH, 0, expected + static_cast<uint32_t>(4.0f * sqrtf(static_cast<float>(expected))) + 2, expected);
-                uint32_t most = 0;
-#pragma unroll 1
-                for (uint32_t i = 0; i < taken; ++i) {
-                    const uint32_t key = sample[i * MID_THREADS];
-                    most = key >> SH == at.hi && key > most ? key : most;
-                }
-                most = wave_max(most);
-                if (lane == 63 && most != 0) atomicMax(&l.few[0], most);
-                __syncthreads();
-                guess = l.few[0];
-                bound = at.lo < NSB ? at.lo << SH : 1u;
-            }
-            for (;;) {
-                uint32_t gt = 0, eq = 0, ge = 0;
-                each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
-#pragma unroll
-                    for (int e = 0; e < MID_GE; ++e) {
-                        const uint32_t key = mid_key<VEC>(r[e]);
-                        gt += key > guess ? 1u : 0u;
-                        eq += ((key == guess) & (i + e < n)) ? 1u : 0u;
-                        ge += key >= bound ? 1u : 0u;
-                    }
-                });
-                gt = lane_value(wave_incl_scan(gt), 63);
-                eq = lane_value(wave_incl_scan(eq), 63);
-                ge = lane_value(wave_incl_scan(ge), 63);
+    if (kout != 0) {  // uniform
+        // The list: keys from `from` on, `total` in all; this wavefront's share of it is `len` entries from `entries` on, in index order.
+        const uint2 *entries = segment;
+        uint32_t len = own, from = lo, total = candidates, by = shift;
+        MidPick t{0, 0};
+        bool found = false;  // t is the k-th key and the number of keys above it
+        if (__builtin_expect(!segments || candidates < kout, 0)) {  // uniform
+            uint2 *list = l.list[0];
+            // What the numbers of a wavefront's keys above and not below a guess, and not below a bound, say of the list to make: from where on, how many entries, and those
+            // of the wavefronts before.  False: nothing.
+            uint32_t all_in = 0;
+            auto found_by = [&](uint32_t guess, uint32_t bound, uint32_t gt, uint32_t ge, uint32_t in) {
                 __syncthreads();
                 if (lane == 0) {
                     l.sm[0][w] = gt;
-                    l.sm[1][w] = eq;
-                    l.sm[2][w] = ge;
+                    l.sm[1][w] = ge;
+                    l.sm[2][w] = in;
                 }
                 __syncthreads();
-                const uint32_t of = lane & (MID_WAVES - 1), its_gt = l.sm[0][of], its_ties = l.sm[1][of], its_ge = l.sm[2][of];
+                const uint32_t of = lane & (MID_WAVES - 1), its_gt = l.sm[0][of], its_ties = l.sm[1][of] - its_gt, its_in = l.sm[2][of];
                 auto row_scan = [](uint32_t v) {  // over 16 lanes
                     v = row_shr_add<DPP_SHR1>(v);
                     v = row_shr_add<DPP_SHR2>(v);
                     v = row_shr_add<DPP_SHR4>(v);
                     return row_shr_add<DPP_SHR8>(v);
                 };
-                const uint32_t ties_to = row_scan(its_ties), ge_to = row_scan(its_ge), all_gt = lane_value(row_scan(its_gt), MID_WAVES - 1);
-                const uint32_t all_ge = lane_value(ge_to, MID_WAVES - 1);
-                if (all_gt < kout && kout <= all_gt + lane_value(ties_to, MID_WAVES - 1)) {  // uniform, as what follows: it is the k-th key
+                const uint32_t ties_to = row_scan(its_ties), all_gt = lane_value(row_scan(its_gt), MID_WAVES - 1);
+                const uint32_t all_ge = all_gt + lane_value(ties_to, MID_WAVES - 1);
+                all_in = lane_value(row_scan(its_in), MID_WAVES - 1);
+                uint32_t its;
+                if (all_gt < kout && kout <= all_ge) {  // uniform, as what follows: it is the k-th key
                     t = MidPick{guess, all_gt};
-                    // (a wavefront before which the quota of ties is used up lists none of its own)
-                    const uint32_t q = kout - all_gt, lists = its_gt + (ties_to - its_ties < q ? its_ties : 0u), up_to = row_scan(lists);
-                    total = lane_value(up_to, MID_WAVES - 1);
-                    before = lane_value(up_to - lists, static_cast<int>(w));
+                    found = true;
+                    // (a wavefront before which the quota of ties is used up lists none of its own.  What lies behind the tensor's end is zero and
+                    // may be listed, behind all ties that are placed.)
+                    const uint32_t q = kout - all_gt;
+                    its = its_gt + (ties_to - its_ties < q ? its_ties : 0u);
                     from = lane_value(ties_to - its_ties, static_cast<int>(w)) < q ? guess : guess + 1;
-                    break;
-                }
-                if (bound != 0 && all_ge >= kout && all_ge <= MID_LIST) {
-                    digits = true;
-                    total = all_ge;
-                    before = lane_value(ge_to - its_ge, static_cast<int>(w));
+                } else if (all_gt >= kout && all_gt <= MID_LIST) {
+                    its = its_gt;
+                    from = guess + 1;
+                } else if (bound != 0 && all_in >= kout && all_in <= MID_LIST) {
+                    its = its_in;
                     from = bound;
-                    break;
+                } else {
+                    return false;
                 }
-                guess = mid_digits(
-                            [&](uint32_t base, uint32_t width, uint32_t by) {
-                                each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
+                const uint32_t up_to = row_scan(its);
+                total = lane_value(up_to, MID_WAVES - 1);
+                before = lane_value(up_to - its, static_cast<int>(w));
+                return true;
+            };
+            auto list_group = [&](uint32_t i, const uint32_t(&r)[MID_GE], uint32_t unsigned_bits, bool sums, uint32_t &to) {
+                bool keep[MID_GE];
+                uint32_t pos = to;
 #pragma unroll
-                                    for (int e = 0; e < MID_GE; ++e) {
-                                        const uint32_t d = mid_key<VEC>(r[e]) - base;
-                                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), (i + e < n) & (d >> (width - 1) >> 1 == 0));
-                                    }
-                                });
-                            },
-                            0, largest != 0 ? 32u - static_cast<uint32_t>(__builtin_clz(largest)) : 0u, kout, l.h, l.sm[0], &l.s_pick)
-                            .T;
-                bound = 0;
-            }
-        }
-        acc = 0.0;
-        uint32_t to = before;
-        each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) {
-            bool keep[MID_GE];
-            uint32_t pos = to;
+                for (int e = 0; e < MID_GE; ++e) {
+                    keep[e] = (r[e] & unsigned_bits) >= from;
+                    const uint64_t b = __ballot(keep[e]);
+                    pos = lanes_below_plus(b, pos);
+                    to += static_cast<uint32_t>(__popcll(b));
+                    if (sums) {  // uniform
+                        const double xd = static_cast<double>(keep[e] ? 0.0f : value_of<VEC>(r[e]));
+                        acc = fma(xd, xd, acc);
+                    }
+                }
 #pragma unroll
-            for (int e = 0; e < MID_GE; ++e) {
-                keep[e] = (mid_key<VEC>(r[e]) >= from) & (i + e < n);
-                const uint64_t b = __ballot(keep[e]);
-                pos = lanes_below_plus(b, pos);
-                to += static_cast<uint32_t>(__popcll(b));
-                const double xd = static_cast<double>(keep[e] ? 0.0f : value_of<VEC>(r[e]));
-                acc = fma(xd, xd, acc);
-            }
+                for (int e = 0; e < MID_GE; ++e) {
+                    if (keep[e] & (pos < MID_LIST)) list[pos] = make_uint2(i + e, r[e]);
+                    pos += keep[e] ? 1u : 0u;
+                }
+            };
+            bool counted = false, again = false;
+            // (some candidates more are listed sooner than counted)
+            if ((skewed && !roomy) || candidates < kout || candidates > 2 * kout + MID_LOOSE || candidates > MID_LIST) {
+                // Equal keys, sorted values: every sixteenth element says what the k-th key may be, and a bound that is closer.  From each group of 256 one
+                // of sixteen consecutive elements, another one in the next group.
+                uint32_t sample[MID_GROUPS / 4], guess = 0, bound = 0;  // (fewer than k are not zero: then zero is the threshold)
 #pragma unroll
-            for (int e = 0; e < MID_GE; ++e) {
-                if (keep[e] & (pos < MID_LIST)) list[pos] = make_uint2(i + e, r[e]);
-                pos += keep[e] ? 1u : 0u;
-            }
-        });
-        total = total < MID_LIST ? total : MID_LIST;
-        __syncthreads();
-        const uint32_t share = (total + MID_THREADS - 1) / MID_THREADS * 64, mine = w * share + lane;  // entries of a wavefront
-        auto each = [&](auto &&f) {
-#pragma unroll 1
-            for (uint32_t j = 0; j < share; j += 64) {
-                const bool in = mine + j < total;
-                const uint2 c = list[in ? mine + j : 0u];
-                f(c.x, c.y, in);
-            }
-        };
-        if (digits)
-            t = mid_digits(
-                [&](uint32_t base, uint32_t width, uint32_t by) {
-                    each([&](uint32_t, uint32_t r, bool in) {
-                        const uint32_t d = mid_key<VEC>(r) - base;
-                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), in & (d >> (width - 1) >> 1 == 0));
+                for (int i = 0; i < MID_GROUPS / 4; ++i) {
+                    const uint32_t r0 = lane & 1 ? raw(4 * i + 1, i) : raw(4 * i, i), r1 = lane & 1 ? raw(4 * i + 3, i) : raw(4 * i + 2, i);
+                    sample[i] = mid_key<VEC>(lane & 2 ? r1 : r0);
+                }
+                if ((skewed && !roomy) || candidates >= kout) {  // uniform
+                    const uint32_t wide_by = bits > MID_SAMPLE_BITS ? bits - MID_SAMPLE_BITS : 0;
+                    __syncthreads();  // (all are done with h)
+                    l.h[threadIdx.x] = 0;
+                    if (threadIdx.x == 0) l.few[0] = 0;
+                    __syncthreads();
+#pragma unroll
+                    for (int i = 0; i < MID_GROUPS / 4; ++i)
+                        if (4 * i < static_cast<int>(groups)) hist_add(l.h, (sample[i] - lo) >> wide_by, sample[i] >= lo);
+                    __syncthreads();
+                    const uint32_t expected = (kout + 15) / 16;
+                    const RankedBins at = ranked_bins(l.h, largest > lo ? (largest - lo) >> wide_by : 0, 0, expected + static_cast<uint32_t>(4.0f * sqrtf(static_cast<float>(expected))) + 2, expected);
+                    uint32_t most = 0;
+#pragma unroll
+                    for (int i = 0; i < MID_GROUPS / 4; ++i) most = sample[i] >= lo && (sample[i] - lo) >> wide_by == at.hi && sample[i] > most ? sample[i] : most;
+                    most = wave_max(most);
+                    if (lane == 63 && most != 0) atomicMax(&l.few[0], most);
+                    __syncthreads();
+                    guess = l.few[0];
+                    bound = at.lo < NSB ? lo + (at.lo << wide_by) : lo;
+                }
+                for (int tries = 0; !counted && tries < 3; ++tries) {
+                    uint32_t gt = 0, ge = 0, in = 0;
+                    pass([&](int j, uint32_t unsigned_bits) {
+#pragma unroll
+                        for (int e = 0; e < MID_GE; ++e) {
+                            const uint32_t key = raw(j, e) & unsigned_bits;
+                            gt += static_cast<uint32_t>(__popcll(__ballot(key > guess)));
+                            ge += static_cast<uint32_t>(__popcll(__ballot(key >= guess)));
+                            in += static_cast<uint32_t>(__popcll(__ballot(key >= bound)));
+                        }
                     });
-                },
-                from, largest > from ? 32u - static_cast<uint32_t>(__builtin_clz(largest - from)) : 0u, kout, l.h, l.sm[0], &l.s_pick);
-        __syncthreads();  // (the counts in sm have been read)
-        acc += place_entries<VEC, MID_WAVES>(each, VEC == TAG_F32 ? t.T : t.T << 16, kout - t.above, kout, op, wide, l.sm[0]);
-    } else if (kout != 0) {
-        auto each = [&](auto &&f) {
-#pragma unroll 1
-            for (uint32_t j = 0; j < own; j += 64) {
-                const bool in = j + lane < own;
-                const uint2 c = segment[in ? j + lane : 0u];
-                f(c.x, c.y, in);
+                    counted = found_by(guess, bound, gt, ge, in);
+                    if (!counted) {  // the next smaller one of the sample
+                        if (threadIdx.x == 0) l.few[0] = 0;
+                        uint32_t most = 0;
+#pragma unroll
+                        for (int i = 0; i < MID_GROUPS / 4; ++i) most = sample[i] < guess && sample[i] > most ? sample[i] : most;
+                        most = wave_max(most);
+                        __syncthreads();
+                        if (lane == 63 && most != 0) atomicMax(&l.few[0], most);
+                        __syncthreads();
+                        guess = l.few[0];
+                        if (all_in < kout) bound = lo;
+                    }
+                }
+                acc = 0.0;
+                again = !counted;
+                counted = true;
             }
-        };
-        // The bin of the k-th key, looked for from the bound upwards, where it is: `below` candidates are in the bins before it.  Every wavefront for
-        // itself, four bins to a lane.
-        uint32_t B = 0, here = 0, below = 0;
-        const uint32_t from_below = candidates - kout + 1;
-        for (uint32_t base = 0; base < MID_FIRST; base += 256) {
-            const uint4 c = reinterpret_cast<const uint4 *>(l.first)[base / 4 + lane];
-            const uint32_t sum = c.x + c.y + c.z + c.w, inc = wave_incl_scan(sum), total = lane_value(inc, 63);
-            if (below + total < from_below) {  // uniform
-                below += total;
-                continue;
+            if (__builtin_expect(!again, 1)) {
+                uint32_t to = before;
+                pass([&](int j, uint32_t unsigned_bits) {
+                    uint32_t r[MID_GE];
+#pragma unroll
+                    for (int e = 0; e < MID_GE; ++e) r[e] = raw(j, e);
+                    list_group(i0 + j * GROUP, r, unsigned_bits, counted, to);
+                });
+            } else {
+                // The sample's elements were no help (a few values, and their places in the tensor have a period that the sample meets).  The elements are read
+                // again for every pass; what lies behind the end counts as zeros, which are no larger than the k-th key.
+                const uint32_t T = mid_digits(
+                                       [&](uint32_t base, uint32_t width, uint32_t down) {
+                                           each_group([&](uint32_t, const uint32_t(&r)[MID_GE]) {
+#pragma unroll
+                                               for (int e = 0; e < MID_GE; ++e) {
+                                                   const uint32_t d = mid_key<VEC>(r[e]) - base;
+                                                   hist_add(l.h, (d >> down) & (MID_DIGIT - 1), d >> (width - 1) >> 1 == 0);
+                                               }
+                                           });
+                                       },
+                                       0, largest != 0 ? 32u - static_cast<uint32_t>(__builtin_clz(largest)) : 0u, kout, l.h, l.sm[0], &l.s_pick)
+                                       .T;
+                uint32_t gt = 0, ge = 0;
+                each_group([&](uint32_t, const uint32_t(&r)[MID_GE]) {
+#pragma unroll
+                    for (int e = 0; e < MID_GE; ++e) {
+                        gt += static_cast<uint32_t>(__popcll(__ballot(mid_key<VEC>(r[e]) > T)));
+                        ge += static_cast<uint32_t>(__popcll(__ballot(mid_key<VEC>(r[e]) >= T)));
+                    }
+                });
+                found_by(T, 0, gt, ge, 0);
+                uint32_t to = before;
+                each_group([&](uint32_t i, const uint32_t(&r)[MID_GE]) { list_group(i, r, mid_key<VEC>(0xFFFFFFFFu), true, to); });
             }
-            const int in = __builtin_ctzll(__ballot(below + inc >= from_below));
-            below += lane_value(inc - sum, in);
-            const uint32_t n0 = lane_value(c.x, in), n1 = lane_value(c.y, in), n2 = lane_value(c.z, in), n3 = lane_value(c.w, in);
-            B = base + 4 * in;
-            here = n0;
-            if (below + here < from_below) below += here, here = n1, ++B;
-            if (below + here < from_below) below += here, here = n2, ++B;
-            if (below + here < from_below) below += here, here = n3, ++B;
-            break;
-        }
-        uint32_t T = lo + (B << shift), above = candidates - below - here;
-        if (shift != 0 && here <= 64) {  // uniform
-            each([&](uint32_t, uint32_t r, bool in) {
-                if (in & ((mid_key<VEC>(r) - lo) >> shift == B)) l.few[atomicAdd(&l.nfew, 1u)] = mid_key<VEC>(r);
-            });
+            total = total < MID_LIST ? total : MID_LIST;
+            const uint32_t range = largest > from ? 32u - static_cast<uint32_t>(__builtin_clz(largest - from)) : 0u;
+            by = range > MID_FIRST_BITS ? range - MID_FIRST_BITS : 0u;
+            if (!found) reinterpret_cast<uint2 *>(l.first)[threadIdx.x] = make_uint2(0, 0);
             __syncthreads();
-            const uint32_t key = lane < here ? l.few[lane] : 0u, krem = kout - above;
-            uint32_t larger = 0, not_smaller = 0;
-            for (uint32_t i = 0; i < here; ++i) {
-                const uint32_t other = lane_value(key, static_cast<int>(i));
-                larger += other > key ? 1u : 0u;
-                not_smaller += other >= key ? 1u : 0u;
+            if (!found) {  // uniform
+                // (lanes far apart in the list: sorted values)
+                const uint32_t rows = ((total + 63) / 64) | 1u;
+#pragma unroll 1
+                for (uint32_t j = w; j < rows; j += MID_WAVES) {
+                    const uint32_t at = lane * rows + j;
+                    const uint32_t r = list[at < total ? at : 0u].y;
+                    hist_add(l.first, (mid_key<VEC>(r) - from) >> by, at < total);
+                }
+                __syncthreads();
             }
-            const int is = __builtin_ctzll(__ballot(lane < here && larger < krem && krem <= not_smaller) | 1ull << 63);
-            T = lane_value(key, is);
-            above += lane_value(larger, is);
-        } else if (shift != 0) {
-            const MidPick t = mid_digits(
-                [&](uint32_t base, uint32_t width, uint32_t by) {
-                    each([&](uint32_t, uint32_t r, bool in) {
-                        const uint32_t d = mid_key<VEC>(r) - base;
-                        hist_add(l.h, (d >> by) & (MID_DIGIT - 1), in & (d >> (width - 1) >> 1 == 0));
-                    });
-                },
-                T, shift, kout - above, l.h, l.sm[0], &l.s_pick);
-            T = t.T;
-            above += t.above;
+            const uint32_t share = (total + MID_THREADS - 1) / MID_THREADS * 64, at = w * share;
+            entries = list + at;
+            len = at < total ? (total - at < share ? total - at : share) : 0u;
         }
-        acc += place_entries<VEC, MID_WAVES>(each, VEC == TAG_F32 ? T : T << 16, kout - above, kout, op, wide, l.sm[0]);
+        auto each = [&](auto &&f) {
+#pragma unroll 1
+            for (uint32_t j = 0; j < len; j += 64) {
+                const bool in = j + lane < len;
+                const uint2 c = entries[in ? j + lane : 0u];
+                f(c.x, c.y, in);
+            }
+        };
+        if (!found) {
+            // The bin of the k-th key, looked for from the bound upwards, where it is: `below` candidates are in the bins before it.  Every wavefront for
+            // itself, four bins to a lane.
+            uint32_t B = 0, here = 0, below = 0;
+            const uint32_t from_below = total - kout + 1;
+            for (uint32_t base = 0; base < MID_FIRST; base += 256) {
+                const uint4 c = reinterpret_cast<const uint4 *>(l.first)[base / 4 + lane];
+                const uint32_t sum = c.x + c.y + c.z + c.w, inc = wave_incl_scan(sum), all = lane_value(inc, 63);
+                if (below + all < from_below) {  // uniform
+                    below += all;
+                    continue;
+                }
+                const int in = __builtin_ctzll(__ballot(below + inc >= from_below));
+                below += lane_value(inc - sum, in);
+                const uint32_t n0 = lane_value(c.x, in), n1 = lane_value(c.y, in), n2 = lane_value(c.z, in), n3 = lane_value(c.w, in);
+                B = base + 4 * in;
+                here = n0;
+                if (below + here < from_below) below += here, here = n1, ++B;
+                if (below + here < from_below) below += here, here = n2, ++B;
+                if (below + here < from_below) below += here, here = n3, ++B;
+                break;
+            }
+            t = MidPick{from + (B << by), total - below - here};
+            if (by != 0 && here <= 64) {  // uniform
+                each([&](uint32_t, uint32_t r, bool in) {
+                    if (in & ((mid_key<VEC>(r) - from) >> by == B)) l.few[atomicAdd(&l.nfew, 1u)] = mid_key<VEC>(r);
+                });
+                __syncthreads();
+                const uint32_t key = lane < here ? l.few[lane] : 0u, krem = kout - t.above;
+                uint32_t larger = 0, not_smaller = 0;
+                for (uint32_t i = 0; i < here; ++i) {
+                    const uint32_t other = lane_value(key, static_cast<int>(i));
+                    larger += other > key ? 1u : 0u;
+                    not_smaller += other >= key ? 1u : 0u;
+                }
+                const int is = __builtin_ctzll(__ballot(lane < here && larger < krem && krem <= not_smaller) | 1ull << 63);
+                t = MidPick{lane_value(key, is), t.above + lane_value(larger, is)};
+            } else if (by != 0) {
+                uint32_t least_not = 0, most = 0;
+                each([&](uint32_t, uint32_t r, bool in) {
+                    const uint32_t key = mid_key<VEC>(r);
+                    in = in & ((key - from) >> by == B);
+                    least_not = in && ~key > least_not ? ~key : least_not;
+                    most = in && key > most ? key : most;
+                });
+                least_not = wave_max(least_not);
+                most = wave_max(most);
+                if (lane == 63 && most != 0) {
+                    atomicMax(&l.least_not, least_not);
+                    atomicMax(&l.most, most);
+                }
+                __syncthreads();
+                if (l.most == ~l.least_not) {  // uniform: equal ones
+                    t.T = l.most;
+                } else {
+                const MidPick d = mid_digits(
+                    [&](uint32_t base, uint32_t width, uint32_t down) {
+                        each([&](uint32_t, uint32_t r, bool in) {
+                            const uint32_t d = mid_key<VEC>(r) - base;
+                            hist_add(l.h, (d >> down) & (MID_DIGIT - 1), in & (d >> (width - 1) >> 1 == 0));
+                        });
+                    },
+                    t.T, by, kout - t.above, l.h, l.sm[0], &l.s_pick);
+                t = MidPick{d.T, t.above + d.above};
+                }
+            }
+        }
+        if (found) __syncthreads();  // (the counts in sm have been read)
+        acc += place_entries<VEC, MID_WAVES>(each, VEC == TAG_F32 ? t.T : t.T << 16, kout - t.above, kout, op, wide, l.sm[0]);
     }
     float *err = a.err_out != nullptr ? a.err_out + blockIdx.x : nullptr;
     if (a.wire != 0) {
@@ -4422,13 +4506,13 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
     };
     // Only small tensors: one launch, one workgroup per tensor, no workspace traffic.
     bool all_small = true, all_mid = true;
-    int64_t longest = 0;
+    int64_t longest = 0, its_k = 0;
     for (int32_t s = 0; s < S; ++s) {
         all_small = all_small && n[s] <= SMALL_N;
-        all_mid = all_mid && mid_takes(n[s], k[s], n_total) && reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
-        longest = n[s] > longest ? n[s] : longest;
+        all_mid = all_mid && mid_takes(n[s], k[s], n_total, dt == ADATOPK_F32) && reinterpret_cast<uintptr_t>(dense[s]) % 4 == 0;
+        if (n[s] > longest) longest = n[s], its_k = k[s];
     }
-    if (all_small && !(all_mid && dt == ADATOPK_F32 && longest > SMALL_LONG)) {
+    if (all_small && !(all_mid && mid_takes_small(longest, its_k, dt == ADATOPK_F32))) {
         for (int32_t s0 = 0; s0 < S; s0 += SMALL_MAXSEG) {
             SmallLaunch sl{};
             const int32_t cnt = (S - s0 < SMALL_MAXSEG) ? S - s0 : SMALL_MAXSEG;
