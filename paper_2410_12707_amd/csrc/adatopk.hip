@@ -578,18 +578,18 @@ __device__ __forceinline__ uint32_t block_incl_scan_and_sum(uint32_t v, uint32_t
 // tensor, sorted data) a histogram pass gets several times slower.  So when at least half of the
 // wavefront is active and at least a quarter of it shares the bin of the first active lane, those
 // lanes are counted with a single add.  Only the lanes that execute the call take part in it.
-__device__ __forceinline__ void hist_add(uint32_t *h, uint32_t bin, bool active) {
+template <uint32_t COUNT = 1> __device__ __forceinline__ void hist_add(uint32_t *h, uint32_t bin, bool active) {  // COUNT: elements per lane
     const uint64_t act = __ballot(active);
     if (__popcll(act) >= 32) {  // wave-uniform
         const int leader = __ffsll(static_cast<unsigned long long>(act)) - 1;
         const uint32_t lbin = __builtin_amdgcn_readlane(bin, leader);
         const uint64_t same = __ballot(active && bin == lbin);
         if (__popcll(same) >= 16) {
-            if (static_cast<int>(threadIdx.x & 63) == leader) atomicAdd(&h[lbin], static_cast<uint32_t>(__popcll(same)));
+            if (static_cast<int>(threadIdx.x & 63) == leader) atomicAdd(&h[lbin], COUNT * static_cast<uint32_t>(__popcll(same)));
             active = active && bin != lbin;
         }
     }
-    if (active) atomicAdd(&h[bin], 1u);
+    if (active) atomicAdd(&h[bin], COUNT);
 }
 
 // Histogram counts of a wavefront that works through dense, ordered data (a chunk that is read
@@ -610,17 +610,17 @@ struct BinRun {
         if (pend != 0 && (threadIdx.x & 63) == 0) bin_add(h, ref, pend);
         pend = 0;
     }
-    template <typename P> __device__ __forceinline__ void add(P h, uint32_t bin, bool active) {
+    template <uint32_t COUNT = 1, typename P> __device__ __forceinline__ void add(P h, uint32_t bin, bool active) {
         const uint64_t act = __ballot(active);
         const uint64_t same = __ballot(active && bin == ref);
-        pend += static_cast<uint32_t>(__popcll(same));
+        pend += COUNT * static_cast<uint32_t>(__popcll(same));
         if (same != act) {  // wave-uniform: a lane is on another bin, the run moves there
             flush(h);
             const int leader = __ffsll(static_cast<unsigned long long>(act & ~same)) - 1;
             ref = __builtin_amdgcn_readlane(bin, leader);
             const uint64_t moved = __ballot(active && bin == ref);
-            pend = static_cast<uint32_t>(__popcll(moved));
-            if (active && bin != ref && !((same >> (threadIdx.x & 63)) & 1ull)) bin_add(h, bin, 1u);
+            pend = COUNT * static_cast<uint32_t>(__popcll(moved));
+            if (active && bin != ref && !((same >> (threadIdx.x & 63)) & 1ull)) bin_add(h, bin, COUNT);
         }
     }
 };
@@ -1016,10 +1016,10 @@ template <int VEC> __global__ __launch_bounds__(BLOCK) void k_hist1(Launch a) {
 // for the next tile's loads drain it).  List slots beyond the chunk's capacity are counted, not
 // stored: such a chunk is read from the input again by the kernels that follow.  A tile that alone
 // holds more than STAGE_CAP pairs (a quarter of its elements: a constant tensor, many ties, the kept
-// end of sorted data) does not go through the stage; in the scan of a single tensor it gives the
+// end of sorted data) does not go through the stage; in a launch of at most one chunk per compute unit it gives the
 // chunk's list up at once, so that nothing more is stored for a chunk that will be read again
 // (storing such tiles until the list was full cost a constant tensor 50 MB of writes that nobody
-// read); in the speculative scan of a batch it stores directly while the list has room.  (The exact scan knows
+// read); in a launch of more chunks it stores directly while the list has room.  (The exact scan knows
 // beforehand which chunks get a list: listed_room.)
 constexpr int STAGE_CAP = 2048;
 
@@ -1037,6 +1037,33 @@ __device__ __forceinline__ void flush_stage(const uint2 *stage, uint32_t from, u
         hist_add(hw, window_bin(key_of<VEC>(pr.y), lo, shw), true);
     }
 }
+
+// The window bins of a lane's elements of a group, and whether all are kept and in one bin, as in sorted values: those are counted at once.  (One by one, elements four
+// apart in a wavefront are on more bins than hist_add and BinRun merge.  Scan, us, one element after another per lane / so: six tensors of 4 M sorted fp32 values that keep a quarter
+// 54 / 31, in f16 a fifth 69 / 53, 25 M fp32 values sorted by magnitude 52 / 36.)
+template <int VEC, int NT> struct LaneBins {
+    using St = Stream<VEC, NT>;
+    uint32_t bin[St::GE];
+    bool one;
+    __device__ __forceinline__ LaneBins(const uint32_t (&dw)[St::SLOTS], int j, const bool (&keep)[St::GE], uint32_t lo, uint32_t shw) {
+        one = true;
+#pragma unroll
+        for (int e = 0; e < St::GE; ++e) {
+            bin[e] = window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw);
+            one = one & keep[e] & (bin[e] == bin[0]);
+        }
+    }
+    // Counts the other lanes' elements one by one if those are a few (where one bin ends and the next begins); whether they were.
+    __device__ __forceinline__ bool few_others(uint32_t *h, const bool (&keep)[St::GE]) const {
+        if (__popcll(__ballot(!one)) > 8) return false;  // wave-uniform
+        if (!one) {
+#pragma unroll
+            for (int e = 0; e < St::GE; ++e)
+                if (keep[e]) atomicAdd(&h[bin[e]], 1u);
+        }
+        return true;
+    }
+};
 
 template <int VEC, bool FAST, bool RUNS, bool DENSE, int NT>
 __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::SLOTS],
@@ -1176,8 +1203,7 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
             }
         }
     } else if (RUNS) {
-        // A dense tile in the variant with one workgroup per compute unit, whose register budget has
-        // room for it: the window bins by runs.  Nothing is stored, the list is given up.
+        // A dense tile in a launch of one chunk per compute unit: the window bins by runs.  Nothing is stored, the list is given up.
         cap = 0;
         // A wavefront whose whole share of the tile is kept and sits in one bin (a constant tensor) adds once.
         const uint32_t bin0 = __builtin_amdgcn_readfirstlane(window_bin(key_of<VEC>(elem_of<VEC>(dw[0], 0)), lo, shw));
@@ -1190,18 +1216,54 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
             if (lane == 0) atomicAdd(&hw[bin0], wc);
         } else {
             BinRun run;
+            // (The first group says which: values in no order gain nothing by it, 25 M fp32 that keep 30 % 134 / 140 us.)
+            const bool in_order = __popcll(__ballot(LaneBins<VEC, NT>(dw, 0, keep[0], lo, shw).one)) >= 32;  // wave-uniform
+            if (in_order) {
 #pragma unroll
-            for (int j = 0; j < St::GROUPS; ++j)
+                for (int j = 0; j < St::GROUPS; ++j) {
+                    const LaneBins<VEC, NT> b(dw, j, keep[j], lo, shw);
+                    run.template add<St::GE>(hw, b.bin[0], b.one);
+                    if (b.few_others(hw, keep[j])) continue;  // wave-uniform
 #pragma unroll
-                for (int e = 0; e < St::GE; ++e) run.add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e]);
+                    for (int e = 0; e < St::GE; ++e) run.add(hw, b.bin[e], keep[j][e] && !b.one);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < St::GROUPS; ++j)
+#pragma unroll
+                    for (int e = 0; e < St::GE; ++e) run.add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e]);
+            }
             run.flush(hw);
         }
     } else {
-        // (the variant with two workgroups per compute unit has no register to spare for a list that
-        // ends early: it stores while the list has room)
+        // (where tensors share the launch the list stores while it has room)
 #pragma unroll
         for (int j = 0; j < St::GROUPS; ++j) {
             uint32_t pos = slot_base;
+            const bool room = slot_base + 64 * St::GE <= cap;
+            if ((m[j][0] & m[j][1] & m[j][2] & m[j][3]) == ~0ull && (room || slot_base >= cap)) {  // wave-uniform
+                // A group that is kept whole (sorted values, equal keys): one store of four elements per lane.  (Element by element a wavefront's store takes every fourth
+                // word of a kilobyte.)
+                typedef int32_t Indices __attribute__((ext_vector_type(St::GE), aligned(4)));
+                typedef uint32_t Values __attribute__((ext_vector_type(St::GD), aligned(sizeof(R))));
+                const int32_t i = static_cast<int32_t>(i_lane + j * 64 * St::GE);
+                const uint32_t at = slot_base + lane * St::GE;
+                if (room) {
+                    Values v;
+#pragma unroll
+                    for (int d = 0; d < St::GD; ++d) v[d] = dw[j * St::GD + d];
+                    *reinterpret_cast<Indices *>(Li + at) = Indices{i, i + 1, i + 2, i + 3};
+                    *reinterpret_cast<Values *>(Lv + at) = v;
+                }
+                const LaneBins<VEC, NT> b(dw, j, keep[j], lo, shw);
+                hist_add<St::GE>(hw, b.bin[0], b.one);
+                if (!b.few_others(hw, keep[j])) {  // wave-uniform
+#pragma unroll
+                    for (int e = 0; e < St::GE; ++e) hist_add(hw, b.bin[e], !b.one);
+                }
+                slot_base += 64 * St::GE;
+                continue;
+            }
 #pragma unroll
             for (int e = 0; e < St::GE; ++e) pos = lanes_below_plus(m[j][e], pos);
 #pragma unroll
@@ -1596,7 +1658,7 @@ template <bool SHARED> __device__ __forceinline__ uint32_t listed_room(const Lau
     return B < NB1 && candidates > list_cap(sg) ? 0u : list_cap(sg);  // (B = NB1: nothing is kept, nothing reaches the window)
 }
 
-template <int VEC, bool SPEC, bool ALONE, bool DENSE = false>
+template <int VEC, bool SPEC, bool ALONE, bool DENSE = false, bool RUNS = ALONE>
 __global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch a) {
     constexpr int NT = ALONE ? SCAN_THREADS : BLOCK;
     using St = Stream<VEC, NT>;
@@ -1655,7 +1717,7 @@ __global__ __launch_bounds__(ALONE ? SCAN_THREADS : BLOCK, 4) void k_scan(Launch
             a.state[s].shwB = shw;
         }
     }
-    scan_chunk<VEC, SPEC, ALONE, false, SPEC, DENSE, NT>(a, s, g, chunk, lo, shw, room, buf, l);
+    scan_chunk<VEC, SPEC, RUNS, false, SPEC, DENSE, NT>(a, s, g, chunk, lo, shw, room, buf, l);
 }
 
 // ------------------------------------------------------------------ list kernels
@@ -4350,7 +4412,8 @@ inline uint32_t norm_workgroups(uint32_t S) { return (S + XCDS - 1) / XCDS * XCD
 // counted and listed at once, and what is left is the prologue in front and the rows behind, which the smaller workgroup's fewer wavefronts are through
 // sooner.  512 / 1024 threads, compress, us: one tile, exact, 1 Mi fp32 at 30 % 28.3 / 29.2, four bf16 tensors of 180 K at 30 % 21.3 / 22.0; from a sample, 786 K fp32 at
 // 5 % 17.9 / 18.5, at 0.3 % (32 K samples) 19.4 / 19.0, 2 M bf16 at 1 % 13.0 / 13.5, 786 K f16 at 20 % 13.8 / 14.2; two tiles and more, fp32 3 M at 60 %
-// 41.6 / 39.7, 25 M at 25 % 133.8 / 120.3, 12 M bf16 at 25 % 62.9 / 59.5.
+// 41.6 / 39.7, 25 M at 25 % 133.8 / 120.3, 12 M bf16 at 25 % 62.9 / 59.5.  Either way a launch of one chunk per compute unit gives the list of a dense tile up at once
+// (393 K equal fp32 values, list stored / given up, scan 9.0 / 6.2).
 inline bool scan_alone(const Launch &a, bool sampled, int elems_per_dword) {
     if (sampled && a.S == 1 && static_cast<int>(a.seg[0].flags >> FLAG_SAMPLE_SHIFT & 15u) * SAMPLE_BATCH * BLOCK * elems_per_dword >= SAMPLE_ELEMS) return true;
     int32_t longest = 0;
@@ -4365,11 +4428,12 @@ inline bool scan_alone(const Launch &a, bool sampled, int elems_per_dword) {
 // `dense`: the tensors that speculate are FLAG_DENSE.
 template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool speculate, bool no_lists, bool dense, hipStream_t st) {
     const dim3 grid(total_chunks);
-    const bool one_per_cu = total_chunks <= CTARGET_ONE;  // the scan can afford the deeper pipeline
+    const bool one_per_cu = total_chunks <= CTARGET_ONE;  // chunks to a compute unit: dense tiles give their list up, and the scan may have 1024 threads
     if (dense) {
         launch(ST_SPEC, k_scan<VEC, true, false, true>, grid, st, a);
     } else if (speculate) {
         if (one_per_cu && scan_alone(a, true, VEC / 4)) launch<SCAN_THREADS>(ST_SPEC, k_scan<VEC, true, true>, grid, st, a);
+        else if (one_per_cu) launch(ST_SPEC, k_scan<VEC, true, false, false, true>, grid, st, a);
         else launch(ST_SPEC, k_scan<VEC, true, false>, grid, st, a);
     }
     const dim3 parts(a.parts);
@@ -4389,6 +4453,7 @@ template <int VEC> adatopk_status launch_batch(Launch &a, int total_chunks, bool
     } else {
         launch(ST_HIST1, k_hist1<VEC>, grid, st, a);
         if (one_per_cu && scan_alone(a, false, VEC / 4)) launch<SCAN_THREADS>(ST_SCAN, k_scan<VEC, false, true>, grid, st, a);
+        else if (one_per_cu) launch(ST_SCAN, k_scan<VEC, false, false, false, true>, grid, st, a);
         else launch(ST_SCAN, k_scan<VEC, false, false>, grid, st, a);
         if constexpr (VEC == TAG_F32) {  // the 16-bit types have no last digit to refine
             if (dense) launch(ST_REFINE, k_refine<VEC, false, true>, parts, st, a);
