@@ -22,7 +22,7 @@ extern "C" {
 
 /* on != 0: from now on every kernel of a compress / decompress call is launched with a
  * start and a stop HIP event that carry the timestamps of the dispatch itself (events are
- * created on the first enable).  on == 0: plain launches.  Returns ADATOPK_OK or
+ * created as they are needed).  on == 0: plain launches.  Returns ADATOPK_OK or
  * ADATOPK_ERUNTIME. */
 adatopk_status adatopk_measure_enable(int32_t on);
 
@@ -32,7 +32,8 @@ int32_t adatopk_measure_stage_count(void);
 const char *adatopk_measure_stage_name(int32_t stage);
 
 /* Waits for the stop events of the kernels launched since the last read and stores the
- * duration of the most recent launch of every stage in milliseconds into
+ * summed duration of the launches of every stage (a batch is launched in groups; the first 64 of
+ * a stage count) in milliseconds into
  * ms_out[adatopk_measure_stage_count()] (host memory); stages that did not run since
  * the last read are reported as -1.  Returns ADATOPK_OK or ADATOPK_ERUNTIME. */
 adatopk_status adatopk_measure_read(float *ms_out);

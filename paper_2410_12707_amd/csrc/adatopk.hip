@@ -4380,9 +4380,10 @@ enum Stage {
 const char *const kStageNames[NSTAGE] = {"k_scan_spec", "k_judge", "k_hist1", "k_scan", "k_refine", "k_emit",
                                          "k_fill", "k_scatter", "k_merge", "k_small", "k_keep_all", "k_mid", "k_place_dense"};
 bool g_measure = false;
-bool g_events_made = false;
-hipEvent_t g_start[NSTAGE], g_stop[NSTAGE];
-bool g_ran[NSTAGE];  // launched, with events, since the last read
+bool g_enabled_once = false;
+constexpr int MEASURE_LAUNCHES = 64;  // of a stage between two reads that are timed (a batch is launched in groups); more are launched plainly
+hipEvent_t g_start[NSTAGE][MEASURE_LAUNCHES], g_stop[NSTAGE][MEASURE_LAUNCHES];
+int g_made[NSTAGE], g_ran[NSTAGE];  // events created; launched, with events, since the last read
 int32_t g_judge_missing = 0;  // workgroups that k_judge is launched without
 int32_t g_judge_rounds = -1;  // its rounds of waiting, if not negative
 #endif
@@ -4390,10 +4391,14 @@ int32_t g_judge_rounds = -1;  // its rounds of waiting, if not negative
 template <int NT = BLOCK, typename K, typename... Args>
 inline void launch(int stage, K kernel, dim3 grid, hipStream_t st, Args... args) {
 #ifdef ADATOPK_MEASURE_BUILD
-    if (g_measure) {
-        hipExtLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, g_start[stage], g_stop[stage], 0, args...);
-        g_ran[stage] = true;
-        return;
+    if (g_measure && g_ran[stage] < MEASURE_LAUNCHES) {
+        const int i = g_ran[stage];
+        if (i < g_made[stage] || (hipEventCreate(&g_start[stage][i]) == hipSuccess && hipEventCreate(&g_stop[stage][i]) == hipSuccess)) {
+            if (i == g_made[stage]) ++g_made[stage];
+            hipExtLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, g_start[stage][i], g_stop[stage][i], 0, args...);
+            ++g_ran[stage];
+            return;
+        }
     }
 #endif
     (void)stage;
@@ -5132,14 +5137,9 @@ adatopk_status adatopk_decompress_wire(const void *wire, size_t wire_bytes, adat
 #ifdef ADATOPK_MEASURE_BUILD
 // ---- measurement hooks
 adatopk_status adatopk_measure_enable(int32_t on) {
-    if (on && !g_events_made) {
-        for (int i = 0; i < NSTAGE; ++i)
-            if (hipEventCreate(&g_start[i]) != hipSuccess || hipEventCreate(&g_stop[i]) != hipSuccess)
-                return ADATOPK_ERUNTIME;
-        g_events_made = true;
-    }
+    g_enabled_once = g_enabled_once || on != 0;
     g_measure = on != 0;
-    for (int i = 0; i < NSTAGE; ++i) g_ran[i] = false;
+    for (int i = 0; i < NSTAGE; ++i) g_ran[i] = 0;
     return ADATOPK_OK;
 }
 
@@ -5150,13 +5150,16 @@ const char *adatopk_measure_stage_name(int32_t stage) {
 }
 
 adatopk_status adatopk_measure_read(float *ms_out) {
-    if (!ms_out || !g_events_made) return ADATOPK_EINVAL;
+    if (!ms_out || !g_enabled_once) return ADATOPK_EINVAL;
     for (int i = 0; i < NSTAGE; ++i) {
-        ms_out[i] = -1.0f;
-        if (!g_ran[i]) continue;
-        g_ran[i] = false;
-        if (hipEventSynchronize(g_stop[i]) != hipSuccess) return ADATOPK_ERUNTIME;
-        if (hipEventElapsedTime(&ms_out[i], g_start[i], g_stop[i]) != hipSuccess) return ADATOPK_ERUNTIME;
+        const int ran = g_ran[i];
+        g_ran[i] = 0;
+        ms_out[i] = ran != 0 ? 0.0f : -1.0f;
+        for (int j = 0; j < ran; ++j) {
+            float ms = 0.0f;
+            if (hipEventSynchronize(g_stop[i][j]) != hipSuccess || hipEventElapsedTime(&ms, g_start[i][j], g_stop[i][j]) != hipSuccess) return ADATOPK_ERUNTIME;
+            ms_out[i] += ms;
+        }
     }
     return ADATOPK_OK;
 }
