@@ -107,13 +107,21 @@ def judge_reads(state_words, kth_key: int) -> int:
     return 2 if not state_words[6] and kth_key < state_words[0] else 0
 
 
-def input_passes(stage_us, input_bytes: int, judged: int) -> int:
-    """Full reads of the input in a step: the passes that ran, and what the judging kernel read.  A pass over the input
+def placed_from_input(ns, ks, itemsize: int):
+    """(elements, kept elements) of the tensors of a batch that k_place_dense places: those that keep more than 21 %
+    (16-bit types: a quarter) and no more than 99.5 %, of 2^20 elements and more."""
+    dense = [(n, k) for n, k in zip(ns, ks) if n >= 1 << 20 and (n // 100 * 21 if itemsize == 4 else n // 4) < k <= 0.995 * n]
+    return sum(n for n, _ in dense), sum(k for _, k in dense)
+
+
+def input_passes(stage_us, input_bytes: int, judged: int, placed_share: float = 0):
+    """Full reads of the input in a step: the passes that ran, what the judging kernel read, and the share of the input that
+    k_place_dense reads once more.  A pass over the input
     that finishes faster than the peak allows did not read it (the exact passes return at once when the
     speculative pass held, and the other way round)."""
     ran = sum(1 for nm in ("k_scan_spec", "k_hist1", "k_scan", "k_small", "k_mid")
               if nm in stage_us and input_bytes / stage_us[nm] / 1e3 <= HBM_PEAK_GBS)
-    return ran + (judged if "k_judge" in stage_us else 0)
+    return ran + (judged if "k_judge" in stage_us else 0) + (placed_share if "k_place_dense" in stage_us else 0)
 
 
 def load_workload(wl, name):
@@ -242,23 +250,32 @@ class Bench:
         least = self.val.abs().min().cpu().view(torch.int16 if self.esize == 2 else torch.int32)
         return judge_reads([int(v) for v in words], int(least) << (16 if self.esize == 2 else 0))
 
+    def placed(self):
+        """placed_from_input of a call whose tensors a launch of k_place_dense takes."""
+        return placed_from_input([t.size for t in self.w.tensors], self.ks, self.esize) if self.S > 1 else (0, 0)
+
     def algorithmic_bytes(self):
-        """What each full-size kernel must move per launch (b bytes per value, n elements, k kept)."""
+        """What each full-size kernel must move per step (b bytes per value, n elements, k kept; tensors kept whole are no
+        business of the selection's kernels)."""
         b, n, k = self.esize, self.n, self.k
         judged = self.judged()
+        placed, placed_k = self.placed()
+        whole = sum(t.size for t, kept in zip(self.w.tensors, self.ks) if kept == t.size)
+        n_select, k_select = n - whole, k - whole
         return {
             **({"k_judge": judged * b * n} if judged else {}),  # (its other work is on the chunks' lists)
-            "k_scan_spec": b * n + (4 + b) * k,  # one read of the input + the candidate pairs written (at least the k kept ones)
-            "k_hist1": b * n,                    # exact passes (when they do not return at once): one read of the input ...
-            "k_scan": b * n + (4 + b) * k,       # ... and another, with the candidate pairs written
+            "k_scan_spec": b * n_select + (4 + b) * (k_select - placed_k),  # one read of the input + the candidate pairs written (at least the kept ones that are listed)
+            **({"k_place_dense": b * placed + (4 + b) * placed_k} if placed else {}),  # the dense tensors of a batch once more, and their pairs
+            "k_hist1": b * n_select,             # exact passes (when they do not return at once): one read of the input ...
+            "k_scan": b * n_select + (4 + b) * k_select,  # ... and another, with the candidate pairs written
             "k_merge": b * n + (4 + b) * k,      # one write of the dense output + the pairs read
             "k_small": b * n + (4 + b) * k,      # one-launch paths: one read of the input + the pairs
             "k_mid": b * n + (4 + b) * k,
         }
 
-    def step_bytes(self, input_reads: int) -> int:
+    def step_bytes(self, input_reads: float) -> float:
         """Bytes a step moves at the least: `input_reads` full reads of the input (one when the speculative
-        pass holds, two for the exact passes), the output written once, the kept pairs written and read back."""
+        pass holds, two for the exact passes; what is placed from the input is read once more), the output written once, the kept pairs written and read back."""
         return (input_reads + 1) * self.esize * self.n + 2 * (4 + self.esize) * self.k
 
     def parity(self, orc, s: int = 0) -> bool:
@@ -429,7 +446,7 @@ def other_config_line(B, torch, np, wl, orc, name):
     med = median(us)
     dense = bench.n * bench.esize
     stage_us = {nm: v["median_us"] for nm, v in bench.stage_medians(20).items()}
-    reads = input_passes(stage_us, bench.esize * bench.n, bench.judged())
+    reads = round(input_passes(stage_us, bench.esize * bench.n, bench.judged(), bench.placed()[0] / max(bench.n, 1)), 3)
     line = {"config": name, "workload": w.name, "dtype": w.dtype, "tensors": bench.S, "n": bench.n, "k": bench.k,
             "step_us_median": round(med, 2), "step_us_min_max": [round(min(us), 2), round(max(us), 2)],
             "dense_input_GBs": round(dense / med / 1e3, 1), "stage_us": stage_us, "input_reads_per_step": reads,
@@ -594,7 +611,7 @@ def main() -> int:
     # return at once when the speculative pass held (and the other way round), so they are left out.
     algo = {nm: v for nm, v in bench.algorithmic_bytes().items()
             if nm in stage_us and v / stage_us[nm] / 1e3 <= HBM_PEAK_GBS}
-    input_reads = input_passes(stage_us, bench.esize * n, bench.judged())
+    input_reads = round(input_passes(stage_us, bench.esize * n, bench.judged(), bench.placed()[0] / max(n, 1)), 3)
     traffic = measured_traffic() if args.config == "2" else None
 
     def roof(nm):

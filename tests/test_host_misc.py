@@ -140,3 +140,15 @@ def test_extension_is_rebuilt_after_a_change_of_the_header(tmp_path, monkeypatch
     assert not b.marshal_is_stale()
     os.utime(paths[1], (3, 3))
     assert b.marshal_is_stale()
+
+
+def test_bench_counts_what_is_placed_from_the_input():
+    import bench
+
+    m = 1 << 20
+    ns, ks = [8 * m, 8 * m, 8 * m, 8 * m, m - 1, 2 * m], [m // 8, 2 * m, 4 * m, 8 * m, m // 2, 2 * m - 1]
+    assert bench.placed_from_input(ns, ks, 4) == (16 * m, 6 * m)  # not: listed, kept whole, short, all but one kept
+    assert bench.placed_from_input(ns, ks, 2) == (8 * m, 4 * m)   # 16-bit types list a quarter
+    batch = {"k_scan_spec": 161.0, "k_hist1": 8.0, "k_scan": 8.0, "k_refine": 23.0, "k_emit": 9.0, "k_place_dense": 76.0}
+    assert bench.input_passes(batch, 805_306_368, 0, 0.25) == 1.25
+    assert bench.input_passes({k: v for k, v in batch.items() if k != "k_place_dense"}, 805_306_368, 0, 0.25) == 1
