@@ -1217,21 +1217,18 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
         } else {
             BinRun run;
             // (The first group says which: values in no order gain nothing by it, 25 M fp32 that keep 30 % 134 / 140 us.)
-            const bool in_order = __popcll(__ballot(LaneBins<VEC, NT>(dw, 0, keep[0], lo, shw).one)) >= 32;  // wave-uniform
-            if (in_order) {
+            const bool in_order = VEC == TAG_F32 && __popcll(__ballot(LaneBins<VEC, NT>(dw, 0, keep[0], lo, shw).one)) >= 32;  // wave-uniform
 #pragma unroll
-                for (int j = 0; j < St::GROUPS; ++j) {
+            for (int j = 0; j < St::GROUPS; ++j) {
+                bool one = false;
+                if (in_order) {
                     const LaneBins<VEC, NT> b(dw, j, keep[j], lo, shw);
                     run.template add<St::GE>(hw, b.bin[0], b.one);
                     if (b.few_others(hw, keep[j])) continue;  // wave-uniform
-#pragma unroll
-                    for (int e = 0; e < St::GE; ++e) run.add(hw, b.bin[e], keep[j][e] && !b.one);
+                    one = b.one;
                 }
-            } else {
 #pragma unroll
-                for (int j = 0; j < St::GROUPS; ++j)
-#pragma unroll
-                    for (int e = 0; e < St::GE; ++e) run.add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e]);
+                for (int e = 0; e < St::GE; ++e) run.add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e] && !one);
             }
             run.flush(hw);
         }
@@ -1239,46 +1236,43 @@ __device__ __forceinline__ void scan_tile(const uint32_t (&dw)[Stream<VEC, NT>::
         // (where tensors share the launch the list stores while it has room)
 #pragma unroll
         for (int j = 0; j < St::GROUPS; ++j) {
-            uint32_t pos = slot_base;
-            const bool room = slot_base + 64 * St::GE <= cap;
-            if ((m[j][0] & m[j][1] & m[j][2] & m[j][3]) == ~0ull && (room || slot_base >= cap)) {  // wave-uniform
+            const bool whole = (m[j][0] & m[j][1] & m[j][2] & m[j][3]) == ~0ull, room = slot_base + 64 * St::GE <= cap;  // wave-uniform
+            bool one = false;
+            if (whole && (room || slot_base >= cap)) {
                 // A group that is kept whole (sorted values, equal keys): one store of four elements per lane.  (Element by element a wavefront's store takes every fourth
                 // word of a kilobyte.)
-                typedef int32_t Indices __attribute__((ext_vector_type(St::GE), aligned(4)));
-                typedef uint32_t Values __attribute__((ext_vector_type(St::GD), aligned(sizeof(R))));
-                const int32_t i = static_cast<int32_t>(i_lane + j * 64 * St::GE);
-                const uint32_t at = slot_base + lane * St::GE;
                 if (room) {
+                    typedef int32_t Indices __attribute__((ext_vector_type(St::GE), aligned(4)));
+                    typedef uint32_t Values __attribute__((ext_vector_type(St::GD), aligned(sizeof(R))));
+                    const int32_t i = static_cast<int32_t>(i_lane + j * 64 * St::GE);
+                    const uint32_t at = slot_base + lane * St::GE;
                     Values v;
 #pragma unroll
                     for (int d = 0; d < St::GD; ++d) v[d] = dw[j * St::GD + d];
                     *reinterpret_cast<Indices *>(Li + at) = Indices{i, i + 1, i + 2, i + 3};
                     *reinterpret_cast<Values *>(Lv + at) = v;
                 }
+                slot_base += 64 * St::GE;
                 const LaneBins<VEC, NT> b(dw, j, keep[j], lo, shw);
                 hist_add<St::GE>(hw, b.bin[0], b.one);
-                if (!b.few_others(hw, keep[j])) {  // wave-uniform
+                if (b.few_others(hw, keep[j])) continue;  // wave-uniform
+                one = b.one;
+            } else {
+                uint32_t pos = slot_base;
 #pragma unroll
-                    for (int e = 0; e < St::GE; ++e) hist_add(hw, b.bin[e], !b.one);
-                }
-                slot_base += 64 * St::GE;
-                continue;
-            }
+                for (int e = 0; e < St::GE; ++e) pos = lanes_below_plus(m[j][e], pos);
 #pragma unroll
-            for (int e = 0; e < St::GE; ++e) pos = lanes_below_plus(m[j][e], pos);
-#pragma unroll
-            for (int e = 0; e < St::GE; ++e) {
-                if (keep[j][e]) {
-                    const uint32_t raw = St::elem(dw, j, e);
-                    if (pos < cap) {
+                for (int e = 0; e < St::GE; ++e) {
+                    if (keep[j][e] && pos < cap) {
                         Li[pos] = static_cast<int32_t>(i_lane + j * 64 * St::GE + e);
-                        Lv[pos] = static_cast<R>(raw);
+                        Lv[pos] = static_cast<R>(St::elem(dw, j, e));
                     }
-                    hist_add(hw, window_bin(key_of<VEC>(raw), lo, shw), true);
-                    ++pos;
+                    pos += keep[j][e] ? 1u : 0u;
+                    slot_base += __popcll(m[j][e]);
                 }
-                slot_base += __popcll(m[j][e]);
             }
+#pragma unroll
+            for (int e = 0; e < St::GE; ++e) hist_add(hw, window_bin(key_of<VEC>(St::elem(dw, j, e)), lo, shw), keep[j][e] && !one);
         }
     }
     running += tot;
