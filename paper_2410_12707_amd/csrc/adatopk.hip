@@ -106,6 +106,11 @@ constexpr int LIST_DIV = 4;           // a chunk's candidate list holds up to a 
 constexpr int MAXSUB = 8;             // parts that the list kernels cut a chunk's candidates into, at most ...
 constexpr int MAXSUB_ONE = 4;         // ... and for a single tensor, whose chunks are a quarter as long as a large batch's
 constexpr int SUB_ENTRIES = 8192;     // ... so that a part has about this many
+// ... and for the dense tensors of a large batch (FLAG_DENSE).  Where their windows hold, a chunk's list is one part and the others' workgroups return; where they
+// miss, k_refine reads chunks of eight tiles and more, whose many parts are rounds of prologues.  k_refine, us, 1 / 2 / 4 / 8 parts at most, 32 Mi values: normal, 95 %
+// kept 6.9 / 8.5 / 14.2 / 16.4; one key throughout, 65 % 38.2 / 37.5 / 42.3 / 57.3, 95 % 50.4 / 54.6 / 55.6 / 66.1; 65 % behind a ReLU 60 / 55 / 56 / 68; 97 % zeros, 95 %
+// 70 / 59 / 63 / 73; 128 Mi of 97 % zeros, 65 % 247 / 204 / 202 / 201.
+constexpr int MAXSUB_DENSE = 2;
 constexpr int MAXSEG = 64;            // segments per launch (the table travels as kernel arguments)
 constexpr int64_t SPLIT_MIN_N = 16 << 20;  // elements of either kind from which a batch's speculating and exact tensors are launched apart
 constexpr int CTARGET = 512;          // chunks of a launch of several tensors, at most (two workgroups per compute unit)
@@ -158,7 +163,7 @@ constexpr double DENSE_MAX_KEEP = 0.995;
 // 16-bit types: 8 deviations, a list that is a little longer costs nothing there (a window's bins are 16 binades).
 // And the scan is not made where the sample says that a window is not worth it: the k-th key is zero or not, as it happens; it is among keys so thin
 // that a bracket of DENSE_SPANS windows holds it; or all but one in DENSE_ALIKE keys are in its bin, and the lists would overflow.  Behind a ReLU, about as many kept as are not zero, exact passes /
-// scan and passes / so: 48 % 348 / 405 / 322, 50 % 405 / 431 / 384, bf16 50 % 282 / 270 / 237; one key throughout, 50 % 338 / 353 / 334, 25 % 315 / 330 / 349, 70 % 320 / 374 / 361.
+// scan and passes / so: 48 % 348 / 405 / 322, 50 % 405 / 431 / 376, bf16 50 % 282 / 270 / 238; one key throughout, 50 % 338 / 353 / 301, 25 % 314 / 330 / 306, 70 % 323 / 374 / 336, 95 % 180 / 233 / 201 (four tensors).
 constexpr double DENSE_SIGMAS_F32 = 5.0, DENSE_SIGMAS_16 = 8.0;
 constexpr uint32_t DENSE_SPANS = 6, DENSE_ALIKE = 8;
 constexpr size_t MERGE_SPANS = 1024;       // output spans aimed at by the one-kernel decompress
@@ -4716,7 +4721,7 @@ adatopk_status compress_impl(const void *const *dense, const int64_t *n, const i
             uint32_t sl = 0;
             if (dt == ADATOPK_F32 && ns > 0 && !(no_lists && listless(s))) {
                 const double kept = static_cast<double>(ks) / static_cast<double>(ns) * static_cast<double>(E[i] < ns ? E[i] : ns);
-                const uint32_t most = S == 1 ? MAXSUB_ONE : MAXSUB;  // what the workspace of this call was laid out for
+                const uint32_t most = dense_group ? MAXSUB_DENSE : (S == 1 ? MAXSUB_ONE : MAXSUB);  // (the workspace of this call was laid out for the last two)
                 while ((1u << sl) < most && 1.35 * kept >= static_cast<double>(SUB_ENTRIES << sl)) ++sl;
                 // A chunk without a list has as many entries as elements, however much is kept: parts shorter than SUB_ENTRIES leave
                 // the last ones of a chunk empty (chunks of five tiles, eight parts: three), and each costs a workgroup's prologue.

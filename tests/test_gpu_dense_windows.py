@@ -83,3 +83,10 @@ def test_no_scan_for_a_window_that_is_not_worth_it(dtype):
     scan = Batch(xs, 0.5).stages()["k_scan_spec"]
     for alike in ([torch.relu(x) for x in xs], [torch.ones_like(x) for x in xs], [torch.zeros_like(x) for x in xs]):
         assert Batch(alike, 0.5).stages()["k_scan_spec"] < 0.5 * scan
+
+
+@pytest.mark.parametrize("value", [0.0, 1.0])
+def test_a_batch_of_one_key_has_few_parts_per_chunk(value):
+    # without lists the last digit's kernel reads what each of the exact passes has read
+    stages = Batch([torch.full((8 << 20,), value, device="cuda") for _ in range(4)], 0.65).stages()
+    assert stages["k_refine"] < 0.8 * (stages["k_hist1"] + stages["k_scan"])
